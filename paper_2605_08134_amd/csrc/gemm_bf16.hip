@@ -16,10 +16,9 @@
 // MFMA fragment reads apply the same XOR (measured conflict-free for 16-byte
 // reads: 246 of 256 B/clk/CU).
 //
-// Each wave computes the TRANSPOSED tile with v_mfma_f32_32x32x16_bf16 (weight
-// fragment as the first operand): a lane then owns one output row and runs of 4
-// consecutive output columns, which gives 8-byte stores and keeps a row's values
-// inside one lane.
+// Each wave computes the TRANSPOSED tile (weight fragment as the first MFMA operand): a lane
+// then owns one output row and runs of 4 consecutive output columns (8 in the large tiles),
+// which gives 8- or 16-byte stores and keeps a row's values inside one lane.
 //
 // k-parts.  A projection with few output tiles and a long k (the scored query columns
 // for all rows: 1024 x 128 x 4096) can cut k into ranges that run as separate
@@ -129,6 +128,37 @@ __device__ __forceinline__ void store4(const GemmDev& p, float* c32, long tok, i
   o[2] = (bf16_t)v2;
   o[3] = (bf16_t)v3;
   *reinterpret_cast<bf16x4*>(cbase + tok * p.ldc + (col - seg * p.seg_n)) = o;
+}
+
+// Eight neighbouring output columns col .. col + 7 (col a multiple of 8; a segment, whose width
+// is a multiple of 32, holds all of them): one 16-byte store where store4 makes two of 8.
+__device__ __forceinline__ void store8(const GemmDev& p, long tok, int col, const float* v) {
+  if (p.swiglu_pairs) {
+    bf16x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (bf16_t)(v[2 * e] / (1.0f + __expf(-v[2 * e])) * v[2 * e + 1]);
+    *reinterpret_cast<bf16x4*>(p.c0 + tok * p.ldc + (col >> 1)) = o;
+    return;
+  }
+  float y[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) y[e] = v[e];
+#pragma unroll
+  for (int h = 0; h < 8; h += 4) {
+    if (p.c32 && col + h < p.c32_cols) {
+      const f32x4 o = {y[h], y[h + 1], y[h + 2], y[h + 3]};
+      *reinterpret_cast<f32x4*>(p.c32 + tok * p.c32_cols + col + h) = o;
+    }
+    if (p.rope && col + h < p.rope_cols)
+      rope_rotate4(p.rope, p.rope_dh, p.rope_seq, tok, col + h, y[h], y[h + 1], y[h + 2], y[h + 3]);
+  }
+  const int seg = col / p.seg_n;
+  bf16_t* cbase = seg == 0 ? p.c0 : (seg == 1 ? p.c1 : p.c2);
+  if (!cbase) return;
+  bf16x8 o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = (bf16_t)y[e];
+  *reinterpret_cast<bf16x8*>(cbase + tok * p.ldc + (col - seg * p.seg_n)) = o;
 }
 
 // Tile order: GROUP_M row-tiles per column step (the tiles that run at the same time on one
@@ -566,6 +596,256 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
   return true;
 }
 
+// ---- large tiles: 256 x (64 TN), eight waves in two groups that take turns ---------------
+// Waves w and w + 4 sit on the same SIMD.  Waves 0-3 (group 0) own the left half of the tile's
+// columns, waves 4-7 (group 1) the right half, each wave 64 rows x 32 TN columns.  A k-step of 64 is
+// cut into TN phases, one per block of 32 columns, and a phase into a memory part (fragment
+// reads of the phase from LDS, waits) and a matrix part (16 MFMAs), with a workgroup barrier
+// after each.  Group 1 runs one barrier behind group 0, so on every SIMD one wave multiplies while
+// the other reads: neither the LDS reads nor the barriers leave the matrix pipe idle.
+//   * The global -> LDS loads are issued between the MFMAs of the matrix part, one or two per phase
+//     and wave.  In the memory part, or ahead of its reads, the vector-memory queue holds up the
+//     wave that the others wait for: 2930 and 3870 cycles per k-step of a 256 x 256 tile, against
+//     2300 between the MFMAs (2048 is what the MFMAs alone take).
+//   * v_mfma_f32_16x16x32_bf16 and not 32x32x16: it moves fewer accumulator registers per flop, and
+//     these kernels run at the power limit (1.6-1.9 GHz of 2.4 under load): 16384 x 12288 x 4096 takes
+//     1140 us against 1285 us although a k-step has 9 % more cycles.
+//   * The weight rows of a fragment are permuted (row 8 a + b of a 32-row block feeds result row
+//     4 a + b of the first MFMA, row 8 a + 4 + b the second, a, b = 0 .. 3), so that a lane ends up with
+//     eight neighbouring output columns: 16-byte stores, half the store requests (the epilogue of a
+//     256 x 256 tile: 5.1 against 11 thousand cycles).  The chunk XOR of a weight row follows that
+//     order ((row >> 1) & 1 | ((row >> 3) & 3) << 1), which keeps the reads conflict-free.
+//   * LDS: two stages, each freed region by region.  The A rows of k-step kt are read in phase 0 only
+//     and column block j in phase j (block 0 already in the last phase of kt - 1); a region is filled
+//     again for kt + 2 from the phase after on, so a load has 3.5 (TN = 3) or 4.5 phases (TN = 4) of
+//     512 MFMA cycles to arrive.
+// Measured with gathered-row support and all (us, before: one k-loop that every wave runs in step):
+// 16384 x 12288 x 4096 1540 -> 1140 (1.45 PFLOP/s), 1024 x 12288 x 4096 98 -> 78, 1024 x 24576 x 4096
+// 206 -> 154.
+constexpr int kPpRows = 256;
+template <int TN>
+constexpr int pp_smem_bytes() {
+  return 2 * (kPpRows + 64 * TN) * ROW_BYTES;
+}
+// chunk XOR of row r of a 32-row weight block
+__device__ __forceinline__ int pp_bkey(int r) { return ((r >> 1) & 1) | (((r >> 3) & 3) << 1); }
+
+// vblock, forced_tile_*, lidx and the result as in gemm_tile; called by all 512 threads.
+template <int TN>
+__device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsigned char* smem, const int vblock,
+                                             lds_idx_t lidx = nullptr) {
+  static_assert(TN == 3 || TN == 4, "column blocks of 32 per wave");
+  constexpr int BM = kPpRows, BN = 64 * TN;
+  constexpr int ASZ = BM * ROW_BYTES, BSZ = BN * ROW_BYTES, STAGE_BYTES = ASZ + BSZ;
+
+  const int tiles_m = (m + BM - 1) / BM, tiles_n = (p.n + BN - 1) / BN;
+  const int total = tiles_m * tiles_n;
+  const int per_xcd = (total + 7) >> 3;
+  const int slot = vblock >> 3;
+  if (slot >= per_xcd) return false;
+  const int unit = (vblock & 7) * per_xcd + slot;
+  if (unit >= total) return false;
+  int tile_m, tile_n;
+  tile_of_unit(unit, tiles_m, tiles_n, tile_m, tile_n);
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave >> 2, wm = wave & 3;
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int KT = p.k / BK;
+
+  // ---- global -> LDS: per k-step a wave loads 4 groups of 8 A rows and one group of 8 weight rows
+  // of each column block (block j: rows 32 j .. of the left and of the right half, 64 in all).
+  // Rows past the end re-read the last one.
+  const bf16_t* src_a[4];
+  const bf16_t* src_b[TN];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = (wave * 4 + i) * 8 + (lane >> 3);
+    int row = m0 + r;
+    row = row < m ? row : m - 1;
+    src_a[i] = p.a + row_token(p.idx, lidx, row) * p.lda + ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int r = wave * 8 + (lane >> 3);
+    int col = n0 + (r >> 5) * (32 * TN) + j * 32 + (r & 31);
+    col = col < p.n ? col : p.n - 1;
+    src_b[j] = p.wt + (long)col * p.k + ((lane & 7) ^ pp_bkey(r & 31)) * 8;
+  }
+  long tok_out[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = m0 + wm * 64 + i * 16 + l16;
+    tok_out[i] = row_token(p.idx, lidx, row < m ? row : m - 1);
+  }
+  if (lidx) __syncthreads();
+  // (k-steps past the end re-read the last one into a region nobody reads any more, so that the
+  // number of loads in flight is the same in every phase of every k-step)
+  auto load_a = [&](int i, int kt) __attribute__((always_inline)) {
+    const int k = kt < KT ? kt : KT - 1;
+    __builtin_amdgcn_global_load_lds((gptr_t)(src_a[i] + k * BK),
+                                     (lptr_t)(smem + (kt & 1) * STAGE_BYTES + (wave * 4 + i) * 1024), 16, 0, 0);
+  };
+  auto load_b = [&](int j, int kt) __attribute__((always_inline)) {
+    const int k = kt < KT ? kt : KT - 1;
+    __builtin_amdgcn_global_load_lds((gptr_t)(src_b[j] + k * BK),
+                                     (lptr_t)(smem + (kt & 1) * STAGE_BYTES + ASZ + j * 64 * ROW_BYTES + wave * 1024),
+                                     16, 0, 0);
+  };
+
+  f32x4 acc[4][2 * TN];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2 * TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int a_off = (wm * 64 + l16) * ROW_BYTES;
+  int a_koff[2], b_koff[2][2];
+  const int brow = (l16 >> 2) * 8 + (l16 & 3);
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    a_koff[ks] = ((ks * 4 + kq) ^ ((l16 >> 1) & 7)) * 16;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      b_koff[h][ks] = (grp * 32 + brow + 4 * h) * ROW_BYTES + (((ks * 4 + kq) ^ pp_bkey(brow + 4 * h)) * 16);
+  }
+  bf16x8 fa[4][2], fb[2][2][2];  // A fragments of a k-step; weight fragments of two column blocks
+  auto read_a = [&](int kt) __attribute__((always_inline)) {
+    const unsigned char* st = smem + (kt & 1) * STAGE_BYTES + a_off;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) fa[i][ks] = *reinterpret_cast<const bf16x8*>(st + i * 16 * ROW_BYTES + a_koff[ks]);
+  };
+  auto read_b = [&](int set, int j, int kt) __attribute__((always_inline)) {
+    const unsigned char* st = smem + (kt & 1) * STAGE_BYTES + ASZ + j * 64 * ROW_BYTES;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) fb[set][h][ks] = *reinterpret_cast<const bf16x8*>(st + b_koff[h][ks]);
+  };
+  // MFMAs [first, last) of the 16 of column block j
+  auto mma = [&](int set, int j, int first, int last) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      if (t < first || t >= last) continue;
+      const int ks = t >> 3, i = (t >> 1) & 3, h = t & 1;
+      acc[i][j * 2 + h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][h][ks], fa[i][ks], acc[i][j * 2 + h], 0, 0, 0);
+    }
+  };
+  // end of a memory part: all but N of the wave's loads have landed, its LDS reads have returned
+  auto end_mem = [&](auto n_c) __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt_and_barrier<decltype(n_c)::value>();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // a matrix part: the MFMAs of column block j with up to four loads between them
+  auto matrix = [&](int set, int j, auto l1, auto l2, auto l3, auto l4) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_setprio(1);
+    mma(set, j, 0, 4);
+    __builtin_amdgcn_sched_barrier(0);
+    l1();
+    __builtin_amdgcn_sched_barrier(0);
+    mma(set, j, 4, 8);
+    __builtin_amdgcn_sched_barrier(0);
+    l2();
+    __builtin_amdgcn_sched_barrier(0);
+    mma(set, j, 8, 12);
+    __builtin_amdgcn_sched_barrier(0);
+    l3();
+    __builtin_amdgcn_sched_barrier(0);
+    mma(set, j, 12, 14);
+    __builtin_amdgcn_sched_barrier(0);
+    l4();
+    __builtin_amdgcn_sched_barrier(0);
+    mma(set, j, 14, 16);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto none = []() __attribute__((always_inline)) {};
+#define DARE_N(n) std::integral_constant<int, n>{}
+#define DARE_A(i) [&]() __attribute__((always_inline)) { load_a(i, kt + 2); }
+#define DARE_B(j, d) [&]() __attribute__((always_inline)) { load_b(j, kt + d); }
+
+  // Loads in the order in which they are needed: block 0 of a k-step, its A rows, its blocks
+  // 1 .. TN - 1.  The counts below are the loads issued after the last one that the next phase reads.
+  load_b(0, 0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) load_a(i, 0);
+#pragma unroll
+  for (int j = 1; j < TN; ++j) load_b(j, 0);
+  load_b(0, 1);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) load_a(i, 1);
+  load_b(1, 1);
+  if constexpr (TN == 4) load_b(2, 1);
+  wait_vmcnt_and_barrier<TN == 4 ? 10 : 8>();
+  read_b(0, 0, 0);
+  if (grp == 1) asm volatile("s_barrier" ::: "memory");
+  if constexpr (TN == 4) {
+    for (int kt = 0; kt < KT; ++kt) {
+      read_a(kt);
+      end_mem(DARE_N(9));
+      matrix(0, 0, DARE_B(3, 1), none, DARE_B(0, 2), none);
+      read_b(1, 1, kt);
+      end_mem(DARE_N(10));
+      matrix(1, 1, DARE_A(0), none, DARE_A(1), none);
+      read_b(0, 2, kt);
+      end_mem(DARE_N(10));
+      matrix(0, 2, DARE_A(2), none, DARE_A(3), none);
+      read_b(1, 3, kt);
+      read_b(0, 0, kt + 1);
+      end_mem(DARE_N(8));
+      matrix(1, 3, DARE_B(1, 2), none, DARE_B(2, 2), none);
+    }
+  } else {
+    auto kstep = [&](int kt, auto set_c) __attribute__((always_inline)) {
+      constexpr int S = decltype(set_c)::value;  // fragment set of block 0 (alternates: TN is odd)
+      read_a(kt);
+      end_mem(DARE_N(7));
+      matrix(S, 0, DARE_B(2, 1), none, DARE_B(0, 2), none);
+      read_b(S ^ 1, 1, kt);
+      end_mem(DARE_N(7));
+      matrix(S ^ 1, 1, DARE_A(0), DARE_A(1), DARE_A(2), DARE_A(3));
+      read_b(S, 2, kt);
+      read_b(S ^ 1, 0, kt + 1);
+      end_mem(DARE_N(7));
+      matrix(S, 2, none, DARE_B(1, 2), none, none);
+    };
+    int kt = 0;
+    for (; kt + 1 < KT; kt += 2) {
+      kstep(kt, DARE_N(0));
+      kstep(kt + 1, DARE_N(1));
+    }
+    if (kt < KT) kstep(kt, DARE_N(0));
+  }
+#undef DARE_N
+#undef DARE_A
+#undef DARE_B
+  if (grp == 0) asm volatile("s_barrier" ::: "memory");
+  wait_vmcnt<0>();
+
+  // acc[i][2 j + h][e] = C[row, col], row = m0 + 64 wm + 16 i + l16, col = n0 + 32 TN grp + 32 j + 8 kq + 4 h + e
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (m0 + wm * 64 + i * 16 + l16 >= m) continue;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int col = n0 + grp * (32 * TN) + j * 32 + kq * 8;
+      if (col >= p.n) continue;
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = acc[i][j * 2 + (e >> 2)][e & 3];
+      store8(p, tok_out[i], col, v);
+    }
+  }
+  return true;
+}
+
 // ---- very few rows (at most 16 TMS): a stream over the weight matrix ------------------
 // With a handful of refreshed rows (one or two tokens unmasked per denoising step) the
 // projection is a matrix-vector product in disguise: what matters is that every CU pulls on
@@ -648,6 +928,13 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) gemm_bf16_kernel(GemmDe
   const int m = p.m_dev ? *p.m_dev : p.m_max;
   if (m <= 0) return;
   gemm_tile<BM, BN, WAVES_M, WAVES_N, STAGES>(p, m, smem, threadIdx.x, blockIdx.x);
+}
+
+template <int TN>
+__global__ void __launch_bounds__(512) gemm_bf16_pp_kernel(GemmDev p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[pp_smem_bytes<TN>()];
+  const int m = p.m_max;
+  gemm_tile_pp<TN>(p, m, smem, blockIdx.x);
 }
 
 // ---- row count read on the device: the tile shape follows it -------------------------
@@ -742,10 +1029,10 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
   int* sel_wave_tot = reinterpret_cast<int*>(smem);
   int32_t* sel_list = reinterpret_cast<int32_t*>(smem + 64);
   static_assert(2 * smem_bytes<64, 64, 4>() <= kWideSmem && smem_bytes<64, 64, 8>() <= kWideSmem &&
-                    smem_bytes<256, 256, 2>() <= kWideSmem &&
+                    pp_smem_bytes<4>() <= kWideSmem &&
                     smem_bytes<128, 192, 3>() <= kWideSmem && smem_bytes<128, 96, 4>() <= kWideSmem &&
                     smem_bytes<128, 48, 5>() <= kWideSmem && smem_bytes<128, 64, 4>() <= kWideSmem &&
-                    smem_bytes<256, 192, 2>() <= kWideSmem,
+                    pp_smem_bytes<3>() <= kWideSmem,
                 "shared buffer too small");
   int m;
   lds_idx_t lidx = nullptr;
@@ -800,7 +1087,7 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
     };
     for (int vb = blockIdx.x; vb < whole_end; vb += G) {
       next_tile();
-      gemm_tile<256, 256, 2, 4, 2>(p, m, smem, threadIdx.x, vb, 0, 1, lidx);
+      gemm_tile_pp<4>(p, m, smem, vb, lidx);
     }
     if (cut) {
       // child c: the parents of an XCD slot stay on their XCD (c & 7), 4 children per parent
@@ -817,7 +1104,7 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
       }
     }
   } else if (p.n % 192 == 0 && tiles_of(m, p.n, 256, 192) >= kWideFullTiles) {
-    passes([&](int vb) { return gemm_tile<256, 192, 4, 2, 2>(p, m, smem, threadIdx.x, vb, 0, 1, lidx); });
+    passes([&](int vb) { return gemm_tile_pp<3>(p, m, smem, vb, lidx); });
   } else if (p.n % 192 == 0 && one_round(tiles_of(m, p.n, 128, 192))) {
     gemm_tile16<128, 192, 4, 2, 3>(p, m, smem, threadIdx.x, blockIdx.x, lidx);  // (at most one tile per workgroup)
   } else if (m > 64 && p.n % 48 == 0 && one_round(tiles_of(m, p.n, 128, 48))) {
@@ -893,6 +1180,13 @@ hipError_t launch_fixed(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int TN>
+hipError_t launch_pp(const GemmArgs& g, hipStream_t s) {
+  const int tiles = tiles_of(g.m_max, g.n, kPpRows, 64 * TN);
+  hipLaunchKernelGGL(gemm_bf16_pp_kernel<TN>, dim3(grid_for(tiles)), dim3(512), 0, s, to_dev(g));
+  return hipGetLastError();
+}
+
 hipError_t launch_rows_wide(const GemmArgs& g, hipStream_t s) {
   // worst case over the row counts 1 .. m_max of the blocks any of the shapes needs (the
   // 64 x 64 shape is only chosen below kWideBigTiles 128 x 128 tiles, each of which holds
@@ -918,14 +1212,18 @@ hipError_t launch_rows_wide(const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   if (g.m_dev || g.sel_mask) return launch_rows_wide(g, s);
-  // Row count known on the host.  Measured on MI355X (256 CUs): 256 x 256 tiles have
-  // the least LDS-fill traffic per flop and win once they fill the chip; 256 x 192
-  // gives exactly 256 tiles for 1024 x 12288; 128 x 128 with 8 waves is the best
-  // shape when the larger ones would leave most CUs idle.
-  auto tiles = [&](int bm, int bn) { return ((g.m_max + bm - 1) / bm) * ((g.n + bn - 1) / bn); };
-  if (g.n % 256 == 0 && tiles(256, 256) >= 512) return launch_fixed<256, 256, 2, 4, 2>(g, s);
-  if (g.n % 192 == 0 && tiles(256, 192) >= 224) return launch_fixed<256, 192, 4, 2, 2>(g, s);
-  if (g.n % 256 == 0 && tiles(256, 256) >= 224) return launch_fixed<256, 256, 2, 4, 2>(g, s);
+  // Row count known on the host.  Once 256-row tiles fill most of the chip, the ping-pong tile
+  // wins: 256 x 192 costs about 3/4 of 256 x 256 (1870 against 2500 cycles per k-step), so the narrow
+  // one is taken where it needs fewer quarter-rounds of the 256 CUs (1024 x 12288: one full round
+  // against one round with 64 CUs idle, 78 against 85 us; 2331 x 12288: three against two, 209 against
+  // 198 us).  128 x 128 with 8 waves is the best shape when the larger ones would leave most CUs idle.
+  auto tiles = [&](int bm, int bn) { return tiles_of(g.m_max, g.n, bm, bn); };
+  if (g.k_parts <= 1) {
+    const int t3 = tiles(kPpRows, 192), t4 = tiles(kPpRows, 256);
+    const int q3 = 3 * ((t3 + 255) / 256), q4 = 4 * ((t4 + 255) / 256);
+    if (t3 >= 224 && (q3 < q4 || t4 < 176)) return launch_pp<3>(g, s);
+    if (t4 >= 176) return launch_pp<4>(g, s);
+  }
   if (g.m_max > 64 && g.n % 128 == 0 && tiles(128, 128) >= 64) return launch_fixed<128, 128, 4, 2, 4>(g, s);
   return launch_fixed<64, 64, 2, 2, 4>(g, s);
 }

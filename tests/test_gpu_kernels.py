@@ -56,6 +56,26 @@ def test_gemm_all_rows(B, dtype, m, n, k, seg):
     assert rel_err(host(c32), want[:, :c32_cols]) <= 2e-6     # fp32 accumulators, unrounded
 
 
+@pytest.mark.parametrize("m,n,k,seg,tile", [
+    (1000, 12288, 64, 4096, "256 x 192, one k-step, ragged rows"),
+    (961, 12096, 192, 12096, "256 x 192, an odd number of k-steps, one row in the last tile's last 64"),
+    (1024, 12480, 128, 4160, "256 x 256, ragged columns"),
+    (1793, 8192, 320, 4096, "256 x 256, five k-steps, one row in the last tile"),
+])
+def test_gemm_all_rows_large_tiles(B, m, n, k, seg, tile):
+    r = _rng(m + n + k)
+    a = store(r.standard_normal((m, k), dtype=np.float32), "bf16")
+    w = store(r.standard_normal((k, n), dtype=np.float32) * np.float32(0.05), "bf16")
+    wt = B.dare_k_pack_weight(dev(w, "bf16"))
+    outs = [torch.full((m, seg), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(n // seg)]
+    c32 = torch.full((m, 68), float("nan"), dtype=torch.float32, device="cuda")    # ends inside a lane's eight columns
+    B.dare_k_gemm(dev(a, "bf16"), wt, outs, seg, c32=c32)
+    torch.cuda.synchronize()
+    want = a.astype(np.float64) @ w.astype(np.float64)
+    assert_close(np.concatenate([host(o) for o in outs], axis=1), want, "bf16")
+    assert rel_err(host(c32), want[:, :68]) <= 2e-6     # fp32 accumulators, unrounded
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("count", [0, 1, 16, 17, 32, 33, 129, 205])
 def test_gemm_selected_rows_device_count(B, dtype, count):
