@@ -1,13 +1,25 @@
-// fp32 debug path of the row-selected projection C[t, :] = A[t, :] . W (same
-// contract as the bf16 kernel; Alg. 1 lines 2, 6-7, 11, Alg. 2 lines 2, 7, 11).
-// Plain LDS-tiled FMA kernel: 64 x 64 tile, k in steps of 16, 4 x 4 outputs per
-// thread, every output one fp32 sum in k order.
+// fp32 path of the row-selected projection C[t, :] = A[t, :] . W (same contract as the
+// bf16 kernel; Alg. 1 lines 2, 6-7, 11, Alg. 2 lines 2, 7, 11) on v_mfma_f32_16x16x4_f32.
+//
+// Fragments go from global memory straight into registers: lane L of a wave holds row L & 15
+// and the four neighbouring k of chunk L >> 4, so one 16-byte load per 16 rows feeds four MFMAs
+// (MFMA j multiplies element j of every chunk; A and W agree on that order).  The weight
+// fragment is the first operand: a lane then owns one output row and four neighbouring columns.
+//
+// Every output is the sum of four sums over the quarters of k, added in order, whatever the
+// tile shape: a row's projection does not depend on the number of rows or columns it is
+// computed with, bit for bit (a query that did not change keeps a drift score of exactly 0
+// across modes, which project it in launches of different width).
+//
+// What bounds it.  Small shapes (128 x 256 x 256): the latency of a workgroup, launch, one round
+// of loads, sum, store.  Four waves take a quarter of k each, 4 x 16 k in flight per wave, and 16 x 16
+// tiles give the most workgroups: 16.6 -> 3.8 us against a 64 x 64 LDS tile that walked k in steps of 16
+// with two barriers each.  Larger shapes: the matrix pipe (157 TFLOP/s nominal; 112 reached)
+// and the loads that feed it, hence 64 x 64 wave tiles, 64 MFMAs per 8 loads.
 #include "dare_common.h"
 
 namespace dare {
 namespace {
-
-constexpr int FBM = 64, FBN = 64, FBK = 16, FLD = FBM + 4;
 
 struct GemmF32Dev {
   const float* a;
@@ -23,70 +35,133 @@ struct GemmF32Dev {
   int rope_cols, rope_dh, rope_seq;
 };
 
-__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmF32Dev p) {
-  __shared__ __attribute__((aligned(16))) float As[FBK][FLD];
-  __shared__ __attribute__((aligned(16))) float Bs[FBK][FLD];
-  const int m = p.m_dev ? *p.m_dev : p.m_max;
-  const int m0 = blockIdx.x * FBM, n0 = blockIdx.y * FBN;
-  if (m0 >= m) return;
-  const int tid = threadIdx.x;
-  const int lr = tid >> 2, lk = (tid & 3) * 4;  // staging: row, k offset
-  int arow = m0 + lr;
-  arow = arow < m ? arow : m - 1;
-  const long atok = p.idx ? (long)p.idx[arow] : (long)arow;
-  int bcol = n0 + lr;
-  bcol = bcol < p.n ? bcol : p.n - 1;
-  const float* asrc = p.a + atok * p.lda + lk;
-  const float* bsrc = p.wt + (long)bcol * p.k + lk;
-  const int ty = tid >> 4, tx = tid & 15;
-
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-
-  for (int k0 = 0; k0 < p.k; k0 += FBK) {
-    const f32x4 va = *reinterpret_cast<const f32x4*>(asrc + k0);
-    const f32x4 vb = *reinterpret_cast<const f32x4*>(bsrc + k0);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      As[lk + j][lr] = va[j];
-      Bs[lk + j][lr] = vb[j];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < FBK; ++kk) {
-      const f32x4 a4 = *reinterpret_cast<const f32x4*>(&As[kk][ty * 4]);
-      const f32x4 b4 = *reinterpret_cast<const f32x4*>(&Bs[kk][tx * 4]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a4[i], b4[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-
-  const int col = n0 + tx * 4;
-  if (col >= p.n) return;
+// four neighbouring output columns col .. col + 3 (col a multiple of 4) of token tok
+__device__ __forceinline__ void store4_f32(const GemmF32Dev& p, long tok, int col, f32x4 v) {
   const int seg = col / p.seg_n;
   float* cbase = seg == 0 ? p.c0 : (seg == 1 ? p.c1 : p.c2);
+  if (p.c32 && col < p.c32_cols)  // the scored columns: before any rotation
+    *reinterpret_cast<f32x4*>(p.c32 + tok * p.c32_cols + col) = v;
+  if (!cbase) return;
+  float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+  if (p.rope && col < p.rope_cols) rope_rotate4(p.rope, p.rope_dh, p.rope_seq, tok, col, v0, v1, v2, v3);
+  const f32x4 o = {v0, v1, v2, v3};
+  *reinterpret_cast<f32x4*>(cbase + tok * p.ldc + (col - seg * p.seg_n)) = o;
+}
+
+constexpr int kKParts = 4;  // quarters of k (k is a multiple of 64: whole steps of 16 each)
+
+// Four waves, wave tile 16 TM x 16 TN.  SPLIT: all waves on one tile, a quarter of k each, sums
+// added through LDS; else 2 x 2 wave tiles per workgroup and every wave takes all quarters.  UNR:
+// steps of 16 k whose loads are in flight at once (registers allow one for 64 x 64 wave tiles, whose
+// 64 MFMAs per step cover a load).
+template <int TM, int TN, bool SPLIT, int UNR>
+__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmF32Dev p) {
+  constexpr int SIDE = SPLIT ? 1 : 2;
+  constexpr int BM = 16 * TM * SIDE, BN = 16 * TN * SIDE;
+  const int m = p.m_dev ? *p.m_dev : p.m_max;
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  if (m0 >= m) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int wm = SPLIT ? 0 : (wave & 1), wn = SPLIT ? 0 : (wave >> 1);
+
+  long tok[TM];
+  const float* asrc[TM];
+  const float* bsrc[TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
-    if (row >= m) continue;
-    const long tok = p.idx ? (long)p.idx[row] : (long)row;
-    float v0 = acc[i][0], v1 = acc[i][1], v2 = acc[i][2], v3 = acc[i][3];
-    if (p.c32 && col < p.c32_cols) {  // the scored columns: before any rotation
-      const f32x4 o = {v0, v1, v2, v3};
-      *reinterpret_cast<f32x4*>(p.c32 + tok * p.c32_cols + col) = o;
-    }
-    if (cbase) {
-      if (p.rope && col < p.rope_cols) rope_rotate4(p.rope, p.rope_dh, p.rope_seq, tok, col, v0, v1, v2, v3);
-      const f32x4 o = {v0, v1, v2, v3};
-      *reinterpret_cast<f32x4*>(cbase + tok * p.ldc + (col - seg * p.seg_n)) = o;
-    }
+  for (int i = 0; i < TM; ++i) {
+    int row = m0 + (wm * TM + i) * 16 + l16;
+    row = row < m ? row : m - 1;
+    tok[i] = p.idx ? (long)p.idx[row] : (long)row;
+    asrc[i] = p.a + tok[i] * p.lda + kq * 4;
   }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    int col = n0 + (wn * TN + j) * 16 + l16;
+    col = col < p.n ? col : p.n - 1;
+    bsrc[j] = p.wt + (long)col * p.k + kq * 4;
+  }
+
+  const int steps = p.k / (16 * kKParts);  // per quarter
+  // the sum over quarter `part`, chunks of UNR steps whose loads are all in flight at once
+  auto quarter = [&](int part, f32x4 (&acc)[TM][TN]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int kbase = part * steps * 16;
+    for (int s = 0; s < steps; s += UNR) {
+      f32x4 fa[UNR][TM], fb[UNR][TN];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const int k0 = kbase + (s + u < steps ? s + u : steps - 1) * 16;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[u][i] = *reinterpret_cast<const f32x4*>(asrc[i] + k0);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[u][j] = *reinterpret_cast<const f32x4*>(bsrc[j] + k0);
+      }
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        if (s + u >= steps) break;  // (uniform)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[u][j][e], fa[u][i][e], acc[i][j], 0, 0, 0);
+      }
+    }
+  };
+
+  // acc[i][j][e] = C[row, col]: row = base + 16 i + l16, col = base + 16 j + 4 kq + e
+  if constexpr (SPLIT) {
+    __shared__ f32x4 part_sum[kKParts][TM * TN][64];
+    f32x4 acc[TM][TN];
+    quarter(wave, acc);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) part_sum[wave][i * TN + j][lane] = acc[i][j];
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TM * TN; ++t) {
+      if (t % 4 != wave) continue;
+      const int i = t / TN, j = t % TN;
+      f32x4 v = part_sum[0][t][lane];
+#pragma unroll
+      for (int w = 1; w < kKParts; ++w) v += part_sum[w][t][lane];
+      const int row = m0 + i * 16 + l16, col = n0 + j * 16 + kq * 4;
+      if (row < m && col < p.n) store4_f32(p, tok[i], col, v);
+    }
+  } else {
+    f32x4 sum[TM][TN];
+    quarter(0, sum);
+    for (int part = 1; part < kKParts; ++part) {
+      f32x4 acc[TM][TN];
+      quarter(part, acc);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) sum[i][j] += acc[i][j];
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int row = m0 + (wm * TM + i) * 16 + l16, col = n0 + (wn * TN + j) * 16 + kq * 4;
+        if (row < m && col < p.n) store4_f32(p, tok[i], col, sum[i][j]);
+      }
+  }
+}
+
+template <int TM, int TN, bool SPLIT, int UNR>
+hipError_t launch_shape(const GemmF32Dev& p, hipStream_t s) {
+  constexpr int BM = 16 * TM * (SPLIT ? 1 : 2), BN = 16 * TN * (SPLIT ? 1 : 2);
+  const int tm = (p.m_max + BM - 1) / BM, tn = (p.n + BN - 1) / BN;
+  if (tm == 0 || tn == 0) return hipSuccess;
+  hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, SPLIT, UNR>), dim3(tm, tn), dim3(256), 0, s, p);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -112,10 +187,16 @@ hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
   p.rope_cols = g.rope_cols;
   p.rope_dh = g.rope_dh;
   p.rope_seq = g.rope_seq;
-  const int tm = (g.m_max + FBM - 1) / FBM, tn = (g.n + FBN - 1) / FBN;
-  if (tm == 0 || tn == 0) return hipSuccess;
-  hipLaunchKernelGGL(gemm_f32_kernel, dim3(tm, tn), dim3(256), 0, s, p);
-  return hipGetLastError();
+  // The largest tile that gives most of the chip's 256 CUs a workgroup.  Measured (us; before: 64 x 64
+  // tiles through LDS): 1024 x 12288 x 4096 1334 -> 919 (128 x 128), 1024 x 2048 x 2048 141 -> 80 and
+  // 514 x 3072 x 1024 74 -> 46 (64 x 64; 129 and 59 with 32 x 32), 64 x 4096 x 4096 235 -> 41 (32 x 32; 60 with
+  // 16 x 16, 83 with 64 x 64).
+  auto tiles = [&](int b) { return (long)((g.m_max + b - 1) / b) * ((g.n + b - 1) / b); };
+  constexpr long kFill = 192;
+  if (tiles(128) >= kFill) return launch_shape<4, 4, false, 1>(p, s);
+  if (tiles(64) >= kFill) return launch_shape<4, 4, true, 1>(p, s);
+  if (tiles(32) >= kFill) return launch_shape<2, 2, true, 4>(p, s);
+  return launch_shape<1, 1, true, 4>(p, s);
 }
 
 }  // namespace dare

@@ -76,6 +76,44 @@ def test_gemm_all_rows_large_tiles(B, m, n, k, seg, tile):
     assert rel_err(host(c32), want[:, :68]) <= 2e-6     # fp32 accumulators, unrounded
 
 
+@pytest.mark.parametrize("m,n,k,tile", [
+    (17, 80, 64, "16 x 16, one step per quarter of k"),
+    (150, 1296, 320, "32 x 32, five steps per quarter (a chunk of four and a rest), ragged both ways"),
+    (600, 1296, 448, "64 x 64, ragged both ways"),
+    (1473, 2064, 192, "128 x 128, ragged both ways"),
+])
+def test_gemm_f32_tile_shapes_agree_bit_for_bit(B, m, n, k, tile):
+    """The sum over k has one order whatever the tile shape: a row of the launch equals the
+    same row projected alone, for the first 16 columns alone as well."""
+    r = _rng(m + n + k)
+    a = r.standard_normal((m, k), dtype=np.float32)
+    w = r.standard_normal((k, n), dtype=np.float32) * np.float32(0.05)
+    wt, ad = B.dare_k_pack_weight(dev(w, "f32")), dev(a, "f32")
+
+    def project(rows, weight):
+        out = torch.full((rows.shape[0], weight.shape[0]), float("nan"), device="cuda")
+        B.dare_k_gemm(rows, weight, [out], weight.shape[0])
+        torch.cuda.synchronize()
+        return host(out)
+
+    got = project(ad, wt)
+    assert rel_err(got, a.astype(np.float64) @ w.astype(np.float64)) <= 2e-6
+    assert np.array_equal(project(ad[m - 1:].contiguous(), wt)[0], got[m - 1])
+    assert np.array_equal(project(ad, wt[:16].contiguous()), got[:, :16])
+
+
+@pytest.mark.parametrize("seq,dh", [(1, 128), (31, 64), (33, 128), (129, 64), (161, 128)])
+def test_attention_f32_edges(B, seq, dh):
+    """Key-waves without a tile, ragged 32-key tiles and ragged 16-row query blocks."""
+    q, k, v, _ = _attn_case(seq + dh, 2, seq, 2, dh, "f32", 1.0)
+    out = torch.full((2 * seq, 2 * dh), float("nan"), device="cuda")
+    B.dare_k_attention(dev(q, "f32"), dev(k, "f32"), dev(v, "f32"), out, 2, seq, 2, dh)
+    torch.cuda.synchronize()
+    for b in range(2):
+        sl = slice(b * seq, (b + 1) * seq)
+        assert rel_err(host(out)[sl], orc.attention_rows(q[sl], k[sl], v[sl], 2)) <= 1e-5
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("count", [0, 1, 16, 17, 32, 33, 129, 205])
 def test_gemm_selected_rows_device_count(B, dtype, count):
