@@ -26,6 +26,8 @@ struct dare_ctx {
   size_t q_new_elems;
   int32_t* sel_idx;    // [max tokens]
   int32_t* sel_off;    // [max_batch + 1]
+  float* split_tiles;  // workspace of projections whose k is cut in two, or nullptr
+  int* split_count;
   // the block around the layer (dare_block_attach)
   bool has_block, has_bias;
   dare_block_config block;
@@ -86,7 +88,7 @@ struct DeviceGuard {
 
 void free_ctx(dare_ctx* c) {
   if (!c) return;
-  void* bufs[] = {c->wqkv_t, c->wo_t, c->q_buf, c->attn_buf, c->q_new, c->sel_idx, c->sel_off, c->gain, c->bias, c->h_buf, c->rope_table, c->tau_dev, c->scores_buf,
+  void* bufs[] = {c->wqkv_t, c->wo_t, c->q_buf, c->attn_buf, c->q_new, c->sel_idx, c->sel_off, c->split_tiles, c->split_count, c->gain, c->bias, c->h_buf, c->rope_table, c->tau_dev, c->scores_buf,
                   c->stat_sum, c->act_idx, c->act_off};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -145,6 +147,8 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   c->wqkv_t = c->wo_t = c->q_buf = c->attn_buf = nullptr;
   c->q_new = nullptr;
   c->sel_idx = c->sel_off = nullptr;
+  c->split_tiles = nullptr;
+  c->split_count = nullptr;
   c->has_block = c->has_bias = false;
   c->gain = c->bias = c->h_buf = nullptr;
   c->rope_table = nullptr;
@@ -159,6 +163,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   // projection has enough tiles without cutting k)
   c->q_new_elems = (size_t)max_tok * c->score_width;
   if (max_tok <= 4096) c->q_new_elems *= 8;
+  const bool split = cfg->dtype == DARE_BF16 && gemm_may_split(max_tok, cfg->hidden);
   struct { void** p; size_t bytes; } allocs[] = {
       {&c->wqkv_t, 3 * d * d * c->esize},
       {&c->wo_t, d * d * c->esize},
@@ -167,6 +172,8 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
       {(void**)&c->q_new, c->q_new_elems * sizeof(float)},
       {(void**)&c->sel_idx, (size_t)max_tok * sizeof(int32_t)},
       {(void**)&c->sel_off, ((size_t)cfg->max_batch + 1) * sizeof(int32_t)},
+      {(void**)&c->split_tiles, split ? gemm_split_tiles_bytes() : 0},
+      {(void**)&c->split_count, split ? kSplitTiles * sizeof(int) : 0},
   };
   for (auto& a : allocs) {
     if (a.bytes == 0) continue;
@@ -184,6 +191,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
     e = launch_pack_weight(cfg->dtype, w3[i], cfg->hidden, cfg->hidden,
                            static_cast<char*>(c->wqkv_t) + (size_t)i * d * d * c->esize, cfg->hidden, s);
   if (e == hipSuccess) e = launch_pack_weight(cfg->dtype, wo, cfg->hidden, cfg->hidden, c->wo_t, cfg->hidden, s);
+  if (e == hipSuccess && split) e = launch_zero_words(c->split_count, kSplitTiles / 2, s);  // (64-bit words)
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) {
     dare_status st = fail_hip(nullptr, e, "weight packing");
@@ -266,6 +274,8 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
   g.rope = bx.rope;  // queries and keys are rotated as they are written; the fp32 copy
   g.rope_dh = cf.head_dim;  // that feeds the score is not
   g.rope_seq = seq;
+  g.split_tiles = ctx->split_tiles;
+  g.split_count = ctx->split_count;
   if (mode == DARE_MODE_DENSE || mode == DARE_MODE_O) {
     g.n = 3 * d;  // Q, K, V for every row (App. E.2; Alg. 2 lines 2 and 7)
     g.c[0] = ctx->q_buf;
@@ -385,6 +395,8 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
   o.m_max = n_tok;
   o.ldc = d;
   o.seg_n = d;
+  o.split_tiles = ctx->split_tiles;
+  o.split_count = ctx->split_count;
   if (sel_o) {
     o.idx = ctx->sel_idx;
     o.m_dev = n_sel;

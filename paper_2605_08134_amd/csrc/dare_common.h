@@ -57,8 +57,17 @@ struct GemmArgs {
   int32_t* sel_idx_out2;
   int32_t* sel_off_out;
   int32_t* sel_count_out;
+  // optional workspace for tiles whose k is cut in two (bf16, row count known on the host):
+  // gemm_split_tiles_bytes() bytes and kSplitTiles counters that are 0 before the first launch and
+  // that every launch leaves at 0; one launch at a time
+  float* split_tiles;
+  int* split_count;
 };
 constexpr int kSelMaxTokens = 2048;
+constexpr int kSplitTiles = 128;  // 256 x 128 tiles: two workgroups each fill the 256 CUs once
+constexpr size_t gemm_split_tiles_bytes() { return (size_t)kSplitTiles * 256 * 128 * sizeof(float); }
+// whether some projection of up to m rows to n columns can use that workspace
+constexpr bool gemm_may_split(long m, long n) { return (m + 255) / 256 * ((n + 127) / 128) >= kSplitTiles / 2; }
 
 // Rotation of the channel pairs (v0, v1) and (v2, v3) of four neighbouring output
 // columns col .. col + 3 (col a multiple of 4) of token tok.

@@ -69,6 +69,10 @@ struct GemmDev {
   int32_t* sel_idx_out2;
   int32_t* sel_off_out;
   int32_t* sel_count_out;
+  // two workgroups on the halves of k of one tile (gemm_tile_pp): [tiles] fp32 tiles and
+  // counters; nullptr = one workgroup per tile
+  float* split_tiles;
+  int* split_count;
 };
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
@@ -615,45 +619,54 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
 //     eight neighbouring output columns: 16-byte stores, half the store requests (the epilogue of a
 //     256 x 256 tile: 5.1 against 11 thousand cycles).  The chunk XOR of a weight row follows that
 //     order ((row >> 1) & 1 | ((row >> 3) & 3) << 1), which keeps the reads conflict-free.
-//   * LDS: two stages, each freed region by region.  The A rows of k-step kt are read in phase 0 only
+//   * LDS: two stages (three for TN = 2), each freed region by region.  The A rows of k-step kt are read in phase 0 only
 //     and column block j in phase j (block 0 already in the last phase of kt - 1); a region is filled
 //     again for kt + 2 from the phase after on, so a load has 3.5 (TN = 3) or 4.5 phases (TN = 4) of
 //     512 MFMA cycles to arrive.
 // Measured with gathered-row support and all (us, before: one k-loop that every wave runs in step):
 // 16384 x 12288 x 4096 1540 -> 1140 (1.45 PFLOP/s), 1024 x 12288 x 4096 98 -> 78, 1024 x 24576 x 4096
-// 206 -> 154.
+// 206 -> 154.  TN = 2 against 128 x 128 tiles: 2048 x 4096 x 4096 83 -> 59; with the k of a tile cut over
+// two workgroups (below; 64 to 128 tiles, which leave half of the CUs idle), inside a model step:
+// 1024 x 4096 x 12288 122 -> 97, 1024 x 4096 x 4096 50 -> 45.  A k-step takes 1610 cycles for 1024 of MFMAs:
+// every byte of LDS written or read for it at 128 B per cycle is 1400.
 constexpr int kPpRows = 256;
 template <int TN>
+constexpr int pp_stages() { return TN == 2 ? 3 : 2; }
+template <int TN>
 constexpr int pp_smem_bytes() {
-  return 2 * (kPpRows + 64 * TN) * ROW_BYTES;
+  return pp_stages<TN>() * (kPpRows + 64 * TN) * ROW_BYTES;
 }
 // chunk XOR of row r of a 32-row weight block
 __device__ __forceinline__ int pp_bkey(int r) { return ((r >> 1) & 1) | (((r >> 3) & 3) << 1); }
 
 // vblock, forced_tile_*, lidx and the result as in gemm_tile; called by all 512 threads.
-template <int TN>
+template <int TN, bool SPLIT = false>
 __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsigned char* smem, const int vblock,
                                              lds_idx_t lidx = nullptr) {
-  static_assert(TN == 3 || TN == 4, "column blocks of 32 per wave");
+  static_assert(TN >= 2 && TN <= 4, "column blocks of 32 per wave");
+  static_assert(!SPLIT || TN == 2, "k is cut for the narrow tile only");
   constexpr int BM = kPpRows, BN = 64 * TN;
-  constexpr int ASZ = BM * ROW_BYTES, BSZ = BN * ROW_BYTES, STAGE_BYTES = ASZ + BSZ;
+  constexpr int ASZ = BM * ROW_BYTES, BSZ = BN * ROW_BYTES, STAGE_BYTES = ASZ + BSZ, STAGES = pp_stages<TN>();
+  constexpr int PARTS = SPLIT ? 2 : 1;
 
   const int tiles_m = (m + BM - 1) / BM, tiles_n = (p.n + BN - 1) / BN;
-  const int total = tiles_m * tiles_n;
+  const int total = tiles_m * tiles_n * PARTS;
   const int per_xcd = (total + 7) >> 3;
   const int slot = vblock >> 3;
   if (slot >= per_xcd) return false;
   const int unit = (vblock & 7) * per_xcd + slot;
   if (unit >= total) return false;
+  const int tile = unit / PARTS;
   int tile_m, tile_n;
-  tile_of_unit(unit, tiles_m, tiles_n, tile_m, tile_n);
+  tile_of_unit(tile, tiles_m, tiles_n, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave >> 2, wm = wave & 3;
   const int l16 = lane & 15, kq = lane >> 4;
-  const int KT = p.k / BK;
+  const int KT = p.k / BK / PARTS;
+  const int k_first = SPLIT ? (unit & 1) * KT * BK : 0;
 
   // ---- global -> LDS: per k-step a wave loads 4 groups of 8 A rows and one group of 8 weight rows
   // of each column block (block j: rows 32 j .. of the left and of the right half, 64 in all).
@@ -665,14 +678,14 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
     const int r = (wave * 4 + i) * 8 + (lane >> 3);
     int row = m0 + r;
     row = row < m ? row : m - 1;
-    src_a[i] = p.a + row_token(p.idx, lidx, row) * p.lda + ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+    src_a[i] = p.a + row_token(p.idx, lidx, row) * p.lda + ((lane & 7) ^ ((r >> 1) & 7)) * 8 + k_first;
   }
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int r = wave * 8 + (lane >> 3);
     int col = n0 + (r >> 5) * (32 * TN) + j * 32 + (r & 31);
     col = col < p.n ? col : p.n - 1;
-    src_b[j] = p.wt + (long)col * p.k + ((lane & 7) ^ pp_bkey(r & 31)) * 8;
+    src_b[j] = p.wt + (long)col * p.k + ((lane & 7) ^ pp_bkey(r & 31)) * 8 + k_first;
   }
   long tok_out[4];
 #pragma unroll
@@ -683,16 +696,15 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   if (lidx) __syncthreads();
   // (k-steps past the end re-read the last one into a region nobody reads any more, so that the
   // number of loads in flight is the same in every phase of every k-step)
+  auto stage = [&](int kt) __attribute__((always_inline)) { return smem + (kt % STAGES) * STAGE_BYTES; };
   auto load_a = [&](int i, int kt) __attribute__((always_inline)) {
     const int k = kt < KT ? kt : KT - 1;
-    __builtin_amdgcn_global_load_lds((gptr_t)(src_a[i] + k * BK),
-                                     (lptr_t)(smem + (kt & 1) * STAGE_BYTES + (wave * 4 + i) * 1024), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((gptr_t)(src_a[i] + k * BK), (lptr_t)(stage(kt) + (wave * 4 + i) * 1024), 16, 0, 0);
   };
   auto load_b = [&](int j, int kt) __attribute__((always_inline)) {
     const int k = kt < KT ? kt : KT - 1;
     __builtin_amdgcn_global_load_lds((gptr_t)(src_b[j] + k * BK),
-                                     (lptr_t)(smem + (kt & 1) * STAGE_BYTES + ASZ + j * 64 * ROW_BYTES + wave * 1024),
-                                     16, 0, 0);
+                                     (lptr_t)(stage(kt) + ASZ + j * 64 * ROW_BYTES + wave * 1024), 16, 0, 0);
   };
 
   f32x4 acc[4][2 * TN];
@@ -713,14 +725,14 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   }
   bf16x8 fa[4][2], fb[2][2][2];  // A fragments of a k-step; weight fragments of two column blocks
   auto read_a = [&](int kt) __attribute__((always_inline)) {
-    const unsigned char* st = smem + (kt & 1) * STAGE_BYTES + a_off;
+    const unsigned char* st = stage(kt) + a_off;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int i = 0; i < 4; ++i) fa[i][ks] = *reinterpret_cast<const bf16x8*>(st + i * 16 * ROW_BYTES + a_koff[ks]);
   };
   auto read_b = [&](int set, int j, int kt) __attribute__((always_inline)) {
-    const unsigned char* st = smem + (kt & 1) * STAGE_BYTES + ASZ + j * 64 * ROW_BYTES;
+    const unsigned char* st = stage(kt) + ASZ + j * 64 * ROW_BYTES;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -768,7 +780,7 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   };
   auto none = []() __attribute__((always_inline)) {};
 #define DARE_N(n) std::integral_constant<int, n>{}
-#define DARE_A(i) [&]() __attribute__((always_inline)) { load_a(i, kt + 2); }
+#define DARE_A(i, d) [&]() __attribute__((always_inline)) { load_a(i, kt + d); }
 #define DARE_B(j, d) [&]() __attribute__((always_inline)) { load_b(j, kt + d); }
 
   // Loads in the order in which they are needed: block 0 of a k-step, its A rows, its blocks
@@ -783,7 +795,12 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   for (int i = 0; i < 4; ++i) load_a(i, 1);
   load_b(1, 1);
   if constexpr (TN == 4) load_b(2, 1);
-  wait_vmcnt_and_barrier<TN == 4 ? 10 : 8>();
+  if constexpr (TN == 2) {
+    load_b(0, 2);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_a(i, 2);
+  }
+  wait_vmcnt_and_barrier<TN == 4 ? 10 : (TN == 3 ? 8 : 12)>();
   read_b(0, 0, 0);
   if (grp == 1) asm volatile("s_barrier" ::: "memory");
   if constexpr (TN == 4) {
@@ -793,14 +810,24 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
       matrix(0, 0, DARE_B(3, 1), none, DARE_B(0, 2), none);
       read_b(1, 1, kt);
       end_mem(DARE_N(10));
-      matrix(1, 1, DARE_A(0), none, DARE_A(1), none);
+      matrix(1, 1, DARE_A(0, 2), none, DARE_A(1, 2), none);
       read_b(0, 2, kt);
       end_mem(DARE_N(10));
-      matrix(0, 2, DARE_A(2), none, DARE_A(3), none);
+      matrix(0, 2, DARE_A(2, 2), none, DARE_A(3, 2), none);
       read_b(1, 3, kt);
       read_b(0, 0, kt + 1);
       end_mem(DARE_N(8));
       matrix(1, 3, DARE_B(1, 2), none, DARE_B(2, 2), none);
+    }
+  } else if constexpr (TN == 2) {
+    for (int kt = 0; kt < KT; ++kt) {
+      read_a(kt);
+      end_mem(DARE_N(10));
+      matrix(0, 0, DARE_B(1, 2), none, DARE_B(0, 3), none);
+      read_b(1, 1, kt);
+      read_b(0, 0, kt + 1);
+      end_mem(DARE_N(8));
+      matrix(1, 1, DARE_A(0, 3), DARE_A(1, 3), DARE_A(2, 3), DARE_A(3, 3));
     }
   } else {
     auto kstep = [&](int kt, auto set_c) __attribute__((always_inline)) {
@@ -810,7 +837,7 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
       matrix(S, 0, DARE_B(2, 1), none, DARE_B(0, 2), none);
       read_b(S ^ 1, 1, kt);
       end_mem(DARE_N(7));
-      matrix(S ^ 1, 1, DARE_A(0), DARE_A(1), DARE_A(2), DARE_A(3));
+      matrix(S ^ 1, 1, DARE_A(0, 2), DARE_A(1, 2), DARE_A(2, 2), DARE_A(3, 2));
       read_b(S, 2, kt);
       read_b(S ^ 1, 0, kt + 1);
       end_mem(DARE_N(7));
@@ -828,6 +855,46 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
 #undef DARE_B
   if (grp == 0) asm volatile("s_barrier" ::: "memory");
   wait_vmcnt<0>();
+
+  // The workgroup that arrives first at a tile leaves its sums in the workspace and goes; the
+  // second one adds them to its own (a sum of two does not depend on which came first) and stores
+  // the tile.  It may have to wait until the sums are complete, and only then: the first
+  // workgroup is running by then and waits for nobody.  The sums are written and read at device
+  // scope (sc1: past whatever an XCD's L2 holds), and counted once every wave's stores have
+  // completed, so no fence, which would write back the whole L2 (20-40 us), is needed.
+  if constexpr (SPLIT) {
+    constexpr int kDeviceScope = 16;  // cache policy sc1
+    constexpr int kComplete = 4;      // counter: 1 per workgroup that has arrived, 4 for complete sums
+    const auto sums = __builtin_amdgcn_make_buffer_rsrc(p.split_tiles + (long)tile * (BM * BN), 0, BM * BN * 4, 0x00027000);
+    int* count = p.split_count + tile;
+    int* seen = reinterpret_cast<int*>(smem);
+    __syncthreads();
+    if (tid == 0) *seen = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (*seen == 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2 * TN; ++j)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), sums,
+                                                 ((i * 2 * TN + j) * 512 + tid) * 16, 0, kDeviceScope);
+      wait_vmcnt<0>();
+      __syncthreads();
+      if (tid == 0) __hip_atomic_fetch_add(count, kComplete, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return true;
+    }
+    if (tid == 0) {
+      while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < kComplete) __builtin_amdgcn_s_sleep(1);
+      __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2 * TN; ++j)
+        acc[i][j] += __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                   sums, ((i * 2 * TN + j) * 512 + tid) * 16, 0, kDeviceScope));
+  }
 
   // acc[i][2 j + h][e] = C[row, col], row = m0 + 64 wm + 16 i + l16, col = n0 + 32 TN grp + 32 j + 8 kq + 4 h + e
 #pragma unroll
@@ -930,11 +997,11 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) gemm_bf16_kernel(GemmDe
   gemm_tile<BM, BN, WAVES_M, WAVES_N, STAGES>(p, m, smem, threadIdx.x, blockIdx.x);
 }
 
-template <int TN>
+template <int TN, bool SPLIT>
 __global__ void __launch_bounds__(512) gemm_bf16_pp_kernel(GemmDev p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[pp_smem_bytes<TN>()];
   const int m = p.m_max;
-  gemm_tile_pp<TN>(p, m, smem, blockIdx.x);
+  gemm_tile_pp<TN, SPLIT>(p, m, smem, blockIdx.x);
 }
 
 // ---- row count read on the device: the tile shape follows it -------------------------
@@ -1161,6 +1228,8 @@ GemmDev to_dev(const GemmArgs& g) {
   p.sel_idx_out2 = g.sel_idx_out2;
   p.sel_off_out = g.sel_off_out;
   p.sel_count_out = g.sel_count_out;
+  p.split_tiles = g.split_tiles;
+  p.split_count = g.split_count;
   return p;
 }
 
@@ -1180,10 +1249,11 @@ hipError_t launch_fixed(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int TN>
+template <int TN, bool SPLIT = false>
 hipError_t launch_pp(const GemmArgs& g, hipStream_t s) {
   const int tiles = tiles_of(g.m_max, g.n, kPpRows, 64 * TN);
-  hipLaunchKernelGGL(gemm_bf16_pp_kernel<TN>, dim3(grid_for(tiles)), dim3(512), 0, s, to_dev(g));
+  hipLaunchKernelGGL((gemm_bf16_pp_kernel<TN, SPLIT>), dim3(grid_for(SPLIT ? 2 * tiles : tiles)), dim3(512), 0, s,
+                     to_dev(g));
   return hipGetLastError();
 }
 
@@ -1216,13 +1286,19 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   // wins: 256 x 192 costs about 3/4 of 256 x 256 (1870 against 2500 cycles per k-step), so the narrow
   // one is taken where it needs fewer quarter-rounds of the 256 CUs (1024 x 12288: one full round
   // against one round with 64 CUs idle, 78 against 85 us; 2331 x 12288: three against two, 209 against
-  // 198 us).  128 x 128 with 8 waves is the best shape when the larger ones would leave most CUs idle.
+  // 198 us).  256 x 128 takes over while it fills more than half of the CUs, and with two workgroups
+  // per tile while it fills half of that (16 k-steps each at least, or the hand-over, about 5 us, eats
+  // the gain).  128 x 128 with 8 waves is the best shape when the larger ones would leave most CUs idle.
   auto tiles = [&](int bm, int bn) { return tiles_of(g.m_max, g.n, bm, bn); };
+  const int ksteps = g.k / BK;
   if (g.k_parts <= 1) {
     const int t3 = tiles(kPpRows, 192), t4 = tiles(kPpRows, 256);
     const int q3 = 3 * ((t3 + 255) / 256), q4 = 4 * ((t4 + 255) / 256);
     if (t3 >= 224 && (q3 < q4 || t4 < 176)) return launch_pp<3>(g, s);
     if (t4 >= 176) return launch_pp<4>(g, s);
+    const int t2 = tiles(kPpRows, 128);
+    if (t2 > kSplitTiles) return launch_pp<2>(g, s);
+    if (g.split_tiles && t2 >= kSplitTiles / 2 && ksteps % 2 == 0 && ksteps >= 32) return launch_pp<2, true>(g, s);
   }
   if (g.m_max > 64 && g.n % 128 == 0 && tiles(128, 128) >= 64) return launch_fixed<128, 128, 4, 2, 4>(g, s);
   return launch_fixed<64, 64, 2, 2, 4>(g, s);

@@ -113,6 +113,8 @@ struct dare_model {
   uint8_t* mask;      // [max tokens] reuse mask of the layer being run
   int32_t* act_idx;   // frozen prefix: rows that are not frozen
   int32_t* act_off;
+  float* split_tiles; // workspace of projections whose k is cut in two, or nullptr
+  int* split_count;
   int rule, prefix;
   std::vector<void*> owned;
   std::string err;
@@ -203,9 +205,12 @@ dare_status dare_model_create(const dare_model_config* cfg, void* hip_stream, da
   m->layers.assign(cfg->n_layers, nullptr);
   m->mem.assign(cfg->n_layers, dare_model::LayerMem{});
   m->embed = m->final_gain = m->head_t = nullptr;
+  m->split_tiles = nullptr;
+  m->split_count = nullptr;
   m->rule = DARE_RULE_SCORE;
   m->prefix = 0;
   const size_t d = cfg->hidden, es = m->esize, tok = (size_t)max_tok;
+  const bool split = cfg->dtype == DARE_BF16 && gemm_may_split(max_tok, cfg->hidden);
   struct { void** p; size_t bytes; bool zero; } bufs[] = {
       {&m->x, tok * d * es, false},          {&m->h2, tok * d * es, false},
       {&m->h1, tok * d * es, false},
@@ -213,10 +218,12 @@ dare_status dare_model_create(const dare_model_config* cfg, void* hip_stream, da
       {&m->f, tok * d * es, false},          {&m->rows_buf, tok * d * es, false},
       {(void**)&m->mask, tok, false},        {(void**)&m->act_idx, tok * sizeof(int32_t), false},
       {(void**)&m->act_off, ((size_t)cfg->max_batch + 1) * sizeof(int32_t), false},
+      {(void**)&m->split_tiles, split ? gemm_split_tiles_bytes() : 0, false},
+      {(void**)&m->split_count, split ? kSplitTiles * sizeof(int) : 0, true},
       {&m->embed, (size_t)cfg->vocab * d * es, false}, {&m->final_gain, d * es, false},
   };
   for (auto& b : bufs)
-    if ((e = alloc(m, b.p, b.bytes, b.zero)) != hipSuccess) {
+    if (b.bytes && (e = alloc(m, b.p, b.bytes, b.zero)) != hipSuccess) {
       dare_status st = mfail_hip(nullptr, e, "hipMalloc");
       free_model(m);
       return st;
@@ -449,6 +456,8 @@ dare_status dare_model_step(dare_model* m, const int32_t* modes, const float* th
     h.ldc = d;
     h.seg_n = d;
     h.k_parts = 1;
+    h.split_tiles = m->split_tiles;
+    h.split_count = m->split_count;
     e = c.dtype == DARE_BF16 ? launch_gemm_bf16(h, s) : launch_gemm_f32(h, s);
     if (e != hipSuccess) return mfail_hip(m, e, "down projection");
     if (l + 1 < c.n_layers) {

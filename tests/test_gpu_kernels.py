@@ -61,6 +61,8 @@ def test_gemm_all_rows(B, dtype, m, n, k, seg):
     (961, 12096, 192, 12096, "256 x 192, an odd number of k-steps, one row in the last tile's last 64"),
     (1024, 12480, 128, 4160, "256 x 256, ragged columns"),
     (1793, 8192, 320, 4096, "256 x 256, five k-steps, one row in the last tile"),
+    (2100, 2112, 64, 2112, "256 x 128, one k-step, ragged both ways"),
+    (2305, 2048, 320, 2048, "256 x 128, five k-steps, one row in the last tile"),
 ])
 def test_gemm_all_rows_large_tiles(B, m, n, k, seg, tile):
     r = _rng(m + n + k)

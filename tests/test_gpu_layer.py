@@ -20,6 +20,23 @@ def _run(case, gl, state, mode, tau, **kw):
     return pu.check_step(got, want, state, mode, tau, case["dtype"]), got, want
 
 
+# ------------------------------------------------------------------ projections with k cut in two
+@pytest.mark.parametrize("seq", [1793, 2048])
+@pytest.mark.parametrize("mode", [orc.MODE_DENSE, orc.MODE_KV])
+def test_projection_cut_along_k(seq, mode):
+    """All-row projections to 2048 columns in 256 x 128 tiles, two workgroups on the halves of a
+    tile's k (1793 rows: one row in the last row tile).  Three calls in a row: the counters of the
+    workspace are back at 0 after each, and the sum does not depend on who arrives first."""
+    case = synth.make_case("llada8b", seed=seq, batch=1, seq=seq, hidden=2048, n_heads=16, head_dim=128)
+    state, gl = pu.oracle_fill(case), pu.GpuLayer(case)
+    _, first, _ = _run(case, gl, state, mode, synth.TAU_SEPARATING)
+    for _ in range(2):
+        again = gl.step(mode, synth.TAU_SEPARATING, case["x_cur"], state)
+        for key in ("out", "k_cache", "v_cache", "q_prev"):
+            assert np.array_equal(again[key], first[key]), key
+    gl.layer.destroy()
+
+
 # ------------------------------------------------------------------ tiny fp32 layer
 @pytest.fixture(scope="module")
 def tiny():
