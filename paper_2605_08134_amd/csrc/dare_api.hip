@@ -28,6 +28,7 @@ struct dare_ctx {
   int32_t* sel_off;    // [max_batch + 1]
   float* split_tiles;  // workspace of projections whose k is cut in two, or nullptr
   int* split_count;
+  int* score_count;    // [kScoreTiles] counters of the scored-column projection (bf16)
   // the block around the layer (dare_block_attach)
   bool has_block, has_bias;
   dare_block_config block;
@@ -88,7 +89,7 @@ struct DeviceGuard {
 
 void free_ctx(dare_ctx* c) {
   if (!c) return;
-  void* bufs[] = {c->wqkv_t, c->wo_t, c->q_buf, c->attn_buf, c->q_new, c->sel_idx, c->sel_off, c->split_tiles, c->split_count, c->gain, c->bias, c->h_buf, c->rope_table, c->tau_dev, c->scores_buf,
+  void* bufs[] = {c->wqkv_t, c->wo_t, c->q_buf, c->attn_buf, c->q_new, c->sel_idx, c->sel_off, c->split_tiles, c->split_count, c->score_count, c->gain, c->bias, c->h_buf, c->rope_table, c->tau_dev, c->scores_buf,
                   c->stat_sum, c->act_idx, c->act_off};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -148,7 +149,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   c->q_new = nullptr;
   c->sel_idx = c->sel_off = nullptr;
   c->split_tiles = nullptr;
-  c->split_count = nullptr;
+  c->split_count = c->score_count = nullptr;
   c->has_block = c->has_bias = false;
   c->gain = c->bias = c->h_buf = nullptr;
   c->rope_table = nullptr;
@@ -174,6 +175,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
       {(void**)&c->sel_off, ((size_t)cfg->max_batch + 1) * sizeof(int32_t)},
       {(void**)&c->split_tiles, split ? gemm_split_tiles_bytes() : 0},
       {(void**)&c->split_count, split ? kSplitTiles * sizeof(int) : 0},
+      {(void**)&c->score_count, cfg->dtype == DARE_BF16 ? kScoreTiles * sizeof(int) : 0},
   };
   for (auto& a : allocs) {
     if (a.bytes == 0) continue;
@@ -192,6 +194,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
                            static_cast<char*>(c->wqkv_t) + (size_t)i * d * d * c->esize, cfg->hidden, s);
   if (e == hipSuccess) e = launch_pack_weight(cfg->dtype, wo, cfg->hidden, cfg->hidden, c->wo_t, cfg->hidden, s);
   if (e == hipSuccess && split) e = launch_zero_words(c->split_count, kSplitTiles / 2, s);  // (64-bit words)
+  if (e == hipSuccess && c->score_count) e = launch_zero_words(c->score_count, kScoreTiles / 2, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) {
     dare_status st = fail_hip(nullptr, e, "weight packing");
@@ -245,7 +248,6 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
   const bool sel_o = mode == DARE_MODE_O || mode == DARE_MODE_KVO;
   const int32_t* n_sel = ctx->sel_off + batch;  // device count of refreshed tokens
   hipError_t e;
-  int k_parts = 1;
 
   // Frozen prefix: "all rows" below means the rows of this list, and their results go into
   // the caches at their token index as the refreshed rows' do.
@@ -258,58 +260,85 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
     return fail_hip(ctx, e, "active-row list");
   const int32_t* act_idx = pre ? ctx->act_idx : nullptr;
 
-  // 1. Query projection feeding the score (Alg. 1/2 line 2), together with whatever
-  //    else this mode projects for all rows.
-  GemmArgs g{};
-  g.a = hidden;
-  g.lda = d;
-  g.k = d;
-  g.m_max = n_act;
-  g.idx = act_idx;
-  g.ldc = d;
-  g.seg_n = d;
-  g.c32 = ctx->q_new;
-  g.c32_cols = sw;
-  g.wt = wq_t;
-  g.rope = bx.rope;  // queries and keys are rotated as they are written; the fp32 copy
-  g.rope_dh = cf.head_dim;  // that feeds the score is not
-  g.rope_seq = seq;
-  g.split_tiles = ctx->split_tiles;
-  g.split_count = ctx->split_count;
-  if (mode == DARE_MODE_DENSE || mode == DARE_MODE_O) {
-    g.n = 3 * d;  // Q, K, V for every row (App. E.2; Alg. 2 lines 2 and 7)
-    g.c[0] = ctx->q_buf;
-    g.c[1] = k_cache;
-    g.c[2] = v_cache;
-    g.rope_cols = 2 * d;
-  } else if (mode == DARE_MODE_KV) {
-    g.n = d;  // Q for every row (Alg. 1 line 2)
-    g.c[0] = ctx->q_buf;
-    g.rope_cols = d;
-  } else {
-    g.rope = nullptr;
-    g.n = sw;  // only the scored columns of Q for every row
-    // few output tiles, long k: cut k into ranges that the score kernel adds up
-    if (cf.dtype == DARE_BF16) {
-      const int tiles = ((n_act + 63) / 64) * ((sw + 63) / 64), ksteps = d / 64;
-      while (tiles * k_parts * 2 <= 256 && k_parts * 2 <= 8 && ksteps % (k_parts * 2) == 0 &&
-             ksteps / (k_parts * 2) >= 4 && (size_t)n_tok * sw * (k_parts * 2) <= ctx->q_new_elems)
-        k_parts *= 2;
-      g.k_parts = k_parts;
-      g.c32_part_stride = (long)n_tok * sw;
-    }
-  }
-  if ((e = gemm(ctx, g, s)) != hipSuccess) return fail_hip(ctx, e, "query projection");
-
-  // 2. Drift score, reuse decision, score-cache update (Alg. 1/2 lines 3-5).  Under the
-  //    quantile rule the score kernel's decision is replaced by the one the select
-  //    kernel takes; with statistics on, that kernel also (or only) adds up the scores.
   const bool by_rate = ctx->rule == DARE_RULE_QUANTILE;
   float* sc = scores;
   if (!sc && (by_rate || ctx->stats_on)) sc = ctx->scores_buf;
-  e = launch_score(ctx->q_new, sw, sw, k_parts, (long)n_tok * sw, q_prev, n_tok, by_rate ? 0.f : threshold,
-                   mode == DARE_MODE_DENSE || by_rate, sc, nullptr, reuse_mask, seq, P, s);
-  if (e != hipSuccess) return fail_hip(ctx, e, "score");
+
+  // 1. + 2. Query projection feeding the score (Alg. 1/2 line 2), together with whatever
+  //    else this mode projects for all rows; drift score, reuse decision, score-cache update
+  //    (Alg. 1/2 lines 3-5).  Under the quantile rule this decision is replaced by the one
+  //    the select kernel takes; with statistics on, that kernel also (or only) adds up the scores.
+  // Scored columns alone: few output tiles, long k.  k is cut into ranges whose sums are added up
+  // afterwards, so that workgroups can share a tile.
+  int k_ranges = 1;
+  if (mode == DARE_MODE_KVO && cf.dtype == DARE_BF16) {
+    const int tiles = ((n_act + 63) / 64) * ((sw + 63) / 64), ksteps = d / 64;
+    while (tiles * k_ranges * 2 <= 256 && k_ranges * 2 <= 8 && ksteps % (k_ranges * 2) == 0 &&
+           ksteps / (k_ranges * 2) >= 4 && (size_t)n_tok * sw * (k_ranges * 2) <= ctx->q_new_elems)
+      k_ranges *= 2;
+  }
+  if (mode == DARE_MODE_KVO && cf.dtype == DARE_BF16 && sw == cf.head_dim) {
+    // only the scored columns of Q for every row, scored in the same launch
+    ScoreProjArgs g{};
+    g.a = hidden;
+    g.wt = wq_t;
+    g.k = d;
+    g.width = sw;
+    g.k_ranges = k_ranges;
+    g.m = n_act;
+    g.idx = act_idx;
+    g.q_prev = q_prev;
+    g.threshold = by_rate ? 0.f : threshold;
+    g.force_refresh = by_rate;
+    g.scores = sc;
+    g.mask = reuse_mask;
+    g.batch = batch;
+    g.seq = seq;
+    g.prefix = P;
+    g.sums = ctx->q_new;
+    g.sums_elems = ctx->q_new_elems;
+    g.count = ctx->score_count;
+    if ((e = launch_score_proj(g, s)) != hipSuccess) return fail_hip(ctx, e, "scored query columns");
+  } else {
+    GemmArgs g{};
+    g.a = hidden;
+    g.lda = d;
+    g.k = d;
+    g.m_max = n_act;
+    g.idx = act_idx;
+    g.ldc = d;
+    g.seg_n = d;
+    g.c32 = ctx->q_new;
+    g.c32_cols = sw;
+    g.wt = wq_t;
+    g.rope = bx.rope;  // queries and keys are rotated as they are written; the fp32 copy
+    g.rope_dh = cf.head_dim;  // that feeds the score is not
+    g.rope_seq = seq;
+    g.split_tiles = ctx->split_tiles;
+    g.split_count = ctx->split_count;
+    if (mode == DARE_MODE_DENSE || mode == DARE_MODE_O) {
+      g.n = 3 * d;  // Q, K, V for every row (App. E.2; Alg. 2 lines 2 and 7)
+      g.c[0] = ctx->q_buf;
+      g.c[1] = k_cache;
+      g.c[2] = v_cache;
+      g.rope_cols = 2 * d;
+    } else if (mode == DARE_MODE_KV) {
+      g.n = d;  // Q for every row (Alg. 1 line 2)
+      g.c[0] = ctx->q_buf;
+      g.rope_cols = d;
+    } else {
+      g.rope = nullptr;
+      g.n = sw;  // only the scored columns of Q for every row
+      if (cf.dtype == DARE_BF16) {
+        g.k_parts = k_ranges;
+        g.c32_part_stride = (long)n_tok * sw;
+      }
+    }
+    if ((e = gemm(ctx, g, s)) != hipSuccess) return fail_hip(ctx, e, "query projection");
+    e = launch_score(ctx->q_new, sw, sw, g.k_parts > 1 ? g.k_parts : 1, (long)n_tok * sw, q_prev, n_tok, by_rate ? 0.f : threshold,
+                     mode == DARE_MODE_DENSE || by_rate, sc, nullptr, reuse_mask, seq, P, s);
+    if (e != hipSuccess) return fail_hip(ctx, e, "score");
+  }
   if (by_rate || ctx->stats_on) {
     const int rank = by_rate ? (int)ceilf(threshold * (float)(seq - P)) : -1;
     double* sum = ctx->stats_on ? ctx->stat_sum : nullptr;
@@ -444,7 +473,7 @@ dare_status dare_layer_step(dare_ctx* ctx, int mode, float threshold, int batch,
 namespace {
 
 // Layout of the static scratch (bytes): queries | attention rows | fp32 scored query (up to
-// 8 k-range slabs) | refreshed-row list | per-sequence offsets.
+// 8 k-range slabs) | refreshed-row list | per-sequence offsets | counters of the scored columns.
 constexpr size_t kStaticRowBytes = DARE_STATIC_MAX_ROW_BYTES;          // batch * seq * hidden * sizeof(dtype)
 constexpr size_t kStaticScoreElems = DARE_STATIC_MAX_SCORE_ELEMS;     // fp32 elements of the scored query, slabs included
 constexpr size_t kStaticMaxTokens = kStaticRowBytes / (64 * 2);        // hidden >= 64, two bytes per element
@@ -453,9 +482,10 @@ constexpr size_t kStaticOffAttn = kStaticOffQ + kStaticRowBytes;
 constexpr size_t kStaticOffScore = kStaticOffAttn + kStaticRowBytes;
 constexpr size_t kStaticOffIdx = kStaticOffScore + kStaticScoreElems * sizeof(float);
 constexpr size_t kStaticOffOff = kStaticOffIdx + kStaticMaxTokens * sizeof(int32_t);
-constexpr size_t kStaticBytes = kStaticOffOff + (kStaticMaxTokens + 64) * sizeof(int32_t);
+constexpr size_t kStaticOffCount = kStaticOffOff + (kStaticMaxTokens + 64) * sizeof(int32_t);
+constexpr size_t kStaticBytes = kStaticOffCount + kScoreTiles * sizeof(int);
 static_assert(kStaticOffAttn % 256 == 0 && kStaticOffScore % 256 == 0 && kStaticOffIdx % 256 == 0 &&
-                  kStaticOffOff % 256 == 0, "scratch regions must stay aligned");
+                  kStaticOffOff % 256 == 0 && kStaticOffCount % 256 == 0, "scratch regions must stay aligned");
 
 }  // namespace
 
@@ -549,8 +579,13 @@ dare_status dare_layer_step_static(const dare_config* cfg, const void* wqkv_t, c
   c.q_new_elems = kStaticScoreElems;
   c.sel_idx = reinterpret_cast<int32_t*>(base + kStaticOffIdx);
   c.sel_off = reinterpret_cast<int32_t*>(base + kStaticOffOff);
+  c.score_count = reinterpret_cast<int*>(base + kStaticOffCount);
   c.rule = DARE_RULE_SCORE;
   st = check_step_args(&c, mode, threshold, batch, seq, hidden, q_prev, k_cache, v_cache, o_cache, out, reuse_mask);
+  // (counters that overlapping calls, which race for this array, may have left behind)
+  if (st == DARE_OK && mode == DARE_MODE_KVO && cfg->dtype == DARE_BF16 &&
+      (e = launch_zero_words(c.score_count, kScoreTiles / 2, static_cast<hipStream_t>(hip_stream))) != hipSuccess)
+    st = fail_hip(&c, e, "counters");
   if (st == DARE_OK)
     st = step_impl(&c, mode, threshold, batch, seq, hidden, q_prev, k_cache, v_cache, o_cache, out, reuse_mask,
                    sel_idx, sel_count, scores, BlockExtras{nullptr, nullptr}, hip_stream);

@@ -82,6 +82,41 @@ __device__ __forceinline__ void rope_rotate4(const float* __restrict__ table, in
   v2 = a2;
   v3 = a3;
 }
+
+// Drift score of one token from the sums <q, p>, |q|^2, |p|^2 (Sec. 3.1 eq. 1)
+__device__ __forceinline__ float drift_score(float dot, float nq, float np) {
+  return 1.0f - dot / fmaxf(sqrtf(nq * np), 1e-30f);
+}
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// Scored query columns of the listed rows and what follows from them in one launch: drift score,
+// reuse decision, score-cache update (bf16; width 64 or 128).
+struct ScoreProjArgs {
+  const void* a;         // [*, k] hidden states
+  const void* wt;        // [width, k] packed weight of the scored columns
+  int k, width;
+  int k_ranges;          // 1, 2, 4 or 8, dividing k / 64: the sum over k is that of this many ranges
+  int m;                 // rows
+  const int32_t* idx;    // their token ids, or nullptr: 0 .. m-1
+  float* q_prev;         // [*, width] score cache
+  float threshold;
+  int force_refresh;
+  float* scores;         // [*] or nullptr
+  uint8_t* mask;         // [*]
+  int batch, seq, prefix;  // tokens [0, prefix) of every sequence: mask 1, score 0, nothing else
+  // workspace for row tiles whose k is cut over workgroups: fp32 sums, and counters that are 0
+  // before the launch and that the launch leaves at 0; nullptr = one workgroup per row tile
+  float* sums;
+  size_t sums_elems;
+  int* count;            // [kScoreTiles]
+};
+constexpr int kScoreTiles = 256;
+hipError_t launch_score_proj(const ScoreProjArgs& g, hipStream_t s);
+
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s);
 

@@ -1197,6 +1197,218 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
   }
 }
 
+// ---- scored query columns of all rows, with the score ---------------------------------
+// One launch for what were three dependent steps of a few microseconds each (projection in
+// k-range slabs, a second kernel that added the slabs and scored): BM rows x all WIDTH scored
+// columns per workgroup, so that a workgroup holds whole queries and can score them.  What bounds
+// it is the operands that a CU pulls, (BM + WIDTH) rows of k; with few row tiles k is cut over
+// KP workgroups, each of which leaves its sums at device scope (as in gemm_tile_pp), and the
+// last one to arrive adds them up.
+// Sum over k: that of the caller's ranges of k, added up as a binary tree whatever BM and KP are,
+// so the route (workspace or not) does not show in a query.
+// Measured (projection + score + the gap between them -> this launch, inside a step): 1024 rows
+// 7.6 + 4.9 + 2.4 -> 11 us, 8192 rows 45 + 7.7 + 2.4 -> 38 us, 16384 rows 52 + 9.4 + 2.4 -> 45 us.
+struct ScoreProjDev {
+  const bf16_t* a;
+  const bf16_t* wt;
+  const int32_t* idx;
+  float* q_prev;
+  float* scores;
+  uint8_t* mask;
+  float* sums;
+  int* count;
+  int k, m, k_parts, ranges;  // workgroups per row tile; ranges of the summation tree
+  int force_refresh, batch, seq, prefix;
+  float threshold;
+};
+
+template <int BM, int WIDTH, int WAVES_M, int WAVES_N>
+__global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) score_proj_kernel(ScoreProjDev p) {
+  constexpr int NW = WAVES_M * WAVES_N, NT = NW * 64, STAGES = 5;
+  constexpr int WM = BM / WAVES_M, WN = WIDTH / WAVES_N;
+  constexpr int TM = WM / 16, TN = WN / 16, KS = BK / 32;
+  constexpr int STAGE_BYTES = (BM + WIDTH) * ROW_BYTES;
+  constexpr int GROUPS = (BM + WIDTH) / 8;
+  constexpr int LPW = (GROUPS + NW - 1) / NW;  // surplus loads repeat the last group
+  constexpr int LDQ = WIDTH + 4;
+  static_assert(WM % 16 == 0 && WN % 16 == 0 && BM % NW == 0, "wave tiles of 16 x 16, whole rows per wave");
+  static_assert(BM * LDQ * 4 <= STAGES * STAGE_BYTES, "the queries must fit into the stage memory");
+  static_assert(LPW * (STAGES - 1) < 64, "vmcnt range");
+  // (one LDS array only: with a second one the compiler tracks which of them a global -> LDS load
+  // may write, and puts s_waitcnt vmcnt(0) in front of the fragment reads, which drains the ring)
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE_BYTES];
+  int& arrived = *reinterpret_cast<int*>(smem);
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // frozen tokens: always reused, never scored
+  for (long i = (long)blockIdx.x * NT + tid; i < (long)p.batch * p.prefix; i += (long)gridDim.x * NT) {
+    const long tok = i / p.prefix * p.seq + i % p.prefix;
+    if (p.scores) p.scores[tok] = 0.f;
+    p.mask[tok] = 1;
+  }
+
+  const int tile = blockIdx.x / p.k_parts, part = blockIdx.x % p.k_parts;
+  const int m0 = tile * BM;
+  const int wave_m = wave % WAVES_M, wave_n = wave / WAVES_M;
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int KT = p.k / BK / p.k_parts;      // k-steps of this workgroup
+  const int range = p.k / BK / p.ranges;    // k-steps of a range of the tree
+
+  const bf16_t* src[LPW];
+  int grp[LPW];
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) {
+    grp[i] = wave * LPW + i < GROUPS ? wave * LPW + i : GROUPS - 1;
+    const int r = grp[i] * 8 + (lane >> 3);
+    const long off = (long)part * KT * BK + ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+    if (r < BM) {
+      const int row = m0 + r < p.m ? m0 + r : p.m - 1;
+      src[i] = p.a + row_token(p.idx, nullptr, row) * p.k + off;
+    } else {
+      src[i] = p.wt + (long)(r - BM) * p.k + off;
+    }
+  }
+  auto issue_loads = [&](int kt) __attribute__((always_inline)) {
+    unsigned char* base = smem + (kt % STAGES) * STAGE_BYTES;
+    const int k = kt < KT ? kt : KT - 1;
+#pragma unroll
+    for (int i = 0; i < LPW; ++i)
+      __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + k * BK), (lptr_t)(base + grp[i] * 8 * ROW_BYTES), 16, 0, 0);
+  };
+
+  f32x4 acc[TM][TN], level[3][TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = level[0][i][j] = level[1][i][j] = level[2][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int sw = (l16 >> 1) & 7;
+  const int a_row_off = (wave_m * WM + l16) * ROW_BYTES;
+  const int b_row_off = (BM + wave_n * WN + l16) * ROW_BYTES;
+
+#pragma unroll
+  for (int s = 0; s < STAGES - 1; ++s) issue_loads(s);
+  int done = 0, in_range = 0;  // ranges complete, k-steps of the current one
+  for (int kt = 0; kt < KT; ++kt) {
+    wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
+    issue_loads(kt + STAGES - 1);
+    const unsigned char* st = smem + (kt % STAGES) * STAGE_BYTES;
+    bf16x8 fa[KS][TM], fb[KS][TN];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int koff = ((ks * 4 + kq) ^ sw) * 16;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[ks][i] = *reinterpret_cast<const bf16x8*>(st + a_row_off + i * 16 * ROW_BYTES + koff);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[ks][j] = *reinterpret_cast<const bf16x8*>(st + b_row_off + j * 16 * ROW_BYTES + koff);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    if (++in_range < range) continue;
+    // a range is complete: up the tree (the last one of the workgroup ends as its whole sum in acc)
+    in_range = 0;
+    const bool last = kt + 1 == KT;
+    bool carry = true;
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+      if (!carry) break;
+      if ((done >> l) & 1) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = level[l][i][j] + acc[i][j];
+      } else if (!last) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            level[l][i][j] = acc[i][j];
+            acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
+        carry = false;
+      }
+    }
+    ++done;
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+
+  if (p.k_parts > 1) {
+    constexpr int kDeviceScope = 16;  // cache policy sc1
+    constexpr int kSlot = BM * WIDTH * 4;
+    const auto slots = __builtin_amdgcn_make_buffer_rsrc(p.sums + (long)tile * p.k_parts * (BM * WIDTH), 0, p.k_parts * kSlot, 0x00027000);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), slots, part * kSlot + ((i * TN + j) * NT + tid) * 16, 0, kDeviceScope);
+    wait_vmcnt<0>();
+    __syncthreads();
+    if (tid == 0) arrived = __hip_atomic_fetch_add(p.count + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (arrived != p.k_parts - 1) return;
+    if (tid == 0) __hip_atomic_store(p.count + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        f32x4 w[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          w[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+          if (q < p.k_parts)
+            w[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(slots, q * kSlot + ((i * TN + j) * NT + tid) * 16, 0, kDeviceScope));
+        }
+        f32x4 v = w[0] + w[1];  // (the tree above the workgroups)
+        if (p.k_parts > 2) v += w[2] + w[3];
+        if (p.k_parts > 4) v += (w[4] + w[5]) + (w[6] + w[7]);
+        acc[i][j] = v;
+      }
+  }
+
+  // acc[i][j][e] = query[row, col]: row = wave_m*WM + 16 i + l16, col = wave_n*WN + 16 j + 4 kq + e
+  float* qs = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      *reinterpret_cast<f32x4*>(qs + (wave_m * WM + i * 16 + l16) * LDQ + wave_n * WN + j * 16 + kq * 4) = acc[i][j];
+  __syncthreads();
+  // score: a wave per row, two neighbouring channels per lane, the three sums with one lane
+  // assignment and one butterfly (an unchanged query gives dot == |q|^2 == |p|^2 bit for bit)
+  constexpr int RPW = BM / NW;
+  const int c = lane * 2;
+  f32x2 prev[RPW];
+  long tok[RPW];
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) {
+    const int row = m0 + wave * RPW + r;
+    tok[r] = row_token(p.idx, nullptr, row < p.m ? row : p.m - 1);
+    prev[r] = c < WIDTH ? *reinterpret_cast<const f32x2*>(p.q_prev + tok[r] * WIDTH + c) : f32x2{0.f, 0.f};
+  }
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) {
+    if (m0 + wave * RPW + r >= p.m) break;
+    f32x2 q = {0.f, 0.f};
+    if (c < WIDTH) {
+      q = *reinterpret_cast<const f32x2*>(qs + (wave * RPW + r) * LDQ + c);
+      *reinterpret_cast<f32x2*>(p.q_prev + tok[r] * WIDTH + c) = q;  // the score cache takes this step's query
+    }
+    const float dot = wave_sum(fmaf(q[1], prev[r][1], q[0] * prev[r][0]));
+    const float nq = wave_sum(fmaf(q[1], q[1], q[0] * q[0]));
+    const float np = wave_sum(fmaf(prev[r][1], prev[r][1], prev[r][0] * prev[r][0]));
+    if (lane == 0) {
+      const float s = drift_score(dot, nq, np);
+      if (p.scores) p.scores[tok[r]] = s;
+      p.mask[tok[r]] = (!p.force_refresh && s <= p.threshold) ? 1 : 0;
+    }
+  }
+}
+
 GemmDev to_dev(const GemmArgs& g) {
   GemmDev p;
   p.a = static_cast<const bf16_t*>(g.a);
@@ -1302,6 +1514,62 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   }
   if (g.m_max > 64 && g.n % 128 == 0 && tiles(128, 128) >= 64) return launch_fixed<128, 128, 4, 2, 4>(g, s);
   return launch_fixed<64, 64, 2, 2, 4>(g, s);
+}
+
+hipError_t launch_score_proj(const ScoreProjArgs& g, hipStream_t s) {
+  if (g.m == 0) return hipSuccess;
+  const int ranges = g.k_ranges;
+  // Rows per workgroup and workgroups per row tile, by what a workgroup takes (us): its operands at
+  // 100 KB/us; when k is cut, 3 for the hand-over and the slots that the last workgroup reads back at
+  // 40 KB/us; 0.04 per row to score.  Fitted at 1024 rows of 4096, width 128 (rows / workgroups per
+  // tile): 16/4 11.0 us, 16/2 13.6, 32/4 12.7, 32/8 13.1, 64/4 16.1, 64/8 16.4.
+  int bm = 64, kp = 1;
+  double best = 1e30;
+  for (int b = 16; b <= 64; b *= 2)
+    for (int q = 1; q <= ranges; q *= 2) {
+      const long tiles = (g.m + b - 1) / b;
+      const size_t slots = (size_t)tiles * q * b * g.width;
+      if (q > 1 && (!g.sums || tiles > kScoreTiles || slots > g.sums_elems)) continue;
+      const double rounds = (double)((tiles * q + 255) / 256);
+      const double pull = rounds * (b + g.width) * (double)(g.k / q) * 2 / 100e3;
+      const double cost = pull + (q > 1 ? 3.0 + (double)q * b * g.width * 4 / 40e3 : 0.0) + 0.04 * b;
+      if (cost < best) {
+        best = cost;
+        bm = b;
+        kp = q;
+      }
+    }
+  ScoreProjDev p;
+  p.a = static_cast<const bf16_t*>(g.a);
+  p.wt = static_cast<const bf16_t*>(g.wt);
+  p.idx = g.idx;
+  p.q_prev = g.q_prev;
+  p.scores = g.scores;
+  p.mask = g.mask;
+  p.sums = g.sums;
+  p.count = g.count;
+  p.k = g.k;
+  p.m = g.m;
+  p.k_parts = kp;
+  p.ranges = ranges;
+  p.force_refresh = g.force_refresh;
+  p.batch = g.batch;
+  p.seq = g.seq;
+  p.prefix = g.prefix;
+  p.threshold = g.threshold;
+  const dim3 grid((unsigned)((g.m + bm - 1) / bm * kp));
+  if (g.width == 128) {
+    if (bm == 16) hipLaunchKernelGGL((score_proj_kernel<16, 128, 1, 8>), grid, dim3(512), 0, s, p);
+    else if (bm == 32) hipLaunchKernelGGL((score_proj_kernel<32, 128, 2, 4>), grid, dim3(512), 0, s, p);
+    else hipLaunchKernelGGL((score_proj_kernel<64, 128, 2, 4>), grid, dim3(512), 0, s, p);
+  } else if (g.width == 64) {
+    if (bm == 16) hipLaunchKernelGGL((score_proj_kernel<16, 64, 1, 4>), grid, dim3(256), 0, s, p);
+    else if (bm == 32) hipLaunchKernelGGL((score_proj_kernel<32, 64, 2, 4>), grid, dim3(512), 0, s, p);
+    else hipLaunchKernelGGL((score_proj_kernel<64, 64, 4, 2>), grid, dim3(512), 0, s, p);
+  } else {
+    return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace dare

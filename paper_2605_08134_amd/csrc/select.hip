@@ -33,12 +33,6 @@ __global__ void __launch_bounds__(256) pack_weight_kernel(const T* __restrict__ 
 // butterfly, so a token whose query did not change gets dot == |q|^2 == |p|^2
 // bit for bit and a score of exactly 0.
 // ---------------------------------------------------------------------------
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 __global__ void __launch_bounds__(256) score_kernel(const float* __restrict__ q_new, int ld_new,
                                                    int width, int n_parts, long part_stride,
                                                    float* __restrict__ q_prev,
@@ -89,8 +83,7 @@ __global__ void __launch_bounds__(256) score_kernel(const float* __restrict__ q_
   nq = wave_sum(nq);
   np = wave_sum(np);
   if (lane == 0) {
-    const float den = fmaxf(sqrtf(nq * np), 1e-30f);
-    const float s = 1.0f - dot / den;
+    const float s = drift_score(dot, nq, np);
     if (scores) scores[tok] = s;
     if (scores2) scores2[tok] = s;
     mask[tok] = (!force_refresh && s <= threshold) ? 1 : 0;

@@ -37,6 +37,52 @@ def test_projection_cut_along_k(seq, mode):
     gl.layer.destroy()
 
 
+# ------------------------------------------------------------------ scored columns with the score
+@pytest.mark.parametrize("batch,seq,hidden,heads,dh,prefix", [
+    (1, 37, 256, 4, 64, 0), (3, 333, 512, 4, 128, 11),        # 16 rows per workgroup, ragged
+    (2, 1000, 4096, 32, 128, 0), (1, 1000, 2048, 32, 64, 3),  # row tiles with k cut over workgroups
+    (4, 4075, 512, 4, 128, 0), (4, 4075, 512, 8, 64, 100),    # 64 rows per workgroup
+])
+def test_scored_columns(batch, seq, hidden, heads, dh, prefix):
+    """Score cache, scores and masks of the launch that projects the scored columns and scores them,
+    against float64 on the same bf16 inputs (fp32 sums over k: 2e-6 relative; the score is a
+    difference of 1 and a ratio of such sums: 2e-6 absolute).  The second call sees its own
+    queries: every score is exactly 0, whichever workgroup added the sums."""
+    from paper_2605_08134_amd import binding as B
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq + hidden)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device="cuda")
+    w = [(rnd(hidden, hidden) * 0.02).bfloat16() for _ in range(4)]
+    layer = B.DareLayer(*w, n_heads=heads, max_batch=batch, max_seq=seq)
+    layer.set_prefix(prefix)
+    x = rnd(batch, seq, hidden).bfloat16()
+    q = x.double().view(-1, hidden) @ w[0][:, :dh].double()
+    prev = (q + 0.3 * q.std() * rnd(batch * seq, dh).double()).float()
+    q_prev = prev.clone().view(batch, seq, dh)
+    caches = [torch.zeros_like(x) for _ in range(3)]
+    mask = torch.full((batch, seq), 7, dtype=torch.uint8, device="cuda")
+    scores = torch.full((batch, seq), float("nan"), device="cuda")
+    step = lambda: layer.layer_step(B.MODE_KVO, 2.5, x, q_prev, *caches, caches[2], mask, scores=scores)
+    step()
+    frozen = torch.zeros(batch, seq, dtype=torch.bool, device="cuda")
+    frozen[:, :prefix] = True
+    f = frozen.view(-1)
+    p = prev.double()
+    want = 1 - (q * p).sum(1) / (q.norm(dim=1) * p.norm(dim=1))
+    want[f] = 0
+    got = q_prev.view(-1, dh)
+    assert float((got.double() - q)[~f].norm() / q[~f].norm()) <= 2e-6
+    assert torch.equal(got[f], prev[f])
+    assert float((scores.view(-1).double() - want).abs().max()) <= 2e-6
+    assert bool((mask == 1).all())
+    before = q_prev.clone()
+    for _ in range(2):
+        scores.fill_(float("nan"))
+        step()
+        assert bool((scores == 0).all()) and torch.equal(q_prev, before)
+    layer.destroy()
+
+
 # ------------------------------------------------------------------ tiny fp32 layer
 @pytest.fixture(scope="module")
 def tiny():
