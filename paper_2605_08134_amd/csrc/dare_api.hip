@@ -28,6 +28,8 @@ struct dare_ctx {
   int32_t* sel_off;    // [max_batch + 1]
   float* split_tiles;  // workspace of projections whose k is cut in two, or nullptr
   int* split_count;
+  float* part_out;     // workspace of refreshed-row attention whose keys are cut, or nullptr
+  int* part_count;
   int* score_count;    // [kScoreTiles] counters of the scored-column projection (bf16)
   // the block around the layer (dare_block_attach)
   bool has_block, has_bias;
@@ -89,7 +91,7 @@ struct DeviceGuard {
 
 void free_ctx(dare_ctx* c) {
   if (!c) return;
-  void* bufs[] = {c->wqkv_t, c->wo_t, c->q_buf, c->attn_buf, c->q_new, c->sel_idx, c->sel_off, c->split_tiles, c->split_count, c->score_count, c->gain, c->bias, c->h_buf, c->rope_table, c->tau_dev, c->scores_buf,
+  void* bufs[] = {c->wqkv_t, c->wo_t, c->q_buf, c->attn_buf, c->q_new, c->sel_idx, c->sel_off, c->split_tiles, c->split_count, c->score_count, c->part_out, c->part_count, c->gain, c->bias, c->h_buf, c->rope_table, c->tau_dev, c->scores_buf,
                   c->stat_sum, c->act_idx, c->act_off};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -149,7 +151,8 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   c->q_new = nullptr;
   c->sel_idx = c->sel_off = nullptr;
   c->split_tiles = nullptr;
-  c->split_count = c->score_count = nullptr;
+  c->split_count = c->score_count = c->part_count = nullptr;
+  c->part_out = nullptr;
   c->has_block = c->has_bias = false;
   c->gain = c->bias = c->h_buf = nullptr;
   c->rope_table = nullptr;
@@ -165,6 +168,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   c->q_new_elems = (size_t)max_tok * c->score_width;
   if (max_tok <= 4096) c->q_new_elems *= 8;
   const bool split = cfg->dtype == DARE_BF16 && gemm_may_split(max_tok, cfg->hidden);
+  const bool cut = cfg->dtype == DARE_BF16 && attn_may_cut(cfg->max_seq);
   struct { void** p; size_t bytes; } allocs[] = {
       {&c->wqkv_t, 3 * d * d * c->esize},
       {&c->wo_t, d * d * c->esize},
@@ -175,6 +179,8 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
       {(void**)&c->sel_off, ((size_t)cfg->max_batch + 1) * sizeof(int32_t)},
       {(void**)&c->split_tiles, split ? gemm_split_tiles_bytes() : 0},
       {(void**)&c->split_count, split ? kSplitTiles * sizeof(int) : 0},
+      {(void**)&c->part_out, cut ? attn_parts_elems(cfg->head_dim) * sizeof(float) : 0},
+      {(void**)&c->part_count, cut ? kAttnParts * sizeof(int) : 0},
       {(void**)&c->score_count, cfg->dtype == DARE_BF16 ? kScoreTiles * sizeof(int) : 0},
   };
   for (auto& a : allocs) {
@@ -194,6 +200,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
                            static_cast<char*>(c->wqkv_t) + (size_t)i * d * d * c->esize, cfg->hidden, s);
   if (e == hipSuccess) e = launch_pack_weight(cfg->dtype, wo, cfg->hidden, cfg->hidden, c->wo_t, cfg->hidden, s);
   if (e == hipSuccess && split) e = launch_zero_words(c->split_count, kSplitTiles / 2, s);  // (64-bit words)
+  if (e == hipSuccess && cut) e = launch_zero_words(c->part_count, kAttnParts / 2, s);
   if (e == hipSuccess && c->score_count) e = launch_zero_words(c->score_count, kScoreTiles / 2, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) {
@@ -412,6 +419,8 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
   a.idx = sel_o ? ctx->sel_idx : act_idx;
   a.sel_off = sel_o ? ctx->sel_off : (pre ? ctx->act_off : nullptr);
   a.many_rows = !sel_o && pre;
+  a.part_out = ctx->part_out;
+  a.part_count = ctx->part_count;
   if ((e = attn(ctx, a, s)) != hipSuccess) return fail_hip(ctx, e, "attention");
 
   // 6. Output projection (Alg. 1 line 11; Alg. 2 lines 9-11 with the cache after Wo).

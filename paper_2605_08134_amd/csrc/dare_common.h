@@ -129,7 +129,16 @@ struct AttnArgs {
   const int32_t* idx;      // optional selected rows
   const int32_t* sel_off;  // [batch+1] when idx != nullptr
   bool many_rows;          // the listed rows are most of each sequence (a frozen prefix), not a few
+  // optional workspace for query blocks whose keys are cut over workgroups (bf16, refreshed rows):
+  // attn_parts_elems() floats and kAttnParts counters that are 0 before the first launch and
+  // that every launch leaves at 0; one launch at a time
+  float* part_out;
+  int* part_count;
 };
+constexpr int kAttnParts = 256;  // parts of a launch, at most: one per CU
+constexpr size_t attn_parts_elems(int head_dim) { return (size_t)kAttnParts * 64 * 2 * (head_dim / 2 + 2); }
+// whether a step of up to seq tokens per sequence can use that workspace (parts of 8 x 128 keys)
+constexpr bool attn_may_cut(int seq) { return (seq + 127) / 128 >= 16; }
 hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t s);
 

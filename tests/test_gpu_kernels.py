@@ -362,6 +362,38 @@ def test_attention_selected_rows(B, dtype, batch, seq, heads, dh, frac):
             assert_close(got[sl][rows], want, dtype, slack=8.0)
 
 
+@pytest.mark.parametrize("batch,seq,heads,dh,frac", [
+    (5, 300, 32, 64, 0.6),        # more than 256 blocks of 64 rows: blocks of 128
+    (70, 40, 1, 64, 0.5),         # more sequences than lanes
+    (2, 300, 32, 128, 0.9),       # 64 x 5 blocks: 128 rows, ragged
+])
+def test_attention_block_layout_from_the_counts(B, batch, seq, heads, dh, frac):
+    """Per element: a probability p_i rounded to bf16 is off by at most 2^-9 p_i, in the sum over
+    p_i v_i and in the row sum alike, and the output is rounded once more:
+    |error| <= 2^-9 (sum_i p_i |v_i| + 2 |out|), and 1e-5 for the fp32 arithmetic.  (A bound on the
+    output's rms, as above, does not hold for the few rows that one key dominates.)"""
+    q, k, v, reuse = _attn_case(seq + dh, batch, seq, heads, dh, "bf16", frac)
+    idx, _, off = orc.selection(reuse)
+    idx_full = np.full(batch * seq, 10 ** 6, dtype=np.int32)
+    idx_full[:len(idx)] = idx
+    out = torch.full((batch * seq, heads * dh), 5.0, dtype=torch.bfloat16, device="cuda")
+    B.dare_k_attention(dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), out, batch, seq, heads, dh,
+                       idx=dev(idx_full), sel_off=dev(off))
+    torch.cuda.synchronize()
+    got = host(out).astype(np.float64).reshape(batch, seq, heads, dh)
+    assert np.all(got[reuse] == 5.0)
+    for b in range(batch):
+        rows = np.flatnonzero(~reuse[b])
+        sl = slice(b * seq, (b + 1) * seq)
+        Q, K, V = (a[sl].astype(np.float64).reshape(seq, heads, dh).transpose(1, 0, 2) for a in (q, k, v))
+        z = Q[:, rows] @ K.transpose(0, 2, 1) / np.sqrt(dh)
+        pr = np.exp(z - z.max(-1, keepdims=True))
+        pr /= pr.sum(-1, keepdims=True)
+        want = pr @ V
+        bound = 2.0 ** -9 * (pr @ np.abs(V) + 2 * np.abs(want)) + 1e-5
+        assert np.all(np.abs(got[b, rows].transpose(1, 0, 2) - want) <= bound)
+
+
 def test_attention_large_logits_are_stable(B):
     q, k, v, _ = _attn_case(77, 1, 192, 1, 128, "bf16", 1.0)
     q = store(q * 30.0, "bf16")

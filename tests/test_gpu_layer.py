@@ -83,6 +83,22 @@ def test_scored_columns(batch, seq, hidden, heads, dh, prefix):
     layer.destroy()
 
 
+# ------------------------------------------------------------------ attention with the keys cut
+@pytest.mark.parametrize("seq,heads,dh,fraction", [(1921, 2, 128, 0.002), (4100, 1, 128, 0.02), (2900, 4, 64, 0.05)])
+def test_few_rows_of_a_long_sequence(seq, heads, dh, fraction):
+    """A few query blocks over 1921 keys and more: two to four workgroups share the keys of a
+    block.  The result does not depend on which of them arrives last."""
+    case = synth.make_case("llada8b", seed=seq, batch=1, seq=seq, hidden=heads * dh, n_heads=heads, head_dim=dh,
+                           fraction=fraction)
+    state, gl = pu.oracle_fill(case), pu.GpuLayer(case)
+    _, first, _ = _run(case, gl, state, orc.MODE_KVO, synth.TAU_SEPARATING)
+    assert int(first["sel_count"][0]) == int(case["perturbed"].sum())
+    for _ in range(3):
+        again = gl.step(orc.MODE_KVO, synth.TAU_SEPARATING, case["x_cur"], state)
+        assert np.array_equal(again["out"], first["out"])
+    gl.layer.destroy()
+
+
 # ------------------------------------------------------------------ tiny fp32 layer
 @pytest.fixture(scope="module")
 def tiny():
