@@ -997,6 +997,12 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) gemm_bf16_kernel(GemmDe
   gemm_tile<BM, BN, WAVES_M, WAVES_N, STAGES>(p, m, smem, threadIdx.x, blockIdx.x);
 }
 
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
+__global__ void __launch_bounds__(512) gemm_bf16_tile16_kernel(GemmDev p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[smem_bytes<BM, BN, STAGES>()];
+  gemm_tile16<BM, BN, WAVES_M, WAVES_N, STAGES>(p, p.m_max, smem, threadIdx.x, blockIdx.x);
+}
+
 template <int TN, bool SPLIT>
 __global__ void __launch_bounds__(512) gemm_bf16_pp_kernel(GemmDev p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[pp_smem_bytes<TN>()];
@@ -1461,6 +1467,13 @@ hipError_t launch_fixed(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
+hipError_t launch_tile16(const GemmArgs& g, hipStream_t s) {
+  hipLaunchKernelGGL((gemm_bf16_tile16_kernel<BM, BN, WAVES_M, WAVES_N, STAGES>),
+                     dim3(grid_for(tiles_of(g.m_max, g.n, BM, BN))), dim3(512), 0, s, to_dev(g));
+  return hipGetLastError();
+}
+
 template <int TN, bool SPLIT = false>
 hipError_t launch_pp(const GemmArgs& g, hipStream_t s) {
   const int tiles = tiles_of(g.m_max, g.n, kPpRows, 64 * TN);
@@ -1503,7 +1516,14 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   // the gain).  128 x 128 with 8 waves is the best shape when the larger ones would leave most CUs idle.
   auto tiles = [&](int bm, int bn) { return tiles_of(g.m_max, g.n, bm, bn); };
   const int ksteps = g.k / BK;
-  if (g.k_parts <= 1) {
+  // One row tile (the output embedding of a few rows): a stream over the weights, of which 256-row
+  // tiles pull as many bytes of repeated rows as of weights.  64 and 128 rows with the 16-wide MFMA
+  // shape and as many weight rows in flight as fit (us, before in 256-row tiles; 1.04 GB of weights,
+  // k = 4096): 32 x 126464 229 -> 174 (5.9 TB/s), 64 x 126464 243 -> 205, 128 x 126464 244 -> 220,
+  // 128 x 24576 40 (128 x 128 tiles, 32-wide) -> 37.
+  if (g.k_parts <= 1 && g.m_max <= 64 && tiles(64, 128) >= 192) return launch_tile16<64, 128, 4, 2, 5>(g, s);
+  if (g.k_parts <= 1 && g.m_max > 64 && g.m_max <= 128 && tiles(128, 128) >= 64) return launch_tile16<128, 128, 4, 2, 4>(g, s);
+  if (g.k_parts <= 1 && g.m_max > 128) {
     const int t3 = tiles(kPpRows, 192), t4 = tiles(kPpRows, 256);
     const int q3 = 3 * ((t3 + 255) / 256), q4 = 4 * ((t4 + 255) / 256);
     if (t3 >= 224 && (q3 < q4 || t4 < 176)) return launch_pp<3>(g, s);

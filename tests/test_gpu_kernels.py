@@ -63,6 +63,10 @@ def test_gemm_all_rows(B, dtype, m, n, k, seg):
     (1793, 8192, 320, 4096, "256 x 256, five k-steps, one row in the last tile"),
     (2100, 2112, 64, 2112, "256 x 128, one k-step, ragged both ways"),
     (2305, 2048, 320, 2048, "256 x 128, five k-steps, one row in the last tile"),
+    (33, 24640, 64, 24640, "64 x 128, one k-step, ragged both ways"),
+    (64, 24576, 448, 8192, "64 x 128, seven k-steps, full tiles"),
+    (65, 8256, 64, 8256, "128 x 128, one row tile, one k-step, ragged both ways"),
+    (128, 8192, 320, 4096, "128 x 128, one row tile, five k-steps"),
 ])
 def test_gemm_all_rows_large_tiles(B, m, n, k, seg, tile):
     r = _rng(m + n + k)
