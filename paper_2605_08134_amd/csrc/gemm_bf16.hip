@@ -1511,7 +1511,8 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   // wins: 256 x 192 costs about 3/4 of 256 x 256 (1870 against 2500 cycles per k-step), so the narrow
   // one is taken where it needs fewer quarter-rounds of the 256 CUs (1024 x 12288: one full round
   // against one round with 64 CUs idle, 78 against 85 us; 2331 x 12288: three against two, 209 against
-  // 198 us).  256 x 128 takes over while it fills more than half of the CUs, and with two workgroups
+  // 198 us).  256 x 128 takes over while it fills more than half of the CUs (unless 128 x 128 does with
+  // one round: 520 x 6144 x 4096 39 us, a round of 256 x 128 at that k 59), and with two workgroups
   // per tile while it fills half of that (16 k-steps each at least, or the hand-over, about 5 us, eats
   // the gain).  128 x 128 with 8 waves is the best shape when the larger ones would leave most CUs idle.
   auto tiles = [&](int bm, int bn) { return tiles_of(g.m_max, g.n, bm, bn); };
@@ -1529,7 +1530,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
     if (t3 >= 224 && (q3 < q4 || t4 < 176)) return launch_pp<3>(g, s);
     if (t4 >= 176) return launch_pp<4>(g, s);
     const int t2 = tiles(kPpRows, 128);
-    if (t2 > kSplitTiles) return launch_pp<2>(g, s);
+    if (t2 > kSplitTiles && tiles(128, 128) > 256) return launch_pp<2>(g, s);
     if (g.split_tiles && t2 >= kSplitTiles / 2 && ksteps % 2 == 0 && ksteps >= 32) return launch_pp<2, true>(g, s);
   }
   if (g.m_max > 64 && g.n % 128 == 0 && tiles(128, 128) >= 64) return launch_fixed<128, 128, 4, 2, 4>(g, s);
