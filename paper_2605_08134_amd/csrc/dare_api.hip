@@ -167,7 +167,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   // projection has enough tiles without cutting k)
   c->q_new_elems = (size_t)max_tok * c->score_width;
   if (max_tok <= 4096) c->q_new_elems *= 8;
-  const bool split = cfg->dtype == DARE_BF16 && gemm_may_split(max_tok, cfg->hidden);
+  const bool split = cfg->dtype == DARE_BF16 && gemm_may_split(max_tok, cfg->hidden, cfg->hidden);
   const bool cut = cfg->dtype == DARE_BF16 && attn_may_cut(cfg->max_seq);
   struct { void** p; size_t bytes; } allocs[] = {
       {&c->wqkv_t, 3 * d * d * c->esize},

@@ -6,6 +6,7 @@
 
 #include "dare.h"
 #include "dare_kernels.h"
+#include "gemm_route.h"
 
 namespace dare {
 
@@ -64,10 +65,7 @@ struct GemmArgs {
   int* split_count;
 };
 constexpr int kSelMaxTokens = 2048;
-constexpr int kSplitTiles = 128;  // 256 x 128 tiles: two workgroups each fill the 256 CUs once
-constexpr size_t gemm_split_tiles_bytes() { return (size_t)kSplitTiles * 256 * 128 * sizeof(float); }
-// whether some projection of up to m rows to n columns can use that workspace
-constexpr bool gemm_may_split(long m, long n) { return (m + 255) / 256 * ((n + 127) / 128) >= kSplitTiles / 2; }
+constexpr size_t gemm_split_tiles_bytes() { return (size_t)kSplitTiles * kPpRows * 128 * sizeof(float); }
 
 // Rotation of the channel pairs (v0, v1) and (v2, v3) of four neighbouring output
 // columns col .. col + 3 (col a multiple of 4) of token tok.

@@ -40,11 +40,12 @@
 #include <type_traits>
 
 #include "dare_common.h"
+#include "gemm_route.h"
 
 namespace dare {
 namespace {
 
-constexpr int BK = 64;            // k per stage: one 128-byte row segment
+constexpr int BK = kRouteBK;      // k per stage: one 128-byte row segment
 constexpr int ROW_BYTES = BK * 2;
 constexpr int GROUP_M = 8;        // row-tiles walked before the next column-tile
 
@@ -629,7 +630,6 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
 // two workgroups (below; 64 to 128 tiles, which leave half of the CUs idle), inside a model step:
 // 1024 x 4096 x 12288 122 -> 97, 1024 x 4096 x 4096 50 -> 45.  A k-step takes 1610 cycles for 1024 of MFMAs:
 // every byte of LDS written or read for it at 128 B per cycle is 1400.
-constexpr int kPpRows = 256;
 template <int TN>
 constexpr int pp_stages() { return TN == 2 ? 3 : 2; }
 template <int TN>
@@ -1025,9 +1025,6 @@ __global__ void __launch_bounds__(512) gemm_bf16_pp_kernel(GemmDev p) {
 constexpr int kWideSmem = smem_bytes<128, 128, 4>();
 constexpr int kWideBigTiles = 160, kWideSingle = 256, kWideFullTiles = 200;
 constexpr int kWideGrid = 256;  // workgroups of a launch: one per CU
-__host__ __device__ inline int tiles_of(int m, int n, int bm, int bn) {
-  return ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
-}
 // a tile count that fills most of the chip's 256 CUs in a single round
 __host__ __device__ inline bool one_round(int tiles) { return tiles >= 192 && tiles <= 256; }
 // The refreshed-row list from the mask bytes, by every workgroup for itself (Alg. 1/2 line 5
@@ -1477,6 +1474,7 @@ hipError_t launch_tile16(const GemmArgs& g, hipStream_t s) {
 template <int TN, bool SPLIT = false>
 hipError_t launch_pp(const GemmArgs& g, hipStream_t s) {
   const int tiles = tiles_of(g.m_max, g.n, kPpRows, 64 * TN);
+  if (SPLIT && (tiles > kSplitTiles || !g.split_tiles || !g.split_count)) return hipErrorInvalidValue;
   hipLaunchKernelGGL((gemm_bf16_pp_kernel<TN, SPLIT>), dim3(grid_for(SPLIT ? 2 * tiles : tiles)), dim3(512), 0, s,
                      to_dev(g));
   return hipGetLastError();
@@ -1507,34 +1505,17 @@ hipError_t launch_rows_wide(const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   if (g.m_dev || g.sel_mask) return launch_rows_wide(g, s);
-  // Row count known on the host.  Once 256-row tiles fill most of the chip, the ping-pong tile
-  // wins: 256 x 192 costs about 3/4 of 256 x 256 (1870 against 2500 cycles per k-step), so the narrow
-  // one is taken where it needs fewer quarter-rounds of the 256 CUs (1024 x 12288: one full round
-  // against one round with 64 CUs idle, 78 against 85 us; 2331 x 12288: three against two, 209 against
-  // 198 us).  256 x 128 takes over while it fills more than half of the CUs (unless 128 x 128 does with
-  // one round: 520 x 6144 x 4096 39 us, a round of 256 x 128 at that k 59), and with two workgroups
-  // per tile while it fills half of that (16 k-steps each at least, or the hand-over, about 5 us, eats
-  // the gain).  128 x 128 with 8 waves is the best shape when the larger ones would leave most CUs idle.
-  auto tiles = [&](int bm, int bn) { return tiles_of(g.m_max, g.n, bm, bn); };
-  const int ksteps = g.k / BK;
-  // One row tile (the output embedding of a few rows): a stream over the weights, of which 256-row
-  // tiles pull as many bytes of repeated rows as of weights.  64 and 128 rows with the 16-wide MFMA
-  // shape and as many weight rows in flight as fit (us, before in 256-row tiles; 1.04 GB of weights,
-  // k = 4096): 32 x 126464 229 -> 174 (5.9 TB/s), 64 x 126464 243 -> 205, 128 x 126464 244 -> 220,
-  // 128 x 24576 40 (128 x 128 tiles, 32-wide) -> 37.
-  if (g.k_parts <= 1 && g.m_max <= 64 && tiles(64, 128) >= 192) return launch_tile16<64, 128, 4, 2, 5>(g, s);
-  if (g.k_parts <= 1 && g.m_max > 64 && g.m_max <= 128 && tiles(128, 128) >= 64) return launch_tile16<128, 128, 4, 2, 4>(g, s);
-  if (g.k_parts <= 1 && g.m_max > 128) {
-    const int t3 = tiles(kPpRows, 192), t4 = tiles(kPpRows, 256);
-    const int q3 = 3 * ((t3 + 255) / 256), q4 = 4 * ((t4 + 255) / 256);
-    if (t3 >= 224 && (q3 < q4 || t4 < 176)) return launch_pp<3>(g, s);
-    if (t4 >= 176) return launch_pp<4>(g, s);
-    const int t2 = tiles(kPpRows, 128);
-    if (t2 > kSplitTiles && tiles(128, 128) > 256) return launch_pp<2>(g, s);
-    if (g.split_tiles && t2 >= kSplitTiles / 2 && ksteps % 2 == 0 && ksteps >= 32) return launch_pp<2, true>(g, s);
+  switch (gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles != nullptr)) {
+    case GemmRoute::kRows64: return launch_tile16<64, 128, 4, 2, 5>(g, s);
+    case GemmRoute::kRows128: return launch_tile16<128, 128, 4, 2, 4>(g, s);
+    case GemmRoute::kPp192: return launch_pp<3>(g, s);
+    case GemmRoute::kPp256: return launch_pp<4>(g, s);
+    case GemmRoute::kPp128: return launch_pp<2>(g, s);
+    case GemmRoute::kPp128Split: return launch_pp<2, true>(g, s);
+    case GemmRoute::kTile128: return launch_fixed<128, 128, 4, 2, 4>(g, s);
+    case GemmRoute::kTile64: return launch_fixed<64, 64, 2, 2, 4>(g, s);
   }
-  if (g.m_max > 64 && g.n % 128 == 0 && tiles(128, 128) >= 64) return launch_fixed<128, 128, 4, 2, 4>(g, s);
-  return launch_fixed<64, 64, 2, 2, 4>(g, s);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_score_proj(const ScoreProjArgs& g, hipStream_t s) {

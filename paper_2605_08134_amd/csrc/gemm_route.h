@@ -1,0 +1,62 @@
+// Tile shape of a bf16 projection whose row count the host knows, as plain host arithmetic: no HIP
+// here, so that the rule can be evaluated over its whole range without a GPU.
+#pragma once
+
+namespace dare {
+
+enum class GemmRoute {
+  kTile64,      // 64 x 64, four waves
+  kTile128,     // 128 x 128, eight waves
+  kRows64,      // 64 x 128 on the 16-wide MFMA shape: one row tile
+  kRows128,     // 128 x 128 on the 16-wide MFMA shape: one row tile
+  kPp128,       // ping-pong tiles of 256 rows x 128, 192, 256 columns
+  kPp192,
+  kPp256,
+  kPp128Split,  // 256 x 128, two workgroups on the halves of a tile's k; needs the workspace
+};
+
+constexpr int kRouteBK = 64;        // k per k-step
+constexpr int kPpRows = 256;        // rows of a ping-pong tile
+constexpr int kSplitTiles = 128;    // tiles the workspace holds: two workgroups each fill the 256 CUs once
+constexpr int kSplitMinSteps = 32;  // k-steps of a tile whose k is cut: 16 each, or the hand-over (about 5 us) eats the gain
+
+constexpr int tiles_of(int m, int n, int bm, int bn) { return ((m + bm - 1) / bm) * ((n + bn - 1) / bn); }
+
+// Whether some projection of at most m rows with this n and k takes the route that needs the workspace
+constexpr bool gemm_may_split(long m, long n, long k) {
+  return (m + kPpRows - 1) / kPpRows * ((n + 127) / 128) >= kSplitTiles / 2 && k / kRouteBK % 2 == 0 &&
+         k / kRouteBK >= kSplitMinSteps;
+}
+
+// Once 256-row tiles fill most of the chip, the ping-pong tile
+// wins: 256 x 192 costs about 3/4 of 256 x 256 (1870 against 2500 cycles per k-step), so the narrow
+// one is taken where it needs fewer quarter-rounds of the 256 CUs (1024 x 12288: one full round
+// against one round with 64 CUs idle, 78 against 85 us; 2331 x 12288: three against two, 209 against
+// 198 us).  256 x 128 takes over while it fills more than half of the CUs (unless 128 x 128 does with
+// one round: 520 x 6144 x 4096 39 us, a round of 256 x 128 at that k 59), and with two workgroups
+// per tile where there are kSplitTiles / 2 to kSplitTiles of them.  128 x 128 with 8 waves is the best
+// shape when the larger ones would leave most CUs idle.
+// One row tile (the output embedding of a few rows): a stream over the weights, of which 256-row
+// tiles pull as many bytes of repeated rows as of weights.  64 and 128 rows with the 16-wide MFMA
+// shape and as many weight rows in flight as fit (us, before in 256-row tiles; 1.04 GB of weights,
+// k = 4096): 32 x 126464 229 -> 174 (5.9 TB/s), 64 x 126464 243 -> 205, 128 x 126464 244 -> 220,
+// 128 x 24576 40 (128 x 128 tiles, 32-wide) -> 37.
+constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace) {
+  const int t128 = tiles_of(m, n, 128, 128);
+  if (k_parts <= 1 && m <= 64 && tiles_of(m, n, 64, 128) >= 192) return GemmRoute::kRows64;
+  if (k_parts <= 1 && m > 64 && m <= 128 && t128 >= 64) return GemmRoute::kRows128;
+  if (k_parts <= 1 && m > 128) {
+    const int t3 = tiles_of(m, n, kPpRows, 192), t4 = tiles_of(m, n, kPpRows, 256);
+    const int q3 = 3 * ((t3 + 255) / 256), q4 = 4 * ((t4 + 255) / 256);
+    if (t3 >= 224 && (q3 < q4 || t4 < 176)) return GemmRoute::kPp192;
+    if (t4 >= 176) return GemmRoute::kPp256;
+    const int t2 = tiles_of(m, n, kPpRows, 128), ksteps = k / kRouteBK;
+    if (t2 > kSplitTiles && t128 > 256) return GemmRoute::kPp128;
+    if (workspace && t2 >= kSplitTiles / 2 && t2 <= kSplitTiles && ksteps % 2 == 0 && ksteps >= kSplitMinSteps)
+      return GemmRoute::kPp128Split;
+  }
+  if (m > 64 && n % 128 == 0 && t128 >= 64) return GemmRoute::kTile128;
+  return GemmRoute::kTile64;
+}
+
+}  // namespace dare

@@ -210,7 +210,7 @@ dare_status dare_model_create(const dare_model_config* cfg, void* hip_stream, da
   m->rule = DARE_RULE_SCORE;
   m->prefix = 0;
   const size_t d = cfg->hidden, es = m->esize, tok = (size_t)max_tok;
-  const bool split = cfg->dtype == DARE_BF16 && gemm_may_split(max_tok, cfg->hidden);
+  const bool split = cfg->dtype == DARE_BF16 && gemm_may_split(max_tok, cfg->hidden, cfg->ffn);
   struct { void** p; size_t bytes; bool zero; } bufs[] = {
       {&m->x, tok * d * es, false},          {&m->h2, tok * d * es, false},
       {&m->h1, tok * d * es, false},

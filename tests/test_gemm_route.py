@@ -1,0 +1,55 @@
+"""The rule that picks the tile shape of an all-row bf16 projection (csrc/gemm_route.h), evaluated
+on the CPU over rows 1 .. 6000 and every hidden size in steps of 64 up to 8192, for the
+projections that a layer and a model make from them.  The route that cuts k over two workgroups
+owns a workspace of kSplitTiles tiles and as many counters: it must never get more, nor be
+taken without a workspace, nor depend on how large a context was made."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SWEEP = r"""
+#include <cstdio>
+#include "gemm_route.h"
+using namespace dare;
+static long bad;
+static void fail(const char* what, int m, int n, int k) {
+  if (bad++ < 10) std::printf("%s: m %d n %d k %d\n", what, m, n, k);
+}
+int main() {
+  long split = 0;
+  for (int d = 64; d <= 8192; d += 64)
+    for (int m = 1; m <= 6000; ++m) {
+      const int shapes[][2] = {{d, d}, {3 * d, d}, {d, 3 * d}, {d, 4 * d}, {6 * d, d}};  // n, k
+      for (const auto& s : shapes) {
+        const int n = s[0], k = s[1];
+        const GemmRoute with = gemm_route(m, n, k, 1, true), without = gemm_route(m, n, k, 1, false);
+        if (without == GemmRoute::kPp128Split) fail("no workspace", m, n, k);
+        if (gemm_route(m, n, k, 2, true) == GemmRoute::kPp128Split) fail("k already in ranges", m, n, k);
+        const int t = tiles_of(m, n, kPpRows, 128);
+        if (with != GemmRoute::kPp128Split) {
+          if (with != without) fail("workspace changes another route", m, n, k);
+          continue;
+        }
+        ++split;
+        if (t > kSplitTiles) fail("more tiles than the workspace holds", m, n, k);
+        if (k / kRouteBK % 2 || k / kRouteBK < kSplitMinSteps) fail("k cannot be cut", m, n, k);
+        // a workspace exists in every context that holds this many rows or more
+        for (int more = 0; more <= 4096; more += 512)
+          if (!gemm_may_split(m + more, n, k)) fail("route without its workspace", m + more, n, k);
+      }
+    }
+  std::printf("split %ld bad %ld\n", split, bad);
+  return bad != 0;
+}
+"""
+
+
+def test_cut_projection_never_exceeds_its_workspace(tmp_path):
+    src, exe = tmp_path / "sweep.cpp", tmp_path / "sweep"
+    src.write_text(SWEEP)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+    assert int(r.stdout.split()[1]) > 1000     # the sweep does reach the route

@@ -37,6 +37,25 @@ def test_projection_cut_along_k(seq, mode):
     gl.layer.destroy()
 
 
+@pytest.mark.parametrize("mode", [orc.MODE_DENSE, orc.MODE_KV, orc.MODE_O])
+@pytest.mark.parametrize("hidden,seq,max_seq", [
+    (3584, 300, 600),     # Q/K/V: 168 tiles of 256 x 128 in a context with a workspace of 128
+    (3584, 1100, 1100),   # Q and the output projection: 140 tiles
+    (2048, 600, 1024),    # Q/K/V: 144 tiles
+])
+def test_projection_of_more_tiles_than_the_workspace_holds(hidden, seq, max_seq, mode):
+    """Tile counts above the workspace's take a route that needs none; the context's other
+    memory (its packed weights among it) is what it was: a second step gives the same result."""
+    case = synth.make_case("llada8b", seed=hidden + seq, batch=1, seq=seq, hidden=hidden, n_heads=hidden // 128,
+                           head_dim=128)
+    state, gl = pu.oracle_fill(case), pu.GpuLayer(case, max_seq=max_seq)
+    _, first, _ = _run(case, gl, state, mode, synth.TAU_SEPARATING)
+    again = gl.step(mode, synth.TAU_SEPARATING, case["x_cur"], state)
+    for key in ("out", "k_cache", "v_cache", "q_prev"):
+        assert np.array_equal(again[key], first[key]), key
+    gl.layer.destroy()
+
+
 # ------------------------------------------------------------------ scored columns with the score
 @pytest.mark.parametrize("batch,seq,hidden,heads,dh,prefix", [
     (1, 37, 256, 4, 64, 0), (3, 333, 512, 4, 128, 11),        # 16 rows per workgroup, ragged

@@ -68,6 +68,22 @@ def test_prefix_small_bf16(shape, P, mode):
     gl.layer.destroy()
 
 
+@pytest.mark.parametrize("P", [400, 424])
+@pytest.mark.parametrize("mode", [orc.MODE_DENSE, orc.MODE_O])
+def test_prefix_leaves_rows_between_the_projection_routes(mode, P):
+    """600 and 624 of 1024 tokens left at hidden 2048: Q/K/V in 144 tiles of 256 x 128, which is more
+    than the workspace of projections with k cut in two holds."""
+    case = synth.make_case("llada8b", seed=83 + P, batch=1, seq=1024, hidden=2048, n_heads=16,
+                           head_dim=128)
+    state, gl = pu.oracle_fill(case), pu.GpuLayer(case)
+    gl.layer.set_prefix(P)
+    want = _oracle(case, state, mode, synth.TAU_SEPARATING, P)
+    got = gl.step(mode, synth.TAU_SEPARATING, case["x_cur"], state)
+    pu.check_step(got, want, state, mode, synth.TAU_SEPARATING, "bf16")
+    _frozen_rows_untouched(got, state, P)
+    gl.layer.destroy()
+
+
 def test_prefix_with_quantile_rule_ranks_the_other_tokens():
     case = synth.make_case("tiny", seed=5, batch=2, seq=96)
     state = pu.oracle_fill(case)
