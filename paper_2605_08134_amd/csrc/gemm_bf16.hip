@@ -1233,14 +1233,16 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) score_proj_kernel(Score
   constexpr int STAGE_BYTES = (BM + WIDTH) * ROW_BYTES;
   constexpr int GROUPS = (BM + WIDTH) / 8;
   constexpr int LPW = (GROUPS + NW - 1) / NW;  // surplus loads repeat the last group
-  constexpr int LDQ = WIDTH + 4;
+  constexpr int LDQ = score_query_stride(WIDTH);
   static_assert(WM % 16 == 0 && WN % 16 == 0 && BM % NW == 0, "wave tiles of 16 x 16, whole rows per wave");
-  static_assert(BM * LDQ * 4 <= STAGES * STAGE_BYTES, "the queries must fit into the stage memory");
   static_assert(LPW * (STAGES - 1) < 64, "vmcnt range");
   // (one LDS array only: with a second one the compiler tracks which of them a global -> LDS load
   // may write, and puts s_waitcnt vmcnt(0) in front of the fragment reads, which drains the ring)
   __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE_BYTES];
-  int& arrived = *reinterpret_cast<int*>(smem);
+  // the arrival number lies behind the queries, which a wave may write while another one still reads it
+  constexpr int ARRIVED = score_arrived_offset(BM, WIDTH);
+  static_assert(ARRIVED + 4 <= STAGES * STAGE_BYTES, "the arrival number must fit into the stage memory");
+  int& arrived = *reinterpret_cast<int*>(smem + ARRIVED);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // frozen tokens: always reused, never scored

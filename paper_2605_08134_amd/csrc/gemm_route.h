@@ -59,4 +59,9 @@ constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace)
   return GemmRoute::kTile64;
 }
 
+// LDS of the scored-column projection once its k loop is over: bm queries, score_query_stride floats
+// apart, from offset 0, and the arrival number of the workgroup
+constexpr int score_query_stride(int width) { return width + 4; }
+constexpr int score_arrived_offset(int bm, int width) { return bm * score_query_stride(width) * 4; }
+
 }  // namespace dare

@@ -45,11 +45,42 @@ int main() {
 """
 
 
-def test_cut_projection_never_exceeds_its_workspace(tmp_path):
+def _run(tmp_path, text):
     src, exe = tmp_path / "sweep.cpp", tmp_path / "sweep"
-    src.write_text(SWEEP)
+    src.write_text(text)
     subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"),
                     str(src), "-o", str(exe)], check=True)
-    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    return subprocess.run([str(exe)], capture_output=True, text=True)
+
+
+def test_cut_projection_never_exceeds_its_workspace(tmp_path):
+    r = _run(tmp_path, SWEEP)
     assert r.returncode == 0, r.stdout
     assert int(r.stdout.split()[1]) > 1000     # the sweep does reach the route
+
+
+SCORE_LDS = r"""
+#include <cstdio>
+#include "gemm_route.h"
+using namespace dare;
+int main() {
+  int bad = 0;
+  for (int width = 64; width <= 128; width += 64)
+    for (int bm = 16; bm <= 64; bm *= 2) {
+      const int at = score_arrived_offset(bm, width);
+      for (int row = 0; row < bm; ++row)
+        for (int col = 0; col < width; ++col) {
+          const int q = (row * score_query_stride(width) + col) * 4;
+          if (q < at + 4 && at < q + 4) ++bad;
+        }
+    }
+  std::printf("%d\n", bad);
+  return bad != 0;
+}
+"""
+
+
+def test_arrival_number_of_the_scored_columns_is_no_query_word(tmp_path):
+    """Every wave of the last workgroup reads the arrival number and then writes its queries into
+    the same LDS array, with no barrier in between: the two must not share a word."""
+    assert _run(tmp_path, SCORE_LDS).returncode == 0
