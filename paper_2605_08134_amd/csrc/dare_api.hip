@@ -321,8 +321,8 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
     g.rope = bx.rope;  // queries and keys are rotated as they are written; the fp32 copy
     g.rope_dh = cf.head_dim;  // that feeds the score is not
     g.rope_seq = seq;
-    g.split_tiles = ctx->split_tiles;
-    g.split_count = ctx->split_count;
+    // (no workspace for a k cut in two: every mode sums the scored columns over k in one order, so
+    // the query of an unchanged token stays the same and its score exactly 0 when the mode changes)
     if (mode == DARE_MODE_DENSE || mode == DARE_MODE_O) {
       g.n = 3 * d;  // Q, K, V for every row (App. E.2; Alg. 2 lines 2 and 7)
       g.c[0] = ctx->q_buf;

@@ -58,7 +58,7 @@ struct GemmArgs {
   int32_t* sel_idx_out2;
   int32_t* sel_off_out;
   int32_t* sel_count_out;
-  // optional workspace for tiles whose k is cut in two (bf16, row count known on the host):
+  // optional workspace for tiles whose k is cut in two (bf16, row count known on the host, no c32):
   // gemm_split_tiles_bytes() bytes and kSplitTiles counters that are 0 before the first launch and
   // that every launch leaves at 0; one launch at a time
   float* split_tiles;

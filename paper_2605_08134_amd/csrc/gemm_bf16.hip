@@ -1507,7 +1507,7 @@ hipError_t launch_rows_wide(const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   if (g.m_dev || g.sel_mask) return launch_rows_wide(g, s);
-  switch (gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles != nullptr)) {
+  switch (gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles && !g.c32)) {
     case GemmRoute::kRows64: return launch_tile16<64, 128, 4, 2, 5>(g, s);
     case GemmRoute::kRows128: return launch_tile16<128, 128, 4, 2, 4>(g, s);
     case GemmRoute::kPp192: return launch_pp<3>(g, s);

@@ -56,6 +56,46 @@ def test_projection_of_more_tiles_than_the_workspace_holds(hidden, seq, max_seq,
     gl.layer.destroy()
 
 
+@pytest.mark.parametrize("first,second,score_head", [
+    (orc.MODE_DENSE, orc.MODE_KV, 0), (orc.MODE_O, orc.MODE_KV, 0), (orc.MODE_KV, orc.MODE_O, 0),
+    (orc.MODE_DENSE, orc.MODE_KV, -1), (orc.MODE_DENSE, orc.MODE_KVO, -1),
+])
+@pytest.mark.parametrize("seq,hidden", [(1024, 4096), (600, 2048), (1100, 3584)])
+def test_unchanged_tokens_score_zero_across_modes(seq, hidden, first, second, score_head):
+    _unchanged_tokens_score_zero(1, seq, hidden, first, second, score_head)
+
+
+@pytest.mark.parametrize("first", [orc.MODE_DENSE, orc.MODE_KV])
+@pytest.mark.parametrize("batch,seq,hidden", [(3, 1400, 512), (2, 2100, 4096)])
+def test_unchanged_tokens_score_zero_in_the_scored_columns_alone(batch, seq, hidden, first):
+    """As many rows as need no cut of k in the launch of the scored columns alone."""
+    _unchanged_tokens_score_zero(batch, seq, hidden, first, orc.MODE_KVO, 0)
+
+
+def _unchanged_tokens_score_zero(batch, seq, hidden, first, second, score_head):
+    """The query of a token whose hidden state did not move is the same bit for bit in the next step,
+    also when that step projects the scored columns in a launch of another width: drift exactly
+    0, reused at threshold 0."""
+    from paper_2605_08134_amd import binding as B
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device="cuda")
+    layer = B.DareLayer(*((rnd(hidden, hidden) * 0.02).bfloat16() for _ in range(4)), n_heads=hidden // 128, max_batch=batch,
+                        max_seq=max(seq, 1100), score_head=score_head)
+    x = rnd(batch, seq, hidden).bfloat16()
+    st = layer.new_state(batch, seq)
+    mask = torch.full((batch, seq), 7, dtype=torch.uint8, device="cuda")
+    scores = torch.full((batch, seq), float("nan"), device="cuda")
+    step = lambda mode, tau: layer.layer_step(mode, tau, x, st["q_prev"], st["k_cache"], st["v_cache"], st["o_cache"],
+                                              st["o_cache"], mask, scores=scores)
+    step(first, -1.0)
+    before = st["q_prev"].clone()
+    step(second, 0.0)
+    assert torch.equal(st["q_prev"], before)
+    assert bool((scores == 0).all()) and bool((mask == 1).all())
+    layer.destroy()
+
+
 # ------------------------------------------------------------------ scored columns with the score
 @pytest.mark.parametrize("batch,seq,hidden,heads,dh,prefix", [
     (1, 37, 256, 4, 64, 0), (3, 333, 512, 4, 128, 11),        # 16 rows per workgroup, ragged
