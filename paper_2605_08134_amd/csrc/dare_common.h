@@ -59,13 +59,13 @@ struct GemmArgs {
   int32_t* sel_off_out;
   int32_t* sel_count_out;
   // optional workspace for tiles whose k is cut in two (bf16, row count known on the host, no c32):
-  // gemm_split_tiles_bytes() bytes and kSplitTiles counters that are 0 before the first launch and
-  // that every launch leaves at 0; one launch at a time
+  // gemm_split_tiles_bytes() bytes (the sums of both halves of every tile) and kSplitTiles counters that
+  // are 0 before the first launch and that every launch leaves even; one launch at a time
   float* split_tiles;
   int* split_count;
 };
 constexpr int kSelMaxTokens = 2048;
-constexpr size_t gemm_split_tiles_bytes() { return (size_t)kSplitTiles * kPpRows * 128 * sizeof(float); }
+constexpr size_t gemm_split_tiles_bytes() { return (size_t)kSplitTiles * 2 * kPpRows * 128 * sizeof(float); }
 
 // Rotation of the channel pairs (v0, v1) and (v2, v3) of four neighbouring output
 // columns col .. col + 3 (col a multiple of 4) of token tok.

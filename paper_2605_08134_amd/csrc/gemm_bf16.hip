@@ -70,8 +70,8 @@ struct GemmDev {
   int32_t* sel_idx_out2;
   int32_t* sel_off_out;
   int32_t* sel_count_out;
-  // two workgroups on the halves of k of one tile (gemm_tile_pp): [tiles] fp32 tiles and
-  // counters; nullptr = one workgroup per tile
+  // two workgroups on the halves of k of one tile (gemm_tile_pp): [tiles][2] fp32 tiles and
+  // [tiles] counters; nullptr = one workgroup per tile
   float* split_tiles;
   int* split_count;
 };
@@ -856,44 +856,46 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   if (grp == 0) asm volatile("s_barrier" ::: "memory");
   wait_vmcnt<0>();
 
-  // The workgroup that arrives first at a tile leaves its sums in the workspace and goes; the
-  // second one adds them to its own (a sum of two does not depend on which came first) and stores
-  // the tile.  It may have to wait until the sums are complete, and only then: the first
-  // workgroup is running by then and waits for nobody.  The sums are written and read at device
-  // scope (sc1: past whatever an XCD's L2 holds), and counted once every wave's stores have
-  // completed, so no fence, which would write back the whole L2 (20-40 us), is needed.
+  // The workgroup that arrives last at a tile adds the other one's sums to its own (a sum of two
+  // does not depend on which came first) and stores the tile; the other one leaves its sums in
+  // its half of the tile's workspace and goes.  Nobody waits: a workgroup that finds the other's sums
+  // complete need not store its own, and of two that both stored theirs the second one counted is
+  // the last (1 us more per launch than a wait for the first one's sums).  The counter's
+  // parity says whether one has arrived: even between launches, whatever the launch before left.
+  // The sums are written and read at device scope (sc1: past whatever an XCD's L2 holds), and counted
+  // once every wave's stores have completed, so no fence, which would write back the whole L2
+  // (20-40 us), is needed.
   if constexpr (SPLIT) {
     constexpr int kDeviceScope = 16;  // cache policy sc1
-    constexpr int kComplete = 4;      // counter: 1 per workgroup that has arrived, 4 for complete sums
-    const auto sums = __builtin_amdgcn_make_buffer_rsrc(p.split_tiles + (long)tile * (BM * BN), 0, BM * BN * 4, 0x00027000);
+    float* slots = p.split_tiles + (long)tile * (PARTS * BM * BN);
+    const auto mine = __builtin_amdgcn_make_buffer_rsrc(slots + (unit & 1) * (BM * BN), 0, BM * BN * 4, 0x00027000);
+    const auto other = __builtin_amdgcn_make_buffer_rsrc(slots + (~unit & 1) * (BM * BN), 0, BM * BN * 4, 0x00027000);
     int* count = p.split_count + tile;
-    int* seen = reinterpret_cast<int*>(smem);
+    int* last = reinterpret_cast<int*>(smem);
     __syncthreads();
-    if (tid == 0) *seen = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) *last = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1;
     __syncthreads();
-    if (*seen == 0) {
+    if (!*last) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 2 * TN; ++j)
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), sums,
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), mine,
                                                  ((i * 2 * TN + j) * 512 + tid) * 16, 0, kDeviceScope);
       wait_vmcnt<0>();
       __syncthreads();
-      if (tid == 0) __hip_atomic_fetch_add(count, kComplete, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return true;
+      if (tid == 0) *last = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1;
+      __syncthreads();
+      if (!*last) return true;
+    } else if (tid == 0) {
+      __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (tid == 0) {
-      while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < kComplete) __builtin_amdgcn_s_sleep(1);
-      __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 2 * TN; ++j)
         acc[i][j] += __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                   sums, ((i * 2 * TN + j) * 512 + tid) * 16, 0, kDeviceScope));
+                                                   other, ((i * 2 * TN + j) * 512 + tid) * 16, 0, kDeviceScope));
   }
 
   // acc[i][2 j + h][e] = C[row, col], row = m0 + 64 wm + 16 i + l16, col = n0 + 32 TN grp + 32 j + 8 kq + 4 h + e
