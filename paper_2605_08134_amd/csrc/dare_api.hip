@@ -26,8 +26,6 @@ struct dare_ctx {
   size_t q_new_elems;
   int32_t* sel_idx;    // [max tokens]
   int32_t* sel_off;    // [max_batch + 1]
-  float* split_tiles;  // workspace of projections whose k is cut in two, or nullptr
-  int* split_count;
   float* part_out;     // workspace of refreshed-row attention whose keys are cut, or nullptr
   int* part_count;
   int* score_count;    // [kScoreTiles] counters of the scored-column projection (bf16)
@@ -91,7 +89,7 @@ struct DeviceGuard {
 
 void free_ctx(dare_ctx* c) {
   if (!c) return;
-  void* bufs[] = {c->wqkv_t, c->wo_t, c->q_buf, c->attn_buf, c->q_new, c->sel_idx, c->sel_off, c->split_tiles, c->split_count, c->score_count, c->part_out, c->part_count, c->gain, c->bias, c->h_buf, c->rope_table, c->tau_dev, c->scores_buf,
+  void* bufs[] = {c->wqkv_t, c->wo_t, c->q_buf, c->attn_buf, c->q_new, c->sel_idx, c->sel_off, c->score_count, c->part_out, c->part_count, c->gain, c->bias, c->h_buf, c->rope_table, c->tau_dev, c->scores_buf,
                   c->stat_sum, c->act_idx, c->act_off};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -150,8 +148,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   c->wqkv_t = c->wo_t = c->q_buf = c->attn_buf = nullptr;
   c->q_new = nullptr;
   c->sel_idx = c->sel_off = nullptr;
-  c->split_tiles = nullptr;
-  c->split_count = c->score_count = c->part_count = nullptr;
+  c->score_count = c->part_count = nullptr;
   c->part_out = nullptr;
   c->has_block = c->has_bias = false;
   c->gain = c->bias = c->h_buf = nullptr;
@@ -167,7 +164,6 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   // projection has enough tiles without cutting k)
   c->q_new_elems = (size_t)max_tok * c->score_width;
   if (max_tok <= 4096) c->q_new_elems *= 8;
-  const bool split = cfg->dtype == DARE_BF16 && gemm_may_split(max_tok, cfg->hidden, cfg->hidden);
   const bool cut = cfg->dtype == DARE_BF16 && attn_may_cut(cfg->max_seq);
   struct { void** p; size_t bytes; } allocs[] = {
       {&c->wqkv_t, 3 * d * d * c->esize},
@@ -177,8 +173,6 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
       {(void**)&c->q_new, c->q_new_elems * sizeof(float)},
       {(void**)&c->sel_idx, (size_t)max_tok * sizeof(int32_t)},
       {(void**)&c->sel_off, ((size_t)cfg->max_batch + 1) * sizeof(int32_t)},
-      {(void**)&c->split_tiles, split ? gemm_split_tiles_bytes() : 0},
-      {(void**)&c->split_count, split ? kSplitTiles * sizeof(int) : 0},
       {(void**)&c->part_out, cut ? attn_parts_elems(cfg->head_dim) * sizeof(float) : 0},
       {(void**)&c->part_count, cut ? kAttnParts * sizeof(int) : 0},
       {(void**)&c->score_count, cfg->dtype == DARE_BF16 ? kScoreTiles * sizeof(int) : 0},
@@ -199,7 +193,6 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
     e = launch_pack_weight(cfg->dtype, w3[i], cfg->hidden, cfg->hidden,
                            static_cast<char*>(c->wqkv_t) + (size_t)i * d * d * c->esize, cfg->hidden, s);
   if (e == hipSuccess) e = launch_pack_weight(cfg->dtype, wo, cfg->hidden, cfg->hidden, c->wo_t, cfg->hidden, s);
-  if (e == hipSuccess && split) e = launch_zero_words(c->split_count, kSplitTiles / 2, s);  // (64-bit words)
   if (e == hipSuccess && cut) e = launch_zero_words(c->part_count, kAttnParts / 2, s);
   if (e == hipSuccess && c->score_count) e = launch_zero_words(c->score_count, kScoreTiles / 2, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -321,8 +314,6 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
     g.rope = bx.rope;  // queries and keys are rotated as they are written; the fp32 copy
     g.rope_dh = cf.head_dim;  // that feeds the score is not
     g.rope_seq = seq;
-    // (no workspace for a k cut in two: every mode sums the scored columns over k in one order, so
-    // the query of an unchanged token stays the same and its score exactly 0 when the mode changes)
     if (mode == DARE_MODE_DENSE || mode == DARE_MODE_O) {
       g.n = 3 * d;  // Q, K, V for every row (App. E.2; Alg. 2 lines 2 and 7)
       g.c[0] = ctx->q_buf;
@@ -433,8 +424,6 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
   o.m_max = n_tok;
   o.ldc = d;
   o.seg_n = d;
-  o.split_tiles = ctx->split_tiles;
-  o.split_count = ctx->split_count;
   if (sel_o) {
     o.idx = ctx->sel_idx;
     o.m_dev = n_sel;

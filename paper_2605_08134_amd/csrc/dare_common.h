@@ -58,7 +58,9 @@ struct GemmArgs {
   int32_t* sel_idx_out2;
   int32_t* sel_off_out;
   int32_t* sel_count_out;
-  // optional workspace for tiles whose k is cut in two (bf16, row count known on the host, no c32):
+  // optional workspace for tiles whose k is cut in two (bf16, row count known on the host).  Not for
+  // projections with c32, whose sums every mode has to form in one order (the query of an unchanged
+  // token then scores exactly 0):
   // gemm_split_tiles_bytes() bytes (the sums of both halves of every tile) and kSplitTiles counters that
   // are 0 before the first launch and that every launch leaves even; one launch at a time
   float* split_tiles;

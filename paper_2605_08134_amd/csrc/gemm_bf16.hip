@@ -627,8 +627,8 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
 // Measured with gathered-row support and all (us, before: one k-loop that every wave runs in step):
 // 16384 x 12288 x 4096 1540 -> 1140 (1.45 PFLOP/s), 1024 x 12288 x 4096 98 -> 78, 1024 x 24576 x 4096
 // 206 -> 154.  TN = 2 against 128 x 128 tiles: 2048 x 4096 x 4096 83 -> 59; with the k of a tile cut over
-// two workgroups (below; 64 to 128 tiles, which leave half of the CUs idle), inside a model step:
-// 1024 x 4096 x 12288 122 -> 97, 1024 x 4096 x 4096 50 -> 45.  A k-step takes 1610 cycles for 1024 of MFMAs:
+// two workgroups (below; 64 to 128 tiles, which leave half of the CUs idle, and a long k), inside a
+// model step: 1024 x 4096 x 12288 122 -> 97.  A k-step takes 1610 cycles for 1024 of MFMAs:
 // every byte of LDS written or read for it at 128 B per cycle is 1400.
 template <int TN>
 constexpr int pp_stages() { return TN == 2 ? 3 : 2; }

@@ -18,7 +18,10 @@ enum class GemmRoute {
 constexpr int kRouteBK = 64;        // k per k-step
 constexpr int kPpRows = 256;        // rows of a ping-pong tile
 constexpr int kSplitTiles = 128;    // tiles the workspace holds: two workgroups each fill the 256 CUs once
-constexpr int kSplitMinSteps = 32;  // k-steps of a tile whose k is cut: 16 each, or the hand-over (about 5 us) eats the gain
+// k-steps of a tile whose k is cut.  The hand-over costs about 5 us and 33 MB written past L2: 1024 x 4096
+// outputs with 64 k-steps gain nothing (a dense layer step 156.4 us with and 157.1 without, a K/V reuse step
+// 173.4 and 172.8), 192 k-steps 25 us of 122; the two time lines cross near 55.
+constexpr int kSplitMinSteps = 96;
 
 constexpr int tiles_of(int m, int n, int bm, int bn) { return ((m + bm - 1) / bm) * ((n + bn - 1) / bn); }
 

@@ -20,13 +20,13 @@ def _run(case, gl, state, mode, tau, **kw):
     return pu.check_step(got, want, state, mode, tau, case["dtype"]), got, want
 
 
-# ------------------------------------------------------------------ projections with k cut in two
+# ------------------------------------------------------------------ all-row projections of 64 and more 256 x 128 tiles
 @pytest.mark.parametrize("seq", [1793, 2048])
 @pytest.mark.parametrize("mode", [orc.MODE_DENSE, orc.MODE_KV])
 def test_projection_cut_along_k(seq, mode):
-    """All-row projections to 2048 columns in 256 x 128 tiles, two workgroups on the halves of a
-    tile's k (1793 rows: one row in the last row tile).  Three calls in a row: the counters of the
-    workspace are back at 0 after each, and the sum does not depend on who arrives first."""
+    """All-row projections to 2048 columns, 128 tiles of 256 x 128 (1793 rows: one row in the last
+    row tile): as many as a cut of k along two workgroups would take, if the layer's k were
+    long enough for it.  Three calls in a row give the same bits."""
     case = synth.make_case("llada8b", seed=seq, batch=1, seq=seq, hidden=2048, n_heads=16, head_dim=128)
     state, gl = pu.oracle_fill(case), pu.GpuLayer(case)
     _, first, _ = _run(case, gl, state, mode, synth.TAU_SEPARATING)
@@ -39,13 +39,13 @@ def test_projection_cut_along_k(seq, mode):
 
 @pytest.mark.parametrize("mode", [orc.MODE_DENSE, orc.MODE_KV, orc.MODE_O])
 @pytest.mark.parametrize("hidden,seq,max_seq", [
-    (3584, 300, 600),     # Q/K/V: 168 tiles of 256 x 128 in a context with a workspace of 128
+    (3584, 300, 600),     # Q/K/V: 168 tiles of 256 x 128 in a workspace holds 128
     (3584, 1100, 1100),   # Q and the output projection: 140 tiles
     (2048, 600, 1024),    # Q/K/V: 144 tiles
 ])
 def test_projection_of_more_tiles_than_the_workspace_holds(hidden, seq, max_seq, mode):
-    """Tile counts above the workspace's take a route that needs none; the context's other
-    memory (its packed weights among it) is what it was: a second step gives the same result."""
+    """Tile counts above what a workspace for a k cut in two holds take a route that needs none, and the
+    context's memory (its packed weights among it) is what it was: a second step gives the same result."""
     case = synth.make_case("llada8b", seed=hidden + seq, batch=1, seq=seq, hidden=hidden, n_heads=hidden // 128,
                            head_dim=128)
     state, gl = pu.oracle_fill(case), pu.GpuLayer(case, max_seq=max_seq)

@@ -104,6 +104,31 @@ def Bm():
     return binding
 
 
+@pytest.mark.parametrize("T,d,prefix", [
+    (2048, 1024, 0), (1793, 1024, 0),    # 64 tiles of 256 x 128; one row in the last row tile
+    (2048, 2048, 0), (1900, 2048, 107),  # 128 tiles; 1793 rows left by the prefix
+    (2305, 2048, 0),                     # 160 tiles: more than the workspace holds
+])
+def test_down_projection_cut_along_k(Bm, T, d, prefix):
+    """The down projection (96 k-steps) with two workgroups on the halves of a tile's k.  Three
+    steps in a row on the same ids: the sum does not depend on which workgroup comes first."""
+    cfg = dict(L=1, d=d, H=d // 128, ffn=6144, V=128, B=1, T=T)
+    params = synth.make_model_params(T, 1, d, cfg["ffn"], cfg["V"], "bf16", with_head=False)
+    m = _build(Bm, params, cfg, "bf16")
+    ids = synth.make_ids(T, 1, T, cfg["V"], T // 2, cfg["V"] - 1)
+    step = lambda: _gpu_step(m, cfg, "bf16", [orc.MODE_DENSE], [0.0], ids)
+    hidden, refreshed, tr = step()
+    caches = _check_step(cfg, "bf16", params, _zero_caches(cfg), [orc.MODE_DENSE], [0.0], ids, hidden, refreshed, tr)
+    if prefix:
+        m.set_prefix(prefix)
+        hidden, refreshed, tr = step()
+        _check_step(cfg, "bf16", params, caches, [orc.MODE_DENSE], [0.0], ids, hidden, refreshed, tr, prefix=prefix)
+    for _ in range(2):
+        again, _, trace = step()
+        assert np.array_equal(again, hidden) and np.array_equal(trace, tr)
+    m.destroy()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_small_model_blockwise_steps(Bm, dtype):
     cfg = dict(L=3, d=256, H=4, ffn=512, V=320, B=2, T=48)
