@@ -237,8 +237,8 @@ dare_status dare_set_prefix(dare_ctx* ctx, int prefix_len);
  * capture that must not meet an allocation, tight serving loops, harnesses that forbid
  * hipMalloc.  It needs no context and calls no hipMalloc, hipFree or any other allocating
  * routine, at the first call or later: the scratch that dare_create would allocate (queries,
- * attention rows, the fp32 scored query, the refreshed-row list) lives in a static device
- * array inside the library, which every GPU the library runs on holds until the process
+ * attention rows, the fp32 scored query, the refreshed-row list, partial sums) lives in a static
+ * device array inside the library, which every GPU the library runs on holds until the process
  * ends.
  *
  *   cfg      as for dare_create; max_batch and max_seq are not used
@@ -252,12 +252,12 @@ dare_status dare_set_prefix(dare_ctx* ctx, int prefix_len);
  *   batch * seq * hidden * sizeof(dtype)  <= DARE_STATIC_MAX_ROW_BYTES
  *   batch * seq * scored width            <= DARE_STATIC_MAX_SCORE_ELEMS
  * (scored width = head_dim, or hidden with score_head = -1); 1024 tokens of hidden 4096 in
- * bf16 fit exactly.  The array takes about 20.5 MiB per GPU.
+ * bf16 fit exactly.  The array takes about 29 MiB per GPU.
  *
  * All calls on one GPU share that GPU's array: two calls whose kernels overlap (different
  * streams, different threads) race; order them on one stream.  Nothing in the scratch has to
  * start at zero, and nothing is kept between calls: every word a kernel reads was written
- * earlier in the same call.
+ * earlier in the same call (counters by a small kernel, where a step uses any).
  *
  * dare_static_init(device) looks up the array's device address ahead of time (the step
  * call does it by itself on first use on a device); call it before a graph capture starts.

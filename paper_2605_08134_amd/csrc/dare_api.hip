@@ -471,7 +471,8 @@ dare_status dare_layer_step(dare_ctx* ctx, int mode, float threshold, int batch,
 namespace {
 
 // Layout of the static scratch (bytes): queries | attention rows | fp32 scored query (up to
-// 8 k-range slabs) | refreshed-row list | per-sequence offsets | counters of the scored columns.
+// 8 k-range slabs) | refreshed-row list | per-sequence offsets | parts of the attention whose keys are
+// cut | counters of the scored columns | counters of the parts.
 constexpr size_t kStaticRowBytes = DARE_STATIC_MAX_ROW_BYTES;          // batch * seq * hidden * sizeof(dtype)
 constexpr size_t kStaticScoreElems = DARE_STATIC_MAX_SCORE_ELEMS;     // fp32 elements of the scored query, slabs included
 constexpr size_t kStaticMaxTokens = kStaticRowBytes / (64 * 2);        // hidden >= 64, two bytes per element
@@ -480,10 +481,11 @@ constexpr size_t kStaticOffAttn = kStaticOffQ + kStaticRowBytes;
 constexpr size_t kStaticOffScore = kStaticOffAttn + kStaticRowBytes;
 constexpr size_t kStaticOffIdx = kStaticOffScore + kStaticScoreElems * sizeof(float);
 constexpr size_t kStaticOffOff = kStaticOffIdx + kStaticMaxTokens * sizeof(int32_t);
-constexpr size_t kStaticOffCount = kStaticOffOff + (kStaticMaxTokens + 64) * sizeof(int32_t);
-constexpr size_t kStaticBytes = kStaticOffCount + kScoreTiles * sizeof(int);
+constexpr size_t kStaticOffParts = kStaticOffOff + (kStaticMaxTokens + 64) * sizeof(int32_t);
+constexpr size_t kStaticOffCount = kStaticOffParts + attn_parts_elems(128) * sizeof(float);
+constexpr size_t kStaticBytes = kStaticOffCount + (kScoreTiles + kAttnParts) * sizeof(int);
 static_assert(kStaticOffAttn % 256 == 0 && kStaticOffScore % 256 == 0 && kStaticOffIdx % 256 == 0 &&
-                  kStaticOffOff % 256 == 0 && kStaticOffCount % 256 == 0, "scratch regions must stay aligned");
+                  kStaticOffOff % 256 == 0 && kStaticOffParts % 256 == 0 && kStaticOffCount % 256 == 0, "scratch regions must stay aligned");
 
 }  // namespace
 
@@ -578,11 +580,17 @@ dare_status dare_layer_step_static(const dare_config* cfg, const void* wqkv_t, c
   c.sel_idx = reinterpret_cast<int32_t*>(base + kStaticOffIdx);
   c.sel_off = reinterpret_cast<int32_t*>(base + kStaticOffOff);
   c.score_count = reinterpret_cast<int*>(base + kStaticOffCount);
+  const bool cut = cfg->dtype == DARE_BF16 && attn_may_cut(seq);
+  if (cut) {
+    c.part_out = reinterpret_cast<float*>(base + kStaticOffParts);
+    c.part_count = c.score_count + kScoreTiles;
+  }
   c.rule = DARE_RULE_SCORE;
   st = check_step_args(&c, mode, threshold, batch, seq, hidden, q_prev, k_cache, v_cache, o_cache, out, reuse_mask);
   // (counters that overlapping calls, which race for this array, may have left behind)
-  if (st == DARE_OK && mode == DARE_MODE_KVO && cfg->dtype == DARE_BF16 &&
-      (e = launch_zero_words(c.score_count, kScoreTiles / 2, static_cast<hipStream_t>(hip_stream))) != hipSuccess)
+  if (st == DARE_OK && cfg->dtype == DARE_BF16 && (mode == DARE_MODE_KVO || (mode == DARE_MODE_O && cut)) &&
+      (e = launch_zero_words(c.score_count, (kScoreTiles + kAttnParts) / 2, static_cast<hipStream_t>(hip_stream))) !=
+          hipSuccess)
     st = fail_hip(&c, e, "counters");
   if (st == DARE_OK)
     st = step_impl(&c, mode, threshold, batch, seq, hidden, q_prev, k_cache, v_cache, o_cache, out, reuse_mask,

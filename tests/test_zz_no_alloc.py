@@ -70,6 +70,31 @@ def test_static_step_equals_layer_step_on_two_calls_in_a_row():
         gl.layer.destroy()
 
 
+@pytest.mark.parametrize("batch,seq,heads,dh,frac", [
+    (1, 1024, 32, 128, 0.2),     # the largest rows: all-row projections in large tiles
+    (1, 2048, 16, 128, 0.004),   # few refreshed rows of many keys: keys cut over workgroups
+    (1, 4100, 2, 64, 0.01), (2, 1921, 8, 128, 0.3),
+])
+@pytest.mark.parametrize("mode", [orc.MODE_DENSE, orc.MODE_KV, orc.MODE_O, orc.MODE_KVO])
+def test_static_step_takes_the_same_routes_at_large_sizes(batch, seq, heads, dh, frac, mode):
+    """Bit for bit also where a step uses more scratch than queries and rows; twice, with another
+    step's contents in the array in between."""
+    from paper_2605_08134_amd import binding as B
+    case = synth.make_case("llada8b", seed=seq, batch=batch, seq=seq, hidden=heads * dh, n_heads=heads, head_dim=dh,
+                           fraction=frac)
+    rng = np.random.Generator(np.random.PCG64(seq))
+    state = {k: pu.store(rng.standard_normal(case["x_cur"].shape), "bf16") for k in ("k_cache", "v_cache", "o_cache")}
+    state["q_prev"] = (case["x_prev"].astype(np.float64) @ case["wq"][:, :dh].astype(np.float64)).astype(np.float32)
+    gl, packed = pu.GpuLayer(case), _packed(B, case)
+    want = gl.step(mode, synth.TAU_SEPARATING, case["x_cur"], state)
+    for other in (orc.MODE_KVO, orc.MODE_O):
+        got, _ = _static_step(B, case, packed, mode, synth.TAU_SEPARATING, state)
+        for k in KEYS:
+            assert np.array_equal(got[k], want[k], equal_nan=True), (mode, k)
+        _static_step(B, case, packed, other, synth.TAU_SEPARATING, state)
+    gl.layer.destroy()
+
+
 def test_static_step_fp32():
     from paper_2605_08134_amd import binding as B
     case = synth.make_case("tiny", seed=57, batch=2, seq=75)
