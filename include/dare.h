@@ -71,6 +71,10 @@ typedef struct {
  * Y = X W (Sec. 3.2 eq. 3, App. E.1).  They are copied and re-packed inside the
  * call; the caller may free them after the call returns (the call synchronises
  * the stream once, it is the only call that does).
+ * Device memory: the packed weights (4 hidden^2 elements), two rows of hidden and the
+ * scored query (fp32; eight times up to 4096 tokens) per token of max_batch * max_seq, and in
+ * bf16 from max_seq 1921 on 8.7 MB (head_dim 128; half for 64) for attention that shares the keys
+ * of few rows among workgroups.
  * Errors: INVALID_ARG (null pointer, bad config), UNSUPPORTED (head_dim not 64
  * or 128, hidden not a multiple of 64), OOM, HIP.  On error *out_ctx is NULL.
  */

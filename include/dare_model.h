@@ -36,8 +36,10 @@ typedef struct {
 } dare_model_config;
 
 /* Allocates the per-layer contexts' scratch, the K/V/O/score caches of every layer
- * ([max_batch, max_seq, hidden] each, zeroed) and the activation buffers.  Weights come
- * with the set_* calls.  hidden, ffn and vocab must be multiples of 64. */
+ * ([max_batch, max_seq, hidden] each, zeroed) and the activation buffers, and one workspace of
+ * partial sums that the layers use in turn (bf16: 33.6 MB where the down projection has 64 and
+ * more tiles of 256 x 128 and ffn >= 6144, 8.7 MB from max_seq 1921 on).  Weights come with the
+ * set_* calls.  hidden, ffn and vocab must be multiples of 64. */
 dare_status dare_model_create(const dare_model_config* cfg, void* hip_stream, dare_model** out);
 
 /* Weights of one layer (copied and re-packed; the caller may free them afterwards):
@@ -79,7 +81,8 @@ dare_status dare_model_step(dare_model* m, const int32_t* modes, const float* th
 dare_status dare_model_logits(dare_model* m, const void* hidden, const int32_t* rows, int n_rows,
                               void* logits, void* hip_stream);
 
-/* The context of one layer (owned by the model), e.g. for dare_drift_stats_*. */
+/* The context of one layer (owned by the model), e.g. for dare_drift_stats_*.  It has no part in the
+ * model's workspace of partial sums: a dare_layer_step on it computes without one. */
 dare_ctx* dare_model_layer(dare_model* m, int layer);
 
 dare_status dare_model_destroy(dare_model* m);

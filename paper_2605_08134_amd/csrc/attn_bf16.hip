@@ -494,15 +494,15 @@ hipError_t launch_dh(const AttnDev& p, const AttnArgs& a, hipStream_t s) {
   // Refreshed rows.  Laying the blocks out on the device costs 1 us, so fewer than 64 (sequence, head)
   // pairs, which blocks of 64 rows serve in one round unless most rows are refreshed, go without.
   if (a.idx && !a.many_rows) {
-    const bool cut = a.part_out && (a.seq + 127) / 128 >= kCutSteps;
+    const bool cut = a.parts.out && (a.seq + 127) / 128 >= kCutSteps;
     const long pairs = (long)a.batch * a.n_heads, blocks = pairs * ((a.seq + 63) / 64);  // with every row refreshed
     if (pairs < 64 && !cut) return launch_variant<DH, 2, 4, 32, 2>(p, a, s);
     if (blocks >= (1l << 23)) return launch_variant<DH, 4, 2, 64, 2>(p, a, s);  // (beyond small_div)
     AttnDev r = p;
     r.n_heads = a.n_heads;
     r.batch = a.batch;
-    r.part_out = a.part_out;
-    r.part_count = a.part_count;
+    r.part_out = a.parts.out;
+    r.part_count = a.parts.count;
     const long grid = cut || blocks >= 256 ? 256 : (blocks + 7) / 8 * 8;
     hipLaunchKernelGGL(attn_rows_bf16_kernel<DH>, dim3((unsigned)grid), dim3(512), 0, s, r);
     return hipGetLastError();

@@ -26,8 +26,7 @@ struct dare_ctx {
   size_t q_new_elems;
   int32_t* sel_idx;    // [max tokens]
   int32_t* sel_off;    // [max_batch + 1]
-  float* part_out;     // workspace of refreshed-row attention whose keys are cut, or nullptr
-  int* part_count;
+  AttnParts parts;     // workspace of refreshed-row attention whose keys are cut, or null
   int* score_count;    // [kScoreTiles] counters of the scored-column projection (bf16)
   // the block around the layer (dare_block_attach)
   bool has_block, has_bias;
@@ -53,6 +52,7 @@ struct dare_ctx {
 struct BlockExtras {
   const float* rope;   // rotary table or nullptr
   const void* x_resid; // hidden state before normalisation when out = x + O, else nullptr
+  AttnParts parts;     // workspace of the attention
 };
 
 namespace {
@@ -89,7 +89,7 @@ struct DeviceGuard {
 
 void free_ctx(dare_ctx* c) {
   if (!c) return;
-  void* bufs[] = {c->wqkv_t, c->wo_t, c->q_buf, c->attn_buf, c->q_new, c->sel_idx, c->sel_off, c->score_count, c->part_out, c->part_count, c->gain, c->bias, c->h_buf, c->rope_table, c->tau_dev, c->scores_buf,
+  void* bufs[] = {c->wqkv_t, c->wo_t, c->q_buf, c->attn_buf, c->q_new, c->sel_idx, c->sel_off, c->score_count, c->parts.out, c->parts.count, c->gain, c->bias, c->h_buf, c->rope_table, c->tau_dev, c->scores_buf,
                   c->stat_sum, c->act_idx, c->act_off};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -115,6 +115,13 @@ const char* dare_last_error(const dare_ctx* ctx) {
 
 dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, const void* wv,
                         const void* wo, void* hip_stream, dare_ctx** out_ctx) {
+  return create_context(cfg, wq, wk, wv, wo, true, hip_stream, out_ctx);
+}
+
+}  // extern "C"
+
+dare_status dare::create_context(const dare_config* cfg, const void* wq, const void* wk, const void* wv,
+                                 const void* wo, bool with_parts, void* hip_stream, dare_ctx** out_ctx) {
   if (out_ctx) *out_ctx = nullptr;
   if (!cfg || !out_ctx) return fail(nullptr, DARE_ERR_INVALID_ARG, "null config or out_ctx");
   if (cfg->struct_size != sizeof(dare_config))
@@ -148,8 +155,8 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   c->wqkv_t = c->wo_t = c->q_buf = c->attn_buf = nullptr;
   c->q_new = nullptr;
   c->sel_idx = c->sel_off = nullptr;
-  c->score_count = c->part_count = nullptr;
-  c->part_out = nullptr;
+  c->score_count = nullptr;
+  c->parts = AttnParts{nullptr, nullptr};
   c->has_block = c->has_bias = false;
   c->gain = c->bias = c->h_buf = nullptr;
   c->rope_table = nullptr;
@@ -164,7 +171,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   // projection has enough tiles without cutting k)
   c->q_new_elems = (size_t)max_tok * c->score_width;
   if (max_tok <= 4096) c->q_new_elems *= 8;
-  const bool cut = cfg->dtype == DARE_BF16 && attn_may_cut(cfg->max_seq);
+  const bool cut = with_parts && cfg->dtype == DARE_BF16 && attn_may_cut(cfg->max_seq);
   struct { void** p; size_t bytes; } allocs[] = {
       {&c->wqkv_t, 3 * d * d * c->esize},
       {&c->wo_t, d * d * c->esize},
@@ -173,8 +180,8 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
       {(void**)&c->q_new, c->q_new_elems * sizeof(float)},
       {(void**)&c->sel_idx, (size_t)max_tok * sizeof(int32_t)},
       {(void**)&c->sel_off, ((size_t)cfg->max_batch + 1) * sizeof(int32_t)},
-      {(void**)&c->part_out, cut ? attn_parts_elems(cfg->head_dim) * sizeof(float) : 0},
-      {(void**)&c->part_count, cut ? kAttnParts * sizeof(int) : 0},
+      {(void**)&c->parts.out, cut ? attn_parts_elems(cfg->head_dim) * sizeof(float) : 0},
+      {(void**)&c->parts.count, cut ? kAttnParts * sizeof(int) : 0},
       {(void**)&c->score_count, cfg->dtype == DARE_BF16 ? kScoreTiles * sizeof(int) : 0},
   };
   for (auto& a : allocs) {
@@ -193,7 +200,7 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
     e = launch_pack_weight(cfg->dtype, w3[i], cfg->hidden, cfg->hidden,
                            static_cast<char*>(c->wqkv_t) + (size_t)i * d * d * c->esize, cfg->hidden, s);
   if (e == hipSuccess) e = launch_pack_weight(cfg->dtype, wo, cfg->hidden, cfg->hidden, c->wo_t, cfg->hidden, s);
-  if (e == hipSuccess && cut) e = launch_zero_words(c->part_count, kAttnParts / 2, s);
+  if (e == hipSuccess && cut) e = launch_zero_words(c->parts.count, kAttnParts / 2, s);
   if (e == hipSuccess && c->score_count) e = launch_zero_words(c->score_count, kScoreTiles / 2, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) {
@@ -204,6 +211,8 @@ dare_status dare_create(const dare_config* cfg, const void* wq, const void* wk, 
   *out_ctx = c;
   return DARE_OK;
 }
+
+extern "C" {
 
 dare_status dare_destroy(dare_ctx* ctx) {
   if (!ctx) return DARE_OK;
@@ -410,8 +419,7 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
   a.idx = sel_o ? ctx->sel_idx : act_idx;
   a.sel_off = sel_o ? ctx->sel_off : (pre ? ctx->act_off : nullptr);
   a.many_rows = !sel_o && pre;
-  a.part_out = ctx->part_out;
-  a.part_count = ctx->part_count;
+  a.parts = bx.parts;
   if ((e = attn(ctx, a, s)) != hipSuccess) return fail_hip(ctx, e, "attention");
 
   // 6. Output projection (Alg. 1 line 11; Alg. 2 lines 9-11 with the cache after Wo).
@@ -461,7 +469,7 @@ dare_status dare_layer_step(dare_ctx* ctx, int mode, float threshold, int batch,
                                    o_cache, out, reuse_mask);
   if (st != DARE_OK) return st;
   return step_impl(ctx, mode, threshold, batch, seq, hidden, q_prev, k_cache, v_cache, o_cache, out,
-                   reuse_mask, sel_idx, sel_count, scores, BlockExtras{nullptr, nullptr}, hip_stream);
+                   reuse_mask, sel_idx, sel_count, scores, BlockExtras{nullptr, nullptr, ctx->parts}, hip_stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -582,8 +590,8 @@ dare_status dare_layer_step_static(const dare_config* cfg, const void* wqkv_t, c
   c.score_count = reinterpret_cast<int*>(base + kStaticOffCount);
   const bool cut = cfg->dtype == DARE_BF16 && attn_may_cut(seq);
   if (cut) {
-    c.part_out = reinterpret_cast<float*>(base + kStaticOffParts);
-    c.part_count = c.score_count + kScoreTiles;
+    c.parts.out = reinterpret_cast<float*>(base + kStaticOffParts);
+    c.parts.count = c.score_count + kScoreTiles;
   }
   c.rule = DARE_RULE_SCORE;
   st = check_step_args(&c, mode, threshold, batch, seq, hidden, q_prev, k_cache, v_cache, o_cache, out, reuse_mask);
@@ -594,7 +602,7 @@ dare_status dare_layer_step_static(const dare_config* cfg, const void* wqkv_t, c
     st = fail_hip(&c, e, "counters");
   if (st == DARE_OK)
     st = step_impl(&c, mode, threshold, batch, seq, hidden, q_prev, k_cache, v_cache, o_cache, out, reuse_mask,
-                   sel_idx, sel_count, scores, BlockExtras{nullptr, nullptr}, hip_stream);
+                   sel_idx, sel_count, scores, BlockExtras{nullptr, nullptr, c.parts}, hip_stream);
   if (st != DARE_OK) g_create_err = c.err;
   return st;
 }
@@ -691,7 +699,7 @@ dare_status dare_block_step(dare_ctx* ctx, int mode, float threshold, int batch,
     if (e != hipSuccess) return fail_hip(ctx, e, "normalisation");
     hidden = ctx->h_buf;
   }
-  BlockExtras bx{bc.rope_base > 0.f ? ctx->rope_table : nullptr, bc.residual ? x : nullptr};
+  BlockExtras bx{bc.rope_base > 0.f ? ctx->rope_table : nullptr, bc.residual ? x : nullptr, ctx->parts};
   return step_impl(ctx, mode, threshold, batch, seq, hidden, q_prev, k_cache, v_cache, o_cache, out,
                    reuse_mask, sel_idx, sel_count, scores, bx, hip_stream);
 }
@@ -701,13 +709,13 @@ dare_status dare_block_step(dare_ctx* ctx, int mode, float threshold, int batch,
 namespace dare {
 dare_status block_core(dare_ctx* ctx, int mode, float threshold, int batch, int seq, const void* h, float* q_prev,
                        void* k_cache, void* v_cache, void* o_cache, uint8_t* reuse_mask, int32_t* sel_count,
-                       void* hip_stream) {
+                       const AttnParts& parts, void* hip_stream) {
   if (!ctx) return DARE_ERR_INVALID_ARG;
   if (!ctx->has_block) return fail(ctx, DARE_ERR_INVALID_ARG, "no block attached");
   dare_status st = check_step_args(ctx, mode, threshold, batch, seq, h, q_prev, k_cache, v_cache, o_cache,
                                    o_cache, reuse_mask);
   if (st != DARE_OK) return st;
-  BlockExtras bx{ctx->block.rope_base > 0.f ? ctx->rope_table : nullptr, nullptr};
+  BlockExtras bx{ctx->block.rope_base > 0.f ? ctx->rope_table : nullptr, nullptr, parts};
   return step_impl(ctx, mode, threshold, batch, seq, h, q_prev, k_cache, v_cache, o_cache, o_cache, reuse_mask,
                    nullptr, sel_count, nullptr, bx, hip_stream);
 }

@@ -120,6 +120,14 @@ hipError_t launch_score_proj(const ScoreProjArgs& g, hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s);
 
+// Workspace for query blocks whose keys are cut over workgroups (bf16, refreshed rows):
+// attn_parts_elems() floats and kAttnParts counters that are 0 before the first launch and
+// that every launch leaves at 0; one launch at a time.  Null pointers: keys are never cut.
+struct AttnParts {
+  float* out;
+  int* count;
+};
+
 struct AttnArgs {
   const void* q;
   const void* k;
@@ -129,11 +137,7 @@ struct AttnArgs {
   const int32_t* idx;      // optional selected rows
   const int32_t* sel_off;  // [batch+1] when idx != nullptr
   bool many_rows;          // the listed rows are most of each sequence (a frozen prefix), not a few
-  // optional workspace for query blocks whose keys are cut over workgroups (bf16, refreshed rows):
-  // attn_parts_elems() floats and kAttnParts counters that are 0 before the first launch and
-  // that every launch leaves at 0; one launch at a time
-  float* part_out;
-  int* part_count;
+  AttnParts parts;
 };
 constexpr int kAttnParts = 256;  // parts of a launch, at most: one per CU
 constexpr size_t attn_parts_elems(int head_dim) { return (size_t)kAttnParts * 64 * 2 * (head_dim / 2 + 2); }
@@ -175,8 +179,14 @@ hipError_t launch_swiglu(int dtype, void* gate, const void* up, int n_rows, int 
 // runtime, which fuses them with its neighbours: `h` is the hidden state already normalised,
 // the block output O goes into o_cache only (no residual sum).  Arguments are checked as
 // in dare_layer_step; rotary embedding as attached to the context.
+// parts: the workspace of a step (its owner runs one step at a time), not the context's.
 dare_status block_core(dare_ctx* ctx, int mode, float threshold, int batch, int seq, const void* h, float* q_prev,
                        void* k_cache, void* v_cache, void* o_cache, uint8_t* reuse_mask, int32_t* sel_count,
-                       void* hip_stream);
+                       const AttnParts& parts, void* hip_stream);
+
+// dare_create, optionally without the workspace of attention whose keys are cut: for contexts whose
+// steps run through block_core.
+dare_status create_context(const dare_config* cfg, const void* wq, const void* wk, const void* wv, const void* wo,
+                           bool with_parts, void* hip_stream, dare_ctx** out_ctx);
 
 }  // namespace dare

@@ -115,6 +115,7 @@ struct dare_model {
   int32_t* act_off;
   float* split_tiles; // workspace of projections whose k is cut in two, or nullptr
   int* split_count;
+  AttnParts parts;    // workspace of attention whose keys are cut, lent to one layer after the other
   int rule, prefix;
   std::vector<void*> owned;
   std::string err;
@@ -207,10 +208,12 @@ dare_status dare_model_create(const dare_model_config* cfg, void* hip_stream, da
   m->embed = m->final_gain = m->head_t = nullptr;
   m->split_tiles = nullptr;
   m->split_count = nullptr;
+  m->parts = AttnParts{nullptr, nullptr};
   m->rule = DARE_RULE_SCORE;
   m->prefix = 0;
   const size_t d = cfg->hidden, es = m->esize, tok = (size_t)max_tok;
   const bool split = cfg->dtype == DARE_BF16 && gemm_may_split(max_tok, cfg->hidden, cfg->ffn);
+  const bool cut = cfg->dtype == DARE_BF16 && attn_may_cut(cfg->max_seq);
   struct { void** p; size_t bytes; bool zero; } bufs[] = {
       {&m->x, tok * d * es, false},          {&m->h2, tok * d * es, false},
       {&m->h1, tok * d * es, false},
@@ -219,7 +222,9 @@ dare_status dare_model_create(const dare_model_config* cfg, void* hip_stream, da
       {(void**)&m->mask, tok, false},        {(void**)&m->act_idx, tok * sizeof(int32_t), false},
       {(void**)&m->act_off, ((size_t)cfg->max_batch + 1) * sizeof(int32_t), false},
       {(void**)&m->split_tiles, split ? gemm_split_tiles_bytes() : 0, false},
-      {(void**)&m->split_count, split ? kSplitTiles * sizeof(int) : 0, true},
+      {(void**)&m->split_count, split ? kSplitTiles * sizeof(int) : 0, false},
+      {(void**)&m->parts.out, cut ? attn_parts_elems(cfg->head_dim) * sizeof(float) : 0, false},
+      {(void**)&m->parts.count, cut ? kAttnParts * sizeof(int) : 0, false},
       {&m->embed, (size_t)cfg->vocab * d * es, false}, {&m->final_gain, d * es, false},
   };
   for (auto& b : bufs)
@@ -247,8 +252,12 @@ dare_status dare_model_create(const dare_model_config* cfg, void* hip_stream, da
         return st;
       }
   }
-  if ((e = hipStreamSynchronize(static_cast<hipStream_t>(hip_stream))) != hipSuccess) {
-    dare_status st = mfail_hip(nullptr, e, "hipStreamSynchronize");
+  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  if (split) e = launch_zero_words(m->split_count, kSplitTiles / 2, s);  // (64-bit words)
+  if (e == hipSuccess && cut) e = launch_zero_words(m->parts.count, kAttnParts / 2, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) {
+    dare_status st = mfail_hip(nullptr, e, "counters");
     free_model(m);
     return st;
   }
@@ -292,7 +301,7 @@ dare_status dare_model_set_layer(dare_model* m, int layer, const void* attn_gain
   lc.score_head = 0;
   lc.device = c.device;
   dare_ctx* ctx = nullptr;
-  dare_status st = dare_create(&lc, wq, wk, wv, wo, hip_stream, &ctx);
+  dare_status st = create_context(&lc, wq, wk, wv, wo, false, hip_stream, &ctx);
   if (st != DARE_OK) return mfail(m, st, std::string("layer context: ") + dare_last_error(nullptr));
   m->layers[layer] = ctx;
   dare_block_config bc{};
@@ -415,7 +424,7 @@ dare_status dare_model_step(dare_model* m, const int32_t* modes, const float* th
     // attention block on the normalised rows; its output O goes to the layer's output cache
     dare_status st = block_core(m->layers[l], modes[l], thresholds[l], batch, seq, m->h1, lm.q_prev, lm.k_cache,
                                 lm.v_cache, lm.o_cache, m->mask, refreshed ? refreshed + (size_t)l * batch : nullptr,
-                                hip_stream);
+                                m->parts, hip_stream);
     if (st != DARE_OK) return mfail(m, st, "layer " + std::to_string(l) + ": " + dare_last_error(m->layers[l]));
     // x <- x + O for every row (frozen rows add their cached O), n = rmsnorm(x)
     e = launch_residual_norm(c.dtype, m->x, lm.o_cache, lm.ffn_gain, c.norm_eps, n_tok, d, m->h2, 0, 0, s);

@@ -129,6 +129,42 @@ def test_down_projection_cut_along_k(Bm, T, d, prefix):
     m.destroy()
 
 
+def test_layers_share_the_workspace_of_attention_with_cut_keys(Bm):
+    """The workspace that steps of 1921 tokens and more use (8.7 MB) is the model's: a layer takes
+    no more memory at 2048 than at 1920 tokens than its own rows do (1/16 of about 14 MB)."""
+    def per_layer(T):
+        free = []
+        for L in (1, 9):
+            cfg = dict(L=L, d=128, H=1, ffn=128, V=128, B=1, T=T)
+            params = synth.make_model_params(1, L, 128, 128, 128, "bf16", with_head=False)
+            m = _build(Bm, params, cfg, "bf16")
+            torch.cuda.synchronize()
+            free.append(torch.cuda.mem_get_info()[0])
+            m.destroy()
+        return (free[0] - free[1]) / 8
+
+    per_layer(1920)                              # (once, for what the allocator keeps)
+    assert per_layer(2048) - per_layer(1920) < 4 * 2 ** 20
+
+
+@pytest.mark.parametrize("T,prefix", [(2048, 0), (4100, 1000)])
+def test_few_rows_of_long_sequences_in_two_layers(Bm, T, prefix):
+    """Both layers cut the keys of their few refreshed rows over workgroups, in one workspace."""
+    cfg = dict(L=2, d=256, H=2, ffn=256, V=256, B=1, T=T)
+    params = synth.make_model_params(T, 2, 256, 256, 256, "bf16", with_head=False)
+    m = _build(Bm, params, cfg, "bf16")
+    ids = synth.make_ids(T, 1, T, 256, T // 2, 255)
+    modes, taus = [orc.MODE_DENSE] * 2, [0.0] * 2
+    caches = _check_step(cfg, "bf16", params, _zero_caches(cfg), modes, taus, ids, *_gpu_step(m, cfg, "bf16", modes, taus, ids))
+    m.set_prefix(prefix)
+    for t in range(3):
+        ids[0, T - 2 - t] = 7 + t
+        modes, taus = [orc.MODE_KVO] * 2, [1e-3] * 2
+        caches = _check_step(cfg, "bf16", params, caches, modes, taus, ids, *_gpu_step(m, cfg, "bf16", modes, taus, ids),
+                             prefix=prefix)
+    m.destroy()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_small_model_blockwise_steps(Bm, dtype):
     cfg = dict(L=3, d=256, H=4, ffn=512, V=320, B=2, T=48)
