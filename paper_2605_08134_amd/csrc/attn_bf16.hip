@@ -66,8 +66,9 @@ __device__ __forceinline__ void wait_all_and_barrier() {
 // step (it cannot tell that such a read and a load into another stage do not meet), which drains
 // the ring and leaves no stage in flight under the value product.
 __device__ __forceinline__ void load_to_lds(const bf16_t* src, unsigned char* lds) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src),
-               "s"((unsigned)(size_t)(lptr_t)lds) : "memory");  // (nothing else here uses m0)
+  // (the address is an operand in M0, set by the compiler, which then knows what M0 holds; a wait state
+  // between the move to M0 and the load)
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"((unsigned)(size_t)(lptr_t)lds) : "memory");
 }
 
 template <int DH, int KW, int TK, int NST>

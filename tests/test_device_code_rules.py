@@ -20,3 +20,13 @@ def test_no_workgroup_waits_for_another(name):
     whatever a counter holds, every launch ends."""
     assert not re.search(r"(while|for)\s*\([^{};]*__hip_atomic_load", _code(name))
     assert "s_sleep" not in _code(name)
+
+
+@pytest.mark.parametrize("name", SOURCES)
+def test_inline_assembly_leaves_m0_to_the_compiler(name):
+    """Loads into LDS take their address from M0, and so do things of the compiler's own: an asm
+    statement gets it as an operand and writes it behind nobody's back."""
+    for stmt in re.findall(r"asm\s+volatile\s*\((.*?)\)\s*;", _code(name), flags=re.S):
+        assert not re.search(r"\bm0\s*,", stmt), stmt
+        if "load_lds" in stmt:
+            assert '"{m0}"' in stmt, stmt
