@@ -802,7 +802,8 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   }
   wait_vmcnt_and_barrier<TN == 4 ? 10 : (TN == 3 ? 8 : 12)>();
   read_b(0, 0, 0);
-  if (grp == 1) asm volatile("s_barrier" ::: "memory");
+  // (group 0 refills the region that these reads take from after this barrier)
+  if (grp == 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   if constexpr (TN == 4) {
     for (int kt = 0; kt < KT; ++kt) {
       read_a(kt);

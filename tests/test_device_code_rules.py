@@ -30,3 +30,12 @@ def test_inline_assembly_leaves_m0_to_the_compiler(name):
         assert not re.search(r"\bm0\s*,", stmt), stmt
         if "load_lds" in stmt:
             assert '"{m0}"' in stmt, stmt
+
+
+def test_ping_pong_groups_part_after_their_first_reads():
+    """gemm_tile_pp: group 1 falls one barrier behind once its first fragment reads have returned; the
+    region they come from may be refilled from that barrier on."""
+    code = _code("gemm_bf16.hip")
+    start = code.index("read_b(0, 0, 0);")
+    assert re.match(r'read_b\(0, 0, 0\);\s*if \(grp == 1\) asm volatile\("s_waitcnt lgkmcnt\(0\)\\n\\ts_barrier"',
+                    code[start:])
