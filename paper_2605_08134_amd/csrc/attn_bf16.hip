@@ -90,7 +90,8 @@ __device__ __forceinline__ int v_swizzle(int key) {
 // [off, off + cnt) of the sequence.  Called by all QW*KW waves of the workgroup.
 template <int DH, int QW, int KW, int TK, int NST>
 __device__ __forceinline__ void attn_block(const AttnDev& p, int b, int h, int qt, int cnt, int off,
-                                           unsigned char* smem, int part = 0, int n_parts = 1, int block = 0) {
+                                           unsigned char* smem, const int tid, int part = 0, int n_parts = 1,
+                                           int block = 0) {
   constexpr int NW = QW * KW;
   constexpr int ROWB = DH * 2;             // bytes per K or V row of one head
   constexpr int CPR = DH / 8;              // 16-byte chunks per row
@@ -107,7 +108,7 @@ __device__ __forceinline__ void attn_block(const AttnDev& p, int b, int h, int q
   static_assert(LPW * (NST - 1) < 64, "vmcnt range");
 
   const int T = p.seq;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (a scalar: M0 addressing)
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (a scalar: M0 addressing)
   const int qw = wave % QW, kw = wave / QW;
   const int l32 = lane & 31, half = lane >> 5;
 
@@ -395,87 +396,109 @@ __global__ void __launch_bounds__(QW* KW * 64) attn_bf16_kernel(AttnDev p) {
     cnt = p.seq;
   }
   if (qt * (32 * QW) >= cnt) return;
-  attn_block<DH, QW, KW, TK, NST>(p, b, h, qt, cnt, off, smem);
+  attn_block<DH, QW, KW, TK, NST>(p, b, h, qt, cnt, off, smem, threadIdx.x);
 }
 
 // Refreshed rows: how many of a sequence's tokens there are is known on the device only, so the
-// grid is one workgroup per CU and the query blocks are laid out from the counts: 64 rows per
-// block while that gives at most one block per CU, else 128 (a K/V tile then feeds twice the rows:
-// 3 x 777 tokens, 194 rows each: 24 against 35 us; 1 x 1024, 205 rows: 18 us against 21 us the other
-// way round).  Few blocks over long sequences leave most CUs without one and the others with a long
-// chain of key steps: their keys are cut over workgroups, in parts of at least kPartSteps steps (the
-// hand-over costs about as much as four).
+// grid is as many workgroups as run at once (kRowsGrid) and the query blocks are laid out from the
+// counts: 64 rows per block while that gives at most one block per workgroup, else 128 (a K/V tile then
+// feeds twice the rows: 3 x 777 tokens, 194 rows each: 24 against 35 us; 1 x 1024, 205 rows: 18 us against
+// 21 us the other way round).  Few blocks over long sequences leave most CUs without one and the others
+// with a long chain of key steps: their keys are cut over workgroups, in parts of at least kPartSteps
+// steps (the hand-over costs about as much as four).
 // Blocks are numbered by sequence, head, part, query block; consecutive ones, which share keys,
 // go to one XCD (workgroup ids are dealt round-robin to the 8 XCDs).
-constexpr int kPartSteps = 8, kCutSteps = 2 * kPartSteps;
-// v / n for 0 <= v < 2^24, n > 0 (a handful of instructions where the exact division takes 40)
+// A wave holds the blocks of 64 sequences, a sequence per lane, summed up along the lanes: the
+// sequence of a block is a ballot away, and a workgroup, whose blocks come in ascending order, walks
+// the sequences twice in all (lane by lane it was 75 ns per sequence and block).
+// v / n for 0 <= v < 2^24, n > 0, the same in all lanes (a handful of instructions where the exact
+// division takes 40)
 __device__ __forceinline__ int small_div(int v, int n) {
-  int q = (int)((float)v * __builtin_amdgcn_rcpf((float)n));
+  int q = __builtin_amdgcn_readfirstlane((int)((float)v * __builtin_amdgcn_rcpf((float)n)));
   const int r = v - q * n;
   if (r >= n) ++q;
   if (r < 0) --q;
   return q;
 }
+// sum over the lanes up to and including this one
+__device__ __forceinline__ int wave_prefix_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8: within 16 lanes
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast 15: lane 15 to row 1, 47 to row 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast 31: lane 31 to rows 2 and 3
+  return v;
+}
+// Workgroups that run at once: one per CU (128 KB of LDS), two with 64 channels per head (64 KB)
 template <int DH>
-__global__ void __launch_bounds__(512) attn_rows_bf16_kernel(AttnDev p) {
+constexpr int kRowsGrid = DH == 64 ? 512 : 256;
+template <int DH>
+__global__ void __launch_bounds__(512, kRowsGrid<DH> / 128) attn_rows_bf16_kernel(AttnDev p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[attn_smem_bytes<DH, 4, 32, 2>()];
   static_assert(attn_smem_bytes<DH, 4, 32, 2>() == attn_smem_bytes<DH, 2, 64, 2>(), "one stage memory for both blocks");
-  const int lane = threadIdx.x & 63;
-  // refreshed rows of sequences c0 + lane; read lane by lane below (scalar work: a wave scan's
-  // cross-lane reads cost 1 us in front of everything else)
-  auto counts = [&](int c0) __attribute__((always_inline)) {
-    const int b = c0 + lane;
-    return b < p.batch ? p.sel_off[b + 1] - p.sel_off[b] : 0;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int off_l = 0, cnt_l = 0;  // the 64 sequences held: first list position and refreshed rows of c0 + lane
+  auto hold = [&](int c0) __attribute__((always_inline)) {
+    const int b = c0 + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
+    off_l = b < p.batch ? p.sel_off[b] : 0;
+    cnt_l = b < p.batch ? p.sel_off[b + 1] - off_l : 0;
   };
-  const int first_counts = counts(0);
   int narrow = 0, wide = 0;  // blocks of 64 and of 128 rows
   for (int c0 = 0; c0 < p.batch; c0 += 64) {
-    const int c = c0 ? counts(c0) : first_counts;
-    for (int l = 0; l < 64 && c0 + l < p.batch; ++l) {
-      const int cnt = __builtin_amdgcn_readlane(c, l);
-      narrow += (cnt + 63) >> 6;
-      wide += (cnt + 127) >> 7;
-    }
+    hold(c0);
+    narrow += __builtin_amdgcn_readlane(wave_prefix_sum((cnt_l + 63) >> 6), 63);
+    wide += __builtin_amdgcn_readlane(wave_prefix_sum((cnt_l + 127) >> 7), 63);
   }
   narrow *= p.n_heads;
   wide *= p.n_heads;
-  const bool is_wide = narrow > 256;
-  const int rows = is_wide ? 128 : 64, blocks = is_wide ? wide : narrow;
+  const bool is_wide = narrow > kRowsGrid<DH>;
+  const int shift = is_wide ? 7 : 6, rows = 1 << shift, blocks = is_wide ? wide : narrow;
   const int steps = (p.seq + 127) >> 7;  // of 128 keys, in either block
   int n_parts = 1;
   if (p.part_out && blocks > 0 && steps >= kCutSteps) {
-    const int room = small_div(256, blocks), most = steps / kPartSteps;
+    const int room = small_div(kAttnParts, blocks), most = steps / kPartSteps;
     n_parts = room < most ? room : most;
     if (n_parts < 1) n_parts = 1;
   }
   const int total = blocks * n_parts, per_xcd = (total + 7) >> 3;
+  const int per_block = p.n_heads * n_parts;  // units per query block of a sequence
+  int c0 = 0, before = 0;                     // sequences held, query blocks in front of them
+  if (p.batch > 64) hold(0);
+  int upto = wave_prefix_sum((cnt_l + rows - 1) >> shift);
   for (int slot = blockIdx.x >> 3; slot < per_xcd; slot += gridDim.x >> 3) {
     const int u = (blockIdx.x & 7) * per_xcd + slot;
     if (u >= total) break;
-    // the sequence: first one whose running total of units exceeds u
-    int b = 0, v = u;
-    for (int c0 = 0, found = 0; !found; c0 += 64) {
-      const int c = c0 ? counts(c0) : first_counts;
-      for (int l = 0; l < 64; ++l) {
-        const int units = ((__builtin_amdgcn_readlane(c, l) + rows - 1) >> (is_wide ? 7 : 6)) * p.n_heads * n_parts;
-        if (v < units) {
-          b = c0 + l;
-          found = 1;
-          break;
-        }
-        v -= units;
-      }
+    // the sequence: first one up to whose end there are more than u units
+    const int w = small_div(u, per_block);
+    for (int held = __builtin_amdgcn_readlane(upto, 63); before + held <= w; held = __builtin_amdgcn_readlane(upto, 63)) {
+      before += held;
+      c0 += 64;
+      hold(c0);
+      upto = wave_prefix_sum((cnt_l + rows - 1) >> shift);
     }
-    const int off = p.sel_off[b], cnt = p.sel_off[b + 1] - off, n_qt = (cnt + rows - 1) / rows;
+    const int l = __builtin_ctzll(__ballot(before + upto > w));
+    const int b = c0 + l, off = __builtin_amdgcn_readlane(off_l, l), cnt = __builtin_amdgcn_readlane(cnt_l, l);
+    const int n_qt = (cnt + rows - 1) >> shift;
+    // units in front of the sequence
+    const int first = (before + __builtin_amdgcn_readlane(upto, l) - n_qt) * per_block, v = u - first;
     const int part_and_head = small_div(v, n_qt), qt = v - part_and_head * n_qt;
     const int h = small_div(part_and_head, n_parts), part = part_and_head - h * n_parts;
     // block number without the parts: what precedes this sequence, then head and query block
-    const int block = small_div(u - v, n_parts) + h * n_qt + qt;
-    if (slot != (int)(blockIdx.x >> 3)) __syncthreads();  // the stage memory is reused
-    if (is_wide)
-      attn_block<DH, 4, 2, 64, 2>(p, b, h, qt, cnt, off, smem, part, n_parts, block);
+    const int block = small_div(first, n_parts) + h * n_qt + qt;
+    // (a thread number that the compiler cannot trace back, nor keep: it would hold it, and what both
+    // blocks derive from it, in registers that the blocks need)
+    unsigned every = ~0u;
+    asm volatile("" : "+s"(every));
+    const int tid = wave * 64 + (int)__builtin_amdgcn_mbcnt_hi(every, __builtin_amdgcn_mbcnt_lo(every, 0));
+    if (is_wide)  // (more than kAttnParts / 2 blocks: one part each)
+      attn_block<DH, 4, 2, 64, 2>(p, b, h, qt, cnt, off, smem, tid);
     else
-      attn_block<DH, 2, 4, 32, 2>(p, b, h, qt, cnt, off, smem, part, n_parts, block);
+      attn_block<DH, 2, 4, 32, 2>(p, b, h, qt, cnt, off, smem, tid, part, n_parts, block);
+    if (slot + (int)(gridDim.x >> 3) >= per_xcd) break;
+    hold(c0);  // (again, rather than in registers that the block needs)
+    upto = wave_prefix_sum((cnt_l + rows - 1) >> shift);
+    __syncthreads();  // the stage memory is reused
   }
 }
 
@@ -492,29 +515,22 @@ hipError_t launch_variant(AttnDev p, const AttnArgs& a, hipStream_t s) {
 
 template <int DH>
 hipError_t launch_dh(const AttnDev& p, const AttnArgs& a, hipStream_t s) {
-  // Refreshed rows.  Laying the blocks out on the device costs 1 us, so fewer than 64 (sequence, head)
-  // pairs, which blocks of 64 rows serve in one round unless most rows are refreshed, go without.
-  if (a.idx && !a.many_rows) {
-    const bool cut = a.parts.out && (a.seq + 127) / 128 >= kCutSteps;
-    const long pairs = (long)a.batch * a.n_heads, blocks = pairs * ((a.seq + 63) / 64);  // with every row refreshed
-    if (pairs < 64 && !cut) return launch_variant<DH, 2, 4, 32, 2>(p, a, s);
-    if (blocks >= (1l << 23)) return launch_variant<DH, 4, 2, 64, 2>(p, a, s);  // (beyond small_div)
-    AttnDev r = p;
-    r.n_heads = a.n_heads;
-    r.batch = a.batch;
-    r.part_out = a.parts.out;
-    r.part_count = a.parts.count;
-    const long grid = cut || blocks >= 256 ? 256 : (blocks + 7) / 8 * 8;
-    hipLaunchKernelGGL(attn_rows_bf16_kernel<DH>, dim3((unsigned)grid), dim3(512), 0, s, r);
-    return hipGetLastError();
+  switch (attn_route(a.batch, a.n_heads, a.seq, a.idx != nullptr, a.many_rows, a.parts.out != nullptr)) {
+    case AttnRoute::kNarrow: return launch_variant<DH, 2, 4, 32, 2>(p, a, s);
+    case AttnRoute::kWide: return launch_variant<DH, 4, 2, 64, 2>(p, a, s);
+    case AttnRoute::kTall: return launch_variant<DH, 8, 1, 64, 2>(p, a, s);
+    case AttnRoute::kLaidOut: break;
   }
-  // Most rows of every sequence and enough of them for a block of 256 query rows per
-  // workgroup (8 query-waves, no key split) to fill the chip: a K/V tile then feeds twice
-  // the MFMAs per byte that enters LDS (8 x 2048 tokens: 547 us against 661; 1 x 4096: 261 against
-  // 295; with 1 x 1024 tokens there are only 128 such blocks: 33 against 24 us).
-  if ((long)a.batch * a.n_heads * ((a.seq + 255) / 256) >= 256)
-    return launch_variant<DH, 8, 1, 64, 2>(p, a, s);
-  return launch_variant<DH, 4, 2, 64, 2>(p, a, s);
+  AttnDev r = p;
+  r.n_heads = a.n_heads;
+  r.batch = a.batch;
+  r.part_out = a.parts.out;
+  r.part_count = a.parts.count;
+  const long blocks = (long)a.batch * a.n_heads * ((a.seq + 63) / 64);  // with every row refreshed
+  const bool cut = a.parts.out && attn_may_cut(a.seq);
+  const long grid = cut || blocks >= kRowsGrid<DH> ? kRowsGrid<DH> : (blocks + 7) / 8 * 8;
+  hipLaunchKernelGGL(attn_rows_bf16_kernel<DH>, dim3((unsigned)grid), dim3(512), 0, s, r);
+  return hipGetLastError();
 }
 
 }  // namespace

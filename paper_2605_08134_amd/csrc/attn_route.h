@@ -1,0 +1,50 @@
+// Kernel of a bf16 attention, as plain host arithmetic: no HIP here, so that the rule can be evaluated
+// over its whole range without a GPU.
+#pragma once
+
+namespace dare {
+
+enum class AttnRoute {
+  kNarrow,  // blocks of 64 query rows, four key-waves; one workgroup per possible block
+  kWide,    // 128 query rows, two key-waves; likewise
+  kTall,    // 256 query rows, no key split; likewise
+  kLaidOut, // one workgroup per CU walks blocks laid out from the refreshed-row counts
+};
+
+constexpr int kPartSteps = 8;               // least key steps (of 128) of a part where keys are cut
+constexpr int kCutSteps = 2 * kPartSteps;   // key steps from which on they can be
+// whether a step of up to seq tokens per sequence can use the workspace of cut keys
+constexpr bool attn_may_cut(int seq) { return (seq + 127) / 128 >= kCutSteps; }
+
+// listed: the query rows are a list; many: that list holds most rows of every sequence (a frozen
+// prefix), not a few (the refreshed rows).
+constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, bool many, bool workspace) {
+  const long pairs = batch * n_heads;
+  auto blocks = [&](int rows) { return pairs * ((seq + rows - 1) / rows); };  // with every row listed
+  if (listed && !many) {
+    // Refreshed rows.  Laying the blocks out on the device takes every workgroup a walk over the
+    // counts, a memory latency per 64 sequences, in front of everything and again between its
+    // blocks, where a key step of a block takes 0.5-1 us: it has to be short against the steps (us, first
+    // with a workgroup per possible block, a few rows of each sequence refreshed: 16 x 256 tokens of 32
+    // heads 31 and 21, 64 x 1024 of 8 heads 72 and 28, 8 x 2048 of 32 heads 144 and 45; the single step of a
+    // short sequence it can only delay).
+    const bool cut = workspace && attn_may_cut(seq);
+    const AttnRoute direct = pairs < 128 ? AttnRoute::kNarrow : AttnRoute::kWide;
+    const long steps = (seq + 127) / 128;
+    if (batch > 8 * steps) return direct;
+    if (blocks(64) >= (1l << 23)) return direct;  // (beyond the kernel's division)
+    if (cut) return AttnRoute::kLaidOut;
+    // Fewer than 64 pairs: narrow blocks serve them in one round unless most rows are refreshed.  No
+    // more possible blocks than CUs: one round whatever is refreshed (4 x 256 of 32 heads 8.6 us, laid
+    // out 9.7).
+    if (pairs < 64 || blocks(direct == AttnRoute::kNarrow ? 64 : 128) <= 256) return direct;
+    return AttnRoute::kLaidOut;
+  }
+  // Most rows of every sequence and enough of them for a block of 256 query rows per
+  // workgroup (8 query-waves, no key split) to fill the chip: a K/V tile then feeds twice
+  // the MFMAs per byte that enters LDS (8 x 2048 tokens: 547 us against 661; 1 x 4096: 261 against
+  // 295; with 1 x 1024 tokens there are only 128 such blocks: 33 against 24 us).
+  return blocks(256) >= 256 ? AttnRoute::kTall : AttnRoute::kWide;
+}
+
+}  // namespace dare

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_route.h"
 #include "dare.h"
 #include "dare_kernels.h"
 #include "gemm_route.h"
@@ -141,8 +142,6 @@ struct AttnArgs {
 };
 constexpr int kAttnParts = 256;  // parts of a launch, at most: one per CU
 constexpr size_t attn_parts_elems(int head_dim) { return (size_t)kAttnParts * 64 * 2 * (head_dim / 2 + 2); }
-// whether a step of up to seq tokens per sequence can use that workspace (parts of 8 x 128 keys)
-constexpr bool attn_may_cut(int seq) { return (seq + 127) / 128 >= 16; }
 hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t s);
 

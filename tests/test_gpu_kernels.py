@@ -368,8 +368,11 @@ def test_attention_selected_rows(B, dtype, batch, seq, heads, dh, frac):
 
 @pytest.mark.parametrize("batch,seq,heads,dh,frac", [
     (5, 300, 32, 64, 0.6),        # more than 256 blocks of 64 rows: blocks of 128
-    (70, 40, 1, 64, 0.5),         # more sequences than lanes
+    (70, 40, 1, 64, 0.5),         # many short sequences: a workgroup per possible block
     (2, 300, 32, 128, 0.9),       # 64 x 5 blocks: 128 rows, ragged
+    (130, 2100, 1, 64, 0.02),     # more sequences than lanes, twice over: 64 rows
+    (66, 1153, 8, 64, 0.08),      # the same, two blocks of 64 rows per (sequence, head) or one of 128
+    (65, 1100, 4, 128, 0.001),    # the same, half of the sequences without a refreshed row
 ])
 def test_attention_block_layout_from_the_counts(B, batch, seq, heads, dh, frac):
     """Per element: a probability p_i rounded to bf16 is off by at most 2^-9 p_i, in the sum over
