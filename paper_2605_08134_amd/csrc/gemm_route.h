@@ -35,8 +35,10 @@ constexpr bool gemm_may_split(long m, long n, long k) {
 // wins: 256 x 192 costs about 3/4 of 256 x 256 (1870 against 2500 cycles per k-step), so the narrow
 // one is taken where it needs fewer quarter-rounds of the 256 CUs (1024 x 12288: one full round
 // against one round with 64 CUs idle, 78 against 85 us; 2331 x 12288: three against two, 209 against
-// 198 us).  256 x 128 takes over while it fills more than half of the CUs (unless 128 x 128 does with
-// one round: 520 x 6144 x 4096 39 us, a round of 256 x 128 at that k 59), and with two workgroups
+// 198 us).  256 x 128 takes over while it fills more than half of the CUs and needs fewer rounds of
+// them than 128 x 128 (a round at k = 4096 takes 59 us against 39: 520 x 6144, 144 tiles against 240, one
+// round each; 600 x 12288, 288 against 480, two each: 96 against 83 us; 1024 x 9216 x 3072, two against
+// three: 78 against 94), and with two workgroups
 // per tile where there are kSplitTiles / 2 to kSplitTiles of them.  128 x 128 with 8 waves is the best
 // shape when the larger ones would leave most CUs idle.
 // One row tile (the output embedding of a few rows): a stream over the weights, of which 256-row
@@ -54,7 +56,7 @@ constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace)
     if (t3 >= 224 && (q3 < q4 || t4 < 176)) return GemmRoute::kPp192;
     if (t4 >= 176) return GemmRoute::kPp256;
     const int t2 = tiles_of(m, n, kPpRows, 128), ksteps = k / kRouteBK;
-    if (t2 > kSplitTiles && t128 > 256) return GemmRoute::kPp128;
+    if (t2 > kSplitTiles && (t2 + 255) / 256 < (t128 + 255) / 256) return GemmRoute::kPp128;
     if (workspace && t2 >= kSplitTiles / 2 && t2 <= kSplitTiles && ksteps % 2 == 0 && ksteps >= kSplitMinSteps)
       return GemmRoute::kPp128Split;
   }

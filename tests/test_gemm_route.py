@@ -27,6 +27,9 @@ int main() {
         if (without == GemmRoute::kPp128Split) fail("no workspace", m, n, k);
         if (gemm_route(m, n, k, 2, true) == GemmRoute::kPp128Split) fail("k already in ranges", m, n, k);
         const int t = tiles_of(m, n, kPpRows, 128);
+        // a round of 256 x 128 tiles takes 1.5 times one of 128 x 128
+        if (without == GemmRoute::kPp128 && (t + 255) / 256 >= (tiles_of(m, n, 128, 128) + 255) / 256)
+          fail("larger tiles in as many rounds", m, n, k);
         if (with != GemmRoute::kPp128Split) {
           if (with != without) fail("workspace changes another route", m, n, k);
           continue;
