@@ -14,8 +14,10 @@
 // What bounds it.  Small shapes (128 x 256 x 256): the latency of a workgroup, launch, one round
 // of loads, sum, store.  Four waves take a quarter of k each, 4 x 16 k in flight per wave, and 16 x 16
 // tiles give the most workgroups: 16.6 -> 3.8 us against a 64 x 64 LDS tile that walked k in steps of 16
-// with two barriers each.  Larger shapes: the matrix pipe (157 TFLOP/s nominal; 112 reached)
-// and the loads that feed it, hence 64 x 64 wave tiles, 64 MFMAs per 8 loads.
+// with two barriers each.  Larger shapes: the matrix pipe (157 TFLOP/s nominal; 117 reached)
+// and the loads that feed it, hence 64 x 64 wave tiles, 64 MFMAs per 8 loads.  The four waves share the
+// tile there too: four tiles of 64 x 64 per workgroup, every wave all of k, are no faster with many
+// rows (1024 x 12288 x 4096 916 us against 880) and waste up to 127 rows of 128 with few.
 #include "dare_common.h"
 
 namespace dare {
@@ -50,117 +52,91 @@ __device__ __forceinline__ void store4_f32(const GemmF32Dev& p, long tok, int co
 
 constexpr int kKParts = 4;  // quarters of k (k is a multiple of 64: whole steps of 16 each)
 
-// Four waves, wave tile 16 TM x 16 TN.  SPLIT: all waves on one tile, a quarter of k each, sums
-// added through LDS; else 2 x 2 wave tiles per workgroup and every wave takes all quarters.  UNR:
-// steps of 16 k whose loads are in flight at once (registers allow one for 64 x 64 wave tiles, whose
-// 64 MFMAs per step cover a load).
-template <int TM, int TN, bool SPLIT, int UNR>
+// Four waves on one tile of 16 TM x 16 TN, a quarter of k each, sums added through LDS.  UNR: steps of 16 k
+// whose loads are in flight at once (registers allow one for 64 x 64, whose 64 MFMAs per step
+// cover a load).
+template <int TM, int TN, int UNR>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmF32Dev p) {
-  constexpr int SIDE = SPLIT ? 1 : 2;
-  constexpr int BM = 16 * TM * SIDE, BN = 16 * TN * SIDE;
+  constexpr int BM = 16 * TM, BN = 16 * TN;
   const int m = p.m_dev ? *p.m_dev : p.m_max;
   const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
   if (m0 >= m) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, kq = lane >> 4;
-  const int wm = SPLIT ? 0 : (wave & 1), wn = SPLIT ? 0 : (wave >> 1);
 
   long tok[TM];
   const float* asrc[TM];
   const float* bsrc[TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
-    int row = m0 + (wm * TM + i) * 16 + l16;
+    int row = m0 + i * 16 + l16;
     row = row < m ? row : m - 1;
     tok[i] = p.idx ? (long)p.idx[row] : (long)row;
     asrc[i] = p.a + tok[i] * p.lda + kq * 4;
   }
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
-    int col = n0 + (wn * TN + j) * 16 + l16;
+    int col = n0 + j * 16 + l16;
     col = col < p.n ? col : p.n - 1;
     bsrc[j] = p.wt + (long)col * p.k + kq * 4;
   }
 
   const int steps = p.k / (16 * kKParts);  // per quarter
-  // the sum over quarter `part`, chunks of UNR steps whose loads are all in flight at once
-  auto quarter = [&](int part, f32x4 (&acc)[TM][TN]) __attribute__((always_inline)) {
+  // the sum over the wave's quarter, chunks of UNR steps whose loads are all in flight at once
+  f32x4 acc[TM][TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int kbase = part * steps * 16;
-    for (int s = 0; s < steps; s += UNR) {
-      f32x4 fa[UNR][TM], fb[UNR][TN];
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int kbase = wave * steps * 16;
+  for (int s = 0; s < steps; s += UNR) {
+    f32x4 fa[UNR][TM], fb[UNR][TN];
 #pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int k0 = kbase + (s + u < steps ? s + u : steps - 1) * 16;
+    for (int u = 0; u < UNR; ++u) {
+      const int k0 = kbase + (s + u < steps ? s + u : steps - 1) * 16;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[u][i] = *reinterpret_cast<const f32x4*>(asrc[i] + k0);
+      for (int i = 0; i < TM; ++i) fa[u][i] = *reinterpret_cast<const f32x4*>(asrc[i] + k0);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) fb[u][j] = *reinterpret_cast<const f32x4*>(bsrc[j] + k0);
-      }
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        if (s + u >= steps) break;  // (uniform)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[u][j][e], fa[u][i][e], acc[i][j], 0, 0, 0);
-      }
+      for (int j = 0; j < TN; ++j) fb[u][j] = *reinterpret_cast<const f32x4*>(bsrc[j] + k0);
     }
-  };
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      if (s + u >= steps) break;  // (uniform)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[u][j][e], fa[u][i][e], acc[i][j], 0, 0, 0);
+    }
+  }
 
-  // acc[i][j][e] = C[row, col]: row = base + 16 i + l16, col = base + 16 j + 4 kq + e
-  if constexpr (SPLIT) {
-    __shared__ f32x4 part_sum[kKParts][TM * TN][64];
-    f32x4 acc[TM][TN];
-    quarter(wave, acc);
+  // acc[i][j][e]: row 16 i + l16, column 16 j + 4 kq + e of the tile
+  __shared__ f32x4 part_sum[kKParts][TM * TN][64];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) part_sum[wave][i * TN + j][lane] = acc[i][j];
-    __syncthreads();
+    for (int j = 0; j < TN; ++j) part_sum[wave][i * TN + j][lane] = acc[i][j];
+  __syncthreads();
 #pragma unroll
-    for (int t = 0; t < TM * TN; ++t) {
-      if (t % 4 != wave) continue;
-      const int i = t / TN, j = t % TN;
-      f32x4 v = part_sum[0][t][lane];
+  for (int t = 0; t < TM * TN; ++t) {
+    if (t % 4 != wave) continue;
+    const int i = t / TN, j = t % TN;
+    f32x4 v = part_sum[0][t][lane];
 #pragma unroll
-      for (int w = 1; w < kKParts; ++w) v += part_sum[w][t][lane];
-      const int row = m0 + i * 16 + l16, col = n0 + j * 16 + kq * 4;
-      if (row < m && col < p.n) store4_f32(p, tok[i], col, v);
-    }
-  } else {
-    f32x4 sum[TM][TN];
-    quarter(0, sum);
-    for (int part = 1; part < kKParts; ++part) {
-      f32x4 acc[TM][TN];
-      quarter(part, acc);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) sum[i][j] += acc[i][j];
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int row = m0 + (wm * TM + i) * 16 + l16, col = n0 + (wn * TN + j) * 16 + kq * 4;
-        if (row < m && col < p.n) store4_f32(p, tok[i], col, sum[i][j]);
-      }
+    for (int w = 1; w < kKParts; ++w) v += part_sum[w][t][lane];
+    const int row = m0 + i * 16 + l16, col = n0 + j * 16 + kq * 4;
+    if (row < m && col < p.n) store4_f32(p, tok[i], col, v);
   }
 }
 
-template <int TM, int TN, bool SPLIT, int UNR>
+template <int TM, int TN, int UNR>
 hipError_t launch_shape(const GemmF32Dev& p, hipStream_t s) {
-  constexpr int BM = 16 * TM * (SPLIT ? 1 : 2), BN = 16 * TN * (SPLIT ? 1 : 2);
+  constexpr int BM = 16 * TM, BN = 16 * TN;
   const int tm = (p.m_max + BM - 1) / BM, tn = (p.n + BN - 1) / BN;
   if (tm == 0 || tn == 0) return hipSuccess;
-  hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, SPLIT, UNR>), dim3(tm, tn), dim3(256), 0, s, p);
+  hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, UNR>), dim3(tm, tn), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
@@ -188,15 +164,14 @@ hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
   p.rope_dh = g.rope_dh;
   p.rope_seq = g.rope_seq;
   // The largest tile that gives most of the chip's 256 CUs a workgroup.  Measured (us; before: 64 x 64
-  // tiles through LDS): 1024 x 12288 x 4096 1334 -> 919 (128 x 128), 1024 x 2048 x 2048 141 -> 80 and
-  // 514 x 3072 x 1024 74 -> 46 (64 x 64; 129 and 59 with 32 x 32), 64 x 4096 x 4096 235 -> 41 (32 x 32; 60 with
-  // 16 x 16, 83 with 64 x 64).
+  // tiles through LDS): 1024 x 12288 x 4096 1325 -> 880, 1024 x 2048 x 2048 141 -> 80 and
+  // 514 x 3072 x 1024 74 -> 46, 32 x 126464 x 4096 920 -> 691, 205 refreshed of 1024 rows x 12288 x 4096 1095 ->
+  // 925 (64 x 64), 64 x 4096 x 4096 235 -> 43 (32 x 32; 64 with 16 x 16, 84 with 64 x 64).
   auto tiles = [&](int b) { return (long)((g.m_max + b - 1) / b) * ((g.n + b - 1) / b); };
   constexpr long kFill = 192;
-  if (tiles(128) >= kFill) return launch_shape<4, 4, false, 1>(p, s);
-  if (tiles(64) >= kFill) return launch_shape<4, 4, true, 1>(p, s);
-  if (tiles(32) >= kFill) return launch_shape<2, 2, true, 4>(p, s);
-  return launch_shape<1, 1, true, 4>(p, s);
+  if (tiles(64) >= kFill) return launch_shape<4, 4, 1>(p, s);
+  if (tiles(32) >= kFill) return launch_shape<2, 2, 4>(p, s);
+  return launch_shape<1, 1, 4>(p, s);
 }
 
 }  // namespace dare

@@ -86,7 +86,7 @@ def test_gemm_all_rows_large_tiles(B, m, n, k, seg, tile):
     (17, 80, 64, "16 x 16, one step per quarter of k"),
     (150, 1296, 320, "32 x 32, five steps per quarter (a chunk of four and a rest), ragged both ways"),
     (600, 1296, 448, "64 x 64, ragged both ways"),
-    (1473, 2064, 192, "128 x 128, ragged both ways"),
+    (1473, 2064, 192, "64 x 64, many tiles, one row in the last row tile's last 16"),
 ])
 def test_gemm_f32_tile_shapes_agree_bit_for_bit(B, m, n, k, tile):
     """The sum over k has one order whatever the tile shape: a row of the launch equals the
