@@ -286,7 +286,7 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
            ksteps / (k_ranges * 2) >= 4 && (size_t)n_tok * sw * (k_ranges * 2) <= ctx->q_new_elems)
       k_ranges *= 2;
   }
-  if (mode == DARE_MODE_KVO && cf.dtype == DARE_BF16 && sw == cf.head_dim) {
+  if (mode == DARE_MODE_KVO && cf.dtype == DARE_BF16 && sw == cf.head_dim && score_in_projection(n_act, d)) {
     // only the scored columns of Q for every row, scored in the same launch
     ScoreProjArgs g{};
     g.a = hidden;

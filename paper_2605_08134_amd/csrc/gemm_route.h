@@ -64,6 +64,14 @@ constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace)
   return GemmRoute::kTile64;
 }
 
+// Scored columns: whether the score is taken in the launch that projects them, rather than in one of its
+// own.  With a long k and one round of 64 x 64 tiles or a little less, the tiles of the plain projection
+// pull less per CU than whole queries do (projection, score and selection of a step that refreshes
+// nothing, k = 4096, one launch against two: 1024 rows 18.0 and 18.3 us, 2048 21.0 and 20.9, 3072 27.0 and 25.9, 4096 27.7 and
+// 25.5, 6144 35.2 and 32.9, 8192, where the plain projection takes larger tiles, 35.9 and 50.9; k = 2048:
+// 4096 rows 22.0 and 22.9).
+constexpr bool score_in_projection(int rows, int k) { return k < 3072 || rows <= 2560 || rows > 8064; }
+
 // LDS of the scored-column projection once its k loop is over: bm queries, score_query_stride floats
 // apart, from offset 0, and the arrival number of the workgroup
 constexpr int score_query_stride(int width) { return width + 4; }

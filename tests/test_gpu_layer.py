@@ -101,6 +101,7 @@ def _unchanged_tokens_score_zero(batch, seq, hidden, first, second, score_head):
     (1, 37, 256, 4, 64, 0), (3, 333, 512, 4, 128, 11),        # 16 rows per workgroup, ragged
     (2, 1000, 4096, 32, 128, 0), (1, 1000, 2048, 32, 64, 3),  # row tiles with k cut over workgroups
     (4, 4075, 512, 4, 128, 0), (4, 4075, 512, 8, 64, 100),    # 64 rows per workgroup
+    (3, 900, 3072, 24, 128, 7), (5, 1000, 4096, 64, 64, 0),   # in two launches
 ])
 def test_scored_columns(batch, seq, hidden, heads, dh, prefix):
     """Score cache, scores and masks of the launch that projects the scored columns and scores them,
