@@ -109,7 +109,7 @@ __device__ __forceinline__ void attn_block(const AttnDev& p, int b, int h, int q
 
   const int T = p.seq;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (a scalar: M0 addressing)
-  const int qw = wave % QW, kw = wave / QW;
+  const int qw = (unsigned)wave % QW, kw = (unsigned)wave / QW;
   const int l32 = lane & 31, half = lane >> 5;
 
   // the query row of this lane
@@ -133,11 +133,13 @@ __device__ __forceinline__ void attn_block(const AttnDev& p, int b, int h, int q
   const bf16_t* ld_src[LPW]; // K or V base + chunk offset
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
-    const int sr = (wave * LPW + i) * RPL + lane / CPR;  // row within the stage
+    // (unsigned: the compiler knows no range of a wave number read from one lane, and signed quotients
+    // took 80 instructions in front of the first load)
+    const unsigned sr = (unsigned)(wave * LPW + i) * RPL + (unsigned)lane / CPR;  // row within the stage
     const int tile = sr / (2 * TK), within = sr % (2 * TK);
     const bool is_v = within >= TK;
-    const int key_local = within % TK;
-    const int chunk = (lane % CPR) ^ (is_v ? v_swizzle<DH>(key_local) : k_swizzle<DH>(key_local));
+    const int key_local = (unsigned)within % TK;
+    const int chunk = ((unsigned)lane % CPR) ^ (is_v ? v_swizzle<DH>(key_local) : k_swizzle<DH>(key_local));
     ld_key[i] = tile * TK + key_local;
     ld_src[i] = (is_v ? vbase : kbase) + chunk * 8;
   }
@@ -442,6 +444,7 @@ __global__ void __launch_bounds__(512, kRowsGrid<DH> / 128) attn_rows_bf16_kerne
   __shared__ __attribute__((aligned(1024))) unsigned char smem[attn_smem_bytes<DH, 4, 32, 2>()];
   static_assert(attn_smem_bytes<DH, 4, 32, 2>() == attn_smem_bytes<DH, 2, 64, 2>(), "one stage memory for both blocks");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __builtin_assume(p.idx != nullptr);
   int off_l = 0, cnt_l = 0;  // the 64 sequences held: first list position and refreshed rows of c0 + lane
   auto hold = [&](int c0) __attribute__((always_inline)) {
     const int b = c0 + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
@@ -466,13 +469,15 @@ __global__ void __launch_bounds__(512, kRowsGrid<DH> / 128) attn_rows_bf16_kerne
     if (n_parts < 1) n_parts = 1;
   }
   const int total = blocks * n_parts, per_xcd = (total + 7) >> 3;
-  const int per_block = p.n_heads * n_parts;  // units per query block of a sequence
+  int per_block = p.n_heads * n_parts;        // units per query block of a sequence
   int c0 = 0, before = 0;                     // sequences held, query blocks in front of them
   if (p.batch > 64) hold(0);
   int upto = wave_prefix_sum((cnt_l + rows - 1) >> shift);
   for (int slot = blockIdx.x >> 3; slot < per_xcd; slot += gridDim.x >> 3) {
     const int u = (blockIdx.x & 7) * per_xcd + slot;
     if (u >= total) break;
+    // (or their reciprocals stay in vector registers, which the block needs)
+    asm volatile("" : "+s"(n_parts), "+s"(per_block));
     // the sequence: first one up to whose end there are more than u units
     const int w = small_div(u, per_block);
     for (int held = __builtin_amdgcn_readlane(upto, 63); before + held <= w; held = __builtin_amdgcn_readlane(upto, 63)) {
