@@ -22,8 +22,9 @@
 // (max, sum, O) and are merged once at the end through LDS, in a fixed order.
 // Few query rows (the refreshed rows of a step) use narrow query blocks with KW > 1,
 // which turns the available waves towards the key axis and fills the chip, and with very few
-// of them the keys of a block are cut over workgroups as well; many rows use wide blocks (128 rows with two key-waves, or 256 rows with none when there are
-// enough of them), which re-read K and V less often.
+// of them the keys of a block are cut over workgroups as well; many rows use wide blocks (128
+// rows with two key-waves, or 256 rows with none when there are enough of them), which re-read K
+// and V less often.  attn_route.h holds the rule.
 #include "dare_common.h"
 
 namespace dare {

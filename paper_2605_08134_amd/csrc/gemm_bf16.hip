@@ -639,7 +639,7 @@ constexpr int pp_smem_bytes() {
 // chunk XOR of row r of a 32-row weight block
 __device__ __forceinline__ int pp_bkey(int r) { return ((r >> 1) & 1) | (((r >> 3) & 3) << 1); }
 
-// vblock, forced_tile_*, lidx and the result as in gemm_tile; called by all 512 threads.
+// vblock, lidx and the result as in gemm_tile; called by all 512 threads.
 template <int TN, bool SPLIT = false>
 __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsigned char* smem, const int vblock,
                                              lds_idx_t lidx = nullptr) {
