@@ -45,7 +45,7 @@ struct AttnDev {
   // keys of a query block cut over workgroups (attn_rows_bf16_kernel): partial results, and
   // counters that are 0 before and after the launch; nullptr = never cut
   float* part_out;
-  int* part_count;
+  unsigned* part_count;
   float scale_log2;
 };
 
@@ -340,11 +340,10 @@ __device__ __forceinline__ void attn_block(const AttnDev& p, int b, int h, int q
       __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), parts, part * kSlot + ml_off, 0, kDeviceScope);
     }
     wait_all_and_barrier();
-    int* arrived = reinterpret_cast<int*>(smem);
-    if (tid == 0) *arrived = __hip_atomic_fetch_add(p.part_count + block, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int* last = reinterpret_cast<int*>(smem);
+    if (tid == 0) *last = arrive_last(p.part_count + block, n_parts);
     __syncthreads();
-    if (*arrived != n_parts - 1) return;
-    if (tid == 0) __hip_atomic_store(p.part_count + block, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!*last) return;
     if (kw == 0 && valid) {
       m_run = -INFINITY;
       l_all = 0.f;

@@ -27,7 +27,7 @@ struct dare_ctx {
   int32_t* sel_idx;    // [max tokens]
   int32_t* sel_off;    // [max_batch + 1]
   AttnParts parts;     // workspace of refreshed-row attention whose keys are cut, or null
-  int* score_count;    // [kScoreTiles] counters of the scored-column projection (bf16)
+  unsigned* score_count;  // [kScoreTiles] counters of the scored-column projection (bf16)
   // the block around the layer (dare_block_attach)
   bool has_block, has_bias;
   dare_block_config block;
@@ -587,7 +587,7 @@ dare_status dare_layer_step_static(const dare_config* cfg, const void* wqkv_t, c
   c.q_new_elems = kStaticScoreElems;
   c.sel_idx = reinterpret_cast<int32_t*>(base + kStaticOffIdx);
   c.sel_off = reinterpret_cast<int32_t*>(base + kStaticOffOff);
-  c.score_count = reinterpret_cast<int*>(base + kStaticOffCount);
+  c.score_count = reinterpret_cast<unsigned*>(base + kStaticOffCount);
   const bool cut = cfg->dtype == DARE_BF16 && attn_may_cut(seq);
   if (cut) {
     c.parts.out = reinterpret_cast<float*>(base + kStaticOffParts);

@@ -21,6 +21,13 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// One of n workgroups arrives at *count (device scope, relaxed): true for the last.  The counter wraps to 0
+// in the same operation, so calls that overlap against the rules (and then compute what they may) leave it
+// at 0 as well once all of their workgroups have arrived, and the next call finds it so.
+__device__ __forceinline__ bool arrive_last(unsigned* count, int n) {
+  return atomicInc(count, (unsigned)n - 1) == (unsigned)n - 1;
+}
+
 constexpr int kWave = 64;
 
 // ---- launchers (defined one per .hip file); all return a hipError_t ----------
@@ -113,7 +120,7 @@ struct ScoreProjArgs {
   // before the launch and that the launch leaves at 0; nullptr = one workgroup per row tile
   float* sums;
   size_t sums_elems;
-  int* count;            // [kScoreTiles]
+  unsigned* count;       // [kScoreTiles]
 };
 constexpr int kScoreTiles = 256;
 hipError_t launch_score_proj(const ScoreProjArgs& g, hipStream_t s);
@@ -126,7 +133,7 @@ hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s);
 // that every launch leaves at 0; one launch at a time.  Null pointers: keys are never cut.
 struct AttnParts {
   float* out;
-  int* count;
+  unsigned* count;
 };
 
 struct AttnArgs {

@@ -1222,7 +1222,7 @@ struct ScoreProjDev {
   float* scores;
   uint8_t* mask;
   float* sums;
-  int* count;
+  unsigned* count;
   int k, m, k_parts, ranges;  // workgroups per row tile; ranges of the summation tree
   int force_refresh, batch, seq, prefix;
   float threshold;
@@ -1242,10 +1242,11 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) score_proj_kernel(Score
   // (one LDS array only: with a second one the compiler tracks which of them a global -> LDS load
   // may write, and puts s_waitcnt vmcnt(0) in front of the fragment reads, which drains the ring)
   __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE_BYTES];
-  // the arrival number lies behind the queries, which a wave may write while another one still reads it
+  // whether this workgroup is the last one lies behind the queries, which a wave may write while another
+  // one still reads it
   constexpr int ARRIVED = score_arrived_offset(BM, WIDTH);
-  static_assert(ARRIVED + 4 <= STAGES * STAGE_BYTES, "the arrival number must fit into the stage memory");
-  int& arrived = *reinterpret_cast<int*>(smem + ARRIVED);
+  static_assert(ARRIVED + 4 <= STAGES * STAGE_BYTES, "the flag must fit into the stage memory");
+  int& last_here = *reinterpret_cast<int*>(smem + ARRIVED);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // frozen tokens: always reused, never scored
@@ -1356,10 +1357,9 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) score_proj_kernel(Score
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), slots, part * kSlot + ((i * TN + j) * NT + tid) * 16, 0, kDeviceScope);
     wait_vmcnt<0>();
     __syncthreads();
-    if (tid == 0) arrived = __hip_atomic_fetch_add(p.count + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) last_here = arrive_last(p.count + tile, p.k_parts);
     __syncthreads();
-    if (arrived != p.k_parts - 1) return;
-    if (tid == 0) __hip_atomic_store(p.count + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!last_here) return;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll

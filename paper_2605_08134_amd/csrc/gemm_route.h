@@ -73,7 +73,7 @@ constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace)
 constexpr bool score_in_projection(int rows, int k) { return k < 3072 || rows <= 2560 || rows > 8064; }
 
 // LDS of the scored-column projection once its k loop is over: bm queries, score_query_stride floats
-// apart, from offset 0, and the arrival number of the workgroup
+// apart, from offset 0, and the word that says whether the workgroup is the last one
 constexpr int score_query_stride(int width) { return width + 4; }
 constexpr int score_arrived_offset(int bm, int width) { return bm * score_query_stride(width) * 4; }
 

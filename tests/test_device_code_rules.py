@@ -23,6 +23,13 @@ def test_no_workgroup_waits_for_another(name):
 
 
 @pytest.mark.parametrize("name", SOURCES)
+def test_arrival_counters_wrap_by_themselves(name):
+    """The arrival that is last takes the counter back to 0 in the same operation: a store of 0 beside
+    it could fall between the arrivals of two overlapping calls and leave the counter off for good."""
+    assert "__hip_atomic_store" not in _code(name)
+
+
+@pytest.mark.parametrize("name", SOURCES)
 def test_inline_assembly_leaves_m0_to_the_compiler(name):
     """Loads into LDS take their address from M0, and so do things of the compiler's own: an asm
     statement gets it as an operand and writes it behind nobody's back."""

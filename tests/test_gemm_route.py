@@ -83,7 +83,7 @@ int main() {
 """
 
 
-def test_arrival_number_of_the_scored_columns_is_no_query_word(tmp_path):
-    """Every wave of the last workgroup reads the arrival number and then writes its queries into
+def test_last_flag_of_the_scored_columns_is_no_query_word(tmp_path):
+    """Every wave of the last workgroup reads that it is the last and then writes its queries into
     the same LDS array, with no barrier in between: the two must not share a word."""
     assert _run(tmp_path, SCORE_LDS).returncode == 0
