@@ -77,12 +77,8 @@ struct GemmArgs {
 constexpr int kSelMaxTokens = 2048;
 constexpr size_t gemm_split_tiles_bytes() { return (size_t)kSplitTiles * 2 * kPpRows * 128 * sizeof(float); }
 
-// Rotation of the channel pairs (v0, v1) and (v2, v3) of four neighbouring output
-// columns col .. col + 3 (col a multiple of 4) of token tok.
-__device__ __forceinline__ void rope_rotate4(const float* __restrict__ table, int dh, int seq, long tok,
-                                             int col, float& v0, float& v1, float& v2, float& v3) {
-  const int pos = (int)(tok % seq);
-  const f32x4 cs = *reinterpret_cast<const f32x4*>(table + ((long)pos * (dh >> 1) + ((col % dh) >> 1)) * 2);
+// Rotation of the channel pairs (v0, v1) and (v2, v3) by the table's (cos, sin) pairs of both
+__device__ __forceinline__ void rope_rotate4(const f32x4 cs, float& v0, float& v1, float& v2, float& v3) {
   const float a0 = v0 * cs[0] - v1 * cs[1], a1 = v0 * cs[1] + v1 * cs[0];
   const float a2 = v2 * cs[2] - v3 * cs[3], a3 = v2 * cs[3] + v3 * cs[2];
   v0 = a0;

@@ -80,10 +80,22 @@ typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 typedef const __attribute__((address_space(3))) int32_t* lds_idx_t;  // a row list held in LDS
 
-// Token id of listed row `row`: from the list in LDS when the kernel derived it itself, else
-// from the caller's list, else the row itself.
-__device__ __forceinline__ long row_token(const int32_t* __restrict__ gidx, lds_idx_t lidx, int row) {
-  return lidx ? (long)lidx[row] : (gidx ? (long)gidx[row] : (long)row);
+// Token ids of listed rows: from the list in LDS when the kernel derived it itself, else from the
+// caller's list, else the rows themselves.  (One branch around all of them: a branch per row takes
+// longer than the reads.)
+template <int N>
+__device__ __forceinline__ void row_tokens(const int32_t* __restrict__ gidx, lds_idx_t lidx, const int (&row)[N],
+                                           int (&tok)[N]) {
+  if (lidx) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) tok[i] = lidx[row[i]];
+  } else if (gidx) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) tok[i] = gidx[row[i]];
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) tok[i] = row[i];
+  }
 }
 
 // Wait until at most N of this wave's vector-memory operations are outstanding
@@ -107,63 +119,87 @@ constexpr int smem_bytes() {
   return STAGES * (BM + BN) * ROW_BYTES;
 }
 
-// Four neighbouring output columns col .. col + 3 (col a multiple of 4) of token tok: the
-// fp32 copy of the scored columns (before any rotation), then rotation, rounding and the
-// store into the column's segment.
-__device__ __forceinline__ void store4(const GemmDev& p, float* c32, long tok, int col, float v0, float v1,
-                                       float v2, float v3) {
-  if (p.swiglu_pairs) {  // (gate, up) pairs: two outputs silu(gate) * up at columns col / 2, col / 2 + 1
-    bf16x2 o;
-    o[0] = (bf16_t)(v0 / (1.0f + __expf(-v0)) * v1);
-    o[1] = (bf16_t)(v2 / (1.0f + __expf(-v2)) * v3);
-    *reinterpret_cast<bf16x2*>(p.c0 + tok * p.ldc + (col >> 1)) = o;
-    return;
-  }
-  if (c32 && col < p.c32_cols) {
-    const f32x4 o = {v0, v1, v2, v3};
-    *reinterpret_cast<f32x4*>(c32 + tok * p.c32_cols + col) = o;
-  }
-  const int seg = col / p.seg_n;
-  bf16_t* cbase = seg == 0 ? p.c0 : (seg == 1 ? p.c1 : p.c2);
-  if (!cbase) return;
-  if (p.rope && col < p.rope_cols) rope_rotate4(p.rope, p.rope_dh, p.rope_seq, tok, col, v0, v1, v2, v3);
-  bf16x4 o;
-  o[0] = (bf16_t)v0;
-  o[1] = (bf16_t)v1;
-  o[2] = (bf16_t)v2;
-  o[3] = (bf16_t)v3;
-  *reinterpret_cast<bf16x4*>(cbase + tok * p.ldc + (col - seg * p.seg_n)) = o;
-}
-
-// Eight neighbouring output columns col .. col + 7 (col a multiple of 8; a segment, whose width
-// is a multiple of 32, holds all of them): one 16-byte store where store4 makes two of 8.
-__device__ __forceinline__ void store8(const GemmDev& p, long tok, int col, const float* v) {
+// Epilogue of a wave tile: W (4 or 8) neighbouring output columns col[j] .. col[j] + W - 1 (col[j] a multiple
+// of W; a segment, whose width is a multiple of 32, holds all of them) of tokens tok[i], live[i] or not,
+// value(i, j, e) each.  Plain: the fp32 copy of the scored columns (before any rotation), then
+// rotation, rounding and the store into the column's segment.  Gated: (gate, up) pairs, W / 2 outputs
+// silu(gate) * up from column col / 2 on.
+// What a launch asks for is settled outside the loops and what a column needs outside that over the rows: decided
+// at every store, with the kernel's arguments read again and a division each for segment and
+// position, the epilogue was as long as a third of the k loop (1024 x 4096 x 4096: 39 -> 34 us).
+template <int W, int TM, int TN, class Value>
+__device__ __forceinline__ void store_tile(const GemmDev& p, float* c32, const int (&tok)[TM], const bool (&live)[TM],
+                                           const int (&col)[TN], Value value) {
+  static_assert(W == 4 || W == 8, "columns of a store");
+  typedef __bf16 out_t __attribute__((ext_vector_type(W)));
+  typedef __bf16 half_t __attribute__((ext_vector_type(W / 2)));
   if (p.swiglu_pairs) {
-    bf16x4 o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = (bf16_t)(v[2 * e] / (1.0f + __expf(-v[2 * e])) * v[2 * e + 1]);
-    *reinterpret_cast<bf16x4*>(p.c0 + tok * p.ldc + (col >> 1)) = o;
+    for (int i = 0; i < TM; ++i) {
+      bf16_t* row = p.c0 + (long)tok[i] * p.ldc;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        half_t o;
+#pragma unroll
+        for (int e = 0; e < W / 2; ++e) {
+          const float g = value(i, j, 2 * e);
+          o[e] = (bf16_t)(g / (1.0f + __expf(-g)) * value(i, j, 2 * e + 1));
+        }
+        if (live[i] && col[j] < p.n) *reinterpret_cast<half_t*>(row + (col[j] >> 1)) = o;
+      }
+    }
     return;
   }
-  float y[8];
+  int pos[TM];
+  if (p.rope) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) y[e] = v[e];
-#pragma unroll
-  for (int h = 0; h < 8; h += 4) {
-    if (p.c32 && col + h < p.c32_cols) {
-      const f32x4 o = {y[h], y[h + 1], y[h + 2], y[h + 3]};
-      *reinterpret_cast<f32x4*>(p.c32 + tok * p.c32_cols + col + h) = o;
-    }
-    if (p.rope && col + h < p.rope_cols)
-      rope_rotate4(p.rope, p.rope_dh, p.rope_seq, tok, col + h, y[h], y[h + 1], y[h + 2], y[h + 3]);
+    for (int i = 0; i < TM; ++i) pos[i] = (unsigned)tok[i] % (unsigned)p.rope_seq;
   }
-  const int seg = col / p.seg_n;
-  bf16_t* cbase = seg == 0 ? p.c0 : (seg == 1 ? p.c1 : p.c2);
-  if (!cbase) return;
-  bf16x8 o;
+  const long ldc = p.ldc;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = (bf16_t)y[e];
-  *reinterpret_cast<bf16x8*>(cbase + tok * p.ldc + (col - seg * p.seg_n)) = o;
+  for (int j = 0; j < TN; ++j) {
+    const int c = col[j];
+    if (c >= p.n) continue;
+    float v[TM][W];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int e = 0; e < W; ++e) v[i][e] = value(i, j, e);
+    if (c32) {
+#pragma unroll
+      for (int h = 0; h < W; h += 4)
+        if (c + h < p.c32_cols) {
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+            if (live[i])
+              *reinterpret_cast<f32x4*>(c32 + (long)tok[i] * p.c32_cols + c + h) =
+                  f32x4{v[i][h], v[i][h + 1], v[i][h + 2], v[i][h + 3]};
+        }
+    }
+    const int seg = (c >= p.seg_n) + (c >= 2 * p.seg_n);
+    bf16_t* cbase = seg == 0 ? p.c0 : (seg == 1 ? p.c1 : p.c2);
+    if (!cbase) continue;
+    cbase += c - seg * p.seg_n;
+    if (p.rope) {
+#pragma unroll
+      for (int h = 0; h < W; h += 4)
+        if (c + h < p.rope_cols) {
+          const float* table = p.rope + (((unsigned)(c + h) % (unsigned)p.rope_dh) >> 1) * 2;
+          f32x4 cs[TM];
+#pragma unroll
+          for (int i = 0; i < TM; ++i) cs[i] = *reinterpret_cast<const f32x4*>(table + (long)pos[i] * p.rope_dh);
+#pragma unroll
+          for (int i = 0; i < TM; ++i) rope_rotate4(cs[i], v[i][h], v[i][h + 1], v[i][h + 2], v[i][h + 3]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      out_t o;
+#pragma unroll
+      for (int e = 0; e < W; ++e) o[e] = (bf16_t)v[i][e];
+      if (live[i]) *reinterpret_cast<out_t*>(cbase + tok[i] * ldc) = o;
+    }
+  }
 }
 
 // Tile order: GROUP_M row-tiles per column step (the tiles that run at the same time on one
@@ -188,8 +224,7 @@ __device__ __forceinline__ void tile_of_unit(const int unit, const int tiles_m, 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
 __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigned char* smem,
                                           const int tid, const int vblock, const int sub = 0,
-                                          const int nsub = 1, lds_idx_t lidx = nullptr,
-                                          const int forced_tile_m = -1, const int forced_tile_n = 0) {
+                                          const int nsub = 1, lds_idx_t lidx = nullptr) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -205,26 +240,19 @@ __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigne
   // in this order)
   const int parts = p.k_parts;
   const int tiles_m = (m + BM - 1) / BM, tiles_n = (p.n + BN - 1) / BN;
-  int tile_m, tile_n, part = 0;
-  bool live = true;
-  if (forced_tile_m >= 0) {  // the caller names the tile (whole k, one tile for all waves)
-    tile_m = forced_tile_m;
-    tile_n = forced_tile_n;
-  } else {
-    const int total = tiles_m * tiles_n * parts;
-    const int blocks = (total + nsub - 1) / nsub;
-    const int per_xcd = (blocks + 7) >> 3;
-    const int slot = vblock >> 3;
-    if (slot >= per_xcd) return false;
-    const int blk = (vblock & 7) * per_xcd + slot;
-    if (blk >= blocks) return false;
-    int unit = blk * nsub + sub;
-    live = unit < total;
-    unit = live ? unit : total - 1;
-    const int logical = unit / parts;
-    part = unit - logical * parts;
-    tile_of_unit(logical, tiles_m, tiles_n, tile_m, tile_n);
-  }
+  const int total = tiles_m * tiles_n * parts;
+  const int blocks = (total + nsub - 1) / nsub;
+  const int per_xcd = (blocks + 7) >> 3;
+  const int slot = vblock >> 3;
+  if (slot >= per_xcd) return false;
+  const int blk = (vblock & 7) * per_xcd + slot;
+  if (blk >= blocks) return false;
+  int unit = blk * nsub + sub;
+  const bool live = unit < total;
+  unit = live ? unit : total - 1;
+  const int logical = unit / parts, part = unit - logical * parts;
+  int tile_m, tile_n;
+  tile_of_unit(logical, tiles_m, tiles_n, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
   // (the wave number as a scalar: LDS addresses of the global -> LDS loads go through M0, and a
@@ -242,15 +270,19 @@ __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigne
   // row (L >> 3) of the group and LDS slot (L & 7); it fetches the k-chunk that
   // the swizzle puts into that slot.  Rows past the end re-read the last row.
   const bf16_t* src[LPW];
+  int row_in[LPW], tok_in[LPW];
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) {
+    const int row = m0 + (wave * LPW + i) * 8 + (lane >> 3);
+    row_in[i] = row < m ? row : m - 1;
+  }
+  row_tokens(p.idx, lidx, row_in, tok_in);
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
     const int r = (wave * LPW + i) * 8 + (lane >> 3);  // row within the stage
     const int chunk = (lane & 7) ^ ((r >> 1) & 7);
     if (r < BM) {
-      int row = m0 + r;
-      row = row < m ? row : m - 1;
-      const long tok = row_token(p.idx, lidx, row);
-      src[i] = p.a + tok * p.lda + chunk * 8 + kt0 * BK;
+      src[i] = p.a + (long)tok_in[i] * p.lda + chunk * 8 + kt0 * BK;
     } else {
       int col = n0 + (r - BM);
       col = col < p.n ? col : p.n - 1;
@@ -259,12 +291,15 @@ __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigne
   }
   // token ids of the rows this lane stores in the epilogue, read now: a list held in LDS
   // (lidx) sits in the stage memory that the first loads overwrite
-  long tok_out[TM];
+  int row_out[TM], tok_out[TM];
+  bool live_out[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int row = m0 + wave_m * WM + i * 32 + l32;
-    tok_out[i] = row_token(p.idx, lidx, row < m ? row : m - 1);
+    live_out[i] = row < m && live;
+    row_out[i] = row < m ? row : m - 1;
   }
+  row_tokens(p.idx, lidx, row_out, tok_out);
   if (lidx) __syncthreads();  // (uniform: every thread of the workgroup has its entries)
   auto issue_loads = [&](int kt, int buf) __attribute__((always_inline)) {
     unsigned char* base = smem + buf * STAGE_BYTES + wave * LPW * 8 * ROW_BYTES;
@@ -398,35 +433,34 @@ __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigne
   // Epilogue.  acc[i][j][r] = C[row, col] with
   //   row = m0 + wave_m*WM + i*32 + l32
   //   col = n0 + wave_n*WN + j*32 + (r/4)*8 + half*4 + r%4
+  int col[4 * TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int row = m0 + wave_m * WM + i * 32 + l32;
-    if (row >= m || !live) continue;
-    const long tok = tok_out[i];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = n0 + wave_n * WN + j * 32 + g * 8 + half * 4;
-        if (col >= p.n) continue;
-        store4(p, c32, tok, col, acc[i][j][g * 4 + 0], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2],
-               acc[i][j][g * 4 + 3]);
-      }
-    }
-  }
+  for (int j = 0; j < 4 * TN; ++j) col[j] = n0 + wave_n * WN + j * 8 + half * 4;
+  store_tile<4>(p, c32, tok_out, live_out, col,
+                [&](int i, int j, int e) __attribute__((always_inline)) { return acc[i][j >> 2][(j & 3) * 4 + e]; });
   return true;
 }
 
-// The same tile with v_mfma_f32_16x16x32_bf16: wave tiles in units of 16, so that 8 waves can
-// share a 128 x 96 tile (32 x 48 each).  129-256 refreshed rows of a 12288-wide output then
-// make 256 workgroups of 8 waves, where the 32-wide MFMA shape allows either 192 workgroups
-// (128 x 128) or 4 waves per workgroup (128 x 96 as 32 x 96).  LDS layout, ring and loads as in
-// gemm_tile; a fragment is 16 rows x 32 k (lane L: row L & 15, k-chunk L >> 4), a k-step holds
-// two such slices, and all fragments of the next k-step are fetched under the MFMAs of the
-// current one.  No teams, no k-parts.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, bool PAIRED = false>
+// Tiles that the CUs get one of, or few: eight waves, v_mfma_f32_16x16x32_bf16 (wave tiles in units of
+// 16, so that eight waves can share a 128 x 96 tile: 129-256 refreshed rows of a 12288-wide output then
+// make 256 workgroups of 8 waves, where the 32-wide shape allows 192 workgroups of 128 x 128).  LDS
+// layout as in gemm_tile; a fragment is 16 rows x 32 k (lane L: row L & 15, k-chunk L >> 4), a k-step
+// holds two such slices, and all fragments of the next k-step are fetched under the MFMAs of the
+// current one.
+// What bounds it is the pull of a CU: the operands come at most at 64 B per cycle, at 100 GB/s where
+// lines come from beyond the L2 (1024 x 4096 x 4096: loads alone 26 us of 33, MFMAs alone 20).  So the whole ring is
+// kept in flight (the stage of k-step kt is filled again for kt + STAGES as soon as the barrier says that its
+// fragments are in registers) and the loads of a k-step are issued one by one between its MFMAs: in a
+// row, a wave that waits for a place in the queue keeps its MFMAs waiting as well.  us, with STAGES - 1
+// stages in flight, loads in a row (3 sets of operands in turn): 1024 x 4096 x 4096 in 128 x 128 tiles
+// 43.5 (32-wide MFMAs) -> 33.1, 205 x 12288 39.2 -> 34.5, 512 x 12288 61.7 -> 54.2, 512 x 8192 45.4 -> 33.5,
+// 512 x 4096 25.1 -> 21.3, 205 x 4096 17.2 -> 14.0, 100 x 12288 30.6 -> 28.0.  The k of a k-step halved
+// between two groups of four waves with twice the wave tile (half the fragment reads) is no faster: 34.4,
+// 35.2, 54.0, 31.5, 21.0, 13.7, 28.4.  No teams, no k-parts.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
 __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsigned char* smem, const int tid,
-                                            const int vblock, lds_idx_t lidx = nullptr) {
+                                            const int vblock, lds_idx_t lidx = nullptr,
+                                            const int forced_tile_m = -1, const int forced_tile_n = 0) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 16, TN = WN / 16;
@@ -435,20 +469,22 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
   constexpr int LPW = (GROUPS + NW - 1) / NW;  // surplus loads repeat the last group
   constexpr int KS = BK / 32;
   static_assert(WM % 16 == 0 && WN % 16 == 0, "wave tile must be a multiple of 16 x 16");
-  static_assert(LPW * (STAGES - 1) < 64, "vmcnt range");
+  static_assert(STAGES >= 3 && LPW * (STAGES - 1) < 64, "vmcnt range");
 
   const int tiles_m = (m + BM - 1) / BM, tiles_n = (p.n + BN - 1) / BN;
-  const int total = tiles_m * tiles_n;
-  const int per_xcd = (total + 7) >> 3;
-  const int slot = vblock >> 3;
-  if (slot >= per_xcd) return false;
-  const int unit = (vblock & 7) * per_xcd + slot;
-  if (unit >= total) return false;
-  const int group_size = GROUP_M * tiles_n;
-  const int first_m = (unit / group_size) * GROUP_M;
-  const int rows_in_group = tiles_m - first_m < GROUP_M ? tiles_m - first_m : GROUP_M;
-  const int rem = unit % group_size;
-  const int tile_m = first_m + rem % rows_in_group, tile_n = rem / rows_in_group;
+  int tile_m, tile_n;
+  if (forced_tile_m >= 0) {  // the caller names the tile
+    tile_m = forced_tile_m;
+    tile_n = forced_tile_n;
+  } else {
+    const int total = tiles_m * tiles_n;
+    const int per_xcd = (total + 7) >> 3;
+    const int slot = vblock >> 3;
+    if (slot >= per_xcd) return false;
+    const int unit = (vblock & 7) * per_xcd + slot;
+    if (unit >= total) return false;
+    tile_of_unit(unit, tiles_m, tiles_n, tile_m, tile_n);
+  }
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
   // (the wave number as a scalar: LDS addresses of the global -> LDS loads go through M0, and a
@@ -459,34 +495,42 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
   const int KT = p.k / BK;
 
   const bf16_t* src[LPW];
-  int grp[LPW];
+  int grp[LPW], row_in[LPW], tok_in[LPW];
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
     grp[i] = wave * LPW + i < GROUPS ? wave * LPW + i : GROUPS - 1;
+    const int row = m0 + grp[i] * 8 + (lane >> 3);
+    row_in[i] = row < m ? row : m - 1;
+  }
+  row_tokens(p.idx, lidx, row_in, tok_in);
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) {
     const int r = grp[i] * 8 + (lane >> 3);
     const int chunk = (lane & 7) ^ ((r >> 1) & 7);
     if (r < BM) {
-      int row = m0 + r;
-      row = row < m ? row : m - 1;
-      src[i] = p.a + row_token(p.idx, lidx, row) * p.lda + chunk * 8;
+      src[i] = p.a + (long)tok_in[i] * p.lda + chunk * 8;
     } else {
       int col = n0 + (r - BM);
       col = col < p.n ? col : p.n - 1;
       src[i] = p.wt + (long)col * p.k + chunk * 8;
     }
   }
-  long tok_out[TM];
+  int row_out[TM], tok_out[TM];
+  bool live_out[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int row = m0 + wave_m * WM + i * 16 + l16;
-    tok_out[i] = row_token(p.idx, lidx, row < m ? row : m - 1);
+    live_out[i] = row < m;
+    row_out[i] = row < m ? row : m - 1;
   }
+  row_tokens(p.idx, lidx, row_out, tok_out);
   if (lidx) __syncthreads();
-  auto issue_loads = [&](int kt, int buf) __attribute__((always_inline)) {
-    unsigned char* base = smem + buf * STAGE_BYTES;
-#pragma unroll
-    for (int i = 0; i < LPW; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + kt * BK), (lptr_t)(base + grp[i] * 8 * ROW_BYTES), 16, 0, 0);
+  // (loads of k-steps past the end repeat the last one, into a stage that nobody reads any more, so
+  // that the count of loads in flight is the same in every k-step)
+  auto issue_load = [&](int i, int kt) __attribute__((always_inline)) {
+    const int k = kt < KT ? kt : KT - 1;
+    __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + k * BK),
+                                     (lptr_t)(smem + (kt % STAGES) * STAGE_BYTES + grp[i] * 8 * ROW_BYTES), 16, 0, 0);
   };
 
   f32x4 acc[TM][TN];
@@ -505,8 +549,8 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
   const int b_row_off = (BM + wave_n * WN + l16) * ROW_BYTES;
 
   bf16x8 fa[2][KS][TM], fb[2][KS][TN];
-  auto load_frags = [&](int buf, int set) __attribute__((always_inline)) {
-    const unsigned char* st = smem + buf * STAGE_BYTES;
+  auto load_frags = [&](int kt, int set) __attribute__((always_inline)) {
+    const unsigned char* st = smem + (kt % STAGES) * STAGE_BYTES;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
@@ -517,7 +561,7 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
         fb[set][ks][j] = *reinterpret_cast<const bf16x8*>(st + b_row_off + j * 16 * ROW_BYTES + koff[ks]);
     }
   };
-  constexpr int NMMA = KS * TM * TN, PRE = 2;
+  constexpr int NMMA = KS * TM * TN, PRE = NMMA / 4 > 0 ? NMMA / 4 : 1;
   auto mma = [&](int set, int first, int last) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < NMMA; ++t) {
@@ -527,77 +571,44 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
     }
   };
 
-  if constexpr (!PAIRED) {
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s) issue_loads(s < KT ? s : KT - 1, s);
+  for (int s = 0; s < STAGES; ++s)
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) issue_load(i, s);
+  wait_vmcnt_and_barrier<LPW*(STAGES - 1)>();
+  load_frags(0, 0);
+  // k-step kt: the barrier publishes stage kt + 1 and, as every wave's fragments of kt have arrived, frees
+  // the stage of kt.  (Two k-steps per trip so that the fragment set index is a compile-time constant.)
+  auto kstep = [&](int kt, auto set_c) __attribute__((always_inline)) {
+    constexpr int SET = decltype(set_c)::value;
+    mma(SET, 0, PRE);
+    __builtin_amdgcn_sched_barrier(0);
     wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
-    load_frags(0, 0);
-    auto kstep = [&](int kt, auto set_c) __attribute__((always_inline)) {
-      constexpr int SET = decltype(set_c)::value;
-      const int nxt = kt + STAGES - 1;
-      issue_loads(nxt < KT ? nxt : KT - 1, nxt % STAGES);
-      mma(SET, 0, PRE);
-      __builtin_amdgcn_sched_barrier(0);
-      wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
-      load_frags((kt + 1) % STAGES, SET ^ 1);
-      __builtin_amdgcn_sched_barrier(0);
-      mma(SET, PRE, NMMA);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    int kt = 0;
-    for (; kt + 1 < KT; kt += 2) {
-      kstep(kt, std::integral_constant<int, 0>{});
-      kstep(kt + 1, std::integral_constant<int, 1>{});
-    }
-    if (kt < KT) kstep(kt, std::integral_constant<int, 0>{});
-  } else {
-    // Two k-steps per barrier (small tiles, whose k-step holds too few MFMAs to carry a
-    // barrier of its own): the ring is filled and drained in pairs of stages.  The barrier
-    // that ends an odd k-step kt lets stages kt+1 and kt+2 be read and the slots of kt-1 and
-    // kt be refilled; the even k-step after it issues the loads of stages kt+STAGES-2 and
-    // kt+STAGES-1 into those two slots and reads stage kt+1 without a barrier.
-    static_assert(STAGES % 2 == 0 && STAGES >= 4, "paired ring");
-    static_assert(LPW * (STAGES - 2) < 64, "vmcnt range");
+    __builtin_amdgcn_sched_barrier(0);
+    load_frags(kt + 1, SET ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int s = 0; s < STAGES - 2; ++s) issue_loads(s < KT ? s : KT - 1, s);
-    wait_vmcnt_and_barrier<LPW*(STAGES - 4)>();
-    load_frags(0, 0);
-    auto kstep = [&](int kt, auto set_c) __attribute__((always_inline)) {
-      constexpr int SET = decltype(set_c)::value;
-      if constexpr (SET == 0) {
-        const int n0s = kt + STAGES - 2, n1s = kt + STAGES - 1;
-        issue_loads(n0s < KT ? n0s : KT - 1, n0s % STAGES);
-        issue_loads(n1s < KT ? n1s : KT - 1, n1s % STAGES);
-      }
-      mma(SET, 0, PRE);
+    for (int i = 0; i < LPW; ++i) {
+      mma(SET, PRE + (NMMA - PRE) * i / LPW, PRE + (NMMA - PRE) * (i + 1) / LPW);
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (SET == 1) wait_vmcnt_and_barrier<LPW*(STAGES - 4)>();
-      load_frags((kt + 1) % STAGES, SET ^ 1);
+      issue_load(i, kt + STAGES);
       __builtin_amdgcn_sched_barrier(0);
-      mma(SET, PRE, NMMA);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    int kt = 0;
-    for (; kt + 1 < KT; kt += 2) {
-      kstep(kt, std::integral_constant<int, 0>{});
-      kstep(kt + 1, std::integral_constant<int, 1>{});
     }
-    if (kt < KT) kstep(kt, std::integral_constant<int, 0>{});
+  };
+  int kt = 0;
+  for (; kt + 1 < KT; kt += 2) {
+    kstep(kt, std::integral_constant<int, 0>{});
+    kstep(kt + 1, std::integral_constant<int, 1>{});
   }
+  if (kt < KT) kstep(kt, std::integral_constant<int, 0>{});
   wait_vmcnt<0>();
 
   // acc[i][j][e] = C[row, col]: row = m0 + wave_m*WM + 16 i + l16, col = n0 + wave_n*WN + 16 j + 4 kq + e
+  int col[TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int row = m0 + wave_m * WM + i * 16 + l16;
-    if (row >= m) continue;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = n0 + wave_n * WN + j * 16 + kq * 4;
-      if (col >= p.n) continue;
-      store4(p, p.c32, tok_out[i], col, acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-    }
-  }
+  for (int j = 0; j < TN; ++j) col[j] = n0 + wave_n * WN + j * 16 + kq * 4;
+  store_tile<4>(p, p.c32, tok_out, live_out, col,
+                [&](int i, int j, int e) __attribute__((always_inline)) { return acc[i][j][e]; });
   return true;
 }
 
@@ -673,12 +684,17 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   // Rows past the end re-read the last one.
   const bf16_t* src_a[4];
   const bf16_t* src_b[TN];
+  int row_in[4], tok_in[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = m0 + (wave * 4 + i) * 8 + (lane >> 3);
+    row_in[i] = row < m ? row : m - 1;
+  }
+  row_tokens(p.idx, lidx, row_in, tok_in);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int r = (wave * 4 + i) * 8 + (lane >> 3);
-    int row = m0 + r;
-    row = row < m ? row : m - 1;
-    src_a[i] = p.a + row_token(p.idx, lidx, row) * p.lda + ((lane & 7) ^ ((r >> 1) & 7)) * 8 + k_first;
+    src_a[i] = p.a + (long)tok_in[i] * p.lda + ((lane & 7) ^ ((r >> 1) & 7)) * 8 + k_first;
   }
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
@@ -687,12 +703,15 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
     col = col < p.n ? col : p.n - 1;
     src_b[j] = p.wt + (long)col * p.k + ((lane & 7) ^ pp_bkey(r & 31)) * 8 + k_first;
   }
-  long tok_out[4];
+  int row_out[4], tok_out[4];
+  bool live_out[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int row = m0 + wm * 64 + i * 16 + l16;
-    tok_out[i] = row_token(p.idx, lidx, row < m ? row : m - 1);
+    live_out[i] = row < m;
+    row_out[i] = row < m ? row : m - 1;
   }
+  row_tokens(p.idx, lidx, row_out, tok_out);
   if (lidx) __syncthreads();
   // (k-steps past the end re-read the last one into a region nobody reads any more, so that the
   // number of loads in flight is the same in every phase of every k-step)
@@ -900,19 +919,12 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   }
 
   // acc[i][2 j + h][e] = C[row, col], row = m0 + 64 wm + 16 i + l16, col = n0 + 32 TN grp + 32 j + 8 kq + 4 h + e
+  int col[TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (m0 + wm * 64 + i * 16 + l16 >= m) continue;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = n0 + grp * (32 * TN) + j * 32 + kq * 8;
-      if (col >= p.n) continue;
-      float v[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = acc[i][j * 2 + (e >> 2)][e & 3];
-      store8(p, tok_out[i], col, v);
-    }
-  }
+  for (int j = 0; j < TN; ++j) col[j] = n0 + grp * (32 * TN) + j * 32 + kq * 8;
+  store_tile<8>(p, p.c32, tok_out, live_out, col, [&](int i, int j, int e) __attribute__((always_inline)) {
+    return acc[i][j * 2 + (e >> 2)][e & 3];
+  });
   return true;
 }
 
@@ -939,14 +951,16 @@ __device__ __forceinline__ void skinny_tile(const GemmDev& p, const int m, unsig
   const int s0 = wave * spw;
   const int s1 = s0 + spw < steps ? s0 + spw : steps;
   const bf16_t* xrow[TMS];
-  long tok[TMS];
+  int row[TMS], tok[TMS];
+  bool live[TMS];
 #pragma unroll
   for (int t = 0; t < TMS; ++t) {
-    int r = t * 16 + l16;
-    r = r < m ? r : m - 1;
-    tok[t] = row_token(p.idx, lidx, r);
-    xrow[t] = p.a + tok[t] * p.lda + kq * 8;
+    live[t] = t * 16 + l16 < m;
+    row[t] = live[t] ? t * 16 + l16 : m - 1;
   }
+  row_tokens(p.idx, lidx, row, tok);
+#pragma unroll
+  for (int t = 0; t < TMS; ++t) xrow[t] = p.a + (long)tok[t] * p.lda + kq * 8;
   if (lidx) __syncthreads();  // a list in LDS shares the memory of the partial sums below
   f32x4* red = reinterpret_cast<f32x4*>(smem);  // [NW][TMS][64]
   for (int grp = blockIdx.x; grp < groups; grp += gridDim.x) {
@@ -975,16 +989,22 @@ __device__ __forceinline__ void skinny_tile(const GemmDev& p, const int m, unsig
         for (int t = 0; t < TMS; ++t)
           acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[u], xf[t][u], acc[t], 0, 0, 0);
     }
+    // (the wait for the MFMAs by hand: the compiler, which has to put it in front of the stores, left it out
+    // here, behind a loop that a second path goes round, and three of four columns were stored too early)
+#pragma unroll
+    for (int t = 0; t < TMS; ++t) asm volatile("s_nop 7\n\ts_nop 1" : "+v"(acc[t]));
 #pragma unroll
     for (int t = 0; t < TMS; ++t) red[(wave * TMS + t) * 64 + lane] = acc[t];
     __syncthreads();
     if (wave == 0) {
 #pragma unroll
       for (int t = 0; t < TMS; ++t) {
-        f32x4 v = red[t * 64 + lane];
-        for (int w = 1; w < NW; ++w) v += red[(w * TMS + t) * 64 + lane];
-        if (t * 16 + l16 < m) store4(p, p.c32, tok[t], n0 + kq * 4, v[0], v[1], v[2], v[3]);
+        acc[t] = red[t * 64 + lane];
+        for (int w = 1; w < NW; ++w) acc[t] += red[(w * TMS + t) * 64 + lane];
       }
+      const int col[1] = {n0 + kq * 4};
+      store_tile<4>(p, p.c32, tok, live, col,
+                    [&](int t, int, int e) __attribute__((always_inline)) { return acc[t][e]; });
     }
     __syncthreads();
   }
@@ -1173,7 +1193,7 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
         const int cm = 2 * tm + (quarter >> 1), cn = 2 * tn + (quarter & 1);
         if (cm * 128 >= m) continue;
         next_tile();
-        gemm_tile<128, 128, 4, 2, 4>(p, m, smem, threadIdx.x, 0, 0, 1, lidx, cm, cn);
+        gemm_tile16<128, 128, 2, 4, 4>(p, m, smem, threadIdx.x, 0, lidx, cm, cn);
       }
     }
   } else if (p.n % 192 == 0 && tiles_of(m, p.n, 256, 192) >= kWideFullTiles) {
@@ -1187,13 +1207,12 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
   } else if (p.n % 96 == 0 && one_round(tiles_of(m, p.n, 128, 96))) {
     gemm_tile16<128, 96, 4, 2, 4>(p, m, smem, threadIdx.x, blockIdx.x, lidx);
   } else if (tiles_of(m, p.n, 128, 128) >= kWideBigTiles) {
-    passes([&](int vb) { return gemm_tile<128, 128, 4, 2, 4>(p, m, smem, threadIdx.x, vb, 0, 1, lidx); });
+    passes([&](int vb) { return gemm_tile16<128, 128, 2, 4, 4>(p, m, smem, threadIdx.x, vb, lidx); });
   } else if (tiles_of(m, p.n, 64, 64) <= kWideSingle) {
     // one tile per workgroup: all eight waves on it (16 x 32 each with the 16-wide MFMA
     // shape; measured 19.2 against 21.1 us for four waves of 32 x 32 at 205 rows, n = 4096),
-    // the whole stage memory as a ring of eight stages with one barrier per two k-steps
-    // (0.3-0.6 us less than four stages and a barrier per k-step at 40-256 rows, n = 4096)
-    gemm_tile16<64, 64, 4, 2, 8, true>(p, m, smem, threadIdx.x, blockIdx.x, lidx);
+    // the whole stage memory as a ring of eight stages
+    gemm_tile16<64, 64, 2, 4, 8>(p, m, smem, threadIdx.x, blockIdx.x, lidx);
   } else {
     const int team = threadIdx.x >> 8;
     passes([&](int vb) {
@@ -1272,7 +1291,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) score_proj_kernel(Score
     const long off = (long)part * KT * BK + ((lane & 7) ^ ((r >> 1) & 7)) * 8;
     if (r < BM) {
       const int row = m0 + r < p.m ? m0 + r : p.m - 1;
-      src[i] = p.a + row_token(p.idx, nullptr, row) * p.k + off;
+      src[i] = p.a + (long)(p.idx ? p.idx[row] : row) * p.k + off;
     } else {
       src[i] = p.wt + (long)(r - BM) * p.k + off;
     }
@@ -1395,7 +1414,8 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) score_proj_kernel(Score
 #pragma unroll
   for (int r = 0; r < RPW; ++r) {
     const int row = m0 + wave * RPW + r;
-    tok[r] = row_token(p.idx, nullptr, row < p.m ? row : p.m - 1);
+    const int listed = row < p.m ? row : p.m - 1;
+    tok[r] = p.idx ? p.idx[listed] : listed;
     prev[r] = c < WIDTH ? *reinterpret_cast<const f32x2*>(p.q_prev + tok[r] * WIDTH + c) : f32x2{0.f, 0.f};
   }
 #pragma unroll
@@ -1512,12 +1532,12 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   if (g.m_dev || g.sel_mask) return launch_rows_wide(g, s);
   switch (gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles && !g.c32)) {
     case GemmRoute::kRows64: return launch_tile16<64, 128, 4, 2, 5>(g, s);
-    case GemmRoute::kRows128: return launch_tile16<128, 128, 4, 2, 4>(g, s);
+    case GemmRoute::kRows128: return launch_tile16<128, 128, 2, 4, 4>(g, s);
     case GemmRoute::kPp192: return launch_pp<3>(g, s);
     case GemmRoute::kPp256: return launch_pp<4>(g, s);
     case GemmRoute::kPp128: return launch_pp<2>(g, s);
     case GemmRoute::kPp128Split: return launch_pp<2, true>(g, s);
-    case GemmRoute::kTile128: return launch_fixed<128, 128, 4, 2, 4>(g, s);
+    case GemmRoute::kTile128: return launch_tile16<128, 128, 2, 4, 4>(g, s);
     case GemmRoute::kTile64: return launch_fixed<64, 64, 2, 2, 4>(g, s);
   }
   return hipErrorInvalidValue;

@@ -39,13 +39,16 @@ struct GemmF32Dev {
 
 // four neighbouring output columns col .. col + 3 (col a multiple of 4) of token tok
 __device__ __forceinline__ void store4_f32(const GemmF32Dev& p, long tok, int col, f32x4 v) {
-  const int seg = col / p.seg_n;
+  const int seg = (col >= p.seg_n) + (col >= 2 * p.seg_n);
   float* cbase = seg == 0 ? p.c0 : (seg == 1 ? p.c1 : p.c2);
   if (p.c32 && col < p.c32_cols)  // the scored columns: before any rotation
     *reinterpret_cast<f32x4*>(p.c32 + tok * p.c32_cols + col) = v;
   if (!cbase) return;
   float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
-  if (p.rope && col < p.rope_cols) rope_rotate4(p.rope, p.rope_dh, p.rope_seq, tok, col, v0, v1, v2, v3);
+  if (p.rope && col < p.rope_cols) {
+    const long at = (long)((unsigned)tok % (unsigned)p.rope_seq) * p.rope_dh + (unsigned)col % (unsigned)p.rope_dh;
+    rope_rotate4(*reinterpret_cast<const f32x4*>(p.rope + at), v0, v1, v2, v3);
+  }
   const f32x4 o = {v0, v1, v2, v3};
   *reinterpret_cast<f32x4*>(cbase + tok * p.ldc + (col - seg * p.seg_n)) = o;
 }

@@ -6,7 +6,7 @@ namespace dare {
 
 enum class GemmRoute {
   kTile64,      // 64 x 64, four waves
-  kTile128,     // 128 x 128, eight waves
+  kTile128,     // 128 x 128 on the 16-wide MFMA shape, eight waves
   kRows64,      // 64 x 128 on the 16-wide MFMA shape: one row tile
   kRows128,     // 128 x 128 on the 16-wide MFMA shape: one row tile
   kPp128,       // ping-pong tiles of 256 rows x 128, 192, 256 columns
@@ -60,7 +60,7 @@ constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace)
     if (workspace && t2 >= kSplitTiles / 2 && t2 <= kSplitTiles && ksteps % 2 == 0 && ksteps >= kSplitMinSteps)
       return GemmRoute::kPp128Split;
   }
-  if (m > 64 && n % 128 == 0 && t128 >= 64) return GemmRoute::kTile128;
+  if (k_parts <= 1 && m > 64 && n % 128 == 0 && t128 >= 64) return GemmRoute::kTile128;
   return GemmRoute::kTile64;
 }
 
