@@ -110,12 +110,15 @@ __device__ __forceinline__ void attn_block(const AttnDev& p, int b, int h, int q
 
   const int T = p.seq;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (a scalar: M0 addressing)
-  const int qw = (unsigned)wave % QW, kw = (unsigned)wave / QW;
+  // (the key-waves of few query rows on a SIMD each: where the second half of a block holds no rows, the
+  // first one has every SIMD's matrix core to itself)
+  const int qw = KW == 4 ? (unsigned)wave / KW : (unsigned)wave % QW, kw = KW == 4 ? (unsigned)wave % KW : (unsigned)wave / QW;
   const int l32 = lane & 31, half = lane >> 5;
 
   // the query row of this lane
   const int j = qt * (32 * QW) + qw * 32 + l32;
   const bool valid = j < cnt;
+  const bool any_row = qt * (32 * QW) + qw * 32 < cnt;  // (the same in all lanes: a wave without rows only loads)
   const int jc = valid ? j : cnt - 1;
   int tok = p.idx ? p.idx[off + jc] : off + jc;
 
@@ -280,107 +283,118 @@ __device__ __forceinline__ void attn_block(const AttnDev& p, int b, int h, int q
     // for a load that nobody reads: 2048 x 8 tokens of 16 heads 236 -> 220 us, 16 x 256 of 32 heads 43 -> 36)
     if (NST > 2 || nxt < n_steps) issue_loads(first + (nxt < n_steps ? nxt : n_steps - 1), nxt % NST);
     const int tile = (first + step) * KW + kw;
-    if (tile < n_tiles) compute(step % NST, tile * TK);
+    if (tile < n_tiles && any_row) compute(step % NST, tile * TK);
   }
   float l_all = l_run + __shfl_xor(l_run, 32, 64);
 
   // ---- merge the key-waves (fixed order), normalise, store ----
-  if (KW > 1) {
-    constexpr int REGS = OT * 16 + 2;
-    static_assert((KW - 1) * QW * REGS * 64 * 4 <= attn_smem_bytes<DH, KW, TK, NST>(),
+  // Every key-wave merges, and stores, its share of the channels: OWN of the accumulator registers of a
+  // lane.  (One wave merging all of them took 2.7 us of the 16 us of a launch over 1024 keys.)
+  constexpr int REGS = OT * 16, OWN = REGS / KW;
+  f32x4 own[OWN / 4];  // registers kw OWN .. of the merged accumulator
+  if constexpr (KW > 1) {
+    constexpr int ML = QW * KW * (KW - 1) * OWN * 64;  // (max, sum) of every wave behind the registers
+    static_assert((ML + QW * KW * 64 * 2) * 4 <= attn_smem_bytes<DH, KW, TK, NST>(),
                   "the merge area must fit into the stage memory");
     wait_all_and_barrier();  // all loads landed, all tiles consumed: stage memory is free
-    float* xch = reinterpret_cast<float*>(smem);
-    if (kw > 0) {
-      float* mine = xch + ((kw - 1) * QW + qw) * REGS * 64 + lane;
-      mine[0] = m_run;
-      mine[64] = l_all;
+    f32x4* xch = reinterpret_cast<f32x4*>(smem) + lane;
+    f32x2* ml = reinterpret_cast<f32x2*>(reinterpret_cast<float*>(smem) + ML) + qw * KW * 64 + lane;
+    ml[kw * 64] = f32x2{m_run, l_all};
+    // slot (query-wave, owner, source): a wave leaves the shares of the others
 #pragma unroll
-      for (int t = 0; t < OT; ++t)
+    for (int o = 0; o < KW; ++o) {
+      f32x4 share[OWN / 4];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mine[(2 + t * 16 + r) * 64] = acc_o[t][r];
-    }
-    __syncthreads();
-    if (kw == 0) {
+      for (int i = 0; i < OWN; ++i) share[i >> 2][i & 3] = acc_o[(o * OWN + i) >> 4][(o * OWN + i) & 15];
+      if (o == kw) {
 #pragma unroll
-      for (int o = 1; o < KW; ++o) {
-        const float* other = xch + ((o - 1) * QW + qw) * REGS * 64 + lane;
-        const float m_o = other[0], l_o = other[64];
-        const float m_new = fmaxf(m_run, m_o);
-        const float sa = __builtin_amdgcn_exp2f(m_run - m_new), sb = __builtin_amdgcn_exp2f(m_o - m_new);
-        m_run = m_new;
-        l_all = l_all * sa + l_o * sb;
+        for (int i = 0; i < OWN / 4; ++i) own[i] = share[i];
+      } else {
+        f32x4* slot = xch + ((qw * KW + o) * (KW - 1) + (kw < o ? kw : kw - 1)) * (OWN / 4) * 64;
 #pragma unroll
-        for (int t = 0; t < OT; ++t)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc_o[t][r] = acc_o[t][r] * sa + other[(2 + t * 16 + r) * 64] * sb;
+        for (int i = 0; i < OWN / 4; ++i) slot[i * 64] = share[i];
       }
     }
+    __syncthreads();
+    f32x2 stat[KW];
+#pragma unroll
+    for (int o = 0; o < KW; ++o) stat[o] = ml[o * 64];
+    m_run = stat[0][0];
+#pragma unroll
+    for (int o = 1; o < KW; ++o) m_run = fmaxf(m_run, stat[o][0]);
+    l_all = 0.f;
+    f32x4 sum[OWN / 4];
+#pragma unroll
+    for (int i = 0; i < OWN / 4; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int o = 0; o < KW; ++o) {
+      const float scale = __builtin_amdgcn_exp2f(stat[o][0] - m_run);
+      l_all += stat[o][1] * scale;
+      const f32x4* slot = xch + ((qw * KW + kw) * (KW - 1) + (o < kw ? o : o - 1)) * (OWN / 4) * 64;
+#pragma unroll
+      for (int i = 0; i < OWN / 4; ++i) sum[i] += (o == kw ? own[i] : slot[i * 64]) * scale;
+    }
+#pragma unroll
+    for (int i = 0; i < OWN / 4; ++i) own[i] = sum[i];
   } else {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) own[i >> 2][i & 3] = acc_o[i >> 4][i & 15];
   }
 
   // ---- keys cut over workgroups: leave (max, sum, O) at device scope (sc1); the last workgroup to
   // arrive at the block merges all parts in their order.  Nobody waits for anybody. ----
   if (n_parts > 1) {
     constexpr int kDeviceScope = 16;                            // cache policy sc1
-    constexpr int kRow = OT * 16 + 2;                           // floats per lane
+    constexpr int kRow = REGS + 2;                              // floats per lane
     constexpr int kSlot = QW * 64 * kRow * 4;                   // bytes of a part
     const auto parts = __builtin_amdgcn_make_buffer_rsrc(p.part_out + (long)block * n_parts * (kSlot / 4), 0, n_parts * kSlot, 0x00027000);
-    const int lane_off = qw * (64 * kRow * 4) + lane * 16, ml_off = qw * (64 * kRow * 4) + OT * 4 * 1024 + lane * 8;
-    if (kw == 0 && valid) {
+    const int own_off = qw * (64 * kRow * 4) + kw * (OWN / 4) * 1024 + lane * 16;
+    const int ml_off = qw * (64 * kRow * 4) + REGS / 4 * 1024 + lane * 8;
+    if (valid) {
 #pragma unroll
-      for (int t = 0; t < OT; ++t)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 v = {acc_o[t][g * 4], acc_o[t][g * 4 + 1], acc_o[t][g * 4 + 2], acc_o[t][g * 4 + 3]};
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), parts, part * kSlot + lane_off + (t * 4 + g) * 1024, 0, kDeviceScope);
-        }
+      for (int i = 0; i < OWN / 4; ++i)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, own[i]), parts, part * kSlot + own_off + i * 1024, 0, kDeviceScope);
       const f32x2 ml = {m_run, l_all};
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), parts, part * kSlot + ml_off, 0, kDeviceScope);
+      if (kw == 0) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), parts, part * kSlot + ml_off, 0, kDeviceScope);
     }
     wait_all_and_barrier();
     int* last = reinterpret_cast<int*>(smem);
     if (tid == 0) *last = arrive_last(p.part_count + block, n_parts);
     __syncthreads();
     if (!*last) return;
-    if (kw == 0 && valid) {
+    if (valid) {
       m_run = -INFINITY;
       l_all = 0.f;
 #pragma unroll
-      for (int t = 0; t < OT; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc_o[t][r] = 0.f;
+      for (int i = 0; i < OWN / 4; ++i) own[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       for (int q = 0; q < n_parts; ++q) {
         const f32x2 ml = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(parts, q * kSlot + ml_off, 0, kDeviceScope));
-        f32x4 v[OT * 4];
+        f32x4 v[OWN / 4];
 #pragma unroll
-        for (int i = 0; i < OT * 4; ++i)
-          v[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(parts, q * kSlot + lane_off + i * 1024, 0, kDeviceScope));
+        for (int i = 0; i < OWN / 4; ++i)
+          v[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(parts, q * kSlot + own_off + i * 1024, 0, kDeviceScope));
         const float m_new = fmaxf(m_run, ml[0]);
         const float sa = __builtin_amdgcn_exp2f(m_run - m_new), sb = __builtin_amdgcn_exp2f(ml[0] - m_new);
         m_run = m_new;
         l_all = l_all * sa + ml[1] * sb;
 #pragma unroll
-        for (int t = 0; t < OT; ++t)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc_o[t][r] = acc_o[t][r] * sa + v[t * 4 + (r >> 2)][r & 3] * sb;
+        for (int i = 0; i < OWN / 4; ++i) own[i] = own[i] * sa + v[i] * sb;
       }
     }
   }
-  if (kw > 0 || !valid) return;
+  if (!valid) return;
   const float inv = 1.0f / l_all;
   asm volatile("" : "+v"(tok));  // (one register until here, or the compiler forms the address in front of the loop)
-  bf16_t* orow = p.out + (long)tok * p.d + h * DH + half * 4;
+  // registers 4 i .. 4 i + 3 of a lane are channels 8 i + 4 half ..
+  bf16_t* orow = p.out + (long)tok * p.d + h * DH + kw * (OWN / 4) * 8 + half * 4;
 #pragma unroll
-  for (int t = 0; t < OT; ++t)
+  for (int i = 0; i < OWN / 4; ++i) {
+    bf16x4 o;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      bf16x4 o;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = (bf16_t)(acc_o[t][g * 4 + e] * inv);
-      *reinterpret_cast<bf16x4*>(orow + t * 32 + g * 8) = o;
-    }
+    for (int e = 0; e < 4; ++e) o[e] = (bf16_t)(own[i][e] * inv);
+    *reinterpret_cast<bf16x4*>(orow + i * 8) = o;
+  }
 }
 
 template <int DH, int QW, int KW, int TK, int NST>
