@@ -401,6 +401,15 @@ def test_attention_block_layout_from_the_counts(B, batch, seq, heads, dh, frac):
         assert np.all(np.abs(got[b, rows].transpose(1, 0, 2) - want) <= bound)
 
 
+@pytest.mark.parametrize("batch,seq,heads,dh,frac", [
+    (1, 257, 4, 128, 0.01), (3, 300, 2, 64, 0.2), (2, 1000, 3, 128, 0.004),  # a few blocks with rows, the others read ahead
+    (2, 515, 3, 64, 0.001),       # a sequence without a refreshed row
+    (1, 1025, 32, 128, 0.2), (1, 513, 32, 64, 0.99),                        # as many blocks as CUs, nearly
+])
+def test_attention_blocks_without_rows_read_ahead(B, batch, seq, heads, dh, frac):
+    test_attention_block_layout_from_the_counts(B, batch, seq, heads, dh, frac)
+
+
 def test_attention_large_logits_are_stable(B):
     q, k, v, _ = _attn_case(77, 1, 192, 1, 128, "bf16", 1.0)
     q = store(q * 30.0, "bf16")
