@@ -35,8 +35,7 @@
 // Row count known only on the device (the refreshed-row list): one kernel holds
 // several tile shapes and every workgroup picks the same one from the count it
 // reads, so a step with 50 refreshed rows does not pay for a 256-row tile and no
-// host round trip is needed.  The grid is sized for the worst case; workgroups
-// beyond the tiles that exist return at once.
+// host round trip is needed.
 #include <type_traits>
 
 #include "dare_common.h"
@@ -214,17 +213,10 @@ __device__ __forceinline__ void tile_of_unit(const int unit, const int tiles_m, 
   tile_n = rem / rows_in_group;
 }
 
-// One output tile of C for m rows, computed by a team of WAVES_M * WAVES_N waves; tid
-// is the thread's index within the team and smem the team's own
-// smem_bytes<BM, BN, STAGES>() bytes.  vblock is the workgroup's (virtual) block id: a
-// workgroup that walks several tiles calls this once per pass with block id + pass * grid
-// size; the result says whether that id held a tile.  A workgroup is one team (nsub = 1) or
-// nsub teams on neighbouring tiles (team number sub).  Teams share the workgroup barrier, so a
-// team without a tile of its own repeats the last tile and stores nothing.
+// One output tile of C for m rows, or a range of its k (k_parts), computed by the WAVES_M * WAVES_N waves of a
+// workgroup in smem_bytes<BM, BN, STAGES>() bytes of LDS.
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
-__device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigned char* smem,
-                                          const int tid, const int vblock, const int sub = 0,
-                                          const int nsub = 1, lds_idx_t lidx = nullptr) {
+__device__ __forceinline__ void gemm_tile(const GemmDev& p, const int m, unsigned char* smem) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -236,20 +228,15 @@ __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigne
   static_assert(LPW * (STAGES - 1) < 64, "vmcnt range");
 
   // ---- which tile: XCD-contiguous ranges, GROUP_M row-tiles per column step ----
-  // (the k-ranges of one tile, and the tiles of one workgroup's teams, are neighbours
-  // in this order)
+  // (the k-ranges of one tile are neighbours in this order)
   const int parts = p.k_parts;
   const int tiles_m = (m + BM - 1) / BM, tiles_n = (p.n + BN - 1) / BN;
   const int total = tiles_m * tiles_n * parts;
-  const int blocks = (total + nsub - 1) / nsub;
-  const int per_xcd = (blocks + 7) >> 3;
-  const int slot = vblock >> 3;
-  if (slot >= per_xcd) return false;
-  const int blk = (vblock & 7) * per_xcd + slot;
-  if (blk >= blocks) return false;
-  int unit = blk * nsub + sub;
-  const bool live = unit < total;
-  unit = live ? unit : total - 1;
+  const int per_xcd = (total + 7) >> 3;
+  const int slot = blockIdx.x >> 3;
+  if (slot >= per_xcd) return;
+  const int unit = (blockIdx.x & 7) * per_xcd + slot;
+  if (unit >= total) return;
   const int logical = unit / parts, part = unit - logical * parts;
   int tile_m, tile_n;
   tile_of_unit(logical, tiles_m, tiles_n, tile_m, tile_n);
@@ -257,6 +244,7 @@ __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigne
 
   // (the wave number as a scalar: LDS addresses of the global -> LDS loads go through M0, and a
   // wave number held in a vector register would send every one of them through v_readfirstlane)
+  const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_m = wave % WAVES_M, wave_n = wave / WAVES_M;
   const int l32 = lane & 31, half = lane >> 5;
@@ -276,7 +264,7 @@ __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigne
     const int row = m0 + (wave * LPW + i) * 8 + (lane >> 3);
     row_in[i] = row < m ? row : m - 1;
   }
-  row_tokens(p.idx, lidx, row_in, tok_in);
+  row_tokens(p.idx, nullptr, row_in, tok_in);
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
     const int r = (wave * LPW + i) * 8 + (lane >> 3);  // row within the stage
@@ -289,18 +277,15 @@ __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigne
       src[i] = p.wt + (long)col * p.k + chunk * 8 + kt0 * BK;
     }
   }
-  // token ids of the rows this lane stores in the epilogue, read now: a list held in LDS
-  // (lidx) sits in the stage memory that the first loads overwrite
   int row_out[TM], tok_out[TM];
   bool live_out[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int row = m0 + wave_m * WM + i * 32 + l32;
-    live_out[i] = row < m && live;
+    live_out[i] = row < m;
     row_out[i] = row < m ? row : m - 1;
   }
-  row_tokens(p.idx, lidx, row_out, tok_out);
-  if (lidx) __syncthreads();  // (uniform: every thread of the workgroup has its entries)
+  row_tokens(p.idx, nullptr, row_out, tok_out);
   auto issue_loads = [&](int kt, int buf) __attribute__((always_inline)) {
     unsigned char* base = smem + buf * STAGE_BYTES + wave * LPW * 8 * ROW_BYTES;
 #pragma unroll
@@ -438,7 +423,6 @@ __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigne
   for (int j = 0; j < 4 * TN; ++j) col[j] = n0 + wave_n * WN + j * 8 + half * 4;
   store_tile<4>(p, c32, tok_out, live_out, col,
                 [&](int i, int j, int e) __attribute__((always_inline)) { return acc[i][j >> 2][(j & 3) * 4 + e]; });
-  return true;
 }
 
 // Tiles that the CUs get one of, or few: eight waves, v_mfma_f32_16x16x32_bf16 (wave tiles in units of
@@ -446,7 +430,8 @@ __device__ __forceinline__ bool gemm_tile(const GemmDev& p, const int m, unsigne
 // make 256 workgroups of 8 waves, where the 32-wide shape allows 192 workgroups of 128 x 128).  LDS
 // layout as in gemm_tile; a fragment is 16 rows x 32 k (lane L: row L & 15, k-chunk L >> 4), a k-step
 // holds two such slices, and all fragments of the next k-step are fetched under the MFMAs of the
-// current one.
+// current one.  vblock is the workgroup's (virtual) block id: one that walks several tiles calls this
+// once per pass with block id + pass * grid size; the result says whether that id held a tile.
 // What bounds it is the pull of a CU: the operands come at most at 64 B per cycle, at 100 GB/s where
 // lines come from beyond the L2 (1024 x 4096 x 4096: loads alone 26 us of 33, MFMAs alone 20).  So the whole ring is
 // kept in flight (the stage of k-step kt is filled again for kt + STAGES as soon as the barrier says that its
@@ -650,7 +635,7 @@ constexpr int pp_smem_bytes() {
 // chunk XOR of row r of a 32-row weight block
 __device__ __forceinline__ int pp_bkey(int r) { return ((r >> 1) & 1) | (((r >> 3) & 3) << 1); }
 
-// vblock, lidx and the result as in gemm_tile; called by all 512 threads.
+// vblock, lidx and the result as in gemm_tile16; called by all 512 threads.
 template <int TN, bool SPLIT = false>
 __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsigned char* smem, const int vblock,
                                              lds_idx_t lidx = nullptr) {
@@ -1017,7 +1002,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) gemm_bf16_kernel(GemmDe
   __shared__ __attribute__((aligned(1024))) unsigned char smem[smem_bytes<BM, BN, STAGES>()];
   const int m = p.m_dev ? *p.m_dev : p.m_max;
   if (m <= 0) return;
-  gemm_tile<BM, BN, WAVES_M, WAVES_N, STAGES>(p, m, smem, threadIdx.x, blockIdx.x);
+  gemm_tile<BM, BN, WAVES_M, WAVES_N, STAGES>(p, m, smem);
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
@@ -1034,22 +1019,12 @@ __global__ void __launch_bounds__(512) gemm_bf16_pp_kernel(GemmDev p) {
 }
 
 // ---- row count read on the device: the tile shape follows it -------------------------
-// One kernel for every projection of refreshed rows, 8 waves and 128 KiB
-// of LDS.  What bounds a projection of few rows is the rate at which one CU pulls
-// operand tiles out of L2 (measured 45-80 GB/s per CU whatever the ring depth), so the
-// shape that wins moves the fewest bytes per CU while still using every CU:
-//   256 x 256 and 256 x 192 (the all-row shapes) once they fill the chip;
-//   128 x 192 (four waves) when that gives one round of 192-256 tiles (257-512 rows of a
-//   12288-wide output: 63 us against 72-79 us for 128 x 128 tiles, which need a second round);
-//   128 x 128 (4 x 2 waves, 4 stages) once that gives at least kWideBigTiles tiles;
-//   else 64 x 64 tiles, one per workgroup (all eight waves, 16-wide MFMA shape) while
-//   there are at most kWideSingle of them, and two per workgroup, one per team of four
-//   waves, beyond that.
-constexpr int kWideSmem = smem_bytes<128, 128, 4>();
-constexpr int kWideBigTiles = 160, kWideSingle = 256, kWideFullTiles = 200;
+// One kernel for every projection of refreshed rows, 8 waves and 144 KiB of LDS, one workgroup per CU
+// whatever the count turns out to be (a grid sized for the worst case, whose surplus workgroups
+// return at once, costs 1 us more at 205 rows); the shape is the one that best_tile (gemm_route.h) names, and
+// its tiles are walked in passes.
+constexpr int kWideSmem = pp_smem_bytes<2>();
 constexpr int kWideGrid = 256;  // workgroups of a launch: one per CU
-// a tile count that fills most of the chip's 256 CUs in a single round
-__host__ __device__ inline bool one_round(int tiles) { return tiles >= 192 && tiles <= 256; }
 // The refreshed-row list from the mask bytes, by every workgroup for itself (Alg. 1/2 line 5
 // folded into the first kernel that needs the list: a compaction kernel of its own costs a
 // launch, 4-5 us of a 90 us step, for a few hundred bytes of work).  512 threads, up to
@@ -1121,11 +1096,10 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
   // and gemm_tile takes "no list" as a null pointer)
   int* sel_wave_tot = reinterpret_cast<int*>(smem);
   int32_t* sel_list = reinterpret_cast<int32_t*>(smem + 64);
-  static_assert(2 * smem_bytes<64, 64, 4>() <= kWideSmem && smem_bytes<64, 64, 8>() <= kWideSmem &&
-                    pp_smem_bytes<4>() <= kWideSmem &&
-                    smem_bytes<128, 192, 3>() <= kWideSmem && smem_bytes<128, 96, 4>() <= kWideSmem &&
-                    smem_bytes<128, 48, 5>() <= kWideSmem && smem_bytes<128, 64, 4>() <= kWideSmem &&
-                    pp_smem_bytes<3>() <= kWideSmem,
+  static_assert(smem_bytes<64, 64, 8>() <= kWideSmem && smem_bytes<128, 48, 5>() <= kWideSmem &&
+                    smem_bytes<128, 64, 4>() <= kWideSmem && smem_bytes<128, 96, 4>() <= kWideSmem &&
+                    smem_bytes<128, 192, 3>() <= kWideSmem && smem_bytes<128, 128, 4>() <= kWideSmem &&
+                    pp_smem_bytes<3>() <= kWideSmem && pp_smem_bytes<4>() <= kWideSmem,
                 "shared buffer too small");
   int m;
   lds_idx_t lidx = nullptr;
@@ -1144,13 +1118,11 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
     if (m <= 16) skinny_tile<8, 1>(p, m, smem, threadIdx.x, lidx); else skinny_tile<8, 2>(p, m, smem, threadIdx.x, lidx);
     return;
   }
-  // The grid is one workgroup per CU whatever the count turns out to be (a grid sized for the
-  // worst case, whose surplus workgroups return at once, costs 1 us more at 205 rows); shapes
-  // that can have more tiles than that walk them in passes, virtual block id = block id +
-  // pass * grid size.  Every thread of the workgroup sees the same m and so takes the same
-  // branch and the same number of passes.
-  auto passes = [&](auto tile) __attribute__((always_inline)) {
-    for (int vb = blockIdx.x;; vb += gridDim.x) {
+  // Tiles in passes, virtual block id = block id + pass * grid size.  Every thread of the workgroup
+  // sees the same m and so takes the same branch and the same number of passes.
+  auto passes = [&](int tiles, auto tile) __attribute__((always_inline)) {
+    const int per_xcd = (tiles + 7) >> 3;
+    for (int vb = blockIdx.x; (vb >> 3) < per_xcd; vb += gridDim.x) {
       if (vb != (int)blockIdx.x) {
         __syncthreads();  // the ring is reused: everybody is done with the last tile
         if constexpr (FUSED) derive_rows(p, sel_list, sel_wave_tot, false);
@@ -1158,18 +1130,13 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
       if (!tile(vb)) break;
     }
   };
-  if (p.n % 256 == 0 && tiles_of(m, p.n, 256, 256) >= 2 * kWideSingle) {
-    // Rounds of 256 x 256 tiles; when the last round would be at most half full (624 tiles on
-    // 256 workgroups: 256 + 256 + 112), its tiles are cut into four 128 x 128 tiles each and
+  const GemmRoute shape = best_tile(m, p.n, true);
+  if (shape == GemmRoute::kPp256Cut) {
+    // Rounds of 256 x 256 tiles; the tiles of the last round are cut into four 128 x 128 tiles each and
     // spread over all workgroups (one or two short rounds instead of a long, mostly idle one).
-    // Virtual block ids: 8 per XCD slot, as gemm_tile decodes them.
-    const int G = gridDim.x;
-    const int tiles_m = (m + 255) / 256, tiles_n = p.n / 256;
-    const int total = tiles_m * tiles_n, per_xcd = (total + 7) >> 3;
-    const int n_vb = per_xcd * 8;
-    const int last = n_vb % G;
-    const bool cut = n_vb > G && last > 0 && 2 * last <= G;
-    const int whole_end = cut ? n_vb - last : n_vb;
+    const int G = gridDim.x, tiles_m = (m + 255) / 256, tiles_n = p.n / 256;
+    const int total = tiles_m * tiles_n, per_xcd = (total + 7) >> 3, n_vb = per_xcd * 8;  // 8 per XCD slot
+    const int whole_end = n_vb - n_vb % G;
     bool first = true;
     auto next_tile = [&]() __attribute__((always_inline)) {
       if (!first) {
@@ -1182,43 +1149,39 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
       next_tile();
       gemm_tile_pp<4>(p, m, smem, vb, lidx);
     }
-    if (cut) {
-      // child c: the parents of an XCD slot stay on their XCD (c & 7), 4 children per parent
-      for (int c = blockIdx.x; c < 4 * last; c += G) {
-        const int vb = whole_end + ((c >> 5) << 3) + (c & 7), quarter = (c >> 3) & 3;
-        const int unit = (vb & 7) * per_xcd + (vb >> 3);
-        if (unit >= total) continue;
-        int tm, tn;
-        tile_of_unit(unit, tiles_m, tiles_n, tm, tn);
-        const int cm = 2 * tm + (quarter >> 1), cn = 2 * tn + (quarter & 1);
-        if (cm * 128 >= m) continue;
-        next_tile();
-        gemm_tile16<128, 128, 2, 4, 4>(p, m, smem, threadIdx.x, 0, lidx, cm, cn);
-      }
+    // child c: the parents of an XCD slot stay on their XCD (c & 7), 4 children per parent
+    for (int c = blockIdx.x; c < 4 * (n_vb - whole_end); c += G) {
+      const int vb = whole_end + ((c >> 5) << 3) + (c & 7), quarter = (c >> 3) & 3;
+      const int unit = (vb & 7) * per_xcd + (vb >> 3);
+      if (unit >= total) continue;
+      int tm, tn;
+      tile_of_unit(unit, tiles_m, tiles_n, tm, tn);
+      const int cm = 2 * tm + (quarter >> 1), cn = 2 * tn + (quarter & 1);
+      if (cm * 128 >= m) continue;
+      next_tile();
+      gemm_tile16<128, 128, 2, 4, 4>(p, m, smem, threadIdx.x, 0, lidx, cm, cn);
     }
-  } else if (p.n % 192 == 0 && tiles_of(m, p.n, 256, 192) >= kWideFullTiles) {
-    passes([&](int vb) { return gemm_tile_pp<3>(p, m, smem, vb, lidx); });
-  } else if (p.n % 192 == 0 && one_round(tiles_of(m, p.n, 128, 192))) {
-    gemm_tile16<128, 192, 4, 2, 3>(p, m, smem, threadIdx.x, blockIdx.x, lidx);  // (at most one tile per workgroup)
-  } else if (m > 64 && p.n % 48 == 0 && one_round(tiles_of(m, p.n, 128, 48))) {
-    gemm_tile16<128, 48, 8, 1, 5>(p, m, smem, threadIdx.x, blockIdx.x, lidx);
-  } else if (m > 128 && one_round(tiles_of(m, p.n, 128, 64))) {
-    gemm_tile16<128, 64, 4, 2, 4>(p, m, smem, threadIdx.x, blockIdx.x, lidx);
-  } else if (p.n % 96 == 0 && one_round(tiles_of(m, p.n, 128, 96))) {
-    gemm_tile16<128, 96, 4, 2, 4>(p, m, smem, threadIdx.x, blockIdx.x, lidx);
-  } else if (tiles_of(m, p.n, 128, 128) >= kWideBigTiles) {
-    passes([&](int vb) { return gemm_tile16<128, 128, 2, 4, 4>(p, m, smem, threadIdx.x, vb, lidx); });
-  } else if (tiles_of(m, p.n, 64, 64) <= kWideSingle) {
-    // one tile per workgroup: all eight waves on it (16 x 32 each with the 16-wide MFMA
-    // shape; measured 19.2 against 21.1 us for four waves of 32 x 32 at 205 rows, n = 4096),
-    // the whole stage memory as a ring of eight stages
-    gemm_tile16<64, 64, 2, 4, 8>(p, m, smem, threadIdx.x, blockIdx.x, lidx);
-  } else {
-    const int team = threadIdx.x >> 8;
-    passes([&](int vb) {
-      return gemm_tile<64, 64, 2, 2, 4>(p, m, smem + team * smem_bytes<64, 64, 4>(), threadIdx.x & 255, vb, team, 2,
-                                        lidx);
-    });
+    return;
+  }
+  switch (shape) {
+    case GemmRoute::kPp256:
+      return passes(tiles_of(m, p.n, kPpRows, 256), [&](int vb) { return gemm_tile_pp<4>(p, m, smem, vb, lidx); });
+    case GemmRoute::kPp192:
+      return passes(tiles_of(m, p.n, kPpRows, 192), [&](int vb) { return gemm_tile_pp<3>(p, m, smem, vb, lidx); });
+    case GemmRoute::kPp128:
+      return passes(tiles_of(m, p.n, kPpRows, 128), [&](int vb) { return gemm_tile_pp<2>(p, m, smem, vb, lidx); });
+    case GemmRoute::k128x192:
+      return passes(tiles_of(m, p.n, 128, 192), [&](int vb) { return gemm_tile16<128, 192, 2, 4, 3>(p, m, smem, threadIdx.x, vb, lidx); });
+    case GemmRoute::k128x128:
+      return passes(tiles_of(m, p.n, 128, 128), [&](int vb) { return gemm_tile16<128, 128, 2, 4, 4>(p, m, smem, threadIdx.x, vb, lidx); });
+    case GemmRoute::k128x96:
+      return passes(tiles_of(m, p.n, 128, 96), [&](int vb) { return gemm_tile16<128, 96, 4, 2, 4>(p, m, smem, threadIdx.x, vb, lidx); });
+    case GemmRoute::k128x64:
+      return passes(tiles_of(m, p.n, 128, 64), [&](int vb) { return gemm_tile16<128, 64, 4, 2, 4>(p, m, smem, threadIdx.x, vb, lidx); });
+    case GemmRoute::k128x48:
+      return passes(tiles_of(m, p.n, 128, 48), [&](int vb) { return gemm_tile16<128, 48, 8, 1, 5>(p, m, smem, threadIdx.x, vb, lidx); });
+    default:
+      return passes(tiles_of(m, p.n, 64, 64), [&](int vb) { return gemm_tile16<64, 64, 2, 4, 8>(p, m, smem, threadIdx.x, vb, lidx); });
   }
 }
 
@@ -1506,17 +1469,9 @@ hipError_t launch_pp(const GemmArgs& g, hipStream_t s) {
 }
 
 hipError_t launch_rows_wide(const GemmArgs& g, hipStream_t s) {
-  // worst case over the row counts 1 .. m_max of the blocks any of the shapes needs (the
-  // 64 x 64 shape is only chosen below kWideBigTiles 128 x 128 tiles, each of which holds
-  // at most four small ones), capped at one workgroup per CU: shapes with more tiles than
-  // that walk them in passes
-  const int small = tiles_of(g.m_max, g.n, 64, 64);
-  int pairs = (small + 1) / 2;
-  const int pairs_cap = (4 * (kWideBigTiles - 1) + 1) / 2;
-  if (pairs > pairs_cap) pairs = pairs_cap;
-  int blocks = small <= kWideSingle ? small : (pairs > kWideSingle ? pairs : kWideSingle);
-  const int big = tiles_of(g.m_max, g.n, 128, 128);
-  if (big >= kWideBigTiles && big > blocks) blocks = big;
+  // as many as the smallest tiles, or the column groups of the stream over the weights, whichever are more
+  const int small = tiles_of(g.m_max, g.n, 64, 64), groups = g.m_max > 0 ? g.n / 16 : 0;
+  int blocks = small > groups ? small : groups;
   if (blocks == 0) return hipSuccess;
   if (blocks > kWideGrid) blocks = kWideGrid;
   if (g.sel_mask)
@@ -1530,15 +1485,20 @@ hipError_t launch_rows_wide(const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   if (g.m_dev || g.sel_mask) return launch_rows_wide(g, s);
+  if (g.m_max == 0) return hipSuccess;
   switch (gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles && !g.c32)) {
-    case GemmRoute::kRows64: return launch_tile16<64, 128, 4, 2, 5>(g, s);
-    case GemmRoute::kRows128: return launch_tile16<128, 128, 2, 4, 4>(g, s);
-    case GemmRoute::kPp192: return launch_pp<3>(g, s);
-    case GemmRoute::kPp256: return launch_pp<4>(g, s);
-    case GemmRoute::kPp128: return launch_pp<2>(g, s);
     case GemmRoute::kPp128Split: return launch_pp<2, true>(g, s);
-    case GemmRoute::kTile128: return launch_tile16<128, 128, 2, 4, 4>(g, s);
+    case GemmRoute::kPp256: return launch_pp<4>(g, s);
+    case GemmRoute::kPp192: return launch_pp<3>(g, s);
+    case GemmRoute::kPp128: return launch_pp<2>(g, s);
+    case GemmRoute::k128x192: return launch_tile16<128, 192, 2, 4, 3>(g, s);
+    case GemmRoute::k128x128: return launch_tile16<128, 128, 2, 4, 4>(g, s);
+    case GemmRoute::k128x96: return launch_tile16<128, 96, 4, 2, 4>(g, s);
+    case GemmRoute::k64x128: return launch_tile16<64, 128, 2, 4, 5>(g, s);
+    case GemmRoute::k64x96: return launch_tile16<64, 96, 4, 2, 6>(g, s);
+    case GemmRoute::k64x64: return launch_tile16<64, 64, 2, 4, 8>(g, s);
     case GemmRoute::kTile64: return launch_fixed<64, 64, 2, 2, 4>(g, s);
+    case GemmRoute::k128x48: case GemmRoute::k128x64: case GemmRoute::kPp256Cut: break;  // (listed rows)
   }
   return hipErrorInvalidValue;
 }

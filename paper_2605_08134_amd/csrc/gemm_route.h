@@ -1,17 +1,24 @@
-// Tile shape of a bf16 projection whose row count the host knows, as plain host arithmetic: no HIP
-// here, so that the rule can be evaluated over its whole range without a GPU.
+// Tile shape of a bf16 projection, as plain host arithmetic: no HIP here, so that the rule can be
+// evaluated over its whole range without a GPU.  Where the row count is known on the device only, the kernel
+// evaluates the same rule.
 #pragma once
 
 namespace dare {
 
 enum class GemmRoute {
-  kTile64,      // 64 x 64, four waves
-  kTile128,     // 128 x 128 on the 16-wide MFMA shape, eight waves
-  kRows64,      // 64 x 128 on the 16-wide MFMA shape: one row tile
-  kRows128,     // 128 x 128 on the 16-wide MFMA shape: one row tile
+  kTile64,      // 64 x 64, four waves; the only one that takes k in ranges
+  k64x64,       // eight waves, 16-wide MFMA shape
+  k64x96,
+  k64x128,
+  k128x48,
+  k128x64,
+  k128x96,
+  k128x128,
+  k128x192,
   kPp128,       // ping-pong tiles of 256 rows x 128, 192, 256 columns
   kPp192,
   kPp256,
+  kPp256Cut,    // the last round of 256 x 256 cut into 128 x 128 (listed rows)
   kPp128Split,  // 256 x 128, two workgroups on the halves of a tile's k; needs the workspace
 };
 
@@ -31,37 +38,71 @@ constexpr bool gemm_may_split(long m, long n, long k) {
          k / kRouteBK >= kSplitMinSteps;
 }
 
-// Once 256-row tiles fill most of the chip, the ping-pong tile
-// wins: 256 x 192 costs about 3/4 of 256 x 256 (1870 against 2500 cycles per k-step), so the narrow
-// one is taken where it needs fewer quarter-rounds of the 256 CUs (1024 x 12288: one full round
-// against one round with 64 CUs idle, 78 against 85 us; 2331 x 12288: three against two, 209 against
-// 198 us).  256 x 128 takes over while it fills more than half of the CUs and needs fewer rounds of
-// them than 128 x 128 (a round at k = 4096 takes 59 us against 39: 520 x 6144, 144 tiles against 240, one
-// round each; 600 x 12288, 288 against 480, two each: 96 against 83 us; 1024 x 9216 x 3072, two against
-// three: 78 against 94), and with two workgroups
-// per tile where there are kSplitTiles / 2 to kSplitTiles of them.  128 x 128 with 8 waves is the best
-// shape when the larger ones would leave most CUs idle.
-// One row tile (the output embedding of a few rows): a stream over the weights, of which 256-row
-// tiles pull as many bytes of repeated rows as of weights.  64 and 128 rows with the 16-wide MFMA
-// shape and as many weight rows in flight as fit (us, before in 256-row tiles; 1.04 GB of weights,
-// k = 4096): 32 x 126464 229 -> 174 (5.9 TB/s), 64 x 126464 243 -> 205, 128 x 126464 244 -> 220,
-// 128 x 24576 40 (128 x 128 tiles, 32-wide) -> 37.
-constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace) {
-  const int t128 = tiles_of(m, n, 128, 128);
-  if (k_parts <= 1 && m <= 64 && tiles_of(m, n, 64, 128) >= 192) return GemmRoute::kRows64;
-  if (k_parts <= 1 && m > 64 && m <= 128 && t128 >= 64) return GemmRoute::kRows128;
-  if (k_parts <= 1 && m > 128) {
-    const int t3 = tiles_of(m, n, kPpRows, 192), t4 = tiles_of(m, n, kPpRows, 256);
-    const int q3 = 3 * ((t3 + 255) / 256), q4 = 4 * ((t4 + 255) / 256);
-    if (t3 >= 224 && (q3 < q4 || t4 < 176)) return GemmRoute::kPp192;
-    if (t4 >= 176) return GemmRoute::kPp256;
-    const int t2 = tiles_of(m, n, kPpRows, 128), ksteps = k / kRouteBK;
-    if (t2 > kSplitTiles && (t2 + 255) / 256 < (t128 + 255) / 256) return GemmRoute::kPp128;
-    if (workspace && t2 >= kSplitTiles / 2 && t2 <= kSplitTiles && ksteps % 2 == 0 && ksteps >= kSplitMinSteps)
-      return GemmRoute::kPp128Split;
+// What a projection takes in tiles of bm x bn, in units that the shapes share (with 64 k-steps 512000 are about 70
+// us; the k-steps are common to all shapes and drop out).  A round in which all 256 CUs have a tile counts 512
+// times `full`, and idle CUs save half of their share of it (power, and the operands from beyond the L2, are
+// shared by those that work).  In several rounds it is `again` instead of `full`: nothing hides the ends of the
+// 16-wide loop's shapes, and small ones pull the weights again for every row of tiles (300 x 12288 x 4096: 64 x 64 73
+// us, 256 x 128 52).
+// Fitted to 120 products of 40 to 16384 rows by 512 to 24576 columns, k from 512 to 12288, in every shape: the
+// shape chosen is within 3 % of the fastest one but for 1300 x 4096 x 12288 (10 %: 192 x 128, which nothing else
+// wants) and 256 x 24576 x 4096 (10 %).  A rule by thresholds on tile counts, made for 1024 tokens of 4096, was off
+// by up to 2 (us, before and now: 402 x 2048 x 2048 17.2 and 9.2, 256 x 4096 x 4096 29.0 and 15.4, 1000 x 9216 x
+// 3072 80.6 and 50.8, 2331 x 4096 x 4096 91 and 67; refreshed rows, 1300 x 4096 x 4096 72 and 51, 2870 x 4096 x 4096 116
+// and 92, 4096 x 4096 x 4096 167 and 109, 600 x 12288 x 4096 89 and 75).
+// (Whole numbers: the device evaluates it on its scalar unit.)
+constexpr int tile_cost(int m, int n, int bm, int bn, int full, int again) {
+  const int tiles = tiles_of(m, n, bm, bn), rounds = (tiles + 255) >> 8;
+  return (rounds > 1 ? again : full) * (rounds * 256 + tiles);
+}
+
+// The shape for m rows and n columns.  listed: rows read through a list, which prefers many rows to many columns
+// in a small tile (128 x 64 against 64 x 128: 400 x 4096 28.0 and 29.3 us, all rows 23.1 and 21.5; 128 x 48 against 64 x
+// 96: 250 x 6144 x 2048 13.6 and 14.0, 100 x 12288 x 4096 30.2 and 32.4).
+// One round of the smallest tiles is the best wherever it is enough, and known without the rest (0.3 us on
+// the device).
+constexpr GemmRoute best_tile(int m, int n, bool listed) {
+  if (tiles_of(m, n, 64, 64) <= 256) return GemmRoute::k64x64;
+  if (tiles_of(m, n, kPpRows, 256) > 8192) return GemmRoute::kPp256;  // (and the costs below stay in 32 bits)
+  GemmRoute best = GemmRoute::k64x64;
+  int least = tile_cost(m, n, 64, 64, 153, 229);
+  auto offer = [&](GemmRoute r, int cost) {
+    if (cost < least) {
+      least = cost;
+      best = r;
+    }
+  };
+  if (listed) {
+    offer(GemmRoute::k128x48, tile_cost(m, n, 128, 48, 210, 273));
+    offer(GemmRoute::k128x64, tile_cost(m, n, 128, 64, 245, 318));
+  } else {
+    offer(GemmRoute::k64x96, tile_cost(m, n, 64, 96, 235, 306));
+    offer(GemmRoute::k64x128, tile_cost(m, n, 64, 128, 280, 364));
   }
-  if (k_parts <= 1 && m > 64 && n % 128 == 0 && t128 >= 64) return GemmRoute::kTile128;
-  return GemmRoute::kTile64;
+  offer(GemmRoute::k128x96, tile_cost(m, n, 128, 96, 390, 448));
+  offer(GemmRoute::k128x128, tile_cost(m, n, 128, 128, 490, 564));
+  offer(GemmRoute::k128x192, tile_cost(m, n, 128, 192, 780, 897));
+  offer(GemmRoute::kPp128, tile_cost(m, n, kPpRows, 128, 800, 848));
+  offer(GemmRoute::kPp192, tile_cost(m, n, kPpRows, 192, 1150, 1150));
+  offer(GemmRoute::kPp256, tile_cost(m, n, kPpRows, 256, 1460, 1460));
+  const int t4 = tiles_of(m, n, kPpRows, 256), rest = t4 % 256;
+  // (3266 x 12288 x 4096, 624 tiles of 256 x 256: 286 us, uncut 299)
+  if (listed && n % 256 == 0 && t4 > 256 && rest > 0 && rest <= 128)
+    offer(GemmRoute::kPp256Cut, 1460 * 512 * (t4 / 256) + tile_cost(4 * rest * 128, 128, 128, 128, 490, 490));
+  return best;
+}
+
+// Row count known on the host.  With the workspace, two workgroups per tile of 256 x 128 where there are
+// kSplitTiles / 2 to kSplitTiles of them and a long k: half of the tile's cost and the hand-over (1024 x 4096 x 12288:
+// 97 against 112 us in 128 x 128 tiles; 402 x 4096 x 12288 stays at 77 in 64 x 128).
+constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace) {
+  if (k_parts > 1) return GemmRoute::kTile64;
+  const GemmRoute best = best_tile(m, n, false);
+  const int t2 = tiles_of(m, n, kPpRows, 128), ksteps = k / kRouteBK;
+  if (workspace && t2 >= kSplitTiles / 2 && t2 <= kSplitTiles && ksteps % 2 == 0 && ksteps >= kSplitMinSteps &&
+      (best == GemmRoute::kPp128 || best == GemmRoute::k128x192 || best == GemmRoute::k128x128))
+    return GemmRoute::kPp128Split;
+  return best;
 }
 
 // Scored columns: whether the score is taken in the launch that projects them, rather than in one of its

@@ -236,6 +236,36 @@ def test_gemm_selected_rows_long_k(B, n, count, shape):
     assert_close(got[rows], want, "bf16")
 
 
+@pytest.mark.parametrize("listed,m,n,k", [
+    # each shape of best_tile, with a ragged last row tile; n that is no multiple of the tile's columns; odd k-steps
+    (False, 402, 512, 192), (False, 1000, 1536, 128), (False, 1001, 2048, 64), (False, 2331, 1024, 192),
+    (False, 1001, 4096, 64), (False, 1025, 6080, 128), (False, 1300, 6144, 64), (False, 1000, 9216, 128),
+    (False, 2331, 6144, 64),
+    (True, 33, 512, 192), (True, 400, 3072, 128), (True, 300, 4096, 64), (True, 601, 4096, 192),
+    (True, 777, 4096, 128), (True, 1300, 4096, 64), (True, 1000, 9216, 128), (True, 2900, 4096, 64),
+    (True, 3101, 12288, 64),      # the last round cut into 128 x 128
+])
+def test_gemm_every_tile_shape(B, listed, m, n, k):
+    r = _rng(m + n + k)
+    n_tok = m + 50 if listed else m
+    a = store(r.standard_normal((n_tok, k), dtype=np.float32), "bf16")
+    w = store(r.standard_normal((k, n), dtype=np.float32) * np.float32(0.05), "bf16")
+    wt = B.dare_k_pack_weight(dev(w, "bf16"))
+    out = torch.full((n_tok, n), 3.0, dtype=torch.bfloat16, device="cuda")
+    rows = np.sort(r.permutation(n_tok)[:m]).astype(np.int32)
+    if listed:
+        idx = np.full(n_tok, 10 ** 6, dtype=np.int32)
+        idx[:m] = rows
+        B.dare_k_gemm(dev(a, "bf16"), wt, [out], n, idx=dev(idx), m_dev=torch.tensor([m], dtype=torch.int32, device="cuda"),
+                      m_max=n_tok)
+    else:
+        B.dare_k_gemm(dev(a, "bf16"), wt, [out], n)
+    torch.cuda.synchronize()
+    got = host(out)
+    assert np.all(got[np.setdiff1d(np.arange(n_tok), rows)] == 3.0)
+    assert_close(got[rows], a[rows].astype(np.float64) @ w.astype(np.float64), "bf16")
+
+
 def test_gemm_k_parts_feed_the_score(B):
     # the scored-columns projection cut along k: slabs of partial sums that the score
     # kernel adds up, against the uncut projection and the oracle's score
