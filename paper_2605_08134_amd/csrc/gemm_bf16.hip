@@ -509,7 +509,6 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
     row_out[i] = row < m ? row : m - 1;
   }
   row_tokens(p.idx, lidx, row_out, tok_out);
-  if (lidx) __syncthreads();
   // (loads of k-steps past the end repeat the last one, into a stage that nobody reads any more, so
   // that the count of loads in flight is the same in every k-step)
   auto issue_load = [&](int i, int kt) __attribute__((always_inline)) {
@@ -697,7 +696,6 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
     row_out[i] = row < m ? row : m - 1;
   }
   row_tokens(p.idx, lidx, row_out, tok_out);
-  if (lidx) __syncthreads();
   // (k-steps past the end re-read the last one into a region nobody reads any more, so that the
   // number of loads in flight is the same in every phase of every k-step)
   auto stage = [&](int kt) __attribute__((always_inline)) { return smem + (kt % STAGES) * STAGE_BYTES; };
@@ -946,7 +944,6 @@ __device__ __forceinline__ void skinny_tile(const GemmDev& p, const int m, unsig
   row_tokens(p.idx, lidx, row, tok);
 #pragma unroll
   for (int t = 0; t < TMS; ++t) xrow[t] = p.a + (long)tok[t] * p.lda + kq * 8;
-  if (lidx) __syncthreads();  // a list in LDS shares the memory of the partial sums below
   f32x4* red = reinterpret_cast<f32x4*>(smem);  // [NW][TMS][64]
   for (int grp = blockIdx.x; grp < groups; grp += gridDim.x) {
     const int n0 = grp << 4;
@@ -1029,7 +1026,7 @@ constexpr int kWideGrid = 256;  // workgroups of a launch: one per CU
 // folded into the first kernel that needs the list: a compaction kernel of its own costs a
 // launch, 4-5 us of a 90 us step, for a few hundred bytes of work).  512 threads, up to
 // kSelMaxTokens tokens, four per thread; ascending by construction.  Returns the count.
-__device__ __forceinline__ int derive_rows(const GemmDev& p, int32_t* list, int* wave_tot, bool publish) {
+__device__ __forceinline__ int derive_rows(const GemmDev& p, int32_t* list, int* wave_tot) {
   const int n_tok = p.sel_batch * p.sel_seq;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int t0 = tid * 4;
@@ -1058,7 +1055,7 @@ __device__ __forceinline__ int derive_rows(const GemmDev& p, int32_t* list, int*
   for (int k = 0; k < 4; ++k)
     if (z[k]) list[rank++] = t0 + k;
   __syncthreads();
-  if (publish && blockIdx.x == 0) {  // what the compaction kernel would have written, for the kernels that follow
+  if (blockIdx.x == 0) {  // what the compaction kernel would have written, for the kernels that follow
     for (int r = tid; r < total; r += 512) {
       p.sel_idx_out[r] = list[r];
       if (p.sel_idx_out2) p.sel_idx_out2[r] = list[r];
@@ -1086,16 +1083,14 @@ __device__ __forceinline__ int derive_rows(const GemmDev& p, int32_t* list, int*
 // so that the plain one carries none of the list handling).
 template <bool FUSED>
 __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kWideSmem];
-  // a row list derived from the mask lives at the start of the stage memory until every
-  // thread has taken the entries it needs (gemm_tile / skinny_tile read them before their
-  // first load into LDS): the list gets no memory of its own, and a workgroup that walks
-  // several tiles derives it again in front of every further pass
-  static_assert(kSelMaxTokens * 4 + 64 <= kWideSmem, "row list must fit the stage memory");
-  // (the list starts 64 bytes in: LDS offset 0 is the null pointer of the LDS address space,
-  // and gemm_tile takes "no list" as a null pointer)
-  int* sel_wave_tot = reinterpret_cast<int*>(smem);
-  int32_t* sel_list = reinterpret_cast<int32_t*>(smem + 64);
+  // A row list derived from the mask lies behind the stage memory for the whole launch.  (In the stage memory
+  // it had to be read before the first load into LDS, a barrier between them, and derived again, seven copies of
+  // that code and 152 spilled scalars, in front of every further pass.  Steps, with the shape in line: 2 x 201 tokens
+  // of hidden 512 28.5 -> 27.6 us, 1 x 1024 of 4096 with 4 refreshed rows 60.9 -> 60.4, with 205 rows 89.8 -> 89.4.
+  // One array for both: see score_proj_kernel.)
+  constexpr int kListBytes = FUSED ? 64 + kSelMaxTokens * 4 : 0;
+  static_assert(kWideSmem + kListBytes <= 160 * 1024, "stage memory and row list must fit the LDS of a CU");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kWideSmem + kListBytes];
   static_assert(smem_bytes<64, 64, 8>() <= kWideSmem && smem_bytes<128, 48, 5>() <= kWideSmem &&
                     smem_bytes<128, 64, 4>() <= kWideSmem && smem_bytes<128, 96, 4>() <= kWideSmem &&
                     smem_bytes<128, 192, 3>() <= kWideSmem && smem_bytes<128, 128, 4>() <= kWideSmem &&
@@ -1104,8 +1099,9 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
   int m;
   lds_idx_t lidx = nullptr;
   if constexpr (FUSED) {
-    m = derive_rows(p, sel_list, sel_wave_tot, true);
-    lidx = (lds_idx_t)sel_list;
+    int32_t* list = reinterpret_cast<int32_t*>(smem + kWideSmem + 64);
+    m = derive_rows(p, list, reinterpret_cast<int*>(smem + kWideSmem));
+    lidx = (lds_idx_t)list;
   } else {
     m = p.m_dev ? *p.m_dev : p.m_max;
   }
@@ -1123,10 +1119,7 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
   auto passes = [&](int tiles, auto tile) __attribute__((always_inline)) {
     const int per_xcd = (tiles + 7) >> 3;
     for (int vb = blockIdx.x; (vb >> 3) < per_xcd; vb += gridDim.x) {
-      if (vb != (int)blockIdx.x) {
-        __syncthreads();  // the ring is reused: everybody is done with the last tile
-        if constexpr (FUSED) derive_rows(p, sel_list, sel_wave_tot, false);
-      }
+      if (vb != (int)blockIdx.x) __syncthreads();  // the ring is reused: everybody is done with the last tile
       if (!tile(vb)) break;
     }
   };
@@ -1139,10 +1132,7 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
     const int whole_end = n_vb - n_vb % G;
     bool first = true;
     auto next_tile = [&]() __attribute__((always_inline)) {
-      if (!first) {
-        __syncthreads();  // the ring is reused: everybody is done with the last tile
-        if constexpr (FUSED) derive_rows(p, sel_list, sel_wave_tot, false);
-      }
+      if (!first) __syncthreads();  // the ring is reused: everybody is done with the last tile
       first = false;
     };
     for (int vb = blockIdx.x; vb < whole_end; vb += G) {

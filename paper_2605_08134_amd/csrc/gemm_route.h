@@ -61,7 +61,9 @@ constexpr int tile_cost(int m, int n, int bm, int bn, int full, int again) {
 // 96: 250 x 6144 x 2048 13.6 and 14.0, 100 x 12288 x 4096 30.2 and 32.4).
 // One round of the smallest tiles is the best wherever it is enough, and known without the rest (0.3 us on
 // the device).
-constexpr GemmRoute best_tile(int m, int n, bool listed) {
+// (In line: called, the kernel gets the shape in a vector register and takes every branch on it, and all that lies
+// behind, under lane masks.)
+__attribute__((always_inline)) constexpr GemmRoute best_tile(int m, int n, bool listed) {
   if (tiles_of(m, n, 64, 64) <= 256) return GemmRoute::k64x64;
   if (tiles_of(m, n, kPpRows, 256) > 8192) return GemmRoute::kPp256;  // (and the costs below stay in 32 bits)
   GemmRoute best = GemmRoute::k64x64;
