@@ -113,6 +113,15 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// The same where `ahead` (0 .. MAX, or more for MAX; the same in all waves) stages of LOADS each may be outstanding
+template <int LOADS, int MAX>
+__device__ __forceinline__ void wait_stages_and_barrier(const int ahead) {
+  if constexpr (MAX > 0) {
+    if (ahead < MAX) return wait_stages_and_barrier<LOADS, MAX - 1>(ahead);
+  }
+  wait_vmcnt_and_barrier<LOADS * MAX>();
+}
+
 template <int BM, int BN, int STAGES>
 constexpr int smem_bytes() {
   return STAGES * (BM + BN) * ROW_BYTES;
@@ -509,10 +518,13 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
     row_out[i] = row < m ? row : m - 1;
   }
   row_tokens(p.idx, lidx, row_out, tok_out);
-  // (loads of k-steps past the end repeat the last one, into a stage that nobody reads any more, so
-  // that the count of loads in flight is the same in every k-step)
+  // TRIM: nothing is loaded past the last k-step (steps of 1 x 1024 x 4096, half of the tokens refreshed: 155.5 ->
+  // 154.2 us).  Otherwise the loads of k-steps past the end repeat the last one, into a stage that nobody reads any
+  // more, so that one loop with one wait serves all k-steps: the last ones of a small tile take less than
+  // fetching code of their own does (2 x 201 x 512 28.4 us as it is and 29.6 with TRIM, 4 of 1024 rows 61.0 and 62.5).
+  constexpr bool TRIM = TM * TN >= 6;
   auto issue_load = [&](int i, int kt) __attribute__((always_inline)) {
-    const int k = kt < KT ? kt : KT - 1;
+    const int k = TRIM || kt < KT ? kt : KT - 1;
     __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + k * BK),
                                      (lptr_t)(smem + (kt % STAGES) * STAGE_BYTES + grp[i] * 8 * ROW_BYTES), 16, 0, 0);
   };
@@ -557,34 +569,63 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
 
 #pragma unroll
   for (int s = 0; s < STAGES; ++s)
+    if (!TRIM || s < KT) {
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) issue_load(i, s);
-  wait_vmcnt_and_barrier<LPW*(STAGES - 1)>();
+      for (int i = 0; i < LPW; ++i) issue_load(i, s);
+    }
+  wait_stages_and_barrier<LPW, STAGES - 1>(TRIM ? KT - 1 : STAGES - 1);
   load_frags(0, 0);
   // k-step kt: the barrier publishes stage kt + 1 and, as every wave's fragments of kt have arrived, frees
   // the stage of kt.  (Two k-steps per trip so that the fragment set index is a compile-time constant.)
-  auto kstep = [&](int kt, auto set_c) __attribute__((always_inline)) {
+  // END: one of the last k-steps, which has nothing left to load and waits for as many loads as are under way.
+  auto kstep = [&](int kt, auto set_c, auto end_c) __attribute__((always_inline)) {
     constexpr int SET = decltype(set_c)::value;
+    constexpr bool END = decltype(end_c)::value;
     mma(SET, 0, PRE);
     __builtin_amdgcn_sched_barrier(0);
-    wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
+    if (!END || kt + 1 < KT) {
+      if constexpr (END)
+        wait_stages_and_barrier<LPW, STAGES - 2>(KT - 2 - kt);
+      else
+        wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
+      __builtin_amdgcn_sched_barrier(0);
+      load_frags(kt + 1, SET ^ 1);
+    }
     __builtin_amdgcn_sched_barrier(0);
-    load_frags(kt + 1, SET ^ 1);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (END) {
+      mma(SET, PRE, NMMA);
+    } else {
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) {
-      mma(SET, PRE + (NMMA - PRE) * i / LPW, PRE + (NMMA - PRE) * (i + 1) / LPW);
-      __builtin_amdgcn_sched_barrier(0);
-      issue_load(i, kt + STAGES);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < LPW; ++i) {
+        mma(SET, PRE + (NMMA - PRE) * i / LPW, PRE + (NMMA - PRE) * (i + 1) / LPW);
+        __builtin_amdgcn_sched_barrier(0);
+        issue_load(i, kt + STAGES);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   };
+  using Yes = std::true_type;
+  using No = std::false_type;
+  using Set0 = std::integral_constant<int, 0>;
+  using Set1 = std::integral_constant<int, 1>;
   int kt = 0;
-  for (; kt + 1 < KT; kt += 2) {
-    kstep(kt, std::integral_constant<int, 0>{});
-    kstep(kt + 1, std::integral_constant<int, 1>{});
+  const int loading = TRIM ? KT - STAGES : KT;
+  for (; kt + 1 < loading; kt += 2) {
+    kstep(kt, Set0{}, No{});
+    kstep(kt + 1, Set1{}, No{});
   }
-  if (kt < KT) kstep(kt, std::integral_constant<int, 0>{});
+  if constexpr (!TRIM) {
+    if (kt < KT) kstep(kt, Set0{}, No{});
+    kt = KT;
+  } else if (kt < loading) {  // an odd number of k-steps load: the last ones begin with set 1
+    kstep(kt, Set0{}, No{});
+    kstep(++kt, Set1{}, Yes{});
+    ++kt;
+  }
+  for (; kt < KT; kt += 2) {
+    kstep(kt, Set0{}, Yes{});
+    if (kt + 1 < KT) kstep(kt + 1, Set1{}, Yes{});
+  }
   wait_vmcnt<0>();
 
   // acc[i][j][e] = C[row, col]: row = m0 + wave_m*WM + 16 i + l16, col = n0 + wave_n*WN + 16 j + 4 kq + e
@@ -625,6 +666,9 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
 // two workgroups (below; 64 to 128 tiles, which leave half of the CUs idle, and a long k), inside a
 // model step: 1024 x 4096 x 12288 122 -> 97.  A k-step takes 1610 cycles for 1024 of MFMAs:
 // every byte of LDS written or read for it at 128 B per cycle is 1400.
+// The last k-steps load nothing and wait for what is under way: a launch of one round had two k-steps of 64
+// pulled in vain and the last load's latency at its end.  Steps: 3 x 777, outputs reused 285.7 -> 282.1 us, 8 x 2048
+// refreshed 534.8 -> 525.2, dense block 2323 -> 2300; a dense step of 1024 tokens 148.6 -> 148.9.
 template <int TN>
 constexpr int pp_stages() { return TN == 2 ? 3 : 2; }
 template <int TN>
@@ -696,15 +740,13 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
     row_out[i] = row < m ? row : m - 1;
   }
   row_tokens(p.idx, lidx, row_out, tok_out);
-  // (k-steps past the end re-read the last one into a region nobody reads any more, so that the
-  // number of loads in flight is the same in every phase of every k-step)
+  // (in front of the loop, k-steps past the end of a short k re-read the last one into a region that nobody
+  // reads, so that the loads in flight are at least those that the loop counts; the loop loads nothing past the end)
   auto stage = [&](int kt) __attribute__((always_inline)) { return smem + (kt % STAGES) * STAGE_BYTES; };
-  auto load_a = [&](int i, int kt) __attribute__((always_inline)) {
-    const int k = kt < KT ? kt : KT - 1;
+  auto load_a = [&](int i, int kt, int k) __attribute__((always_inline)) {
     __builtin_amdgcn_global_load_lds((gptr_t)(src_a[i] + k * BK), (lptr_t)(stage(kt) + (wave * 4 + i) * 1024), 16, 0, 0);
   };
-  auto load_b = [&](int j, int kt) __attribute__((always_inline)) {
-    const int k = kt < KT ? kt : KT - 1;
+  auto load_b = [&](int j, int kt, int k) __attribute__((always_inline)) {
     __builtin_amdgcn_global_load_lds((gptr_t)(src_b[j] + k * BK),
                                      (lptr_t)(stage(kt) + ASZ + j * 64 * ROW_BYTES + wave * 1024), 16, 0, 0);
   };
@@ -782,77 +824,94 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   };
   auto none = []() __attribute__((always_inline)) {};
 #define DARE_N(n) std::integral_constant<int, n>{}
-#define DARE_A(i, d) [&]() __attribute__((always_inline)) { load_a(i, kt + d); }
-#define DARE_B(j, d) [&]() __attribute__((always_inline)) { load_b(j, kt + d); }
+#define DARE_A(on, i, d) [&]() __attribute__((always_inline)) { if constexpr (on) load_a(i, kt + d, kt + d); }
+#define DARE_B(on, j, d) [&]() __attribute__((always_inline)) { if constexpr (on) load_b(j, kt + d, kt + d); }
 
   // Loads in the order in which they are needed: block 0 of a k-step, its A rows, its blocks
   // 1 .. TN - 1.  The counts below are the loads issued after the last one that the next phase reads.
-  load_b(0, 0);
+  const int k1 = KT > 1 ? 1 : 0, k2 = KT > 2 ? 2 : KT - 1;
+  load_b(0, 0, 0);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) load_a(i, 0);
+  for (int i = 0; i < 4; ++i) load_a(i, 0, 0);
 #pragma unroll
-  for (int j = 1; j < TN; ++j) load_b(j, 0);
-  load_b(0, 1);
+  for (int j = 1; j < TN; ++j) load_b(j, 0, 0);
+  load_b(0, 1, k1);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) load_a(i, 1);
-  load_b(1, 1);
-  if constexpr (TN == 4) load_b(2, 1);
+  for (int i = 0; i < 4; ++i) load_a(i, 1, k1);
+  load_b(1, 1, k1);
+  if constexpr (TN == 4) load_b(2, 1, k1);
   if constexpr (TN == 2) {
-    load_b(0, 2);
+    load_b(0, 2, k2);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_a(i, 2);
+    for (int i = 0; i < 4; ++i) load_a(i, 2, k2);
   }
   wait_vmcnt_and_barrier<TN == 4 ? 10 : (TN == 3 ? 8 : 12)>();
   read_b(0, 0, 0);
   // (group 0 refills the region that these reads take from after this barrier)
   if (grp == 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  if constexpr (TN == 4) {
-    for (int kt = 0; kt < KT; ++kt) {
-      read_a(kt);
-      end_mem(DARE_N(9));
-      matrix(0, 0, DARE_B(3, 1), none, DARE_B(0, 2), none);
+  // LEFT: k-steps that follow, STAGES for as many or more; S: fragment set of block 0 (alternates where TN is odd).
+  auto kstep = [&](int kt, auto set_c, auto left_c) __attribute__((always_inline)) {
+    constexpr int S = decltype(set_c)::value, LEFT = decltype(left_c)::value;
+    constexpr bool L1 = LEFT > 0, L2 = LEFT > 1, L3 = LEFT > 2;  // k-steps kt + 1, kt + 2, kt + 3 exist
+    read_a(kt);
+    if constexpr (TN == 4) {
+      end_mem(DARE_N(L1 ? 9 : 2));
+      matrix(0, 0, DARE_B(L1, 3, 1), none, DARE_B(L2, 0, 2), none);
       read_b(1, 1, kt);
-      end_mem(DARE_N(10));
-      matrix(1, 1, DARE_A(0, 2), none, DARE_A(1, 2), none);
+      end_mem(DARE_N(L2 ? 10 : (L1 ? 9 : 1)));
+      matrix(1, 1, DARE_A(L2, 0, 2), none, DARE_A(L2, 1, 2), none);
       read_b(0, 2, kt);
-      end_mem(DARE_N(10));
-      matrix(0, 2, DARE_A(2, 2), none, DARE_A(3, 2), none);
+      end_mem(DARE_N(L2 ? 10 : (L1 ? 7 : 0)));
+      matrix(0, 2, DARE_A(L2, 2, 2), none, DARE_A(L2, 3, 2), none);
       read_b(1, 3, kt);
-      read_b(0, 0, kt + 1);
-      end_mem(DARE_N(8));
-      matrix(1, 3, DARE_B(1, 2), none, DARE_B(2, 2), none);
-    }
-  } else if constexpr (TN == 2) {
-    for (int kt = 0; kt < KT; ++kt) {
-      read_a(kt);
-      end_mem(DARE_N(10));
-      matrix(0, 0, DARE_B(1, 2), none, DARE_B(0, 3), none);
+      if constexpr (L1) read_b(0, 0, kt + 1);
+      end_mem(DARE_N(L2 ? 8 : (L1 ? 3 : 0)));
+      matrix(1, 3, DARE_B(L2, 1, 2), none, DARE_B(L2, 2, 2), none);
+    } else if constexpr (TN == 2) {
+      end_mem(DARE_N(L2 ? 10 : (L1 ? 5 : 0)));
+      matrix(0, 0, DARE_B(L2, 1, 2), none, DARE_B(L3, 0, 3), none);
       read_b(1, 1, kt);
-      read_b(0, 0, kt + 1);
-      end_mem(DARE_N(8));
-      matrix(1, 1, DARE_A(0, 3), DARE_A(1, 3), DARE_A(2, 3), DARE_A(3, 3));
-    }
-  } else {
-    auto kstep = [&](int kt, auto set_c) __attribute__((always_inline)) {
-      constexpr int S = decltype(set_c)::value;  // fragment set of block 0 (alternates: TN is odd)
-      read_a(kt);
-      end_mem(DARE_N(7));
-      matrix(S, 0, DARE_B(2, 1), none, DARE_B(0, 2), none);
+      if constexpr (L1) read_b(0, 0, kt + 1);
+      end_mem(DARE_N(L3 ? 8 : (L2 ? 7 : (L1 ? 1 : 0))));
+      matrix(1, 1, DARE_A(L3, 0, 3), DARE_A(L3, 1, 3), DARE_A(L3, 2, 3), DARE_A(L3, 3, 3));
+    } else {
+      end_mem(DARE_N(L1 ? 7 : 1));
+      matrix(S, 0, DARE_B(L1, 2, 1), none, DARE_B(L2, 0, 2), none);
       read_b(S ^ 1, 1, kt);
-      end_mem(DARE_N(7));
-      matrix(S ^ 1, 1, DARE_A(0, 2), DARE_A(1, 2), DARE_A(2, 2), DARE_A(3, 2));
+      end_mem(DARE_N(L2 ? 7 : (L1 ? 6 : 0)));
+      matrix(S ^ 1, 1, DARE_A(L2, 0, 2), DARE_A(L2, 1, 2), DARE_A(L2, 2, 2), DARE_A(L2, 3, 2));
       read_b(S, 2, kt);
-      read_b(S ^ 1, 0, kt + 1);
-      end_mem(DARE_N(7));
-      matrix(S, 2, none, DARE_B(1, 2), none, none);
-    };
-    int kt = 0;
-    for (; kt + 1 < KT; kt += 2) {
-      kstep(kt, DARE_N(0));
-      kstep(kt + 1, DARE_N(1));
+      if constexpr (L1) read_b(S ^ 1, 0, kt + 1);
+      end_mem(DARE_N(L2 ? 7 : (L1 ? 2 : 0)));
+      matrix(S, 2, none, DARE_B(L2, 1, 2), none, none);
     }
-    if (kt < KT) kstep(kt, DARE_N(0));
+  };
+  // a k-step alone leaves the next one's block 0 in the set where it starts (branches that meet with different
+  // sets cost registers)
+  auto single = [&](int kt, auto left_c) __attribute__((always_inline)) {
+    kstep(kt, DARE_N(0), left_c);
+    if constexpr (TN == 3) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) fb[0][h][ks] = fb[1][h][ks];
+    }
+  };
+  int kt = 0;
+  if constexpr (TN == 3) {
+    for (; kt + 1 < KT - STAGES; kt += 2) {
+      kstep(kt, DARE_N(0), DARE_N(STAGES));
+      kstep(kt + 1, DARE_N(1), DARE_N(STAGES));
+    }
+    if (kt < KT - STAGES) single(kt++, DARE_N(STAGES));
+  } else {
+    for (; kt < KT - STAGES; ++kt) kstep(kt, DARE_N(0), DARE_N(STAGES));
   }
+  if constexpr (STAGES > 2) {
+    if (kt < KT - 2) single(kt++, DARE_N(2));
+  }
+  if (kt < KT - 1) single(kt++, DARE_N(1));
+  kstep(kt, DARE_N(0), DARE_N(0));
 #undef DARE_N
 #undef DARE_A
 #undef DARE_B

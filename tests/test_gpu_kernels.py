@@ -244,6 +244,11 @@ def test_gemm_selected_rows_long_k(B, n, count, shape):
     (True, 33, 512, 192), (True, 400, 3072, 128), (True, 300, 4096, 64), (True, 601, 4096, 192),
     (True, 777, 4096, 128), (True, 1300, 4096, 64), (True, 1000, 9216, 128), (True, 2900, 4096, 64),
     (True, 3101, 12288, 64),      # the last round cut into 128 x 128
+    # k-steps around the length of the ring, odd and even: the last of them load nothing
+    *((False, m, n, k) for m, n in ((1000, 1536), (1001, 4096), (1300, 6144), (1000, 9216), (2331, 6144))
+      for k in (256, 320, 384, 448)),
+    *((True, m, n, k) for m, n in ((400, 3072), (601, 4096), (777, 4096), (1300, 4096), (1000, 9216), (2900, 4096))
+      for k in (256, 320, 384, 448)),
 ])
 def test_gemm_every_tile_shape(B, listed, m, n, k):
     r = _rng(m + n + k)
