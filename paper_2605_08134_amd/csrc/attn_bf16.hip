@@ -42,7 +42,7 @@ struct AttnDev {
   int seq, d;
   int n_heads, n_pairs, n_qt;  // heads, batch*heads, query blocks launched per (sequence, head)
   int batch;
-  int few_per_pair;  // > 0: few listed rows; workgroups per (sequence, head) that run at once
+  int turn, at_once;           // order of the workgroups, readers ahead (attn_turn, attn_at_once)
   // keys of a query block cut over workgroups (attn_rows_bf16_kernel): partial results, and
   // counters that are 0 before and after the launch; nullptr = never cut
   float* part_out;
@@ -422,12 +422,10 @@ __global__ void __launch_bounds__(QW* KW * 64) attn_bf16_kernel(AttnDev p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[attn_smem_bytes<DH, KW, TK, NST>()];
   // Workgroup ids are dealt round-robin to the 8 XCDs.  All query blocks of one
   // (sequence, head) are placed on the same XCD, so its K and V are fetched from HBM
-  // once and re-read from that XCD's L2 by the other blocks.  Few listed rows: the first blocks of all of them, then the
-  // second ones, so that those with rows run before those without.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int per_xcd = (p.n_pairs + 7) >> 3;
-  const int pair = (p.few_per_pair > 0 ? slot % per_xcd : slot / p.n_qt) * 8 + xcd;
-  const int qt = p.few_per_pair > 0 ? slot / per_xcd : slot % p.n_qt;
+  // once and re-read from that XCD's L2 by the other blocks.
+  AttnPlace at = {blockIdx.x >> 3, 0};
+  if (p.n_qt > 1) at = attn_place(at.pair, (unsigned)(p.n_pairs + 7) >> 3, p.n_qt, p.turn);
+  const int pair = at.pair * 8 + (blockIdx.x & 7), qt = at.block;
   if (pair >= p.n_pairs) return;
   const int b = pair / p.n_heads, h = pair % p.n_heads;
   int cnt, off;
@@ -440,8 +438,8 @@ __global__ void __launch_bounds__(QW* KW * 64) attn_bf16_kernel(AttnDev p) {
   }
   if (qt * (32 * QW) >= cnt) {
     const int blocks = (cnt + 32 * QW - 1) / (32 * QW);
-    if (blocks > 0 && qt < p.few_per_pair)
-      read_ahead<DH, QW * KW>(p, b, h, qt - blocks, (p.few_per_pair < p.n_qt ? p.few_per_pair : p.n_qt) - blocks, smem);
+    if (blocks > 0 && qt < p.at_once)
+      read_ahead<DH, QW * KW>(p, b, h, qt - blocks, (p.at_once < p.n_qt ? p.at_once : p.n_qt) - blocks, smem);
     return;
   }
   attn_block<DH, QW, KW, TK, NST>(p, b, h, qt, cnt, off, smem, threadIdx.x);
@@ -555,16 +553,11 @@ __global__ void __launch_bounds__(512, kRowsGrid<DH> / 128) attn_rows_bf16_kerne
 
 template <int DH, int QW, int KW, int TK, int NST>
 hipError_t launch_variant(AttnDev p, const AttnArgs& a, hipStream_t s) {
-  const bool few = a.idx && !a.many_rows;
   p.n_heads = a.n_heads;
   p.n_pairs = a.batch * a.n_heads;
   p.n_qt = (a.seq + 32 * QW - 1) / (32 * QW);
-  if (few) {
-    // Workgroups without rows read ahead while every block has a CU of its own: as many as run at once. An XCD's
-    // share of K and V has to stay in its L2 of 4 MB.
-    const long room = (DH == 64 ? 512 : 256) / p.n_pairs, bytes = (long)((p.n_pairs + 7) / 8) * a.seq * DH * 4;
-    p.few_per_pair = bytes <= (4l << 20) && a.seq > 256 && room > 1 ? (int)room : 1;
-  }
+  p.turn = attn_turn(p.n_pairs, a.idx != nullptr, a.many_rows);
+  p.at_once = a.idx && !a.many_rows ? attn_at_once(p.n_pairs, a.seq, DH) : 0;
   const long grid = (long)((p.n_pairs + 7) / 8) * p.n_qt * 8;
   if (grid > 0x7fffffffL) return hipErrorInvalidValue;
   hipLaunchKernelGGL((attn_bf16_kernel<DH, QW, KW, TK, NST>), dim3((unsigned)grid), dim3(QW * KW * 64), 0, s, p);

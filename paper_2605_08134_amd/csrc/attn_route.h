@@ -47,4 +47,36 @@ constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, b
   return blocks(256) >= 256 ? AttnRoute::kTall : AttnRoute::kWide;
 }
 
+// Order of the workgroups of an XCD where there is one per possible block (kNarrow, kWide, kTall): the first blocks
+// of `turn` (sequence, head)s, then their second ones, and so on; then the next `turn`.
+// Listed rows, how many only the device knows: eight take turns.  One by one, a workgroup with rows lies next to
+// those of the same pair without any, and an XCD, which deals its workgroups round its shader engines, keeps a
+// part of its CUs idle; with all of them in one turn a pair's second block comes when its keys and values have
+// left the L2 (us with one by one, 4, 8, 16, 32, all in one turn: 64 x 512 tokens of 32 heads of 128, 1 % of the rows
+// 386, 129, 128, 126, 129, 130; half 495, 287, 290, 294, 298, 324; every row 530, 537, 540, 541, 526, 611;
+// 64 x 256, three quarters 182, 176, 176, 176, 182, 196).
+constexpr int attn_turn(int pairs, bool listed, bool many) {
+  const int per_xcd = (pairs + 7) / 8;
+  return listed && !many ? (per_xcd < 8 ? per_xcd : 8) : 1;
+}
+struct AttnPlace {
+  unsigned pair, block;  // (sequence, head) of the XCD, query block
+};
+// (unsigned, and no division more than the case needs, none for one block per pair: this is in front of the first
+// load, and a part of a block over a short sequence that shows: 128 x 64 tokens of 32 heads 82.7 -> 80.5 us)
+constexpr AttnPlace attn_place(unsigned slot, unsigned per_xcd, unsigned n_blocks, unsigned turn) {
+  const unsigned t = slot / (turn * n_blocks), in = slot - t * turn * n_blocks, left = per_xcd - t * turn;
+  if (turn == 1) return {t, in};
+  const unsigned width = left < turn ? left : turn, block = in / width;
+  return {t * turn + in - block * width, block};
+}
+
+// Listed rows: workgroups per (sequence, head) that run at once, where those without rows of their own read K and V
+// ahead, else 0.  They do while every block has a CU of its own and an XCD's share of K and V stays in its L2 of 4 MB.
+constexpr int attn_at_once(int pairs, int seq, int head_dim) {
+  const int room = (head_dim == 64 ? 512 : 256) / pairs;
+  const long bytes = (long)((pairs + 7) / 8) * seq * head_dim * 4;
+  return bytes <= (4l << 20) && seq > 256 && room > 1 ? room : 0;
+}
+
 }  // namespace dare

@@ -50,3 +50,64 @@ def test_cut_keys_need_the_workspace_and_long_sequences(route):
 def test_all_rows(route, listed):
     for batch, heads, seq, want in ((8, 32, 2048, TALL), (1, 32, 4096, TALL), (1, 32, 1024, WIDE), (2048, 16, 8, TALL)):
         assert route(batch, heads, seq, listed, listed, True) == want
+
+
+PLACES = r"""
+#include <cstdio>
+#include <vector>
+#include "attn_route.h"
+using namespace dare;
+int main() {
+  int bad = 0;
+  for (int per_xcd = 1; per_xcd <= 40; ++per_xcd)
+    for (int n_blocks = 1; n_blocks <= 9; ++n_blocks)
+      for (int turn : {1, attn_turn(8 * per_xcd, true, false)}) {
+        std::vector<int> at(per_xcd * n_blocks, -1);
+        for (int slot = 0; slot < per_xcd * n_blocks; ++slot) {
+          const AttnPlace x = attn_place(slot, per_xcd, n_blocks, turn);
+          if (x.pair >= (unsigned)per_xcd || x.block >= (unsigned)n_blocks || at[x.pair * n_blocks + x.block] >= 0) ++bad;
+          else at[x.pair * n_blocks + x.block] = slot;
+        }
+        for (int i = 0; i < per_xcd * n_blocks; ++i) {
+          if (i % n_blocks && at[i] - at[i - 1] != (turn == 1 ? 1 : turn < per_xcd - i / n_blocks / turn * turn ? turn : per_xcd - i / n_blocks / turn * turn)) ++bad;
+        }
+      }
+  std::printf("%d\n", bad);
+  return bad != 0;
+}
+"""
+
+
+def test_every_block_has_one_workgroup_and_follows_its_pairs_last_one(tmp_path):
+    """Over all counts of pairs and blocks: each block once, and a pair's next block at most eight workgroups of
+    the XCD behind its last one, however many pairs there are (its keys and values are in the L2 then)."""
+    (tmp_path / "places.cpp").write_text(PLACES)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"),
+                    str(tmp_path / "places.cpp"), "-o", str(tmp_path / "places")], check=True)
+    r = subprocess.run([str(tmp_path / "places")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+TURN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "attn_route.h"
+int main(int, char** a) {
+  std::printf("%d %d", dare::attn_turn(atoi(a[1]), atoi(a[2]), atoi(a[3])), dare::attn_at_once(atoi(a[1]), atoi(a[4]), atoi(a[5])));
+}
+"""
+
+
+def test_turns_and_readers_ahead(tmp_path):
+    (tmp_path / "turn.cpp").write_text(TURN)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"),
+                    str(tmp_path / "turn.cpp"), "-o", str(tmp_path / "turn")], check=True)
+    for (pairs, listed, many, seq, dh), want in {
+        (32, 1, 0, 1024, 128): (4, 8), (32, 1, 1, 1024, 128): (1, 8), (32, 0, 0, 1024, 128): (1, 8),
+        (2048, 1, 0, 512, 128): (8, 0),    # no CU for a reader
+        (8, 1, 0, 201, 128): (1, 0),       # two key steps
+        (60, 1, 0, 1100, 128): (8, 0), (60, 1, 0, 1024, 128): (8, 4), (60, 1, 0, 1024, 64): (8, 8),   # 4 MB of L2
+    }.items():
+        r = subprocess.run([str(tmp_path / "turn")] + [str(v) for v in (pairs, listed, many, seq, dh)],
+                           capture_output=True, text=True, check=True)
+        assert tuple(map(int, r.stdout.split())) == want, (pairs, seq, dh)

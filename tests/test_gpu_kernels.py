@@ -440,6 +440,7 @@ def test_attention_block_layout_from_the_counts(B, batch, seq, heads, dh, frac):
     (1, 257, 4, 128, 0.01), (3, 300, 2, 64, 0.2), (2, 1000, 3, 128, 0.004),  # a few blocks with rows, the others read ahead
     (2, 515, 3, 64, 0.001),       # a sequence without a refreshed row
     (1, 1025, 32, 128, 0.2), (1, 513, 32, 64, 0.99),                        # as many blocks as CUs, nearly
+    (20, 160, 5, 64, 0.6), (33, 300, 3, 128, 0.9),   # more pairs per XCD than take a turn, the last turn short
 ])
 def test_attention_blocks_without_rows_read_ahead(B, batch, seq, heads, dh, frac):
     test_attention_block_layout_from_the_counts(B, batch, seq, heads, dh, frac)
