@@ -1583,6 +1583,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
     case GemmRoute::k64x128: return launch_tile16<64, 128, 2, 4, 5>(g, s);
     case GemmRoute::k64x96: return launch_tile16<64, 96, 4, 2, 6>(g, s);
     case GemmRoute::k64x64: return launch_tile16<64, 64, 2, 4, 8>(g, s);
+    case GemmRoute::kTile128: return launch_fixed<128, 128, 4, 2, 4>(g, s);
     case GemmRoute::kTile64: return launch_fixed<64, 64, 2, 2, 4>(g, s);
     case GemmRoute::k128x48: case GemmRoute::k128x64: case GemmRoute::kPp256Cut: break;  // (listed rows)
   }

@@ -6,7 +6,8 @@
 namespace dare {
 
 enum class GemmRoute {
-  kTile64,      // 64 x 64, four waves; the only one that takes k in ranges
+  kTile64,      // k in ranges: 64 x 64, four waves
+  kTile128,     // k in ranges: 128 x 128, eight waves
   k64x64,       // eight waves, 16-wide MFMA shape
   k64x96,
   k64x128,
@@ -98,7 +99,13 @@ __attribute__((always_inline)) constexpr GemmRoute best_tile(int m, int n, bool 
 // kSplitTiles / 2 to kSplitTiles of them and a long k: half of the tile's cost and the hand-over (1024 x 4096 x 12288:
 // 97 against 112 us in 128 x 128 tiles; 402 x 4096 x 12288 stays at 77 in 64 x 128).
 constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace) {
-  if (k_parts > 1) return GemmRoute::kTile64;
+  if (k_parts > 1) {
+    // A round of 128 x 128, one per CU, takes half as long again as one of 64 x 64, two per CU (us, 128 and 64: 8064 x 128 x
+    // 4096 in two ranges 20.2 and 20.4, 9000 x 128 23.6 and 26.4, 16384 x 128 28.8 and 35.6, 4096 x 4096 194 and 246; 300 x
+    // 4096 x 4096 in four 29.3 and 26.2)
+    const long big = (long)tiles_of(m, n, 128, 128) * k_parts, small = (long)tiles_of(m, n, 64, 64) * k_parts;
+    return n % 128 == 0 && 3 * ((big + 255) / 256) < 2 * ((small + 511) / 512) ? GemmRoute::kTile128 : GemmRoute::kTile64;
+  }
   const GemmRoute best = best_tile(m, n, false);
   const int t2 = tiles_of(m, n, kPpRows, 128), ksteps = k / kRouteBK;
   if (workspace && t2 >= kSplitTiles / 2 && t2 <= kSplitTiles && ksteps % 2 == 0 && ksteps >= kSplitMinSteps &&

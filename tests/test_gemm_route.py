@@ -87,3 +87,27 @@ def test_last_flag_of_the_scored_columns_is_no_query_word(tmp_path):
     """Every wave of the last workgroup reads that it is the last and then writes its queries into
     the same LDS array, with no barrier in between: the two must not share a word."""
     assert _run(tmp_path, SCORE_LDS).returncode == 0
+
+
+RANGES = r"""
+#include <cstdio>
+#include "gemm_route.h"
+using namespace dare;
+int main() {
+  int bad = 0;
+  const struct { int m, n, parts; GemmRoute want; } at[] = {
+      {1024, 128, 8, GemmRoute::kTile64}, {4096, 128, 4, GemmRoute::kTile64},  // a round of either
+      {8192, 128, 2, GemmRoute::kTile64}, {8193, 128, 2, GemmRoute::kTile128}, {9000, 128, 2, GemmRoute::kTile128},
+      {16384, 128, 2, GemmRoute::kTile128}, {4096, 4096, 2, GemmRoute::kTile128}, {65, 8192, 8, GemmRoute::kTile128},
+      {300, 4096, 4, GemmRoute::kTile64}, {9000, 192, 2, GemmRoute::kTile64}};
+  for (const auto& c : at)
+    for (int workspace = 0; workspace < 2; ++workspace)
+        if (gemm_route(c.m, c.n, 4096, c.parts, workspace) != c.want) std::printf("%d x %d\n", c.m, c.n), ++bad;
+  return bad != 0;
+}
+"""
+
+
+def test_k_in_ranges_takes_large_tiles_where_they_need_fewer_rounds(tmp_path):
+    r = _run(tmp_path, RANGES)
+    assert r.returncode == 0, r.stdout

@@ -297,6 +297,25 @@ def test_gemm_k_parts_feed_the_score(B):
     assert rel_err(host(pd), want) <= 2e-6
 
 
+@pytest.mark.parametrize("m,n,k,parts", [
+    (8192, 128, 256, 2), (8193, 128, 256, 2),   # the last size in 64 x 64 tiles, the first in 128 x 128, one row in the last
+    (65, 8192, 512, 8), (1025, 3072, 192, 3),   # 128 x 128: one k-step per range
+    (300, 4096, 768, 4), (200, 192, 512, 4), (1, 64, 128, 2),   # 64 x 64: three k-steps, three column tiles, one row
+])
+def test_gemm_k_in_ranges(B, m, n, k, parts):
+    r = _rng(m + n)
+    a = store(r.standard_normal((m, k), dtype=np.float32), "bf16")
+    w = store(r.standard_normal((k, n), dtype=np.float32) * np.float32(0.05), "bf16")
+    slabs = torch.full((parts + 1, m, n), 7.0, dtype=torch.float32, device="cuda")
+    B.dare_k_gemm(dev(a, "bf16"), B.dare_k_pack_weight(dev(w, "bf16")), [None], n, m_max=m, c32=slabs, k_parts=parts)
+    torch.cuda.synchronize()
+    got = host(slabs)
+    assert np.all(got[parts] == 7.0)
+    for s in range(parts):
+        ks = slice(s * k // parts, (s + 1) * k // parts)
+        assert rel_err(got[s], a[:, ks].astype(np.float64) @ w[ks].astype(np.float64)) <= 2e-6
+
+
 def test_score_kernel(B):
     r = _rng(9)
     n, w, ld = 333, 128, 160
