@@ -222,7 +222,7 @@ __device__ __forceinline__ void tile_of_unit(const int unit, const int tiles_m, 
   tile_n = rem / rows_in_group;
 }
 
-// One output tile of C for m rows, or a range of its k (k_parts), computed by the WAVES_M * WAVES_N waves of a
+// A range of the k (one of k_parts) of an output tile of C for m rows, computed by the WAVES_M * WAVES_N waves of a
 // workgroup in smem_bytes<BM, BN, STAGES>() bytes of LDS.
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
 __device__ __forceinline__ void gemm_tile(const GemmDev& p, const int m, unsigned char* smem) {
@@ -315,7 +315,6 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& p, const int m, unsigne
   // stored at slot chunk ^ ((row >> 1) & 7); the tile bases are multiples of 32,
   // so the XOR term depends on l32 only
   constexpr int KS = BK / 16;
-  static_assert(KS % 2 == 0, "fragment double buffering assumes an even slice count");
   const int sw = (l32 >> 1) & 7;
   int koff[KS];
 #pragma unroll
@@ -328,102 +327,64 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& p, const int m, unsigne
   // a buffer nobody reads any more), so the count of outstanding loads per wave is
   // the same in every iteration and one vmcnt value serves the whole loop.
   //
-  // MFMA operands are double-buffered in registers: the LDS reads of the next unit
-  // of work are issued after the first PRE MFMAs of the current one and complete
-  // under the rest.  The unit is a 16-wide k-slice for large wave tiles; for small
-  // wave tiles (few MFMAs per slice, so nothing to hide an LDS round trip behind)
-  // it is the whole k-step: all fragments of k-step kt+1 are fetched under the MFMAs
-  // of k-step kt.  The barrier that publishes k-step kt+1 sits right before that
-  // fetch: by then every LDS read of k-step kt has been issued and (lgkmcnt 0) has
-  // completed, so its buffer may be refilled after the barrier.
+  // MFMA operands are double-buffered in registers: all fragments of k-step kt+1 are fetched
+  // after the first PRE MFMAs of k-step kt and arrive under the rest.  The barrier that publishes
+  // k-step kt+1 sits right before that fetch: by then every LDS read of k-step kt has been issued
+  // and (lgkmcnt 0) has completed, so its buffer may be refilled after the barrier.
   // The scheduling fences keep the compiler from sinking the LDS reads back down
   // to their first use, which would undo the register double buffering.
-  constexpr bool WHOLE = TM * TN <= 4;
-  constexpr int FS = WHOLE ? KS : 1;  // k-slices held per fragment set
-  bf16x8 fa[2][FS][TM], fb[2][FS][TN];
-  auto load_frags = [&](int buf, int ks, int set, int slot) __attribute__((always_inline)) {
+  bf16x8 fa[2][KS][TM], fb[2][KS][TN];
+  auto load_frags = [&](int buf, int set) __attribute__((always_inline)) {
     const unsigned char* st = smem + buf * STAGE_BYTES;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-      fa[set][slot][i] = *reinterpret_cast<const bf16x8*>(st + a_row_off + i * 32 * ROW_BYTES + koff[ks]);
+    for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-      fb[set][slot][j] = *reinterpret_cast<const bf16x8*>(st + b_row_off + j * 32 * ROW_BYTES + koff[ks]);
-  };
-  // MFMAs [first, last) of the FS x TM x TN grid of one fragment set
-  auto mma = [&](int set, int first, int last) __attribute__((always_inline)) {
+      for (int i = 0; i < TM; ++i)
+        fa[set][ks][i] = *reinterpret_cast<const bf16x8*>(st + a_row_off + i * 32 * ROW_BYTES + koff[ks]);
 #pragma unroll
-    for (int t = 0; t < FS * TM * TN; ++t) {
-      if (t < first || t >= last) continue;
-      const int slot = t / (TM * TN), i = (t / TN) % TM, j = t % TN;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][slot][j], fa[set][slot][i], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < TN; ++j)
+        fb[set][ks][j] = *reinterpret_cast<const bf16x8*>(st + b_row_off + j * 32 * ROW_BYTES + koff[ks]);
     }
   };
-  constexpr int NMMA = FS * TM * TN;
+  // MFMAs [first, last) of the KS x TM x TN grid of one fragment set
+  constexpr int NMMA = KS * TM * TN;
   constexpr int PRE = NMMA >= 8 ? 2 : 1;
+  auto mma = [&](int set, int first, int last) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < NMMA; ++t) {
+      if (t < first || t >= last) continue;
+      const int ks = t / (TM * TN), i = (t / TN) % TM, j = t % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][ks][j], fa[set][ks][i], acc[i][j], 0, 0, 0);
+    }
+  };
 
 #pragma unroll
   for (int s = 0; s < STAGES - 1; ++s) issue_loads(s < KT ? s : KT - 1, s);
   wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
-  if constexpr (WHOLE) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) load_frags(0, ks, 0, ks);
-    // two k-steps per trip so that the fragment set index is a compile-time constant
-    // (a run-time index would push the fragment arrays out of registers)
-    auto kstep = [&](int kt, auto set_c) __attribute__((always_inline)) {
-      constexpr int SET = decltype(set_c)::value;
-      const int nxt = kt + STAGES - 1;
-      issue_loads(nxt < KT ? nxt : KT - 1, nxt % STAGES);
-      mma(SET, 0, PRE);
-      __builtin_amdgcn_sched_barrier(0);
-      wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) load_frags((kt + 1) % STAGES, ks, SET ^ 1, ks);
-      __builtin_amdgcn_sched_barrier(0);
-      mma(SET, PRE, NMMA);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    int kt = 0;
-    for (; kt + 1 < KT; kt += 2) {
-      kstep(kt, std::integral_constant<int, 0>{});
-      kstep(kt + 1, std::integral_constant<int, 1>{});
-    }
-    if (kt < KT) kstep(kt, std::integral_constant<int, 0>{});
-  } else {
-    load_frags(0, 0, 0, 0);
-    for (int kt = 0; kt < KT; ++kt) {
-      const int buf = kt % STAGES;
-      const int nxt = kt + STAGES - 1;
-      // (the wave that is about to issue memory instructions goes first: of the two waves of
-      // a SIMD the other one is then in its MFMAs; measured 1-2 % on the all-row shapes)
-      __builtin_amdgcn_s_setprio(2);
-      issue_loads(nxt < KT ? nxt : KT - 1, nxt % STAGES);
-      __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-      for (int ks = 0; ks < KS - 1; ++ks) {
-        mma(ks & 1, 0, PRE);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(2);
-        load_frags(buf, ks + 1, (ks + 1) & 1, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(0);
-        mma(ks & 1, PRE, NMMA);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      mma((KS - 1) & 1, 0, PRE);
-      __builtin_amdgcn_sched_barrier(0);
-      wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
-      __builtin_amdgcn_s_setprio(2);
-      load_frags((kt + 1) % STAGES, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(0);
-      mma((KS - 1) & 1, PRE, NMMA);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  load_frags(0, 0);
+  // two k-steps per trip so that the fragment set index is a compile-time constant
+  // (a run-time index would push the fragment arrays out of registers)
+  auto kstep = [&](int kt, auto set_c) __attribute__((always_inline)) {
+    constexpr int SET = decltype(set_c)::value;
+    const int nxt = kt + STAGES - 1;
+    issue_loads(nxt < KT ? nxt : KT - 1, nxt % STAGES);
+    mma(SET, 0, PRE);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
+    load_frags((kt + 1) % STAGES, SET ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
+    mma(SET, PRE, NMMA);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int kt = 0;
+  for (; kt + 1 < KT; kt += 2) {
+    kstep(kt, std::integral_constant<int, 0>{});
+    kstep(kt + 1, std::integral_constant<int, 1>{});
   }
+  if (kt < KT) kstep(kt, std::integral_constant<int, 0>{});
   wait_vmcnt<0>();
 
-  float* c32 = p.c32 ? p.c32 + part * p.c32_part_stride : nullptr;
+  float* c32 = p.c32 + part * p.c32_part_stride;
   // Epilogue.  acc[i][j][r] = C[row, col] with
   //   row = m0 + wave_m*WM + i*32 + l32
   //   col = n0 + wave_n*WN + j*32 + (r/4)*8 + half*4 + r%4
@@ -450,7 +411,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& p, const int m, unsigne
 // 43.5 (32-wide MFMAs) -> 33.1, 205 x 12288 39.2 -> 34.5, 512 x 12288 61.7 -> 54.2, 512 x 8192 45.4 -> 33.5,
 // 512 x 4096 25.1 -> 21.3, 205 x 4096 17.2 -> 14.0, 100 x 12288 30.6 -> 28.0.  The k of a k-step halved
 // between two groups of four waves with twice the wave tile (half the fragment reads) is no faster: 34.4,
-// 35.2, 54.0, 31.5, 21.0, 13.7, 28.4.  No teams, no k-parts.
+// 35.2, 54.0, 31.5, 21.0, 13.7, 28.4.
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
 __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsigned char* smem, const int tid,
                                             const int vblock, lds_idx_t lidx = nullptr,
@@ -1052,13 +1013,11 @@ __device__ __forceinline__ void skinny_tile(const GemmDev& p, const int m, unsig
 }
 constexpr int kSkinnyRows = 32, kSkinnyMaxN = 8192;
 
-// ---- one tile shape, chosen on the host (row count known or bounded) --------------
+// ---- one tile shape, chosen on the host (row count known): k in ranges, then whole k --------------
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
-__global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) gemm_bf16_kernel(GemmDev p) {
+__global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) gemm_bf16_ranges_kernel(GemmDev p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[smem_bytes<BM, BN, STAGES>()];
-  const int m = p.m_dev ? *p.m_dev : p.m_max;
-  if (m <= 0) return;
-  gemm_tile<BM, BN, WAVES_M, WAVES_N, STAGES>(p, m, smem);
+  gemm_tile<BM, BN, WAVES_M, WAVES_N, STAGES>(p, p.m_max, smem);
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
@@ -1525,16 +1484,12 @@ GemmDev to_dev(const GemmArgs& g) {
 int grid_for(int tiles) { return ((tiles + 7) / 8) * 8; }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
-hipError_t launch_fixed(const GemmArgs& g, hipStream_t s) {
-  const int tiles = ((g.m_max + BM - 1) / BM) * ((g.n + BN - 1) / BN);
-  if (tiles == 0) return hipSuccess;
+hipError_t launch_ranges(const GemmArgs& g, hipStream_t s) {
   GemmDev p = to_dev(g);
-  if (g.k_parts > 1) {
-    p.k_parts = g.k_parts;
-    p.c32_part_stride = g.c32_part_stride;
-  }
-  hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WAVES_M, WAVES_N, STAGES>), dim3(grid_for(tiles * p.k_parts)),
-                     dim3(WAVES_M * WAVES_N * 64), 0, s, p);
+  p.k_parts = g.k_parts;
+  p.c32_part_stride = g.c32_part_stride;
+  hipLaunchKernelGGL((gemm_bf16_ranges_kernel<BM, BN, WAVES_M, WAVES_N, STAGES>),
+                     dim3(grid_for(tiles_of(g.m_max, g.n, BM, BN) * p.k_parts)), dim3(WAVES_M * WAVES_N * 64), 0, s, p);
   return hipGetLastError();
 }
 
@@ -1583,8 +1538,8 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
     case GemmRoute::k64x128: return launch_tile16<64, 128, 2, 4, 5>(g, s);
     case GemmRoute::k64x96: return launch_tile16<64, 96, 4, 2, 6>(g, s);
     case GemmRoute::k64x64: return launch_tile16<64, 64, 2, 4, 8>(g, s);
-    case GemmRoute::kTile128: return launch_fixed<128, 128, 4, 2, 4>(g, s);
-    case GemmRoute::kTile64: return launch_fixed<64, 64, 2, 2, 4>(g, s);
+    case GemmRoute::kTile128: return launch_ranges<128, 128, 4, 2, 4>(g, s);
+    case GemmRoute::kTile64: return launch_ranges<64, 64, 2, 2, 4>(g, s);
     case GemmRoute::k128x48: case GemmRoute::k128x64: case GemmRoute::kPp256Cut: break;  // (listed rows)
   }
   return hipErrorInvalidValue;
