@@ -95,9 +95,13 @@ __attribute__((always_inline)) constexpr GemmRoute best_tile(int m, int n, bool 
   return best;
 }
 
-// Row count known on the host.  With the workspace, two workgroups per tile of 256 x 128 where there are
-// kSplitTiles / 2 to kSplitTiles of them and a long k: half of the tile's cost and the hand-over (1024 x 4096 x 12288:
-// 97 against 112 us in 128 x 128 tiles; 402 x 4096 x 12288 stays at 77 in 64 x 128).
+// Row count known on the host.  With the workspace, two workgroups per tile of 256 x 128 instead of 128 x 128 tiles where
+// there are kSplitTiles / 2 to kSplitTiles of them and a long k: half of the tile's cost and the hand-over (1024 x 4096 x
+// 12288: 97 against 112 us).  Instead of 128 x 96 from 144 k-steps on, where the 16-wide loop
+// falls behind its cost (model steps of two layers, without and with: 768 x 3072 x 9216 431 and 412 us, 833 x 3072 x 9216 482 and
+// 470, 1089 x 2048 x 12288 512 and 486, 2304 x 1024 x 12288 541 and 520, 512 x 6144 x 12288 720 and 699; with 96 to 128 k-steps
+// 1089 x 2048 x 6144 319 and 326, 2240 x 1024 x 8192 379 and 396, 577 x 4096 x 8192 436 and 426).  64 x 128 stays (2048 x 1024 x
+// 12288 431, cut 480).
 constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace) {
   if (k_parts > 1) {
     // A round of 128 x 128, one per CU, takes half as long again as one of 64 x 64, two per CU (us, 128 and 64: 8064 x 128 x
@@ -109,7 +113,7 @@ constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace)
   const GemmRoute best = best_tile(m, n, false);
   const int t2 = tiles_of(m, n, kPpRows, 128), ksteps = k / kRouteBK;
   if (workspace && t2 >= kSplitTiles / 2 && t2 <= kSplitTiles && ksteps % 2 == 0 && ksteps >= kSplitMinSteps &&
-      (best == GemmRoute::kPp128 || best == GemmRoute::k128x192 || best == GemmRoute::k128x128))
+      (best == GemmRoute::k128x128 || (best == GemmRoute::k128x96 && ksteps >= 144)))
     return GemmRoute::kPp128Split;
   return best;
 }

@@ -111,3 +111,29 @@ int main() {
 def test_k_in_ranges_takes_large_tiles_where_they_need_fewer_rounds(tmp_path):
     r = _run(tmp_path, RANGES)
     assert r.returncode == 0, r.stdout
+
+
+SPLIT = r"""
+#include <cstdio>
+#include "gemm_route.h"
+using namespace dare;
+int main() {
+  int bad = 0;
+  const struct { int m, n, k; bool want; } at[] = {
+      {1024, 4096, 12288, true}, {600, 4096, 12288, true}, {768, 4096, 12288, true}, {768, 3072, 9216, true},
+      {2305, 1024, 9216, true}, {2305, 1024, 6144, false},     // 128 x 96 otherwise: from 144 k-steps on
+      {2048, 2048, 6144, true}, {1793, 2048, 6144, true},      // 128 x 128 otherwise: from 96
+      {2048, 1024, 6144, false}, {1793, 1024, 6144, false}, {402, 4096, 12288, false},   // 64 x 128
+      {2305, 2048, 6144, false}, {1025, 4096, 12288, false},   // more than the workspace holds
+      {1024, 4096, 4096, false}};
+  for (const auto& c : at)
+    if ((gemm_route(c.m, c.n, c.k, 1, true) == GemmRoute::kPp128Split) != c.want)
+      std::printf("%d x %d x %d\n", c.m, c.n, c.k), ++bad;
+  return bad != 0;
+}
+"""
+
+
+def test_which_projections_are_cut_over_two_workgroups(tmp_path):
+    r = _run(tmp_path, SPLIT)
+    assert r.returncode == 0, r.stdout

@@ -104,15 +104,16 @@ def Bm():
     return binding
 
 
-@pytest.mark.parametrize("T,d,prefix", [
-    (2048, 1024, 0), (1793, 1024, 0),    # 64 tiles of 256 x 128; one row in the last row tile
-    (2048, 2048, 0), (1900, 2048, 107),  # 128 tiles; 1793 rows left by the prefix
-    (2305, 2048, 0),                     # 160 tiles: more than the workspace holds
+@pytest.mark.parametrize("T,d,prefix,ffn", [
+    (2048, 1024, 0, 6144), (1793, 1024, 0, 6144),    # 64 tiles of 256 x 128: not cut, 64 x 128 is faster
+    (2048, 2048, 0, 6144), (1900, 2048, 107, 6144),  # 128 tiles; 1793 rows left by the prefix: one in the last row tile
+    (2305, 2048, 0, 6144),                           # 160 tiles: more than the workspace holds
+    (2305, 1024, 0, 9216),                           # 80 tiles, 144 k-steps; one row in the last row tile
 ])
-def test_down_projection_cut_along_k(Bm, T, d, prefix):
-    """The down projection (96 k-steps) with two workgroups on the halves of a tile's k.  Three
+def test_down_projection_cut_along_k(Bm, T, d, prefix, ffn):
+    """The down projection (96 k-steps and more) with two workgroups on the halves of a tile's k.  Three
     steps in a row on the same ids: the sum does not depend on which workgroup comes first."""
-    cfg = dict(L=1, d=d, H=d // 128, ffn=6144, V=128, B=1, T=T)
+    cfg = dict(L=1, d=d, H=d // 128, ffn=ffn, V=128, B=1, T=T)
     params = synth.make_model_params(T, 1, d, cfg["ffn"], cfg["V"], "bf16", with_head=False)
     m = _build(Bm, params, cfg, "bf16")
     ids = synth.make_ids(T, 1, T, cfg["V"], T // 2, cfg["V"] - 1)
