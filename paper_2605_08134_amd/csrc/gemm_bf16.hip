@@ -69,6 +69,7 @@ struct GemmDev {
   int32_t* sel_idx_out2;
   int32_t* sel_off_out;
   int32_t* sel_count_out;
+  int ahead;                // loads of weights per wave while the list is made (ahead_loads)
   // two workgroups on the halves of k of one tile (gemm_tile_pp): [tiles][2] fp32 tiles and
   // [tiles] counters; nullptr = one workgroup per tile
   float* split_tiles;
@@ -1044,11 +1045,14 @@ constexpr int kWideGrid = 256;  // workgroups of a launch: one per CU
 // folded into the first kernel that needs the list: a compaction kernel of its own costs a
 // launch, 4-5 us of a 90 us step, for a few hundred bytes of work).  512 threads, up to
 // kSelMaxTokens tokens, four per thread; ascending by construction.  Returns the count.
-// While the mask is on its way and the list is made, the first 256 k of this XCD's share of the weight rows (tiles
-// are dealt to the XCDs in contiguous ranges of columns) are read ahead into its L2, into 1 KiB of LDS that nobody
-// reads; nothing here waits for them.  What it fills is the time of the mask's round trip and the list.  (One asm
-// block: the compiler waits for these loads with the mask.)  Steps over 1 x 1024 tokens of hidden 4096: 205 refreshed
-// rows 90.0 -> 89.1 us, 4 rows 60.7 -> 60.4.
+// While the mask is on its way and the list is made, the first 256 k of the weight rows are read ahead: an XCD's
+// workgroups, 16 rows each at a time, read its share of them (tiles are dealt to the XCDs in contiguous ranges of
+// columns, as long as there are at most GROUP_M row tiles) into its L2, into 1 KiB of LDS that nobody reads; nothing here
+// waits for them.  What it fills is the time of the mask's round trip and the list.  (The first
+// one in a block with the mask: the compiler waits for loads into LDS with those in front of them.)  Steps over 1 x 1024
+// tokens with 205 refreshed rows, without and with it (us): hidden 4096 89.2 and 87.7, 6144 155.7 and 154.0, 1024 to 3072 and
+// 8192, and 4 rows, no difference beyond the runs'.  The stream over the weights (skinny_tile) deals its columns
+// otherwise and has nothing from it.
 __device__ __forceinline__ int derive_rows(const GemmDev& p, int32_t* list, int* wave_tot, unsigned char* nobody) {
   const int n_tok = p.sel_batch * p.sel_seq;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1056,24 +1060,24 @@ __device__ __forceinline__ int derive_rows(const GemmDev& p, int32_t* list, int*
   const int per_xcd = (p.n + 7) >> 3, first = (blockIdx.x & 7) * per_xcd, slots = gridDim.x >> 3;
   const int last = first + per_xcd < p.n ? first + per_xcd - 1 : p.n - 1;
   const uint8_t* mask[4];
-  const bf16_t* ahead[3];
 #pragma unroll
   for (int k = 0; k < 4; ++k) mask[k] = p.sel_mask + (t0 + k < n_tok ? t0 + k : n_tok - 1);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
+  auto ahead = [&](int i) __attribute__((always_inline)) {
     const int r = first + (((blockIdx.x >> 3) + i * slots) * 8 + wave) * 2 + (lane >> 5);
-    ahead[i] = p.wt + (long)(r < last ? r : last) * p.k + ((lane & 31) * 8 < p.k ? (lane & 31) * 8 : 0);
-  }
+    return p.wt + (long)(r < last ? r : last) * p.k + ((lane & 31) * 8 < p.k ? (lane & 31) * 8 : 0);
+  };
+  const unsigned lds = (unsigned)(size_t)(lptr_t)nobody;
   int reused[4];
   asm volatile(
       "global_load_ubyte %0, %4, off\n\tglobal_load_ubyte %1, %5, off\n\t"
       "global_load_ubyte %2, %6, off\n\tglobal_load_ubyte %3, %7, off\n\t"
-      "global_load_lds_dwordx4 %8, off\n\tglobal_load_lds_dwordx4 %9, off\n\t"
-      "global_load_lds_dwordx4 %10, off\n\ts_waitcnt vmcnt(3)"
+      "global_load_lds_dwordx4 %8, off\n\ts_waitcnt vmcnt(1)"
       : "=&v"(reused[0]), "=&v"(reused[1]), "=&v"(reused[2]), "=&v"(reused[3])
-      : "v"(mask[0]), "v"(mask[1]), "v"(mask[2]), "v"(mask[3]), "v"(ahead[0]), "v"(ahead[1]), "v"(ahead[2]),
-        "{m0}"((unsigned)(size_t)(lptr_t)nobody)
+      : "v"(mask[0]), "v"(mask[1]), "v"(mask[2]), "v"(mask[3]), "v"(ahead(0)), "{m0}"(lds)
       : "memory");
+#pragma unroll 1
+  for (int i = 1; i < p.ahead; ++i)
+    asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(ahead(i)), "{m0}"(lds) : "memory");
   bool z[4];
   int cnt = 0;
 #pragma unroll
@@ -1147,8 +1151,9 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
     m = derive_rows(p, list, reinterpret_cast<int*>(smem + kWideSmem), smem + kWideSmem + 64 + kSelMaxTokens * 4);
     lidx = (lds_idx_t)list;
   } else {
-    // (the weights ahead as in derive_rows, a third of it: the count and the list are a shorter wait.  Steps of 205
-    // refreshed rows of 1 x 1024 x 4096 87.0 -> 86.2 us, of 4 rows 60.2 -> 60.0; 16384 tokens unchanged)
+    // (the weights ahead as in derive_rows, 16 rows per workgroup: the count and the list are a shorter wait, and the
+    // list, which comes behind these loads, must not wait for more.  Steps over 1 x 1024 tokens with 205 refreshed rows, hidden
+    // 1024 40.9 -> 40.6 us, 3072 70.8 -> 70.2, 4096 87.7 -> 86.9; with 4 rows, the stream, no difference; 16384 tokens unchanged)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int per_xcd = (p.n + 7) >> 3, first = (blockIdx.x & 7) * per_xcd;
     const int last = first + per_xcd < p.n ? first + per_xcd - 1 : p.n - 1;
@@ -1476,6 +1481,7 @@ GemmDev to_dev(const GemmArgs& g) {
   p.sel_idx_out2 = g.sel_idx_out2;
   p.sel_off_out = g.sel_off_out;
   p.sel_count_out = g.sel_count_out;
+  p.ahead = 0;
   p.split_tiles = g.split_tiles;
   p.split_count = g.split_count;
   return p;
@@ -1515,10 +1521,13 @@ hipError_t launch_rows_wide(const GemmArgs& g, hipStream_t s) {
   int blocks = small > groups ? small : groups;
   if (blocks == 0) return hipSuccess;
   if (blocks > kWideGrid) blocks = kWideGrid;
+  blocks = grid_for(blocks);
+  GemmDev p = to_dev(g);
+  p.ahead = ahead_loads(g.n, blocks);
   if (g.sel_mask)
-    hipLaunchKernelGGL(gemm_bf16_rows_wide_kernel<true>, dim3(grid_for(blocks)), dim3(512), 0, s, to_dev(g));
+    hipLaunchKernelGGL(gemm_bf16_rows_wide_kernel<true>, dim3(blocks), dim3(512), 0, s, p);
   else
-    hipLaunchKernelGGL(gemm_bf16_rows_wide_kernel<false>, dim3(grid_for(blocks)), dim3(512), 0, s, to_dev(g));
+    hipLaunchKernelGGL(gemm_bf16_rows_wide_kernel<false>, dim3(blocks), dim3(512), 0, s, p);
   return hipGetLastError();
 }
 

@@ -118,6 +118,13 @@ constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace)
   return best;
 }
 
+// Row list made in the kernel: loads per wave that bring the first 256 k of an XCD's share of n weight rows into its L2, two
+// rows by each of eight waves of a workgroup.  At most 8: 2 MB of the L2's 4 with a workgroup on every CU.
+constexpr int ahead_loads(int n, int workgroups) {
+  const int rows = workgroups / 8 * 16, loads = ((n + 7) / 8 + rows - 1) / rows;
+  return loads < 8 ? loads : 8;
+}
+
 // Scored columns: whether the score is taken in the launch that projects them, rather than in one of its
 // own.  With a long k and one round of 64 x 64 tiles or a little less, the tiles of the plain projection
 // pull less per CU than whole queries do (projection, score and selection of a step that refreshes

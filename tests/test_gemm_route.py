@@ -137,3 +137,28 @@ int main() {
 def test_which_projections_are_cut_over_two_workgroups(tmp_path):
     r = _run(tmp_path, SPLIT)
     assert r.returncode == 0, r.stdout
+
+
+AHEAD = r"""
+#include <cstdio>
+#include "gemm_route.h"
+using namespace dare;
+int main() {
+  int bad = 0;
+  for (int n = 64; n <= 49152; n += 64)
+    for (int wg = 8; wg <= 256; wg += 8) {
+      const long per_xcd = (n + 7) / 8, once = wg / 8 * 16, loads = ahead_loads(n, wg);
+      if (loads < 1 || loads > 8 || loads * once * 512 > 2 << 20) ++bad;      // bytes in the L2
+      if (loads < 8 && loads * once < per_xcd) ++bad;                          // the whole share
+      if (loads > 1 && (loads - 1) * once >= per_xcd) ++bad;                   // and no load that only repeats rows
+    }
+  std::printf("%d\n", bad);
+  return bad != 0;
+}
+"""
+
+
+def test_weights_read_ahead_cover_every_width(tmp_path):
+    """Not only the two widths of one hidden size: the share of an XCD whole, up to half of its L2."""
+    r = _run(tmp_path, AHEAD)
+    assert r.returncode == 0, r.stdout
