@@ -6,6 +6,8 @@ taken without a workspace, nor depend on how large a context was made."""
 import os
 import subprocess
 
+import test_gpu_kernels as kernels
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SWEEP = r"""
@@ -162,3 +164,40 @@ def test_weights_read_ahead_cover_every_width(tmp_path):
     """Not only the two widths of one hidden size: the share of an XCD whole, up to half of its L2."""
     r = _run(tmp_path, AHEAD)
     assert r.returncode == 0, r.stdout
+
+
+SHAPES = r"""
+#include <cstdio>
+#include "gemm_route.h"
+using namespace dare;
+int main() {
+  const char* name[] = {"ranges 64 x 64", "ranges 128 x 128", "64 x 64", "64 x 96", "64 x 128", "128 x 48", "128 x 64", "128 x 96",
+                        "128 x 128", "128 x 192", "256 x 128", "256 x 192", "256 x 256", "256 x 256 cut", "split"};
+  static_assert((int)GemmRoute::kPp128Split == 14, "a shape without a name");
+  int listed, m, n;
+  while (std::scanf("%d %d %d", &listed, &m, &n) == 3) std::printf("%s\n", name[(int)best_tile(m, n, listed)]);
+}
+"""
+
+
+def test_gpu_tests_reach_the_shapes_that_they_name(tmp_path):
+    """The sizes of tests/test_gpu_kernels.py, asked of the rule on the CPU: each gets the tile shape that its
+    text names, and between them they take every shape that all rows and that listed rows can get."""
+    src, exe = tmp_path / "shapes.cpp", tmp_path / "shapes"
+    src.write_text(SHAPES)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True)
+    want = dict(kernels.EVERY_TILE)
+    for m, n, _, _, text in kernels.LARGE_TILES:
+        want[False, m, n] = text.split(",")[0]
+    for n, count, text in kernels.LONG_K_TILES:
+        if text.startswith("stream"):
+            assert count <= 32 and n < 8192
+        else:
+            want[True, count, n] = text.split(",")[0]
+    ask = "".join("%d %d %d\n" % size for size in want)
+    got = subprocess.run([str(exe)], input=ask, capture_output=True, text=True, check=True).stdout.splitlines()
+    assert dict(zip(want, got)) == want
+    large = {"128 x 96", "128 x 128", "128 x 192", "256 x 128", "256 x 192", "256 x 256"}
+    assert {want[s] for s in want if not s[0]} == {"64 x 64", "64 x 96", "64 x 128"} | large
+    assert {want[s] for s in want if s[0]} == {"64 x 64", "128 x 48", "128 x 64", "256 x 256 cut"} | large

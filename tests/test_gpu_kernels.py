@@ -56,7 +56,8 @@ def test_gemm_all_rows(B, dtype, m, n, k, seg):
     assert rel_err(host(c32), want[:, :c32_cols]) <= 2e-6     # fp32 accumulators, unrounded
 
 
-@pytest.mark.parametrize("m,n,k,seg,tile", [
+# (the text begins with the tile shape: tests/test_gemm_route.py checks it against the rule)
+LARGE_TILES = [
     (1000, 12288, 64, 4096, "256 x 192, one k-step, ragged rows"),
     (961, 12096, 192, 12096, "256 x 192, an odd number of k-steps, one row in the last tile's last 64"),
     (1024, 12480, 128, 4160, "256 x 256, ragged columns"),
@@ -64,10 +65,13 @@ def test_gemm_all_rows(B, dtype, m, n, k, seg):
     (2100, 2112, 64, 2112, "256 x 128, one k-step, ragged both ways"),
     (2305, 2048, 320, 2048, "256 x 128, five k-steps, one row in the last tile"),
     (33, 24640, 64, 24640, "64 x 128, one k-step, ragged both ways"),
-    (64, 24576, 448, 8192, "64 x 128, seven k-steps, full tiles"),
-    (65, 8256, 64, 8256, "128 x 128, one row tile, one k-step, ragged both ways"),
-    (128, 8192, 320, 4096, "128 x 128, one row tile, five k-steps"),
-])
+    (64, 24576, 448, 8192, "64 x 96, one row tile, seven k-steps, full rows"),
+    (65, 8256, 64, 8256, "64 x 96, one k-step, one row in the last tile"),
+    (128, 8192, 320, 4096, "64 x 64, two row tiles, five k-steps"),
+]
+
+
+@pytest.mark.parametrize("m,n,k,seg,tile", LARGE_TILES)
 def test_gemm_all_rows_large_tiles(B, m, n, k, seg, tile):
     r = _rng(m + n + k)
     a = store(r.standard_normal((m, k), dtype=np.float32), "bf16")
@@ -149,9 +153,8 @@ def test_gemm_selected_rows_device_count(B, dtype, count):
                                          (1024, 700), (1024, 1024), (3072, 2900), (4096, 2561), (4096, 3266),
                                          (4096, 3500)])
 def test_gemm_selected_rows_wide_output(B, n_tok, count):
-    """Wide outputs (n >= 8192) take the 8-wave kernel, whose tile shape follows the
-    device-side row count: one 64 x 64 tile per workgroup, two, 128 x 128, 256 x 192,
-    256 x 256 in rounds over 256 workgroups.  2561, 2900 and 3266 rows leave a last round that
+    """12288 columns, the tile shape follows the device-side row count: 64 x 64, 128 x 48, 128 x 96,
+    256 x 192, 256 x 256 in rounds over 256 workgroups.  2561, 2900 and 3266 rows leave a last round that
     is at most half full and is cut into 128 x 128 tiles (64, 256 and 448 of them, some
     without rows); 3500 rows walk three rounds of whole tiles."""
     r = _rng(count + 77)
@@ -189,30 +192,35 @@ def _long_k_operands(n):
     return _LONG_K[n]
 
 
-@pytest.mark.parametrize("n,count,shape", [
-    (1024, 1100, "64 x 64, two tiles per workgroup"),
-    (4096, 16, "register-fed stream, one row block, full"),
-    (4096, 17, "register-fed stream, two row blocks, one row in the second"),
-    (4096, 24, "register-fed stream, two row blocks"),
-    (4096, 32, "register-fed stream, two full row blocks"),
-    (4096, 33, "64 x 64 on the paired ring, one row tile"),
-    (4096, 64, "64 x 64 on the paired ring, one full row tile"),
-    (4096, 65, "64 x 64 on the paired ring, one row in the second row tile"),
-    (4096, 205, "64 x 64 on the paired ring, four row tiles"),
-    (4096, 256, "64 x 64 on the paired ring, 256 tiles"),
+LONG_K_TILES = [
+    (1024, 1100, "128 x 48, ragged both ways"),
+    (4096, 16, "stream, one row block, full"),
+    (4096, 17, "stream, two row blocks, one row in the second"),
+    (4096, 24, "stream, two row blocks"),
+    (4096, 32, "stream, two full row blocks"),
+    (4096, 33, "64 x 64, one row tile"),
+    (4096, 64, "64 x 64, one full row tile"),
+    (4096, 65, "64 x 64, one row in the second row tile"),
+    (4096, 205, "64 x 64, four row tiles"),
+    (4096, 256, "64 x 64, 256 tiles"),
     (4096, 257, "128 x 64, one row in the third row tile"),
     (4096, 400, "128 x 64"),
-    (12288, 64, "64 x 64, one tile per workgroup, full row tile"),
+    (12288, 64, "64 x 64, full row tile"),
     (12288, 65, "128 x 48, one row beyond 64"),
     (12288, 128, "128 x 48, full row tile"),
     (12288, 129, "128 x 96, one row in the second row tile"),
-    (12288, 24, "64 x 64, one tile per workgroup"),
+    (12288, 24, "64 x 64"),
     (12288, 100, "128 x 48"),
     (12288, 205, "128 x 96"),
-    (12288, 400, "128 x 192"),
-    (12288, 600, "128 x 128"),
+    (12288, 257, "128 x 192, one row in the third row tile"),
+    (12288, 384, "128 x 192, full row tiles"),
+    (12288, 400, "256 x 128"),
+    (12288, 600, "256 x 192"),
     (12288, 900, "256 x 192"),
-])
+]
+
+
+@pytest.mark.parametrize("n,count,shape", LONG_K_TILES)
 def test_gemm_selected_rows_long_k(B, n, count, shape):
     """The device-side tile choice at k = 4096 (64 k-steps: the operand ring of every shape
     runs in its steady state, not only its prologue), rows gathered through a list, output
@@ -236,21 +244,36 @@ def test_gemm_selected_rows_long_k(B, n, count, shape):
     assert_close(got[rows], want, "bf16")
 
 
+# every shape of best_tile: ragged last row tile, n that is no multiple of the tile's columns, odd k-steps
+EVERY_TILE = {
+    (False, 402, 512): "64 x 64", (False, 1000, 1536): "64 x 96", (False, 1001, 2048): "64 x 128",
+    (False, 2331, 1024): "128 x 96", (False, 1001, 4096): "128 x 128", (False, 300, 12288): "128 x 192",
+    (False, 1025, 6080): "256 x 128", (False, 1300, 6144): "256 x 192", (False, 1000, 9216): "256 x 192",
+    (False, 2331, 6144): "256 x 256",
+    (True, 33, 512): "64 x 64", (True, 400, 3072): "128 x 48", (True, 300, 4096): "128 x 64", (True, 601, 4096): "128 x 96",
+    (True, 777, 4096): "128 x 128", (True, 300, 12288): "128 x 192", (True, 1300, 4096): "256 x 128",
+    (True, 1000, 9216): "256 x 192", (True, 2900, 4096): "256 x 256",
+    (True, 3101, 12288): "256 x 256 cut",   # the last round in 128 x 128
+}
+
+
 @pytest.mark.parametrize("listed,m,n,k", [
-    # each shape of best_tile, with a ragged last row tile; n that is no multiple of the tile's columns; odd k-steps
     (False, 402, 512, 192), (False, 1000, 1536, 128), (False, 1001, 2048, 64), (False, 2331, 1024, 192),
     (False, 1001, 4096, 64), (False, 1025, 6080, 128), (False, 1300, 6144, 64), (False, 1000, 9216, 128),
     (False, 2331, 6144, 64),
     (True, 33, 512, 192), (True, 400, 3072, 128), (True, 300, 4096, 64), (True, 601, 4096, 192),
     (True, 777, 4096, 128), (True, 1300, 4096, 64), (True, 1000, 9216, 128), (True, 2900, 4096, 64),
-    (True, 3101, 12288, 64),      # the last round cut into 128 x 128
+    (True, 3101, 12288, 64),
     # k-steps around the length of the ring, odd and even: the last of them load nothing
     *((False, m, n, k) for m, n in ((1000, 1536), (1001, 4096), (1300, 6144), (1000, 9216), (2331, 6144))
       for k in (256, 320, 384, 448)),
     *((True, m, n, k) for m, n in ((400, 3072), (601, 4096), (777, 4096), (1300, 4096), (1000, 9216), (2900, 4096))
       for k in (256, 320, 384, 448)),
+    # 128 x 192, whose ring is the shortest: one to seven k-steps
+    *((listed, 300, 12288, k) for listed in (False, True) for k in (64, 128, 192, 256, 320, 448)),
 ])
 def test_gemm_every_tile_shape(B, listed, m, n, k):
+    assert (listed, m, n) in EVERY_TILE
     r = _rng(m + n + k)
     n_tok = m + 50 if listed else m
     a = store(r.standard_normal((n_tok, k), dtype=np.float32), "bf16")

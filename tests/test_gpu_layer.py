@@ -302,11 +302,11 @@ def test_more_sequences_than_threads_in_the_fused_row_list():
     gl.layer.destroy()
 
 
-def test_refreshed_rows_beyond_one_pass_of_the_grid():
-    """2 x 1024 tokens, all of them refreshed, hidden 2048: the refreshed-row projection of the KV
-    mode (2048 rows x 4096 columns in 128 x 128 tiles = 512 tiles) takes two passes of its 256
-    workgroups and derives its row list from the mask again in front of the second."""
-    case = synth.make_case("llada8b", seed=93, batch=2, seq=1024, hidden=2048, n_heads=16, head_dim=128,
+@pytest.mark.parametrize("hidden", [2048, 3072])
+def test_refreshed_rows_beyond_one_pass_of_the_grid(hidden):
+    """2 x 1024 tokens, all of them refreshed.  Hidden 3072, Q, K and V: 384 tiles of 256 x 192, two passes of
+    the 256 workgroups over the row list that the kernel made from the mask; hidden 2048: 256 tiles at most, one."""
+    case = synth.make_case("llada8b", seed=93, batch=2, seq=1024, hidden=hidden, n_heads=hidden // 128, head_dim=128,
                            fraction=1.0)
     state = pu.oracle_fill(case)
     gl = pu.GpuLayer(case)
@@ -314,10 +314,11 @@ def test_refreshed_rows_beyond_one_pass_of_the_grid():
         info, got, want = _run(case, gl, state, mode, synth.TAU_SEPARATING)
         assert int(got["sel_count"].sum()) == 2048
     # and with a third of the rows kept: rows gathered through the list in both passes
-    case = dict(case, **synth.make_hidden_pair(94, 2, 1024, 2048, 0.66, "bf16"))     # same weights, other rows
+    case = dict(case, **synth.make_hidden_pair(94, 2, 1024, hidden, 0.66, "bf16"))     # same weights, other rows
     state = pu.oracle_fill(case)
-    info, got, want = _run(case, gl, state, orc.MODE_KV, synth.TAU_SEPARATING)
-    assert int(got["sel_count"].sum()) == 2 * 676
+    for mode in (orc.MODE_KV, orc.MODE_KVO):
+        info, got, want = _run(case, gl, state, mode, synth.TAU_SEPARATING)
+        assert int(got["sel_count"].sum()) == 2 * 676
     gl.layer.destroy()
 
 
@@ -349,11 +350,14 @@ def llada():
 # target is stated at, and row counts that put every tile shape of the device-side choice in
 # the refreshed-row projection under a whole-layer check at k = 4096:
 #   1, 24 rows  register-fed stream for Wo (one and two row blocks), 64 x 64 tiles for Q/K/V
-#   51 rows     64 x 64 tiles, one per workgroup
-#   100 rows    128 x 48 (Q/K/V)             133, 205, 256 rows   128 x 96 (Q/K/V), 128 x 64 (K/V alone)
-#   400, 512    128 x 192 (Q/K/V), 128 x 64 (Wo)
-#   600 rows    128 x 128                    1024 rows            256 x 192 (Q/K/V), 128 x 128 (Wo)
-ROWS = [1, 24, 51, 100, 133, 205, 256, 400, 512, 600, 1024]
+#   51 rows     64 x 64 tiles
+#   100 rows    128 x 48 (Q/K/V), 64 x 64 (K/V alone, Wo)
+#   133, 205, 256   128 x 96 (Q/K/V), 128 x 64 (K/V alone), 64 x 64 (Wo)
+#   300 rows    128 x 192 (Q/K/V), 128 x 64 (Wo)
+#   400, 512    256 x 128 (Q/K/V), 128 x 128 (K/V alone), 128 x 64 (Wo)
+#   600 rows    256 x 192 (Q/K/V), 256 x 128 (K/V alone), 128 x 96 (Wo)
+#   1024 rows   256 x 192 (Q/K/V), 256 x 128 (K/V alone), 128 x 128 (Wo)
+ROWS = [1, 24, 51, 100, 133, 205, 256, 300, 400, 512, 600, 1024]
 
 
 @pytest.mark.parametrize("n_rows", ROWS)

@@ -71,7 +71,7 @@ def test_prefix_small_bf16(shape, P, mode):
 @pytest.mark.parametrize("P", [400, 424])
 @pytest.mark.parametrize("mode", [orc.MODE_DENSE, orc.MODE_O])
 def test_prefix_leaves_rows_between_the_projection_routes(mode, P):
-    """600 and 624 of 1024 tokens left at hidden 2048: Q/K/V in 144 tiles of 256 x 128, which is more
+    """600 and 624 of 1024 tokens left at hidden 2048: Q/K/V would be 144 tiles of 256 x 128, which is more
     than a workspace for a k cut in two holds."""
     case = synth.make_case("llada8b", seed=83 + P, batch=1, seq=1024, hidden=2048, n_heads=16,
                            head_dim=128)
