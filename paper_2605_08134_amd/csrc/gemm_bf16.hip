@@ -135,7 +135,7 @@ constexpr int smem_bytes() {
 // silu(gate) * up from column col / 2 on.
 // What a launch asks for is settled outside the loops and what a column needs outside that over the rows: decided
 // at every store, with the kernel's arguments read again and a division each for segment and
-// position, the epilogue was as long as a third of the k loop (1024 x 4096 x 4096: 39 -> 34 us).
+// position, the epilogue was as long as a third of the k loop (its gain is part of gemm_tile16's figures).
 template <int W, int TM, int TN, class Value>
 __device__ __forceinline__ void store_tile(const GemmDev& p, float* c32, const int (&tok)[TM], const bool (&live)[TM],
                                            const int (&col)[TN], Value value) {
@@ -407,12 +407,14 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& p, const int m, unsigne
 // lines come from beyond the L2 (1024 x 4096 x 4096: loads alone 26 us of 33, MFMAs alone 20).  So the whole ring is
 // kept in flight (the stage of k-step kt is filled again for kt + STAGES as soon as the barrier says that its
 // fragments are in registers) and the loads of a k-step are issued one by one between its MFMAs: in a
-// row, a wave that waits for a place in the queue keeps its MFMAs waiting as well.  us, with STAGES - 1
-// stages in flight, loads in a row (3 sets of operands in turn): 1024 x 4096 x 4096 in 128 x 128 tiles
-// 43.5 (32-wide MFMAs) -> 33.1, 205 x 12288 39.2 -> 34.5, 512 x 12288 61.7 -> 54.2, 512 x 8192 45.4 -> 33.5,
-// 512 x 4096 25.1 -> 21.3, 205 x 4096 17.2 -> 14.0, 100 x 12288 30.6 -> 28.0.  The k of a k-step halved
-// between two groups of four waves with twice the wave tile (half the fragment reads) is no faster: 34.4,
-// 35.2, 54.0, 31.5, 21.0, 13.7, 28.4.
+// row, a wave that waits for a place in the queue keeps its MFMAs waiting as well.  us, before (STAGES - 1
+// stages in flight, loads in a row, 32-wide MFMAs for 128 x 128, the epilogue before store_tile) and now, weights in the
+// last-level cache: all rows, 1024 x 4096 x 4096 41.3 and 36.3, 512 x 8192 41.5 and 35.3; listed rows, 205 x 12288 32.2 and
+// 31.4 (weights from HBM 39.4 and 37.6), 205 x 4096 16.7 and 16.4, 512 x 8192 43.3 and 37.1, but 100 x 12288 (128 x 48) 23.1
+// and 23.8.  (The order of a sum over k is that of the instruction: 128 x 128 tiles sum 32 products at a time where they
+// summed 16, results differ from then by single bf16 roundings.)  The k of a k-step halved
+// between two groups of four waves with twice the wave tile (half the fragment reads) is no faster.
+// Some waves repeat the last group of rows (128 x 96: 32 loads for 28 groups).
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
 __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsigned char* smem, const int tid,
                                             const int vblock, lds_idx_t lidx = nullptr,

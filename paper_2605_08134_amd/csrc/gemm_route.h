@@ -47,10 +47,11 @@ constexpr bool gemm_may_split(long m, long n, long k) {
 // us, 256 x 128 52).
 // Fitted to 120 products of 40 to 16384 rows by 512 to 24576 columns, k from 512 to 12288, in every shape: the
 // shape chosen is within 3 % of the fastest one but for 1300 x 4096 x 12288 (10 %: 192 x 128, which nothing else
-// wants) and 256 x 24576 x 4096 (10 %).  A rule by thresholds on tile counts, made for 1024 tokens of 4096, was off
-// by up to 2 (us, before and now: 402 x 2048 x 2048 17.2 and 9.2, 256 x 4096 x 4096 29.0 and 15.4, 1000 x 9216 x
-// 3072 80.6 and 50.8, 2331 x 4096 x 4096 91 and 67; refreshed rows, 1300 x 4096 x 4096 72 and 51, 2870 x 4096 x 4096 116
-// and 92, 4096 x 4096 x 4096 167 and 109, 600 x 12288 x 4096 89 and 75).
+// wants) and 256 x 24576 x 4096 (10 %).  A rule by
+// thresholds on tile counts, made for 1024 tokens of 4096, was off by up to 2 (us, before and now, the loop of gemm_tile16
+// included: 402 x 2048 x 2048 20.6 and 9.6, 256 x 4096 x 4096 34.1 and 16.6, 1000 x 9216 x 3072 75.9 and 50.2, 2331 x 4096 x
+// 4096 97 and 69; refreshed rows, 1300 x 4096 x 4096 75 and 52, 2870 x 4096 x 4096 124 and 82, 4096 x 4096 x 4096 166 and 97,
+// 600 x 12288 x 4096 80 and 65).
 // (Whole numbers: the device evaluates it on its scalar unit.)
 constexpr int tile_cost(int m, int n, int bm, int bn, int full, int again) {
   const int tiles = tiles_of(m, n, bm, bn), rounds = (tiles + 255) >> 8;
@@ -126,11 +127,14 @@ constexpr int ahead_loads(int n, int workgroups) {
 }
 
 // Scored columns: whether the score is taken in the launch that projects them, rather than in one of its
-// own.  With a long k and one round of 64 x 64 tiles or a little less, the tiles of the plain projection
-// pull less per CU than whole queries do (projection, score and selection of a step that refreshes
-// nothing, k = 4096, one launch against two: 1024 rows 18.0 and 18.3 us, 2048 21.0 and 20.9, 3072 27.0 and 25.9, 4096 27.7 and
-// 25.5, 6144 35.2 and 32.9, 8192, where the plain projection takes larger tiles, 35.9 and 50.9; k = 2048:
-// 4096 rows 22.0 and 22.9).
+// own.  Steps of four sequences that refresh a token each, one launch and two (us): k = 4096, 1024 rows 52.5 and
+// 54.7, 2048 60.6 and 62.2, 2560 68.5 and 71.4, 3072 74.9 and 75.8, 4096 78.3 and 80.0, 6144 95.5 and 96.1, 8192 101.5 and
+// 101.4, 12288 120.1 and 124.0, 16384 137.8 and 143.0; k = 3072, 2048 44.6 and 45.6, 2560 55.5 and 55.3, 3072 60.1 and 59.7, 4096 68.8
+// and 66.4, 6144 82.4 and 83.2, 8192 82.6 and 84.9, 12288 100.6 and 105.8; k = 2048, 1024 40.6 and 42.4, 4096 54.9 and
+// 54.9, 16384 91.8 and 96.7.  Up to 2048 rows and from 12288 on, where the plain projection takes larger tiles, one launch is
+// the faster one; between them neither is by more than the runs differ (1 to 3 %).  The lines at k = 3072, 2560 and 8064
+// rows enclose where two launches were 1 to 2 us faster with the tiles that the score's launch has now (score_proj_kernel) and
+// those that the plain projection had then.
 constexpr bool score_in_projection(int rows, int k) { return k < 3072 || rows <= 2560 || rows > 8064; }
 
 // LDS of the scored-column projection once its k loop is over: bm queries, score_query_stride floats
