@@ -201,3 +201,41 @@ def test_gpu_tests_reach_the_shapes_that_they_name(tmp_path):
     large = {"128 x 96", "128 x 128", "128 x 192", "256 x 128", "256 x 192", "256 x 256"}
     assert {want[s] for s in want if not s[0]} == {"64 x 64", "64 x 96", "64 x 128"} | large
     assert {want[s] for s in want if s[0]} == {"64 x 64", "128 x 48", "128 x 64", "256 x 256 cut"} | large
+
+
+LISTED = r"""
+#include <cstdio>
+#include "gemm_route.h"
+using namespace dare;
+// the cost again in 64 bits
+static long cost(long m, long n, long bm, long bn, long full, long again) {
+  const long tiles = (m + bm - 1) / bm * ((n + bn - 1) / bn), rounds = (tiles + 255) / 256;
+  return (rounds > 1 ? again : full) * (rounds * 256 + tiles);
+}
+int main() {
+  long bad = 0, cut = 0;
+  for (int n = 64; n <= 1 << 21; n = n < 32768 ? n + 64 : n * 2 + 64)
+    for (int m = 1; m <= 1 << 20; m = m < 400 ? m + 1 : (m < 20000 ? m + 97 : m * 2 + 1)) {
+      const GemmRoute r = best_tile(m, n, true);
+      const long t4 = (m + 255l) / 256 * ((n + 255l) / 256);
+      if (r == GemmRoute::kTile64 || r == GemmRoute::kTile128 || r == GemmRoute::k64x96 || r == GemmRoute::k64x128 ||
+          r == GemmRoute::kPp128Split) ++bad;                                            // no such shape in the kernel
+      if (t4 > 8192) continue;
+      if (cost(m, n, 64, 64, 153, 229) != tile_cost(m, n, 64, 64, 153, 229) ||
+          cost(m, n, 128, 48, 210, 273) != tile_cost(m, n, 128, 48, 210, 273) ||
+          cost(m, n, 256, 256, 1460, 1460) != tile_cost(m, n, 256, 256, 1460, 1460)) ++bad;   // 32 bits hold it
+      if (r != GemmRoute::kPp256Cut) continue;
+      ++cut;
+      if (n % 256 || t4 <= 256 || t4 % 256 == 0 || t4 % 256 > 128) ++bad;                // whole rounds in front of the cut one
+    }
+  std::printf("cut %ld bad %ld\n", cut, bad);
+  return bad != 0;
+}
+"""
+
+
+def test_listed_rows_over_the_whole_range(tmp_path):
+    """The rule as the kernel evaluates it, up to a million rows and two million columns."""
+    r = _run(tmp_path, LISTED)
+    assert r.returncode == 0, r.stdout
+    assert int(r.stdout.split()[1]) > 1000
