@@ -23,8 +23,12 @@
 // Few query rows (the refreshed rows of a step) use narrow query blocks with KW > 1,
 // which turns the available waves towards the key axis and fills the chip, and with very few
 // of them the keys of a block are cut over workgroups as well; many rows use wide blocks (128
-// rows with two key-waves, or 256 rows with none when there are enough of them), which re-read K
-// and V less often.  attn_route.h holds the rule.
+// rows with two key-waves, or without any when there are enough of them; 256 rows with heads of 64 channels), which
+// re-read K and V less often.  attn_route.h holds the rule.
+// Blocks of 128 rows of heads of 128 channels run attn_wide, which takes 16 x 16 x 32 MFMAs and lets softmax and products of
+// neighbouring key subtiles overlap; everything else runs attn_block, described here.
+#include <type_traits>
+
 #include "dare_common.h"
 
 namespace dare {
@@ -398,6 +402,385 @@ __device__ __forceinline__ void attn_block(const AttnDev& p, int b, int h, int q
   }
 }
 
+// XOR applied to the 16-byte chunk index of a K row / V row of attn_wide.  K fragment: 16 rows at one chunk; V
+// fragment by transpose read: 8 rows at 32 bytes are read at a time.  Linear over the bits of the key.
+template <int DH>
+__device__ __forceinline__ constexpr int wide_k_swizzle(int key) {
+  return DH == 128 ? (key & 15) : ((key >> 1) & 7);
+}
+template <int DH>
+__device__ __forceinline__ constexpr int wide_v_swizzle(int key) {
+  return DH == 128 ? ((key & 3) << 2 | (key >> 2 & 1) << 1) : (key >> 1 & 3) << 1;
+}
+template <int DH, int KW>
+constexpr int wide_smem_bytes() {
+  return 2 * KW * 2 * 64 * DH * 2;
+}
+
+// A block of 32 QW query rows of heads of 128 channels, QW x KW waves: wave (qw, kw) owns 32 rows and every KW-th tile
+// of 64 keys.  Arguments as for attn_block.
+// What bounds it is the issue of a SIMD and power.  In step, the two waves of a SIMD multiplied, then both took their
+// exponentials, and the matrix cores were idle for half of the time (0.52 M of 1.2 M cycles at 8 x 2048 tokens of 32 heads).
+//   * Subtiles of 32 keys: while the logits of one are multiplied, the softmax of the one before and the value product
+//     of the one before that run, an MFMA or two, an exponential, fragment reads, and so on, in one instruction stream.  Fragments
+//     are read three MFMA groups ahead; the barrier of a step lies behind its last fragment, the first ones of the next
+//     step follow it, so a step ends without an empty pipe.
+//   * No maximum of every tile: the reference exponent of a row moves when a lane's sum of probabilities says so.
+//   * v_mfma_f32_16x16x32_bf16, as in the large projections: the clock is 1.8 GHz of 2.4 here, and the same loop with 32 x 32 x 16 takes
+//     2 to 10 % longer (and 30 registers more).
+//   * QW = 4, KW = 1: two workgroups of four waves per CU, out of step with each other, one multiplies while the other
+//     waits at its barrier or starts and ends.  One workgroup of eight waves (256 rows) pulls half as much from the L2 and is
+//     slower all the same wherever sequences are short (3 x 777 tokens 56.9 us, two workgroups 46.5; 16 x 256 34.4 and 31.6;
+//     8 x 2048 510 and 511; 1 x 4096 233 and 240).
+// us, before (32 x 32 x 16, logits, softmax and values one after the other, 256 rows) and now, 32 heads: 8 x 2048 551 and 511 (1.08
+// PFLOP/s), 1 x 4096 254 and 240, 3 x 777 58.6 and 46.5, 16 x 256 35.2 and 31.6; KW = 2, 1 x 1024 22.8 and 21.8.  Heads of 64 channels
+// keep attn_block, whose 120 registers let four waves share a SIMD: they have half of the MFMAs per exponential (8 x 2048 of
+// 32 such heads 283 us, with this loop 282 to 325; 1 x 4096 142 and 150).
+// Not faster: loads between the MFMAs instead of in a row behind the barrier (2 to 6 % slower), four stages (5 % slower),
+// s_setprio around the MFMAs.
+template <int DH, int QW, int KW>
+__device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt, int cnt, int off,
+                                          unsigned char* smem, const int tid) {
+  constexpr int TK = 64, NW = QW * KW;
+  constexpr int ROWB = DH * 2;                     // bytes per K or V row of one head
+  constexpr int CPR = DH / 8;                      // 16-byte chunks per row
+  constexpr int RPL = 64 / CPR;                    // rows covered by one wave load
+  constexpr int TILE_BYTES = TK * ROWB;
+  constexpr int KSTAGE = KW * TILE_BYTES;          // K (or V) of a stage
+  constexpr int KL = KSTAGE / 1024 / NW;           // wave loads of K (or V) per step
+  constexpr int CB = DH / 16;                      // 16-channel blocks of the output
+  constexpr int NP = CB;                           // fragments of K, and of V, that a subtile takes
+  constexpr int AHEAD = 3, RING = AHEAD + 1;       // fragments read ahead of their MFMAs
+  constexpr float kLimit = 4096.f;                 // sum of a lane's probabilities from which on the reference moves
+  static_assert(KSTAGE / 1024 % NW == 0 && NP % RING == 0, "loads and fragments must divide");
+  using Yes = std::true_type;
+  using No = std::false_type;
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+
+  const int T = p.seq;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (a scalar: M0 addressing)
+  const int qw = (unsigned)wave % QW, kw = (unsigned)wave / QW;
+  const int l16 = lane & 15, kq = lane >> 4;
+
+  // the query rows of this lane: 16 r + l16 of the wave's
+  const bool any_row = qt * (32 * QW) + qw * 32 < cnt;  // (the same in all lanes: a wave without rows only loads)
+  int tok[2];
+  bool valid[2];
+  bf16x8 qf[2][DH / 32];
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int j = qt * (32 * QW) + qw * 32 + r * 16 + l16;
+    valid[r] = j < cnt;
+    const int jc = valid[r] ? j : cnt - 1;
+    tok[r] = p.idx ? p.idx[off + jc] : off + jc;
+  }
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int ks = 0; ks < DH / 32; ++ks)
+      qf[r][ks] = *reinterpret_cast<const bf16x8*>(p.q + (long)tok[r] * p.d + h * DH + ks * 32 + kq * 8);
+
+  const int n_tiles = (T + TK - 1) / TK, n_steps = (n_tiles + KW - 1) / KW;
+
+  // ---- global -> LDS: two stages of K, two of V; a stage holds the tiles of the key-waves, a row of 1 KiB loads per wave ----
+  const bf16_t* kbase = p.k + (long)b * T * p.d + h * DH;
+  const bf16_t* vbase = p.v + (long)b * T * p.d + h * DH;
+  const unsigned row_bytes = (unsigned)p.d * 2;
+  const unsigned key0 = (unsigned)wave * KL * RPL + (unsigned)lane / CPR;  // key of this lane's first load at step 0
+  // (the chunk XOR of a key is that of the lane's first key and that of the distance)
+  const unsigned k_chunk = ((unsigned)lane % CPR ^ wide_k_swizzle<DH>(key0)) * 16, v_chunk = ((unsigned)lane % CPR ^ wide_v_swizzle<DH>(key0)) * 16;
+  const unsigned k_src = key0 * row_bytes + k_chunk, v_src = key0 * row_bytes + v_chunk;
+  const unsigned lds0 = (unsigned)(size_t)(lptr_t)smem;
+  auto load_tiles = [&](auto is_v, int step) __attribute__((always_inline)) {
+    constexpr bool V = decltype(is_v)::value;
+    const int k0 = step * (KW * TK);
+    const bf16_t* from = (V ? vbase : kbase) + (long)k0 * p.d;
+    const unsigned to = lds0 + (V ? 2 * KSTAGE : 0) + (step & 1) * KSTAGE + wave * KL * 1024;
+    auto load = [&](unsigned at, int i) __attribute__((always_inline)) {
+      asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(at), "s"(from), "{m0}"(to + i * 1024) : "memory");
+    };
+#define DARE_SWZ(i) ((V ? wide_v_swizzle<DH>((i) * RPL) : wide_k_swizzle<DH>((i) * RPL)) * 16)
+    if (k0 + KW * TK > T) {  // keys past the end re-read the last one
+#pragma unroll
+      for (int i = 0; i < KL; ++i) {
+        const unsigned key = key0 + i * RPL, end = T - 1 - k0;
+        load((key < end ? key : end) * row_bytes + ((V ? v_chunk : k_chunk) ^ DARE_SWZ(i)), i);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < KL; ++i) load(((V ? v_src : k_src) ^ DARE_SWZ(i)) + i * RPL * row_bytes, i);
+    }
+#undef DARE_SWZ
+  };
+  // Publishes K of step + 1 and V of step; every wave has read K of step and V of step - 1, whose stages are filled again
+  auto next_tiles = [&](int step) __attribute__((always_inline)) {
+    wait_vmcnt_and_barrier<0>();
+    if (step + 2 < n_steps) load_tiles(No{}, step + 2);
+    if (step + 1 < n_steps) load_tiles(Yes{}, step + 1);
+  };
+
+  // ---- fragments ----
+  // K fragment j: keys 16 (j & 1) + l16, channels 32 (j / 2) + 8 kq ..
+  // V fragment j, by transpose read: channel 16 j + l16, keys 4 kq .. +3 and 16 + 4 kq .. +3.  Lane i of a group of 16 gives
+  // the address of key i / 4 of the run, channels 4 (i % 4) .. of the block.
+  typedef const __attribute__((address_space(3))) bf16x8* lds_frag_t;
+  unsigned k_at[NP / 2], v_at;
+#pragma unroll
+  for (int ks = 0; ks < NP / 2; ++ks)
+    k_at[ks] = lds0 + kw * TILE_BYTES + l16 * ROWB + ((ks * 4 + kq) ^ wide_k_swizzle<DH>(l16)) * 16;
+  {
+    const int key = kq * 4 + (l16 >> 2);
+    v_at = lds0 + 2 * KSTAGE + kw * TILE_BYTES + key * ROWB + ((l16 >> 1 & 1) ^ wide_v_swizzle<DH>(key)) * 16 + (l16 & 1) * 8;
+  }
+  bf16x8 kf[RING], vf[RING];
+  auto read_k = [&](int j, int sub) __attribute__((always_inline)) {
+    // (keys 16 apart have one chunk XOR)
+    kf[j % RING] = *(lds_frag_t)(k_at[j / 2] + (sub * 32 + (j & 1) * 16) * ROWB);
+  };
+  auto read_v = [&](int j, int sub) __attribute__((always_inline)) {
+    const unsigned at = lds0 + ((v_at - lds0) ^ j * 32) + sub * 32 * ROWB;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(at));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(at + 16 * ROWB));
+    vf[j % RING] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+
+  f32x4 acc[CB][2];         // [channel block][row block]: channels 4 kq .. of the block
+  f32x4 sc[2][2][2];        // logits of two subtiles, [set][row block][16 keys]: keys 4 kq ..
+  bf16x8 pf[2][2];          // probabilities of two subtiles, [set][row block]
+  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < CB; ++c)
+#pragma unroll
+    for (int r = 0; r < 2; ++r) acc[c][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // ---- softmax of a subtile: logit n = 8 row block + key slot ----
+  const bf16x2 ones = {(bf16_t)1.0f, (bf16_t)1.0f};
+  float e0 = 0.f, e1 = 0.f;
+  auto exp_one = [&](const f32x4 (&x)[2][2], int n) __attribute__((always_inline)) {
+    const float v = __builtin_amdgcn_exp2f(fmaf(x[n >> 3][n >> 2 & 1][n & 3], p.scale_log2, -m_run[n >> 3]));
+    if (n & 1) e1 = v; else e0 = v;
+  };
+  // rounded for the value product; the row sum is taken over the probabilities as rounded (v_dot2: += both), so
+  // numerator and denominator carry the same rounding
+  auto round_pair = [&](bf16x8 (&pr)[2], int n, float (&sum)[2]) __attribute__((always_inline)) {
+    const f32x2 v = {e0, e1};
+    const bf16x2 pb = __builtin_convertvector(v, bf16x2);
+    sum[n >> 3] = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, sum[n >> 3], false);
+    pr[n >> 3][n & 7] = pb[0];
+    pr[n >> 3][(n & 7) + 1] = pb[1];
+  };
+  auto mask_keys = [&](f32x4 (&x)[2][2], int kv0) __attribute__((always_inline)) {  // keys past the end
+#pragma unroll
+    for (int n = 0; n < 8; ++n)
+      if (kv0 + (n >> 2) * 16 + kq * 4 + (n & 3) >= T) x[0][n >> 2][n & 3] = x[1][n >> 2][n & 3] = -INFINITY;
+  };
+  // The reference exponents of the rows move to the maxima of this subtile, which is scored again.  Any reference
+  // gives the same result (O and the row sum share it), so they only move when probabilities grow large, which a
+  // lane's sum of them tells without the maximum of every subtile.
+  auto move_reference = [&](const f32x4 (&x)[2][2], bf16x8 (&pr)[2], float (&sum)[2], auto first_c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      float top = x[r][0][0];
+#pragma unroll
+      for (int n = 1; n < 8; ++n) top = fmaxf(top, x[r][n >> 2][n & 3]);
+      const auto rows = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, top), __builtin_bit_cast(unsigned, top), false, false);
+      top = fmaxf(__builtin_bit_cast(float, rows[0]), __builtin_bit_cast(float, rows[1]));
+      const auto half = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, top), __builtin_bit_cast(unsigned, top), false, false);
+      top = fmaxf(__builtin_bit_cast(float, half[0]), __builtin_bit_cast(float, half[1])) * p.scale_log2;  // scale > 0
+      const float m_new = fmaxf(fmaxf(m_run[r], top), -1e30f);  // (finite: logits of -infinity have probability 0)
+      if constexpr (!decltype(first_c)::value) {
+        const float alpha = __builtin_amdgcn_exp2f(m_run[r] - m_new);
+        l_run[r] *= alpha;
+#pragma unroll
+        for (int c = 0; c < CB; ++c) acc[c][r] *= alpha;
+      }
+      m_run[r] = m_new;
+      sum[r] = 0.f;
+    }
+#pragma unroll
+    for (int n = 0; n < 16; n += 2) {
+      exp_one(x, n);
+      exp_one(x, n + 1);
+      round_pair(pr, n, sum);
+    }
+  };
+
+  // One subtile period.  QK: logits of subtile u (into sc[S ^ 1]); SM: softmax of u - 1 (sc[S], into pf[S]); PV: values of
+  // u - 2 (pf[S ^ 1]); three that do not depend on each other, one after the other in small pieces, so that MFMAs,
+  // exponentials and LDS reads run side by side.  MORE: a period follows.
+  auto period = [&](auto s_c, auto qk_c, auto sm_c, auto pv_c, auto more_c, int step) __attribute__((always_inline)) {
+    constexpr int S = decltype(s_c)::value, SUB = S ^ 1;  // SUB: subtile of its tile, of K and V alike
+    constexpr bool QK = decltype(qk_c)::value, SM = decltype(sm_c)::value, PV = decltype(pv_c)::value;
+    constexpr bool MORE = decltype(more_c)::value, EDGE = SUB == 1;  // EDGE: the step's tiles end here
+    constexpr int LPP = 16 / NP;        // logits per fragment
+    constexpr int SPLIT = NP - AHEAD;   // fragment behind whose MFMAs the step's last ones are in registers
+    float sum[2] = {0.f, 0.f};
+    auto softmax = [&](int first, int last) __attribute__((always_inline)) {
+      if constexpr (SM) {
+#pragma unroll
+        for (int n = first; n < last; ++n) {
+          if (n % 2 == 0 && n > 0) round_pair(pf[S], n - 2, sum);
+          exp_one(sc[S], n);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      __builtin_amdgcn_sched_barrier(0);
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      f32x4 (&x)[2][2] = sc[S ^ 1];
+      if constexpr (QK) x[0][j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[j % RING], qf[0][j / 2], j < 2 ? zero : x[0][j & 1], 0, 0, 0);
+      softmax(j * LPP, j * LPP + LPP / 2);
+      if constexpr (QK) x[1][j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[j % RING], qf[1][j / 2], j < 2 ? zero : x[1][j & 1], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (PV) acc[j][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[j % RING], pf[S ^ 1][0], acc[j][0], 0, 0, 0);
+      softmax(j * LPP + LPP / 2, (j + 1) * LPP);
+      if constexpr (PV) acc[j][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[j % RING], pf[S ^ 1][1], acc[j][1], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (j + AHEAD < NP) {
+        if constexpr (QK) read_k(j + AHEAD, SUB);
+        if constexpr (PV) read_v(j + AHEAD, SUB);
+      } else if constexpr (MORE && !EDGE) {
+        if constexpr (QK) read_k(j + AHEAD - NP, 1);
+        if constexpr (PV) read_v(j + AHEAD - NP, 1);
+      }
+      if constexpr (EDGE && MORE) {
+        if (j == SPLIT) {  // all of the step's fragments are in registers: its stages may be filled again
+          if constexpr (SM) asm volatile("" : "+v"(sum[0]), "+v"(sum[1]), "+v"(e0), "+v"(e1));  // (what is done so far stays in front of the branches)
+          next_tiles(step);
+#pragma unroll
+          for (int i = 0; i < NP / 2; ++i) k_at[i] = lds0 + ((k_at[i] - lds0) ^ KSTAGE);
+          if constexpr (PV) v_at = lds0 + ((v_at - lds0) ^ KSTAGE);
+        }
+        if (j > SPLIT) {
+          const int from = AHEAD * (j - SPLIT - 1) / (AHEAD - 1), to = AHEAD * (j - SPLIT) / (AHEAD - 1);
+#pragma unroll
+          for (int i = from; i < to; ++i) {
+            read_k(i, 0);
+            read_v(i, 0);
+          }
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (SM) {
+      round_pair(pf[S], 14, sum);
+      if (__any(fmaxf(sum[0], sum[1]) > kLimit)) move_reference(sc[S], pf[S], sum, No{});
+      l_run[0] += sum[0];
+      l_run[1] += sum[1];
+    }
+  };
+
+  // the wave's tiles; all waves load, and join the barrier of every step
+  int mine = (n_tiles - kw + KW - 1) / KW;
+  mine = !any_row || mine < 0 ? 0 : (mine < n_steps ? mine : n_steps);
+  auto key_of = [&](int step) __attribute__((always_inline)) { return (step * KW + kw) * TK; };
+  load_tiles(No{}, 0);
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int ks = 0; ks < DH / 32; ++ks) asm volatile("" : "+v"(qf[r][ks]));  // (waits for the queries and these keys)
+  wait_vmcnt_and_barrier<0>();
+  load_tiles(Yes{}, 0);
+  if (n_steps > 1) load_tiles(No{}, 1);
+  if (mine > 0) {
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) read_k(j, 0);
+    period(S1{}, Yes{}, No{}, No{}, Yes{}, 0);
+    if (key_of(0) + 32 > T) mask_keys(sc[0], key_of(0));
+    move_reference(sc[0], pf[0], l_run, Yes{});
+    period(S0{}, Yes{}, No{}, No{}, Yes{}, 0);
+    for (int step = 1; step < mine; ++step) {
+      period(S1{}, Yes{}, Yes{}, Yes{}, Yes{}, step);
+      if (key_of(step) + 32 > T) mask_keys(sc[0], key_of(step));
+      period(S0{}, Yes{}, Yes{}, Yes{}, Yes{}, step);
+    }
+    if (key_of(mine - 1) + 64 > T) mask_keys(sc[1], key_of(mine - 1) + 32);
+    period(S1{}, No{}, Yes{}, Yes{}, Yes{}, mine);
+    period(S0{}, No{}, No{}, Yes{}, No{}, mine);
+  }
+  for (int step = mine; step < n_steps; ++step) next_tiles(step);
+
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    l_run[r] += __shfl_xor(l_run[r], 16, 64);
+    l_run[r] += __shfl_xor(l_run[r], 32, 64);
+  }
+
+  // ---- merge the key-waves: every one merges, and stores, its share of the channel blocks ----
+  constexpr int OWN = CB / KW;  // channel blocks of a wave
+  f32x4 own[OWN][2];            // blocks kw OWN ..
+  if constexpr (KW > 1) {
+    constexpr int ML = QW * KW * (KW - 1) * OWN * 2 * 64 * 16;  // bytes of the shares; behind them (max, sum) of every wave
+    static_assert(ML + QW * KW * 64 * 16 <= wide_smem_bytes<DH, KW>(), "the merge area must fit into the stage memory");
+    wait_all_and_barrier();  // all loads landed, all tiles consumed: stage memory is free
+    f32x4* xch = reinterpret_cast<f32x4*>(smem) + lane;
+    f32x4* ml = reinterpret_cast<f32x4*>(smem + ML) + qw * KW * 64 + lane;
+    ml[kw * 64] = f32x4{m_run[0], l_run[0], m_run[1], l_run[1]};
+    // slot (query-wave, owner, source): a wave leaves the shares of the others
+#pragma unroll
+    for (int o = 0; o < KW; ++o)
+      if (o == kw) {
+#pragma unroll
+        for (int i = 0; i < OWN; ++i)
+#pragma unroll
+          for (int r = 0; r < 2; ++r) own[i][r] = acc[o * OWN + i][r];
+      } else {
+        f32x4* slot = xch + ((qw * KW + o) * (KW - 1) + (kw < o ? kw : kw - 1)) * OWN * 2 * 64;
+#pragma unroll
+        for (int i = 0; i < OWN; ++i)
+#pragma unroll
+          for (int r = 0; r < 2; ++r) slot[(i * 2 + r) * 64] = acc[o * OWN + i][r];
+      }
+    __syncthreads();
+    f32x4 stat[KW];
+#pragma unroll
+    for (int o = 0; o < KW; ++o) stat[o] = ml[o * 64];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      float m = stat[0][2 * r], l = 0.f;
+#pragma unroll
+      for (int o = 1; o < KW; ++o) m = fmaxf(m, stat[o][2 * r]);
+      f32x4 sum[OWN];
+#pragma unroll
+      for (int i = 0; i < OWN; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int o = 0; o < KW; ++o) {
+        const float scale = __builtin_amdgcn_exp2f(stat[o][2 * r] - m);
+        l += stat[o][2 * r + 1] * scale;
+        const f32x4* slot = xch + ((qw * KW + kw) * (KW - 1) + (o < kw ? o : o - 1)) * OWN * 2 * 64;
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) sum[i] += (o == kw ? own[i][r] : slot[(i * 2 + r) * 64]) * scale;
+      }
+#pragma unroll
+      for (int i = 0; i < OWN; ++i) own[i][r] = sum[i];
+      l_run[r] = l;
+    }
+  } else {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < OWN; ++i)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) own[i][r] = acc[i][r];
+  }
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    if (!valid[r]) continue;
+    const float inv = 1.0f / l_run[r];
+    asm volatile("" : "+v"(tok[r]));  // (one register until here, or the compiler forms the address in front of the loop)
+    bf16_t* row = p.out + (long)tok[r] * p.d + h * DH + kw * OWN * 16 + kq * 4;
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+      bf16x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (bf16_t)(own[i][r][e] * inv);
+      *reinterpret_cast<bf16x4*>(row + i * 16) = o;
+    }
+  }
+}
+
 // A workgroup without a query block of its own, one of `helpers` of its (sequence, head) on the same
 // XCD: reads the keys and values behind the first step once, in the order of the steps, so that the
 // blocks, whose two stages in flight would wait for every line at the latency of HBM (60 GB/s per CU), find
@@ -418,7 +801,7 @@ __device__ __forceinline__ void read_ahead(const AttnDev& p, int b, int h, int h
 }
 
 template <int DH, int QW, int KW, int TK, int NST>
-__global__ void __launch_bounds__(QW* KW * 64) attn_bf16_kernel(AttnDev p) {
+__global__ void __launch_bounds__(QW* KW * 64, 2) attn_bf16_kernel(AttnDev p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[attn_smem_bytes<DH, KW, TK, NST>()];
   // Workgroup ids are dealt round-robin to the 8 XCDs.  All query blocks of one
   // (sequence, head) are placed on the same XCD, so its K and V are fetched from HBM
@@ -442,7 +825,10 @@ __global__ void __launch_bounds__(QW* KW * 64) attn_bf16_kernel(AttnDev p) {
       read_ahead<DH, QW * KW>(p, b, h, qt - blocks, (p.at_once < p.n_qt ? p.at_once : p.n_qt) - blocks, smem);
     return;
   }
-  attn_block<DH, QW, KW, TK, NST>(p, b, h, qt, cnt, off, smem, threadIdx.x);
+  if constexpr (TK == 64 && DH == 128)
+    attn_wide<DH, QW, KW>(p, b, h, qt, cnt, off, smem, threadIdx.x);
+  else
+    attn_block<DH, QW, KW, TK, NST>(p, b, h, qt, cnt, off, smem, threadIdx.x);
 }
 
 // Refreshed rows: how many of a sequence's tokens there are is known on the device only, so the
@@ -540,10 +926,14 @@ __global__ void __launch_bounds__(512, kRowsGrid<DH> / 128) attn_rows_bf16_kerne
     unsigned every = ~0u;
     asm volatile("" : "+s"(every));
     const int tid = wave * 64 + (int)__builtin_amdgcn_mbcnt_hi(every, __builtin_amdgcn_mbcnt_lo(every, 0));
-    if (is_wide)  // (more than kAttnParts / 2 blocks: one part each)
-      attn_block<DH, 4, 2, 64, 2>(p, b, h, qt, cnt, off, smem, tid);
-    else
+    if (is_wide) {  // (more than kAttnParts / 2 blocks: one part each)
+      if constexpr (DH == 128)
+        attn_wide<DH, 4, 2>(p, b, h, qt, cnt, off, smem, tid);
+      else
+        attn_block<DH, 4, 2, 64, 2>(p, b, h, qt, cnt, off, smem, tid);
+    } else {
       attn_block<DH, 2, 4, 32, 2>(p, b, h, qt, cnt, off, smem, tid, part, n_parts, block);
+    }
     if (slot + (int)(gridDim.x >> 3) >= per_xcd) break;
     hold(c0);  // (again, rather than in registers that the block needs)
     upto = wave_prefix_sum((cnt_l + rows - 1) >> shift);
@@ -566,10 +956,10 @@ hipError_t launch_variant(AttnDev p, const AttnArgs& a, hipStream_t s) {
 
 template <int DH>
 hipError_t launch_dh(const AttnDev& p, const AttnArgs& a, hipStream_t s) {
-  switch (attn_route(a.batch, a.n_heads, a.seq, a.idx != nullptr, a.many_rows, a.parts.out != nullptr)) {
+  switch (attn_route(a.batch, a.n_heads, a.seq, a.idx != nullptr, a.many_rows, a.parts.out != nullptr, DH)) {
     case AttnRoute::kNarrow: return launch_variant<DH, 2, 4, 32, 2>(p, a, s);
     case AttnRoute::kWide: return launch_variant<DH, 4, 2, 64, 2>(p, a, s);
-    case AttnRoute::kTall: return launch_variant<DH, 8, 1, 64, 2>(p, a, s);
+    case AttnRoute::kTall: return launch_variant<DH, DH == 128 ? 4 : 8, 1, 64, 2>(p, a, s);
     case AttnRoute::kLaidOut: break;
   }
   AttnDev r = p;

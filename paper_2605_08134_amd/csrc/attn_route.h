@@ -7,7 +7,7 @@ namespace dare {
 enum class AttnRoute {
   kNarrow,  // blocks of 64 query rows, four key-waves; one workgroup per possible block
   kWide,    // 128 query rows, two key-waves; likewise
-  kTall,    // 256 query rows, no key split; likewise
+  kTall,    // no key split, 128 query rows (heads of 64 channels: 256); likewise
   kLaidOut, // one workgroup per CU walks blocks laid out from the refreshed-row counts
 };
 
@@ -18,7 +18,8 @@ constexpr bool attn_may_cut(int seq) { return (seq + 127) / 128 >= kCutSteps; }
 
 // listed: the query rows are a list; many: that list holds most rows of every sequence (a frozen
 // prefix), not a few (the refreshed rows).
-constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, bool many, bool workspace) {
+constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, bool many, bool workspace,
+                               int head_dim = 128) {
   const long pairs = batch * n_heads;
   auto blocks = [&](int rows) { return pairs * ((seq + rows - 1) / rows); };  // with every row listed
   if (listed && !many) {
@@ -40,10 +41,13 @@ constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, b
     if (pairs < 64 || blocks(direct == AttnRoute::kNarrow ? 64 : 128) <= 256) return direct;
     return AttnRoute::kLaidOut;
   }
-  // Most rows of every sequence and enough of them for a block of 256 query rows per
-  // workgroup (8 query-waves, no key split) to fill the chip: a K/V tile then feeds twice
-  // the MFMAs per byte that enters LDS (8 x 2048 tokens: 547 us against 661; 1 x 4096: 261 against
-  // 295; with 1 x 1024 tokens there are only 128 such blocks: 33 against 24 us).
+  // Most rows of every sequence.  Heads of 128 channels: a workgroup of four waves per block and two of them on a CU,
+  // unless one per CU is enough for all blocks, which then have a second wave per SIMD on the other half of the keys (us,
+  // two key-waves and none, 32 heads: 1 x 1024 tokens, 256 blocks, 21.8 and 33; 1 x 1152 44.8 and 38.5, 1 x 1280 48.5 and 40.6, 1 x
+  // 1536 56.7 and 48.4, 3 x 512 28.6 and 22.9, 2 x 640 31.2 and 24.8, 1 x 1920 63.5 and 63.6).
+  if (head_dim == 128) return blocks(128) > 256 ? AttnRoute::kTall : AttnRoute::kWide;
+  // Heads of 64: enough rows for a block of 256 per workgroup (8 query-waves) to fill the chip: a K/V tile then feeds
+  // twice the MFMAs per byte that enters LDS.
   return blocks(256) >= 256 ? AttnRoute::kTall : AttnRoute::kWide;
 }
 

@@ -13,7 +13,7 @@ PROBE = r"""
 #include <cstdlib>
 #include "attn_route.h"
 int main(int, char** a) {
-  std::printf("%d", (int)dare::attn_route(atol(a[1]), atol(a[2]), atoi(a[3]), atoi(a[4]), atoi(a[5]), atoi(a[6])));
+  std::printf("%d", (int)dare::attn_route(atol(a[1]), atol(a[2]), atoi(a[3]), atoi(a[4]), atoi(a[5]), atoi(a[6]), atoi(a[7])));
 }
 """
 NARROW, WIDE, TALL, LAID_OUT = range(4)
@@ -25,8 +25,8 @@ def route(tmp_path_factory):
     (d / "probe.cpp").write_text(PROBE)
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"), str(d / "probe.cpp"),
                     "-o", str(d / "probe")], check=True)
-    return lambda *args: int(subprocess.run([str(d / "probe")] + [str(int(v)) for v in args], capture_output=True,
-                                            text=True, check=True).stdout)
+    return lambda *args, dh=128: int(subprocess.run([str(d / "probe")] + [str(int(v)) for v in (*args, dh)],
+                                                    capture_output=True, text=True, check=True).stdout)
 
 
 @pytest.mark.parametrize("batch,heads,seq,want", [
@@ -50,6 +50,9 @@ def test_cut_keys_need_the_workspace_and_long_sequences(route):
 def test_all_rows(route, listed):
     for batch, heads, seq, want in ((8, 32, 2048, TALL), (1, 32, 4096, TALL), (1, 32, 1024, WIDE), (2048, 16, 8, TALL)):
         assert route(batch, heads, seq, listed, listed, True) == want
+        assert route(batch, heads, seq, listed, listed, True, dh=64) == want
+    for dh, want in ((128, TALL), (64, WIDE)):   # 288 blocks of 128 rows, 160 of 256
+        assert route(1, 32, 1152, listed, listed, True, dh=dh) == want
 
 
 PLACES = r"""

@@ -488,6 +488,34 @@ def test_attention_blocks_without_rows_read_ahead(B, batch, seq, heads, dh, frac
     test_attention_block_layout_from_the_counts(B, batch, seq, heads, dh, frac)
 
 
+@pytest.mark.parametrize("batch,heads", [(1, 2), (9, 32)])       # two key-waves per block, none
+@pytest.mark.parametrize("seq", [1, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 160, 193, 257])
+def test_attention_blocks_of_128_rows_at_tile_edges(B, batch, heads, seq):
+    """Key counts around a subtile, a tile and a step; logits that grow along the keys, so that the reference
+    exponent moves in the middle (and in the last, ragged tile).  Per element as above, but with the whole rounding
+    error of bf16, whose 8 significant bits leave up to 2^-8 of a value just above a power of two: with one or two keys per
+    row nothing averages it out.  |error| <= 2^-8 (sum_i p_i |v_i| + 2 |out|), and the fp32 arithmetic."""
+    r = _rng(seq + heads)
+    d = heads * 128
+    q, k, v = (r.standard_normal((batch * seq, d)) for _ in range(3))
+    k = (k.reshape(batch, seq, d) * (0.2 + 8.0 * np.arange(seq)[None, :, None] / seq)).reshape(-1, d)
+    q, k, v = (store(a, "bf16") for a in (q, k, v))
+    out = torch.zeros((batch * seq, d), dtype=torch.bfloat16, device="cuda")
+    B.dare_k_attention(dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), out, batch, seq, heads, 128)
+    torch.cuda.synchronize()
+    got = host(out).astype(np.float64).reshape(batch, seq, heads, 128)
+    for b in range(batch):
+        Q, K, V = (a.reshape(batch, seq, heads, 128)[b].astype(np.float64).transpose(1, 0, 2) for a in (q, k, v))
+        z = Q @ K.transpose(0, 2, 1) / np.sqrt(128)
+        pr = np.exp(z - z.max(-1, keepdims=True))
+        pr /= pr.sum(-1, keepdims=True)
+        want = pr @ V
+        # fp32 logits: 128 products each, off by up to 2^-24 of the sum of their magnitudes, a relative error of p
+        fp32 = 2.0 ** -23 * (np.abs(Q) @ np.abs(K).transpose(0, 2, 1)).max(-1, keepdims=True) / np.sqrt(128)
+        bound = (2.0 ** -8 + fp32) * (pr @ np.abs(V) + 2 * np.abs(want)) + 1e-5
+        assert np.all(np.abs(got[b].transpose(1, 0, 2) - want) <= bound)
+
+
 def test_attention_large_logits_are_stable(B):
     q, k, v, _ = _attn_case(77, 1, 192, 1, 128, "bf16", 1.0)
     q = store(q * 30.0, "bf16")
