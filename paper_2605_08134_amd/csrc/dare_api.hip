@@ -354,10 +354,10 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
     if (e != hipSuccess) return fail_hip(ctx, e, "threshold selection");
   }
 
-  // 3. Index list of the refreshed tokens.  With at most kSelMaxTokens tokens the bf16
+  // 3. Index list of the refreshed tokens.  With at most kSelMaxTokens tokens the
   //    refreshed-row projection derives the list itself (and leaves it for the kernels after
-  //    it): one launch less.
-  const bool fused_sel = sel_kv && cf.dtype == DARE_BF16 && n_tok <= kSelMaxTokens;
+  //    it): one launch less.  The fp32 one does with up to kSelMaxTokensF32.
+  const bool fused_sel = sel_kv && n_tok <= (cf.dtype == DARE_F32 ? kSelMaxTokensF32 : kSelMaxTokens);
   if (!fused_sel && (mode != DARE_MODE_DENSE || sel_idx || sel_count)) {
     e = launch_compact(reuse_mask, batch, seq, ctx->sel_idx, sel_idx, sel_count, nullptr,
                        ctx->sel_off, s);

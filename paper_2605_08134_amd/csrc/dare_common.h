@@ -55,11 +55,12 @@ struct GemmArgs {
   // interleaved gate_0, up_0, gate_1, ...): column pair (2j, 2j+1) gives one output
   // silu(gate_j) * up_j at column j of c[0] (bf16 path, one segment, no c32)
   int swiglu_pairs;
-  // Row list derived inside the kernel (bf16, device-count kernel only; replaces idx and
-  // m_dev): the rows are the tokens whose byte in sel_mask [sel_batch * sel_seq] is 0, in
+  // Row list derived inside the kernel (instead of idx and m_dev; bf16: the device-count kernel): the
+  // rows are the tokens whose byte in sel_mask [sel_batch * sel_seq] is 0, in
   // ascending order.  The first workgroup also writes what a compaction kernel would:
   // sel_idx_out (and optionally sel_idx_out2) [tokens], sel_off_out [sel_batch + 1],
-  // optionally sel_count_out [sel_batch].  At most kSelMaxTokens tokens.
+  // optionally sel_count_out [sel_batch].  At most kSelMaxTokens (fp32: kSelMaxTokensF32)
+  // tokens.
   const uint8_t* sel_mask;
   int sel_batch, sel_seq;
   int32_t* sel_idx_out;
@@ -74,7 +75,7 @@ struct GemmArgs {
   float* split_tiles;
   int* split_count;
 };
-constexpr int kSelMaxTokens = 2048;
+constexpr int kSelMaxTokens = 2048, kSelMaxTokensF32 = 1024;
 constexpr size_t gemm_split_tiles_bytes() { return (size_t)kSplitTiles * 2 * kPpRows * 128 * sizeof(float); }
 
 // Rotation of the channel pairs (v0, v1) and (v2, v3) by the table's (cos, sin) pairs of both

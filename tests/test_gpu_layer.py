@@ -302,6 +302,21 @@ def test_more_sequences_than_threads_in_the_fused_row_list():
     gl.layer.destroy()
 
 
+@pytest.mark.parametrize("batch,seq,fraction", [
+    (1, 1, 1.0), (1, 255, 0.5), (2, 128, 0.3), (1, 257, 0.01), (3, 341, 0.2), (1, 1024, 0.1), (1, 1025, 0.1),
+    (300, 3, (0.0, 1.0)),         # more sequences than threads
+])
+def test_f32_row_list_in_the_projection(batch, seq, fraction):
+    """The fp32 refreshed-row projection makes the list itself for up to 1024 tokens, four per thread."""
+    case = synth.make_case("tiny", seed=95, batch=batch, seq=seq, hidden=128, n_heads=2, head_dim=64, fraction=fraction)
+    state = pu.oracle_fill(case)
+    gl = pu.GpuLayer(case)
+    for mode in (orc.MODE_KV, orc.MODE_KVO):
+        _, got, _ = _run(case, gl, state, mode, synth.TAU_SEPARATING)
+        assert np.array_equal(got["sel_count"], case["perturbed"].sum(axis=1))
+    gl.layer.destroy()
+
+
 @pytest.mark.parametrize("hidden", [2048, 3072])
 def test_refreshed_rows_beyond_one_pass_of_the_grid(hidden):
     """2 x 1024 tokens, all of them refreshed.  Hidden 3072, Q, K and V: 384 tiles of 256 x 192, two passes of
