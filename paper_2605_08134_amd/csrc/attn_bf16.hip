@@ -899,8 +899,11 @@ __global__ void __launch_bounds__(512, kRowsGrid<DH> / 128) attn_rows_bf16_kerne
   int c0 = 0, before = 0;                     // sequences held, query blocks in front of them
   if (p.batch > 64) hold(0);
   int upto = wave_prefix_sum((cnt_l + rows - 1) >> shift);
-  for (int slot = blockIdx.x >> 3; slot < per_xcd; slot += gridDim.x >> 3) {
-    const int u = (blockIdx.x & 7) * per_xcd + slot;
+  // Blocks of 128 rows that are left for a last round of at most half of the workgroups: two of 64 rows each instead
+  const int slots = gridDim.x >> 3, whole = DH == 128 ? attn_whole_blocks(per_xcd, slots, is_wide) : per_xcd, n_slots = 2 * per_xcd - whole;
+  for (int slot = blockIdx.x >> 3; slot < n_slots; slot += gridDim.x >> 3) {
+    const bool halved = DH == 128 && slot >= whole;
+    const int u = (blockIdx.x & 7) * per_xcd + (halved ? whole + ((slot - whole) >> 1) : slot);
     if (u >= total) break;
     // (or their reciprocals stay in vector registers, which the block needs)
     asm volatile("" : "+s"(n_parts), "+s"(per_block));
@@ -926,15 +929,20 @@ __global__ void __launch_bounds__(512, kRowsGrid<DH> / 128) attn_rows_bf16_kerne
     unsigned every = ~0u;
     asm volatile("" : "+s"(every));
     const int tid = wave * 64 + (int)__builtin_amdgcn_mbcnt_hi(every, __builtin_amdgcn_mbcnt_lo(every, 0));
-    if (is_wide) {  // (more than kAttnParts / 2 blocks: one part each)
+    if (is_wide && !halved) {  // (more than kAttnParts / 2 blocks: one part each)
       if constexpr (DH == 128)
         attn_wide<DH, 4, 2>(p, b, h, qt, cnt, off, smem, tid);
       else
         attn_block<DH, 4, 2, 64, 2>(p, b, h, qt, cnt, off, smem, tid);
     } else {
-      attn_block<DH, 2, 4, 32, 2>(p, b, h, qt, cnt, off, smem, tid, part, n_parts, block);
+      int q = qt;
+      if (halved) {
+        q = 2 * qt + ((slot - whole) & 1);
+        if (q * 64 >= cnt) continue;  // (the second half of a last block; this round is the last one)
+      }
+      attn_block<DH, 2, 4, 32, 2>(p, b, h, q, cnt, off, smem, tid, part, n_parts, block);
     }
-    if (slot + (int)(gridDim.x >> 3) >= per_xcd) break;
+    if (slot + (int)(gridDim.x >> 3) >= n_slots) break;
     hold(c0);  // (again, rather than in registers that the block needs)
     upto = wave_prefix_sum((cnt_l + rows - 1) >> shift);
     __syncthreads();  // the stage memory is reused

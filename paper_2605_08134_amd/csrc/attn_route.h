@@ -83,4 +83,14 @@ constexpr int attn_at_once(int pairs, int seq, int head_dim) {
   return bytes <= (4l << 20) && seq > 256 && room > 1 ? room : 0;
 }
 
+// Blocks of 128 refreshed rows, per_xcd of them for the `slots` workgroups of an XCD: how many run as they are.  The rest,
+// where it would leave half of the workgroups or more without one in the last round, is cut into blocks of 64 rows, of which
+// that round then has at most one per workgroup (us, whole and halved: 8 x 2048 tokens of 32 heads, 6 % of them 85.3 and 78.3, 12 %
+// 118.7 and 114.9; 3 x 777, half 38.4 and 35.6; 4 x 4096, 20 % 271 and 262; 6 x 1500 of 16 heads, 20 % 56.5 and 51.3).  Heads of 128
+// channels only: with 64 the kernel has no register left for it.
+constexpr int attn_whole_blocks(int per_xcd, int slots, bool wide) {
+  const int rest = per_xcd % slots;
+  return wide && 2 * rest <= slots ? per_xcd - rest : per_xcd;
+}
+
 }  // namespace dare

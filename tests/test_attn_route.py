@@ -114,3 +114,29 @@ def test_turns_and_readers_ahead(tmp_path):
         r = subprocess.run([str(tmp_path / "turn")] + [str(v) for v in (pairs, listed, many, seq, dh)],
                            capture_output=True, text=True, check=True)
         assert tuple(map(int, r.stdout.split())) == want, (pairs, seq, dh)
+
+
+HALVES = r"""
+#include <cstdio>
+#include <vector>
+#include "attn_route.h"
+int main() {
+  for (int slots : {1, 7, 32, 64})
+    for (int n = 0; n < 400; ++n) {
+      const int whole = dare::attn_whole_blocks(n, slots, true), end = 2 * n - whole;
+      if (dare::attn_whole_blocks(n, slots, false) != n || whole > n || (whole < n && (whole % slots || end - whole > slots))) return 1;
+      std::vector<int> rows(2 * n);  // halves of blocks, as the kernel numbers them
+      for (int s = 0; s < end; ++s)
+        if (s < whole) ++rows[2 * s], ++rows[2 * s + 1]; else ++rows[2 * (whole + (s - whole) / 2) + (s - whole) % 2];
+      for (int r : rows) if (r != 1) return 2;
+    }
+  return 0;
+}
+"""
+
+
+def test_every_block_of_128_rows_runs_whole_or_in_two_halves(tmp_path):
+    (tmp_path / "halves.cpp").write_text(HALVES)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"), str(tmp_path / "halves.cpp"),
+                    "-o", str(tmp_path / "halves")], check=True)
+    assert subprocess.run([str(tmp_path / "halves")]).returncode == 0

@@ -450,6 +450,8 @@ def test_attention_selected_rows(B, dtype, batch, seq, heads, dh, frac):
     (130, 2100, 1, 64, 0.02),     # more sequences than lanes, twice over: 64 rows
     (66, 1153, 8, 64, 0.08),      # the same, two blocks of 64 rows per (sequence, head) or one of 128
     (65, 1100, 4, 128, 0.001),    # the same, half of the sequences without a refreshed row
+    (2, 650, 32, 128, 0.9),       # 320 blocks of 128 rows: the last 64 as blocks of 64 rows
+    (2, 650, 32, 128, 0.81),      # the same, 12 and 18 rows in the last blocks: the second half of it is empty
 ])
 def test_attention_block_layout_from_the_counts(B, batch, seq, heads, dh, frac):
     """Per element: a probability p_i rounded to bf16 is off by at most 2^-9 p_i, in the sum over
