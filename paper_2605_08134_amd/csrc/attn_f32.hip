@@ -2,7 +2,7 @@
 // line 8) on v_mfma_f32_16x16x4_f32.
 //
 // A workgroup serves 16 query rows of one (sequence, head); its four waves take every fourth
-// tile of 32 keys.  Transposed logits S^T = K Q^T (key fragment first): lane L holds query
+// tile of 32 keys (16 where a head has 128 channels, whose tiles take twice the registers).  Transposed logits S^T = K Q^T (key fragment first): lane L holds query
 // L & 15 and four neighbouring keys per 16, which is the operand layout of the probabilities in
 // O^T = V^T P^T, so they never leave the lane.  K, V and Q go from global memory straight into
 // registers (a fragment is used by one wave only), all loads of a tile in flight at once.  The
@@ -10,13 +10,16 @@
 //
 // What bounds it: at the short sequences of the fp32 configurations the latency of one
 // workgroup.  128 keys, 26 queries, 4 heads of 64: 14.2 -> 6.4 us against one wave per query that read
-// a key row per lane and walked the values key by key.
+// a key row per lane and walked the values key by key; -> 5.4 us with the first tile requested ahead of the reads that lead
+// to the queries and the loads kept together (the scheduler had spread them over the MFMAs of their uses, a wait each).  Whole KV+O
+// steps by the latter: 1 x 128 tokens of hidden 256 20.6 -> 19.2 us, 8 x 1024 of 256 137 -> 114, with 4 heads of 128 241 -> 219,
+// 4 x 1024 of 4096 3352 -> 3154.
 #include "dare_common.h"
 
 namespace dare {
 namespace {
 
-constexpr int kWaves = 4, kTiles = 2;  // key-waves; 16-key tiles per wave and step
+constexpr int kWaves = 4;  // key-waves
 
 struct AttnF32Dev {
   const float* q;
@@ -42,6 +45,7 @@ __device__ __forceinline__ float query_sum(float v) {
 template <int DH>
 __global__ void __launch_bounds__(kWaves * 64) attn_f32_kernel(AttnF32Dev p) {
   constexpr int C = DH / 16;  // 16-channel tiles
+  constexpr int kTiles = DH == 64 ? 2 : 1;  // 16-key tiles per wave and step
   __shared__ f32x4 o_part[kWaves][C][64];
   __shared__ float m_part[kWaves][16], l_part[kWaves][16];
   const int b = blockIdx.z, h = blockIdx.y;
@@ -57,26 +61,12 @@ __global__ void __launch_bounds__(kWaves * 64) attn_f32_kernel(AttnF32Dev p) {
     cnt = T;
   }
   if ((int)blockIdx.x * 16 >= cnt) return;  // uniform for the workgroup
-  const int j = blockIdx.x * 16 + l16;
-  const bool valid = j < cnt;
-  const int jc = valid ? j : cnt - 1;
-  const long tok = p.idx ? (long)p.idx[off + jc] : (long)(off + jc);
-
-  // channels 16 c + 4 kq .. + 3 of the lane's query
-  f32x4 qf[C];
-#pragma unroll
-  for (int c = 0; c < C; ++c) qf[c] = *reinterpret_cast<const f32x4*>(p.q + tok * p.d + h * DH + c * 16 + kq * 4);
-
   const float* kbase = p.k + (long)b * T * p.d + h * DH;
   const float* vbase = p.v + (long)b * T * p.d + h * DH;
-  f32x4 acc[C];
-#pragma unroll
-  for (int c = 0; c < C; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
-
-  for (int key0 = wave * (16 * kTiles); key0 < T; key0 += kWaves * 16 * kTiles) {
-    f32x4 kf[kTiles][C];
-    float vf[kTiles][4][C];
+  f32x4 kf[kTiles][C];
+  float vf[kTiles][4][C];
+  // (the scheduler moves loads back to their uses, one wait after the other, unless it is kept from it)
+  auto load_tiles = [&](int key0) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
       int key = key0 + t * 16 + l16;
@@ -93,6 +83,27 @@ __global__ void __launch_bounds__(kWaves * 64) attn_f32_kernel(AttnF32Dev p) {
 #pragma unroll
         for (int c = 0; c < C; ++c) vf[t][e][c] = vr[c * 16];
       }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load_tiles(wave * (16 * kTiles));  // (under the two dependent reads that lead to the queries)
+
+  const int j = blockIdx.x * 16 + l16;
+  const bool valid = j < cnt;
+  const int jc = valid ? j : cnt - 1;
+  const long tok = p.idx ? (long)p.idx[off + jc] : (long)(off + jc);
+
+  // channels 16 c + 4 kq .. + 3 of the lane's query
+  f32x4 qf[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) qf[c] = *reinterpret_cast<const f32x4*>(p.q + tok * p.d + h * DH + c * 16 + kq * 4);
+
+  f32x4 acc[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;
+
+  constexpr int kStep = kWaves * 16 * kTiles;
+  for (int key0 = wave * (16 * kTiles); key0 < T; key0 += kStep) {
     // z[t][e]: logit of key key0 + 16 t + 4 kq + e
     f32x4 z[kTiles];
     float m_loc = -INFINITY;
@@ -128,6 +139,7 @@ __global__ void __launch_bounds__(kWaves * 64) attn_f32_kernel(AttnF32Dev p) {
         for (int c = 0; c < C; ++c)
           acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? vf[t][e][c] : 0.f, pr, acc[c], 0, 0, 0);
       }
+    if (key0 + kStep < T) load_tiles(key0 + kStep);
   }
   l_run = query_sum(l_run);
   if (kq == 0) {
