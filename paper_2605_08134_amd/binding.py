@@ -184,9 +184,14 @@ def _ptr(t):
 
 
 def _stream(stream):
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    # the handle alone where torch has it: the Stream object around it takes 2.5 us of a call of 24
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _torch_dtype(dtype):
