@@ -414,8 +414,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& p, const int m, unsigne
 // and 23.8.  (The order of a sum over k is that of the instruction: 128 x 128 tiles sum 32 products at a time where they
 // summed 16, results differ from then by single bf16 roundings.)  The k of a k-step halved
 // between two groups of four waves with twice the wave tile (half the fragment reads) is no faster.
-// Where the groups of rows do not divide among the waves, some waves load one less (128 x 96: 28 groups, score_proj_kernel<16, 128> 18;
-// when they repeated the last group instead, steps of 1 x 1024 with 205 refreshed rows took 88.8 us, now 87.7).
+// Some waves repeat the last group of rows (128 x 96: 32 loads for 28 groups).
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
 __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsigned char* smem, const int tid,
                                             const int vblock, lds_idx_t lidx = nullptr,
@@ -425,8 +424,7 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
   constexpr int TM = WM / 16, TN = WN / 16;
   constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
   constexpr int GROUPS = (BM + BN) / 8;
-  constexpr int LPW = (GROUPS + NW - 1) / NW;
-  constexpr int FULL = GROUPS - (LPW - 1) * NW;  // waves with LPW loads per stage, the others have one less
+  constexpr int LPW = (GROUPS + NW - 1) / NW;  // surplus loads repeat the last group
   constexpr int KS = BK / 32;
   static_assert(WM % 16 == 0 && WN % 16 == 0, "wave tile must be a multiple of 16 x 16");
   static_assert(STAGES >= 3 && LPW * (STAGES - 1) < 64, "vmcnt range");
@@ -454,13 +452,11 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
   const int l16 = lane & 15, kq = lane >> 4;
   const int KT = p.k / BK;
 
-  const bool full = FULL == NW || wave < FULL;
-  const int grp0 = full ? wave * LPW : FULL + wave * (LPW - 1);
   const bf16_t* src[LPW];
   int grp[LPW], row_in[LPW], tok_in[LPW];
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
-    grp[i] = grp0 + i < GROUPS ? grp0 + i : GROUPS - 1;
+    grp[i] = wave * LPW + i < GROUPS ? wave * LPW + i : GROUPS - 1;
     const int row = m0 + grp[i] * 8 + (lane >> 3);
     row_in[i] = row < m ? row : m - 1;
   }
@@ -492,7 +488,6 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
   // fetching code of their own does (2 x 201 x 512 28.4 us as it is and 29.6 with TRIM, 4 of 1024 rows 61.0 and 62.5).
   constexpr bool TRIM = TM * TN >= 6;
   auto issue_load = [&](int i, int kt) __attribute__((always_inline)) {
-    if (i == LPW - 1 && !full) return;
     const int k = TRIM || kt < KT ? kt : KT - 1;
     __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + k * BK),
                                      (lptr_t)(smem + (kt % STAGES) * STAGE_BYTES + grp[i] * 8 * ROW_BYTES), 16, 0, 0);
@@ -542,11 +537,7 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
 #pragma unroll
       for (int i = 0; i < LPW; ++i) issue_load(i, s);
     }
-  auto wait_stages = [&](auto max_c, int ahead) __attribute__((always_inline)) {
-    constexpr int MAX = decltype(max_c)::value;
-    if (full) wait_stages_and_barrier<LPW, MAX>(ahead); else wait_stages_and_barrier<LPW - 1, MAX>(ahead);
-  };
-  wait_stages(std::integral_constant<int, STAGES - 1>{}, TRIM ? KT - 1 : STAGES - 1);
+  wait_stages_and_barrier<LPW, STAGES - 1>(TRIM ? KT - 1 : STAGES - 1);
   load_frags(0, 0);
   // k-step kt: the barrier publishes stage kt + 1 and, as every wave's fragments of kt have arrived, frees
   // the stage of kt.  (Two k-steps per trip so that the fragment set index is a compile-time constant.)
@@ -558,11 +549,9 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
     __builtin_amdgcn_sched_barrier(0);
     if (!END || kt + 1 < KT) {
       if constexpr (END)
-        wait_stages(std::integral_constant<int, STAGES - 2>{}, KT - 2 - kt);
-      else if (full)
-        wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
+        wait_stages_and_barrier<LPW, STAGES - 2>(KT - 2 - kt);
       else
-        wait_vmcnt_and_barrier<(LPW - 1) * (STAGES - 2)>();
+        wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
       __builtin_amdgcn_sched_barrier(0);
       load_frags(kt + 1, SET ^ 1);
     }
@@ -1280,8 +1269,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) score_proj_kernel(Score
   constexpr int TM = WM / 16, TN = WN / 16, KS = BK / 32;
   constexpr int STAGE_BYTES = (BM + WIDTH) * ROW_BYTES;
   constexpr int GROUPS = (BM + WIDTH) / 8;
-  constexpr int LPW = (GROUPS + NW - 1) / NW;
-  constexpr int FULL = GROUPS - (LPW - 1) * NW;  // waves with LPW loads per stage, the others have one less
+  constexpr int LPW = (GROUPS + NW - 1) / NW;  // surplus loads repeat the last group
   constexpr int LDQ = score_query_stride(WIDTH);
   static_assert(WM % 16 == 0 && WN % 16 == 0 && BM % NW == 0, "wave tiles of 16 x 16, whole rows per wave");
   static_assert(LPW * (STAGES - 1) < 64, "vmcnt range");
@@ -1309,13 +1297,11 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) score_proj_kernel(Score
   const int KT = p.k / BK / p.k_parts;      // k-steps of this workgroup
   const int range = p.k / BK / p.ranges;    // k-steps of a range of the tree
 
-  const bool full = FULL == NW || wave < FULL;
-  const int grp0 = full ? wave * LPW : FULL + wave * (LPW - 1);
   const bf16_t* src[LPW];
   int grp[LPW];
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
-    grp[i] = grp0 + i < GROUPS ? grp0 + i : GROUPS - 1;
+    grp[i] = wave * LPW + i < GROUPS ? wave * LPW + i : GROUPS - 1;
     const int r = grp[i] * 8 + (lane >> 3);
     const long off = (long)part * KT * BK + ((lane & 7) ^ ((r >> 1) & 7)) * 8;
     if (r < BM) {
@@ -1329,10 +1315,8 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) score_proj_kernel(Score
     unsigned char* base = smem + (kt % STAGES) * STAGE_BYTES;
     const int k = kt < KT ? kt : KT - 1;
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) {
-      if (i == LPW - 1 && !full) break;
+    for (int i = 0; i < LPW; ++i)
       __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + k * BK), (lptr_t)(base + grp[i] * 8 * ROW_BYTES), 16, 0, 0);
-    }
   };
 
   f32x4 acc[TM][TN], level[3][TM][TN];
@@ -1348,7 +1332,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64) score_proj_kernel(Score
   for (int s = 0; s < STAGES - 1; ++s) issue_loads(s);
   int done = 0, in_range = 0;  // ranges complete, k-steps of the current one
   for (int kt = 0; kt < KT; ++kt) {
-    if (full) wait_vmcnt_and_barrier<LPW*(STAGES - 2)>(); else wait_vmcnt_and_barrier<(LPW - 1) * (STAGES - 2)>();
+    wait_vmcnt_and_barrier<LPW*(STAGES - 2)>();
     issue_loads(kt + STAGES - 1);
     const unsigned char* st = smem + (kt % STAGES) * STAGE_BYTES;
     bf16x8 fa[KS][TM], fb[KS][TN];
