@@ -426,8 +426,8 @@ constexpr int wide_smem_bytes() {
 //     are read three MFMA groups ahead; the barrier of a step lies behind its last fragment, the first ones of the next
 //     step follow it, so a step ends without an empty pipe.
 //   * No maximum of every tile: the reference exponent of a row moves when a lane's sum of probabilities says so.
-//   * v_mfma_f32_16x16x32_bf16, as in the large projections: the clock is 1.8 GHz of 2.4 here, and the same loop with 32 x 32 x 16 takes
-//     2 to 10 % longer (and 30 registers more).
+//   * v_mfma_f32_16x16x32_bf16, as in the large projections: the same loop with 32 x 32 x 16 has 10 % fewer cycles, at 1.8 GHz for 1.9
+//     (of 2.4), and takes up to 10 % longer (and 30 registers more).
 //   * QW = 4, KW = 1: two workgroups of four waves per CU, out of step with each other, one multiplies while the other
 //     waits at its barrier or starts and ends.  One workgroup of eight waves (256 rows) pulls half as much from the L2 and is
 //     slower all the same wherever sequences are short (3 x 777 tokens 56.9 us, two workgroups 46.5; 16 x 256 34.4 and 31.6;
