@@ -402,6 +402,18 @@ __device__ __forceinline__ void attn_block(const AttnDev& p, int b, int h, int q
   }
 }
 
+// Maximum over the lanes L, L ^ 16, L ^ 32 and L ^ 48.  (The swap's words are copied before they are taken for floats:
+// __builtin_bit_cast of an element of a vector reads the first one.)
+__device__ __forceinline__ float quarters_max(float x) {
+  const unsigned own = __builtin_bit_cast(unsigned, x);
+  const auto rows = __builtin_amdgcn_permlane16_swap(own, own, false, false);
+  const unsigned even = rows[0], odd = rows[1];
+  const unsigned pair = __builtin_bit_cast(unsigned, fmaxf(__builtin_bit_cast(float, even), __builtin_bit_cast(float, odd)));
+  const auto halves = __builtin_amdgcn_permlane32_swap(pair, pair, false, false);
+  const unsigned low = halves[0], high = halves[1];
+  return fmaxf(__builtin_bit_cast(float, low), __builtin_bit_cast(float, high));
+}
+
 // XOR applied to the 16-byte chunk index of a K row / V row of attn_wide.  K fragment: 16 rows at one chunk; V
 // fragment by transpose read: 8 rows at 32 bytes are read at a time.  Linear over the bits of the key.
 template <int DH>
@@ -584,10 +596,7 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
       float top = x[r][0][0];
 #pragma unroll
       for (int n = 1; n < 8; ++n) top = fmaxf(top, x[r][n >> 2][n & 3]);
-      const auto rows = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, top), __builtin_bit_cast(unsigned, top), false, false);
-      top = fmaxf(__builtin_bit_cast(float, rows[0]), __builtin_bit_cast(float, rows[1]));
-      const auto half = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, top), __builtin_bit_cast(unsigned, top), false, false);
-      top = fmaxf(__builtin_bit_cast(float, half[0]), __builtin_bit_cast(float, half[1])) * p.scale_log2;  // scale > 0
+      top = quarters_max(top) * p.scale_log2;  // scale > 0
       const float m_new = fmaxf(fmaxf(m_run[r], top), -1e30f);  // (finite: logits of -infinity have probability 0)
       if constexpr (!decltype(first_c)::value) {
         const float alpha = __builtin_amdgcn_exp2f(m_run[r] - m_new);

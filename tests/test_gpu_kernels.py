@@ -518,6 +518,35 @@ def test_attention_blocks_of_128_rows_at_tile_edges(B, batch, heads, seq):
         assert np.all(np.abs(got[b].transpose(1, 0, 2) - want) <= bound)
 
 
+def _one_dominant_key(B, batch, heads, seq, at, log2_logit):
+    """Logits 0 but for key `at`, whose logit is log2_logit in base 2 for every second row (0 for the others); one-hot
+    values.  The output of those rows is the value of that key, of the others the mean of all."""
+    q = torch.zeros((batch * seq, heads, 128), dtype=torch.bfloat16, device="cuda")
+    k, v = torch.zeros_like(q), torch.zeros_like(q)
+    q[::2, :, 0] = 16.0
+    k.view(batch, seq, heads, 128)[:, at, :, 0] = log2_logit / np.log2(np.e) * np.sqrt(128) / 16.0
+    tok = torch.arange(seq, device="cuda")
+    v.view(batch, seq, heads, 128)[:, tok, :, tok % 128] = 1.0
+    out = torch.zeros_like(q)
+    B.dare_k_attention(q, k, v, out, batch, seq, heads, 128)
+    torch.cuda.synchronize()
+    got = out.double().cpu().reshape(batch * seq, heads, 128)
+    want = torch.zeros((128,), dtype=torch.float64)
+    want[at % 128] = 1.0
+    assert torch.equal(got[::2], want.expand_as(got[::2]))                # all of the weight: exact
+    mean = torch.bincount(tok.cpu() % 128, minlength=128).double() / seq  # a probability of 1 each: rounded once
+    assert bool(((got[1::2] - mean).abs() <= 2.0 ** -8 * mean).all())
+
+
+@pytest.mark.parametrize("batch,heads", [(1, 2), (9, 32)])       # two key-waves per block, none
+@pytest.mark.parametrize("seq", [32, 64, 150, 257])
+def test_attention_one_key_far_above_the_others(B, batch, heads, seq):
+    """A logit 250 above the reference exponent in base 2 (its probability overflows unless the reference moves), at
+    every key of the first tile, where each lane holds four of 16, and of the last subtile."""
+    for at in sorted(set(range(0, min(seq, 64), 3)) | set(range(max(0, seq - 33), seq, 4)) | {seq - 1}):
+        _one_dominant_key(B, batch, heads, seq, at, 250.0)
+
+
 def test_attention_large_logits_are_stable(B):
     q, k, v, _ = _attn_case(77, 1, 192, 1, 128, "bf16", 1.0)
     q = store(q * 30.0, "bf16")
