@@ -587,18 +587,25 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
     for (int n = 0; n < 8; ++n)
       if (kv0 + (n >> 2) * 16 + kq * 4 + (n & 3) >= T) x[0][n >> 2][n & 3] = x[1][n >> 2][n & 3] = -INFINITY;
   };
-  // The reference exponents of the rows move to the maxima of this subtile, which is scored again.  Any reference
-  // gives the same result (O and the row sum share it), so they only move when probabilities grow large, which a
-  // lane's sum of them tells without the maximum of every subtile.
+  // The reference exponents of the rows move to the maxima of this subtile, which is scored again; the first ones are the
+  // maxima of the wave's first tile (both subtiles, as the largest probability of a short row is then 1, without a
+  // rounding: error against float64 at 64 keys 1.99e-3, with the first subtile's 2.08e-3, at 201 2.09e-3 and 2.17e-3).
+  // Any reference gives the same result up to rounding (O and the row sum share it), so they only move when
+  // probabilities grow large, which a lane's sum of them tells without the maximum of every subtile.
   auto move_reference = [&](const f32x4 (&x)[2][2], bf16x8 (&pr)[2], float (&sum)[2], auto first_c) __attribute__((always_inline)) {
+    constexpr bool FIRST = decltype(first_c)::value;
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       float top = x[r][0][0];
 #pragma unroll
       for (int n = 1; n < 8; ++n) top = fmaxf(top, x[r][n >> 2][n & 3]);
+      if constexpr (FIRST) {
+#pragma unroll
+        for (int n = 0; n < 8; ++n) top = fmaxf(top, sc[1][r][n >> 2][n & 3]);
+      }
       top = quarters_max(top) * p.scale_log2;  // scale > 0
       const float m_new = fmaxf(fmaxf(m_run[r], top), -1e30f);  // (finite: logits of -infinity have probability 0)
-      if constexpr (!decltype(first_c)::value) {
+      if constexpr (!FIRST) {
         const float alpha = __builtin_amdgcn_exp2f(m_run[r] - m_new);
         l_run[r] *= alpha;
 #pragma unroll
@@ -698,15 +705,18 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
 #pragma unroll
     for (int j = 0; j < AHEAD; ++j) read_k(j, 0);
     period(S1{}, Yes{}, No{}, No{}, Yes{}, 0);
-    if (key_of(0) + 32 > T) mask_keys(sc[0], key_of(0));
-    move_reference(sc[0], pf[0], l_run, Yes{});
     period(S0{}, Yes{}, No{}, No{}, Yes{}, 0);
+    if (key_of(0) + 64 > T) {
+      mask_keys(sc[0], key_of(0));
+      mask_keys(sc[1], key_of(0) + 32);
+    }
+    move_reference(sc[0], pf[0], l_run, Yes{});
     for (int step = 1; step < mine; ++step) {
       period(S1{}, Yes{}, Yes{}, Yes{}, Yes{}, step);
       if (key_of(step) + 32 > T) mask_keys(sc[0], key_of(step));
       period(S0{}, Yes{}, Yes{}, Yes{}, Yes{}, step);
     }
-    if (key_of(mine - 1) + 64 > T) mask_keys(sc[1], key_of(mine - 1) + 32);
+    if (mine > 1 && key_of(mine - 1) + 64 > T) mask_keys(sc[1], key_of(mine - 1) + 32);
     period(S1{}, No{}, Yes{}, Yes{}, Yes{}, mine);
     period(S0{}, No{}, No{}, Yes{}, No{}, mine);
   }
