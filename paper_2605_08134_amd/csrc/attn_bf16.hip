@@ -587,24 +587,30 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
     for (int n = 0; n < 8; ++n)
       if (kv0 + (n >> 2) * 16 + kq * 4 + (n & 3) >= T) x[0][n >> 2][n & 3] = x[1][n >> 2][n & 3] = -INFINITY;
   };
-  // The reference exponents of the rows move to the maxima of this subtile, which is scored again; the first ones are the
-  // maxima of the wave's first tile (both subtiles, as the largest probability of a short row is then 1, without a
-  // rounding: error against float64 at 64 keys 1.99e-3, with the first subtile's 2.08e-3, at 201 2.09e-3 and 2.17e-3).
-  // Any reference gives the same result up to rounding (O and the row sum share it), so they only move when
-  // probabilities grow large, which a lane's sum of them tells without the maximum of every subtile.
-  auto move_reference = [&](const f32x4 (&x)[2][2], bf16x8 (&pr)[2], float (&sum)[2], auto first_c) __attribute__((always_inline)) {
-    constexpr bool FIRST = decltype(first_c)::value;
+  // The reference exponents of the rows move to the maxima of this subtile (BOTH: and of the other set's, of the same
+  // tile), which is scored again.  Any reference gives the same result up to rounding (O and the row sum share it), so
+  // they only move when probabilities grow large, which a lane's sum of them tells without the maximum of every
+  // subtile.  FIRST: there is none yet.
+  // The largest probability of a tile that the reference is taken from is 1, without a rounding, and short rows are the nearer
+  // to their exact value the more of their tiles have that.  So the first reference is the maximum of the wave's first tile, and
+  // without a second key-wave, which would start at a maximum of its own, it moves to that of the second tile too, also
+  // down (lower: how far in base 2, which bounds the probabilities in the sums).  Error against float64 with the first subtile's
+  // maximum, the first tile's, the first two tiles' and with two key-waves, in 10^-3: 64 keys 2.08, 1.99, 1.99, 1.99; 129 keys 2.18,
+  // 2.12, 1.99, 1.99; 300 keys 2.25, 2.23, 2.16, 2.16; 1152 keys 2.32, 2.30, 2.29, 2.28.  The second tile's takes 0.4 to 0.5 us of a
+  // block (3 x 777 tokens of 32 heads 47.4 -> 48.3 us, 8 x 2048 533 -> 538).
+  auto move_reference = [&](const f32x4 (&x)[2][2], bf16x8 (&pr)[2], float (&sum)[2], auto first_c, auto both_c, float lower) __attribute__((always_inline)) {
+    constexpr bool FIRST = decltype(first_c)::value, BOTH = decltype(both_c)::value;
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       float top = x[r][0][0];
 #pragma unroll
       for (int n = 1; n < 8; ++n) top = fmaxf(top, x[r][n >> 2][n & 3]);
-      if constexpr (FIRST) {
+      if constexpr (BOTH) {  // (keys past the end are copies of the last one here)
 #pragma unroll
         for (int n = 0; n < 8; ++n) top = fmaxf(top, sc[1][r][n >> 2][n & 3]);
       }
       top = quarters_max(top) * p.scale_log2;  // scale > 0
-      const float m_new = fmaxf(fmaxf(m_run[r], top), -1e30f);  // (finite: logits of -infinity have probability 0)
+      const float m_new = fmaxf(fmaxf(m_run[r] - lower, top), -1e30f);  // (finite: logits of -infinity have probability 0)
       if constexpr (!FIRST) {
         const float alpha = __builtin_amdgcn_exp2f(m_run[r] - m_new);
         l_run[r] *= alpha;
@@ -683,7 +689,9 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (SM) {
       round_pair(pf[S], 14, sum);
-      if (__any(fmaxf(sum[0], sum[1]) > kLimit)) move_reference(sc[S], pf[S], sum, No{});
+      constexpr bool BOTH = KW == 1 && EDGE;
+      if (__any(fmaxf(sum[0], sum[1]) > (BOTH && step == 1 ? -1.f : kLimit)))  // (the wave's second tile: whatever the sums are)
+        move_reference(sc[S], pf[S], sum, No{}, std::bool_constant<BOTH>{}, BOTH && step == 1 ? 8.f : 0.f);
       l_run[0] += sum[0];
       l_run[1] += sum[1];
     }
@@ -710,7 +718,7 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
       mask_keys(sc[0], key_of(0));
       mask_keys(sc[1], key_of(0) + 32);
     }
-    move_reference(sc[0], pf[0], l_run, Yes{});
+    move_reference(sc[0], pf[0], l_run, Yes{}, Yes{}, 0.f);
     for (int step = 1; step < mine; ++step) {
       period(S1{}, Yes{}, Yes{}, Yes{}, Yes{}, step);
       if (key_of(step) + 32 > T) mask_keys(sc[0], key_of(step));

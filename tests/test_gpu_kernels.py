@@ -519,24 +519,27 @@ def test_attention_blocks_of_128_rows_at_tile_edges(B, batch, heads, seq):
 
 
 @pytest.mark.parametrize("batch,heads", [(1, 8), (9, 32)])       # two key-waves per block, none
-@pytest.mark.parametrize("seq", [32, 50, 64])
-def test_attention_largest_probability_of_a_short_row_is_not_rounded(B, batch, heads, seq):
-    """Up to 64 keys the reference exponent is the row's maximum: the output is that of probabilities rounded to bf16 in
-    front of it, normalised by their sum and rounded once.  fp32 sums and exponentials, off by some 2^-22, give another
-    bf16 value where the result is that close to the middle of two, 2^-8 apart: about one in 10^4 for the output
-    and for a probability, of which up to 64 are in each."""
+@pytest.mark.parametrize("seq", [32, 50, 64, 65, 100, 128])
+def test_attention_largest_probability_of_a_tile_is_not_rounded(B, batch, heads, seq):
+    """Each of the first two tiles of 64 keys has its own maximum as reference exponent: the output is that of
+    probabilities rounded to bf16 relative to it, normalised by their sum and rounded once.  fp32 sums and exponentials, off by
+    some 2^-22, give another bf16 value where the result is that close to the middle of two, 2^-8 apart: about one in
+    10^4 for the output and for a probability, of which up to 128 are in each."""
     r = _rng(seq + heads)
-    q, k, v = (r.standard_normal((batch * seq, heads, 128)) for _ in range(3))
-    q, k, v = (store(a.reshape(-1, heads * 128), "bf16") for a in (1.13 * q, 1.13 * k, v))
+    q, k, v = (store(a * r.standard_normal((batch * seq, heads * 128)), "bf16") for a in (1.13, 1.13, 1.0))
     out = torch.zeros((batch * seq, heads * 128), dtype=torch.bfloat16, device="cuda")
     B.dare_k_attention(dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), out, batch, seq, heads, 128)
     torch.cuda.synchronize()
     Q, K, V = (a.reshape(batch, seq, heads, 128).astype(np.float64).transpose(0, 2, 1, 3) for a in (q, k, v))
     z = Q @ K.transpose(0, 1, 3, 2) / np.sqrt(128)
-    pr = synth.round_to_bf16(np.exp(z - z.max(-1, keepdims=True)).astype(np.float32)).astype(np.float64)
-    want = synth.round_to_bf16((pr @ V / pr.sum(-1, keepdims=True)).astype(np.float32))
+    num, den = 0.0, 0.0
+    for t in range(0, seq, 64):
+        top = z[..., t:t + 64].max(-1, keepdims=True)
+        pr = synth.round_to_bf16(np.exp(z[..., t:t + 64] - top).astype(np.float32)).astype(np.float64) * np.exp(top)
+        num, den = num + pr @ V[..., t:t + 64, :], den + pr.sum(-1, keepdims=True)
+    want = synth.round_to_bf16((num / den).astype(np.float32))
     got = host(out).reshape(batch, seq, heads, 128).transpose(0, 2, 1, 3)
-    assert np.mean(got != want) <= 0.01
+    assert np.mean(got != want) <= 0.02
 
 
 def _one_dominant_key(B, batch, heads, seq, at, log2_logit):
