@@ -610,7 +610,7 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
         for (int n = 0; n < 8; ++n) top = fmaxf(top, sc[1][r][n >> 2][n & 3]);
       }
       top = quarters_max(top) * p.scale_log2;  // scale > 0
-      const float m_new = fmaxf(fmaxf(m_run[r] - lower, top), -1e30f);  // (finite: logits of -infinity have probability 0)
+      const float m_new = fmaxf(fmaxf(m_run[r] - lower, top), -__FLT_MAX__);  // (finite: logits of -infinity have probability 0)
       if constexpr (!FIRST) {
         const float alpha = __builtin_amdgcn_exp2f(m_run[r] - m_new);
         l_run[r] *= alpha;

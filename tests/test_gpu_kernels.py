@@ -571,6 +571,22 @@ def test_attention_one_key_far_above_the_others(B, batch, heads, seq):
         _one_dominant_key(B, batch, heads, seq, at, 250.0)
 
 
+@pytest.mark.parametrize("batch,heads", [(1, 2), (9, 32)])       # two key-waves per block, none
+@pytest.mark.parametrize("seq,at", [(20, 7), (64, 40), (150, 100), (150, 149)])
+def test_attention_rows_of_logits_near_the_lowest_finite(B, batch, heads, seq, at):
+    """Every logit is -2^105, but -2^104 for one key (powers of two: times the scale exact to fp32's rounding): all of the
+    weight is that key's."""
+    q = torch.full((batch * seq, heads, 128), 0.0, dtype=torch.bfloat16, device="cuda")
+    q[:, :, 3] = 2.0 ** 52
+    k, v = torch.zeros_like(q), torch.randn(q.shape, device="cuda").to(torch.bfloat16)
+    k[:, :, 3] = -2.0 ** 53
+    k.view(batch, seq, heads, 128)[:, at, :, 3] = -2.0 ** 52
+    out = torch.zeros_like(q)
+    B.dare_k_attention(q, k, v, out, batch, seq, heads, 128)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(batch, seq, heads, 128), v.view(batch, seq, heads, 128)[:, at:at + 1].expand(batch, seq, heads, 128))
+
+
 def test_attention_large_logits_are_stable(B):
     q, k, v, _ = _attn_case(77, 1, 192, 1, 128, "bf16", 1.0)
     q = store(q * 30.0, "bf16")
