@@ -463,7 +463,9 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
   constexpr int CB = DH / 16;                      // 16-channel blocks of the output
   constexpr int NP = CB;                           // fragments of K, and of V, that a subtile takes
   constexpr int AHEAD = 3, RING = AHEAD + 1;       // fragments read ahead of their MFMAs
-  constexpr float kLimit = 4096.f;                 // sum of a lane's probabilities from which on the reference moves
+  // sum of a lane's probabilities from which on the reference moves (a probability is at most that, as in attn_block, and times
+  // a value of up to 1e36 finite)
+  constexpr float kLimit = 256.f;
   static_assert(KSTAGE / 1024 % NW == 0 && NP % RING == 0, "loads and fragments must divide");
   using Yes = std::true_type;
   using No = std::false_type;

@@ -587,6 +587,25 @@ def test_attention_rows_of_logits_near_the_lowest_finite(B, batch, heads, seq, a
     assert torch.equal(out.view(batch, seq, heads, 128), v.view(batch, seq, heads, 128)[:, at:at + 1].expand(batch, seq, heads, 128))
 
 
+@pytest.mark.parametrize("batch,heads", [(1, 2), (9, 32)])       # two key-waves per block, none
+@pytest.mark.parametrize("growth", [7.5, 11.5])                  # in base 2, over the keys of the first two tiles
+def test_attention_of_values_near_the_largest(B, batch, heads, growth):
+    """Values of 1e36 times a probability of more than 340 are not finite, their weighted mean is.  |error| as above:
+    2^-8 for each of probability, row sum and output; fp32 logits of 10 and exponentials add less than 2^-18."""
+    seq = 150
+    q = torch.zeros((batch * seq, heads, 128), dtype=torch.bfloat16, device="cuda")
+    q[:, :, 0] = 1.0
+    k, v = torch.zeros_like(q), torch.zeros_like(q)
+    k.view(batch, seq, heads, 128)[:, 130, :, 0] = growth / np.log2(np.e) * np.sqrt(128)
+    v.view(batch, seq, heads, 128)[:, 130] = 1e36
+    out = torch.zeros_like(q)
+    B.dare_k_attention(q, k, v, out, batch, seq, heads, 128)
+    torch.cuda.synchronize()
+    weight = float(torch.exp(k.double().max() / np.sqrt(128)))
+    want = float(v.double().max()) * weight / (weight + seq - 1)
+    assert bool(((out.double() - want).abs() <= 3 * 2.0 ** -8 * want).all())
+
+
 def test_attention_large_logits_are_stable(B):
     q, k, v, _ = _attn_case(77, 1, 192, 1, 128, "bf16", 1.0)
     q = store(q * 30.0, "bf16")
