@@ -982,7 +982,7 @@ template <int DH, int QW, int KW, int TK, int NST>
 hipError_t launch_variant(AttnDev p, const AttnArgs& a, hipStream_t s) {
   p.n_heads = a.n_heads;
   p.n_pairs = a.batch * a.n_heads;
-  p.n_qt = (a.seq + 32 * QW - 1) / (32 * QW);
+  p.n_qt = (attn_most_rows(a.seq, a.idx != nullptr, a.many_rows, a.active) + 32 * QW - 1) / (32 * QW);
   p.turn = attn_turn(p.n_pairs, a.idx != nullptr, a.many_rows);
   p.at_once = a.idx && !a.many_rows ? attn_at_once(p.n_pairs, a.seq, DH) : 0;
   const long grid = (long)((p.n_pairs + 7) / 8) * p.n_qt * 8;
@@ -993,7 +993,7 @@ hipError_t launch_variant(AttnDev p, const AttnArgs& a, hipStream_t s) {
 
 template <int DH>
 hipError_t launch_dh(const AttnDev& p, const AttnArgs& a, hipStream_t s) {
-  switch (attn_route(a.batch, a.n_heads, a.seq, a.idx != nullptr, a.many_rows, a.parts.out != nullptr, DH)) {
+  switch (attn_route(a.batch, a.n_heads, a.seq, a.idx != nullptr, a.many_rows, a.parts.out != nullptr, DH, a.active)) {
     case AttnRoute::kNarrow: return launch_variant<DH, 2, 4, 32, 2>(p, a, s);
     case AttnRoute::kWide: return launch_variant<DH, 4, 2, 64, 2>(p, a, s);
     case AttnRoute::kTall: return launch_variant<DH, DH == 128 ? 4 : 8, 1, 64, 2>(p, a, s);

@@ -16,12 +16,18 @@ constexpr int kCutSteps = 2 * kPartSteps;   // key steps from which on they can 
 // whether a step of up to seq tokens per sequence can use the workspace of cut keys
 constexpr bool attn_may_cut(int seq) { return (seq + 127) / 128 >= kCutSteps; }
 
+// Query rows of a sequence, at most.  many: the list holds all rows behind a frozen prefix, `active` of them (0: every row).
+constexpr int attn_most_rows(int seq, bool listed, bool many, int active) {
+  return listed && many && active > 0 ? active : seq;
+}
+
 // listed: the query rows are a list; many: that list holds most rows of every sequence (a frozen
-// prefix), not a few (the refreshed rows).
+// prefix), not a few (the refreshed rows); active as above.
 constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, bool many, bool workspace,
-                               int head_dim = 128) {
+                               int head_dim = 128, int active = 0) {
   const long pairs = batch * n_heads;
-  auto blocks = [&](int rows) { return pairs * ((seq + rows - 1) / rows); };  // with every row listed
+  const int most = attn_most_rows(seq, listed, many, active);
+  auto blocks = [&](int rows) { return pairs * ((most + rows - 1) / rows); };
   if (listed && !many) {
     // Refreshed rows.  Laying the blocks out on the device takes every workgroup a walk over the
     // counts, a memory latency per 64 sequences, in front of everything and again between its
@@ -44,7 +50,9 @@ constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, b
   // Most rows of every sequence.  Heads of 128 channels: a workgroup of four waves per block and two of them on a CU,
   // unless one per CU is enough for all blocks, which then have a second wave per SIMD on the other half of the keys (us,
   // two key-waves and none, 32 heads: 1 x 1024 tokens, 256 blocks, 21.8 and 33; 1 x 1152 44.8 and 38.5, 1 x 1280 48.5 and 40.6, 1 x
-  // 1536 56.7 and 48.4, 3 x 512 28.6 and 22.9, 2 x 640 31.2 and 24.8, 1 x 1920 63.5 and 63.6).
+  // 1536 56.7 and 48.4, 3 x 512 28.6 and 22.9, 2 x 640 31.2 and 24.8, 1 x 1920 63.5 and 63.6).  Frozen rows have no
+  // block (dense steps, blocks of the whole sequence counted and of the others: 1 x 1536 tokens with 512 of them frozen 177 and 162 us,
+  // 1 x 2560 of 16 heads with 768 frozen 145 and 118; heads of 64, 1 x 4096 of 16 with 2048 frozen 114 and 86).
   if (head_dim == 128) return blocks(128) > 256 ? AttnRoute::kTall : AttnRoute::kWide;
   // Heads of 64: enough rows for a block of 256 per workgroup (8 query-waves) to fill the chip: a K/V tile then feeds
   // twice the MFMAs per byte that enters LDS.

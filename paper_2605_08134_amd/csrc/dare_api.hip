@@ -419,6 +419,7 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
   a.idx = sel_o ? ctx->sel_idx : act_idx;
   a.sel_off = sel_o ? ctx->sel_off : (pre ? ctx->act_off : nullptr);
   a.many_rows = !sel_o && pre;
+  a.active = seq - P;
   a.parts = bx.parts;
   if ((e = attn(ctx, a, s)) != hipSuccess) return fail_hip(ctx, e, "attention");
 

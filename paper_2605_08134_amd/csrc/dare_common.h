@@ -142,6 +142,7 @@ struct AttnArgs {
   const int32_t* idx;      // optional selected rows
   const int32_t* sel_off;  // [batch+1] when idx != nullptr
   bool many_rows;          // the listed rows are most of each sequence (a frozen prefix), not a few
+  int active;              // then: how many of each sequence
   AttnParts parts;
 };
 constexpr int kAttnParts = 256;  // parts of a launch, at most: one per CU

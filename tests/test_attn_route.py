@@ -13,7 +13,7 @@ PROBE = r"""
 #include <cstdlib>
 #include "attn_route.h"
 int main(int, char** a) {
-  std::printf("%d", (int)dare::attn_route(atol(a[1]), atol(a[2]), atoi(a[3]), atoi(a[4]), atoi(a[5]), atoi(a[6]), atoi(a[7])));
+  std::printf("%d", (int)dare::attn_route(atol(a[1]), atol(a[2]), atoi(a[3]), atoi(a[4]), atoi(a[5]), atoi(a[6]), atoi(a[7]), atoi(a[8])));
 }
 """
 NARROW, WIDE, TALL, LAID_OUT = range(4)
@@ -25,8 +25,8 @@ def route(tmp_path_factory):
     (d / "probe.cpp").write_text(PROBE)
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"), str(d / "probe.cpp"),
                     "-o", str(d / "probe")], check=True)
-    return lambda *args, dh=128: int(subprocess.run([str(d / "probe")] + [str(int(v)) for v in (*args, dh)],
-                                                    capture_output=True, text=True, check=True).stdout)
+    return lambda *args, dh=128, active=0: int(subprocess.run([str(d / "probe")] + [str(int(v)) for v in (*args, dh, active)],
+                                                              capture_output=True, text=True, check=True).stdout)
 
 
 @pytest.mark.parametrize("batch,heads,seq,want", [
@@ -53,6 +53,15 @@ def test_all_rows(route, listed):
         assert route(batch, heads, seq, listed, listed, True, dh=64) == want
     for dh, want in ((128, TALL), (64, WIDE)):   # 288 blocks of 128 rows, 160 of 256
         assert route(1, 32, 1152, listed, listed, True, dh=dh) == want
+
+
+@pytest.mark.parametrize("batch,heads,seq,active,want", [
+    (1, 32, 1536, 1024, WIDE), (1, 32, 1536, 1025, TALL), (1, 32, 1536, 0, TALL), (2, 32, 700, 444, WIDE),
+    (1, 16, 2560, 1792, WIDE), (1, 32, 1792, 892, WIDE), (1, 32, 4096, 596, WIDE), (4, 32, 4096, 2048, TALL),
+    (8, 16, 300, 256, WIDE), (8, 16, 300, 257, TALL), (17, 16, 40, 30, TALL),
+])
+def test_all_rows_behind_a_frozen_prefix_count_without_it(route, batch, heads, seq, active, want):
+    assert route(batch, heads, seq, True, True, True, active=active) == want
 
 
 PLACES = r"""

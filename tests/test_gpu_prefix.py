@@ -84,6 +84,25 @@ def test_prefix_leaves_rows_between_the_projection_routes(mode, P):
     gl.layer.destroy()
 
 
+@pytest.mark.parametrize("batch,seq,heads,head_dim,P", [
+    (8, 300, 16, 128, 44), (8, 300, 16, 128, 43),     # 256 blocks of 128 active rows and 384, of 384 with the frozen ones
+    (17, 40, 16, 128, 10),                            # one short block per (sequence, head), 272 of them
+    (16, 40, 16, 64, 10),                             # the same of 256 rows, heads of 64
+])
+@pytest.mark.parametrize("mode", [orc.MODE_DENSE, orc.MODE_KV])
+def test_prefix_attention_over_many_blocks(batch, seq, heads, head_dim, P, mode):
+    """The listed rows in the attention kernels with two key-waves and without any."""
+    case = synth.make_case("llada8b", seed=87 + P, batch=batch, seq=seq, hidden=heads * head_dim, n_heads=heads,
+                           head_dim=head_dim)
+    state, gl = pu.oracle_fill(case), pu.GpuLayer(case)
+    gl.layer.set_prefix(P)
+    want = _oracle(case, state, mode, synth.TAU_SEPARATING, P)
+    got = gl.step(mode, synth.TAU_SEPARATING, case["x_cur"], state)
+    pu.check_step(got, want, state, mode, synth.TAU_SEPARATING, "bf16")
+    _frozen_rows_untouched(got, state, P)
+    gl.layer.destroy()
+
+
 def test_prefix_with_quantile_rule_ranks_the_other_tokens():
     case = synth.make_case("tiny", seed=5, batch=2, seq=96)
     state = pu.oracle_fill(case)
