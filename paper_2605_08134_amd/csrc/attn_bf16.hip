@@ -416,17 +416,11 @@ __device__ __forceinline__ float quarters_max(float x) {
 
 // XOR applied to the 16-byte chunk index of a K row / V row of attn_wide.  K fragment: 16 rows at one chunk; V
 // fragment by transpose read: 8 rows at 32 bytes are read at a time.  Linear over the bits of the key.
-template <int DH>
-__device__ __forceinline__ constexpr int wide_k_swizzle(int key) {
-  return DH == 128 ? (key & 15) : ((key >> 1) & 7);
-}
-template <int DH>
-__device__ __forceinline__ constexpr int wide_v_swizzle(int key) {
-  return DH == 128 ? ((key & 3) << 2 | (key >> 2 & 1) << 1) : (key >> 1 & 3) << 1;
-}
-template <int DH, int KW>
-constexpr int wide_smem_bytes() {
-  return 2 * KW * 2 * 64 * DH * 2;
+__device__ __forceinline__ constexpr int wide_k_swizzle(int key) { return key & 15; }
+__device__ __forceinline__ constexpr int wide_v_swizzle(int key) { return (key & 3) << 2 | (key >> 2 & 1) << 1; }
+template <int KW>
+constexpr int wide_smem_bytes() {  // two stages of K and of V, a tile of 64 keys of 128 channels per key-wave in each
+  return 2 * KW * 2 * 64 * 128 * 2;
 }
 
 // A block of 32 QW query rows of heads of 128 channels, QW x KW waves: wave (qw, kw) owns 32 rows and every KW-th tile
@@ -450,11 +444,11 @@ constexpr int wide_smem_bytes() {
 // 32 such heads 283 us, with this loop 282 to 325; 1 x 4096 142 and 150).
 // Not faster: loads between the MFMAs instead of in a row behind the barrier (2 to 6 % slower), four stages (5 % slower),
 // s_setprio around the MFMAs.
-template <int DH, int QW, int KW>
+template <int QW, int KW>
 __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt, int cnt, int off,
                                           unsigned char* smem, const int tid) {
-  constexpr int TK = 64, NW = QW * KW;
-  constexpr int ROWB = DH * 2;                     // bytes per K or V row of one head
+  constexpr int DH = 128, TK = 64, NW = QW * KW;
+  constexpr int ROWB = DH * 2;                     // bytes per K or V row of one head (and a divisor of a token's, as the chunk XOR needs)
   constexpr int CPR = DH / 8;                      // 16-byte chunks per row
   constexpr int RPL = 64 / CPR;                    // rows covered by one wave load
   constexpr int TILE_BYTES = TK * ROWB;
@@ -503,7 +497,7 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
   const unsigned row_bytes = (unsigned)p.d * 2;
   const unsigned key0 = (unsigned)wave * KL * RPL + (unsigned)lane / CPR;  // key of this lane's first load at step 0
   // (the chunk XOR of a key is that of the lane's first key and that of the distance)
-  const unsigned k_chunk = ((unsigned)lane % CPR ^ wide_k_swizzle<DH>(key0)) * 16, v_chunk = ((unsigned)lane % CPR ^ wide_v_swizzle<DH>(key0)) * 16;
+  const unsigned k_chunk = ((unsigned)lane % CPR ^ wide_k_swizzle(key0)) * 16, v_chunk = ((unsigned)lane % CPR ^ wide_v_swizzle(key0)) * 16;
   const unsigned k_src = key0 * row_bytes + k_chunk, v_src = key0 * row_bytes + v_chunk;
   const unsigned lds0 = (unsigned)(size_t)(lptr_t)smem;
   auto load_tiles = [&](auto is_v, int step) __attribute__((always_inline)) {
@@ -514,7 +508,7 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
     auto load = [&](unsigned at, int i) __attribute__((always_inline)) {
       asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(at), "s"(from), "{m0}"(to + i * 1024) : "memory");
     };
-#define DARE_SWZ(i) ((V ? wide_v_swizzle<DH>((i) * RPL) : wide_k_swizzle<DH>((i) * RPL)) * 16)
+#define DARE_SWZ(i) ((V ? wide_v_swizzle((i) * RPL) : wide_k_swizzle((i) * RPL)) * 16)
     if (k0 + KW * TK > T) {  // keys past the end re-read the last one
 #pragma unroll
       for (int i = 0; i < KL; ++i) {
@@ -542,10 +536,10 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
   unsigned k_at[NP / 2], v_at;
 #pragma unroll
   for (int ks = 0; ks < NP / 2; ++ks)
-    k_at[ks] = lds0 + kw * TILE_BYTES + l16 * ROWB + ((ks * 4 + kq) ^ wide_k_swizzle<DH>(l16)) * 16;
+    k_at[ks] = lds0 + kw * TILE_BYTES + l16 * ROWB + ((ks * 4 + kq) ^ wide_k_swizzle(l16)) * 16;
   {
     const int key = kq * 4 + (l16 >> 2);
-    v_at = lds0 + 2 * KSTAGE + kw * TILE_BYTES + key * ROWB + ((l16 >> 1 & 1) ^ wide_v_swizzle<DH>(key)) * 16 + (l16 & 1) * 8;
+    v_at = lds0 + 2 * KSTAGE + kw * TILE_BYTES + key * ROWB + ((l16 >> 1 & 1) ^ wide_v_swizzle(key)) * 16 + (l16 & 1) * 8;
   }
   bf16x8 kf[RING], vf[RING];
   auto read_k = [&](int j, int sub) __attribute__((always_inline)) {
@@ -743,7 +737,7 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
   f32x4 own[OWN][2];            // blocks kw OWN ..
   if constexpr (KW > 1) {
     constexpr int ML = QW * KW * (KW - 1) * OWN * 2 * 64 * 16;  // bytes of the shares; behind them (max, sum) of every wave
-    static_assert(ML + QW * KW * 64 * 16 <= wide_smem_bytes<DH, KW>(), "the merge area must fit into the stage memory");
+    static_assert(ML + QW * KW * 64 * 16 <= wide_smem_bytes<KW>(), "the merge area must fit into the stage memory");
     wait_all_and_barrier();  // all loads landed, all tiles consumed: stage memory is free
     f32x4* xch = reinterpret_cast<f32x4*>(smem) + lane;
     f32x4* ml = reinterpret_cast<f32x4*>(smem + ML) + qw * KW * 64 + lane;
@@ -854,9 +848,10 @@ __global__ void __launch_bounds__(QW* KW * 64, 2) attn_bf16_kernel(AttnDev p) {
       read_ahead<DH, QW * KW>(p, b, h, qt - blocks, (p.at_once < p.n_qt ? p.at_once : p.n_qt) - blocks, smem);
     return;
   }
-  if constexpr (TK == 64 && DH == 128)
-    attn_wide<DH, QW, KW>(p, b, h, qt, cnt, off, smem, threadIdx.x);
-  else
+  if constexpr (TK == 64 && DH == 128) {
+    static_assert(sizeof(smem) == wide_smem_bytes<KW>(), "the stage memory of attn_wide");
+    attn_wide<QW, KW>(p, b, h, qt, cnt, off, smem, threadIdx.x);
+  } else
     attn_block<DH, QW, KW, TK, NST>(p, b, h, qt, cnt, off, smem, threadIdx.x);
 }
 
@@ -959,9 +954,10 @@ __global__ void __launch_bounds__(512, kRowsGrid<DH> / 128) attn_rows_bf16_kerne
     asm volatile("" : "+s"(every));
     const int tid = wave * 64 + (int)__builtin_amdgcn_mbcnt_hi(every, __builtin_amdgcn_mbcnt_lo(every, 0));
     if (is_wide && !halved) {  // (more than kAttnParts / 2 blocks: one part each)
-      if constexpr (DH == 128)
-        attn_wide<DH, 4, 2>(p, b, h, qt, cnt, off, smem, tid);
-      else
+      if constexpr (DH == 128) {
+        static_assert(sizeof(smem) == wide_smem_bytes<2>(), "the stage memory of attn_wide");
+        attn_wide<4, 2>(p, b, h, qt, cnt, off, smem, tid);
+      } else
         attn_block<DH, 4, 2, 64, 2>(p, b, h, qt, cnt, off, smem, tid);
     } else {
       int q = qt;
