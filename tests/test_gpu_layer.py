@@ -317,6 +317,22 @@ def test_f32_row_list_in_the_projection(batch, seq, fraction):
     gl.layer.destroy()
 
 
+@pytest.mark.parametrize("batch,seq,hidden,head_dim,fraction", [
+    (2, 257, 1024, 64, 0.2),      # 288 and 432 tiles of 64 x 64, some 103 rows: the second row tile ragged, seven empty
+    (1, 1024, 512, 128, 0.07),    # 256 and 384 tiles, 72 rows
+    (1, 1024, 512, 64, 1.0),      # the list is full
+])
+def test_f32_row_list_in_the_largest_tiles(batch, seq, hidden, head_dim, fraction):
+    case = synth.make_case("tiny", seed=97, batch=batch, seq=seq, hidden=hidden, n_heads=hidden // head_dim,
+                           head_dim=head_dim, fraction=fraction)
+    state = pu.oracle_fill(case)
+    gl = pu.GpuLayer(case)
+    for mode in (orc.MODE_KV, orc.MODE_KVO):
+        _, got, _ = _run(case, gl, state, mode, synth.TAU_SEPARATING)
+        assert np.array_equal(got["sel_count"], case["perturbed"].sum(axis=1))
+    gl.layer.destroy()
+
+
 @pytest.mark.parametrize("hidden", [2048, 3072])
 def test_refreshed_rows_beyond_one_pass_of_the_grid(hidden):
     """2 x 1024 tokens, all of them refreshed.  Hidden 3072, Q, K and V: 384 tiles of 256 x 192, two passes of
