@@ -47,6 +47,7 @@ struct AttnDev {
   int n_heads, n_pairs, n_qt;  // heads, batch*heads, query blocks launched per (sequence, head)
   int batch;
   int turn, at_once;           // order of the workgroups, readers ahead (attn_turn, attn_at_once)
+  int second;                  // attn_wide without key-waves: tile whose maximum the reference moves to (attn_second_reference)
   // keys of a query block cut over workgroups (attn_rows_bf16_kernel): partial results, and
   // counters that are 0 before and after the launch; nullptr = never cut
   float* part_out;
@@ -589,11 +590,10 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
   // subtile.  FIRST: there is none yet.
   // The largest probability of a tile that the reference is taken from is 1, without a rounding, and short rows are the nearer
   // to their exact value the more of their tiles have that.  So the first reference is the maximum of the wave's first tile, and
-  // without a second key-wave, which would start at a maximum of its own, it moves to that of the second tile too, also
-  // down (lower: how far in base 2, which bounds the probabilities in the sums).  Error against float64 with the first subtile's
-  // maximum, the first tile's, the first two tiles' and with two key-waves, in 10^-3: 64 keys 2.08, 1.99, 1.99, 1.99; 129 keys 2.18,
-  // 2.12, 1.99, 1.99; 300 keys 2.25, 2.23, 2.16, 2.16; 1152 keys 2.32, 2.30, 2.29, 2.28.  The second tile's takes 0.4 to 0.5 us of a
-  // block (3 x 777 tokens of 32 heads 47.4 -> 48.3 us, 8 x 2048 533 -> 538).
+  // where attn_second_reference says so it moves to that of the second tile too, also down (lower: how far in base 2, which
+  // bounds the probabilities in the sums).  Error against float64 with the first subtile's maximum, the first tile's, the first
+  // two tiles' and with two key-waves, in 10^-3: 64 keys 2.08, 1.99, 1.99, 1.99; 129 keys 2.18, 2.12, 1.99, 1.99; 300 keys 2.25, 2.23,
+  // 2.16, 2.16; 1152 keys 2.32, 2.30, 2.29, 2.28.
   auto move_reference = [&](const f32x4 (&x)[2][2], bf16x8 (&pr)[2], float (&sum)[2], auto first_c, auto both_c, float lower) __attribute__((always_inline)) {
     constexpr bool FIRST = decltype(first_c)::value, BOTH = decltype(both_c)::value;
 #pragma unroll
@@ -686,8 +686,9 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
     if constexpr (SM) {
       round_pair(pf[S], 14, sum);
       constexpr bool BOTH = KW == 1 && EDGE;
-      if (__any(fmaxf(sum[0], sum[1]) > (BOTH && step == 1 ? -1.f : kLimit)))  // (the wave's second tile: whatever the sums are)
-        move_reference(sc[S], pf[S], sum, No{}, std::bool_constant<BOTH>{}, BOTH && step == 1 ? 8.f : 0.f);
+      const bool second = BOTH && step == p.second;  // (whatever the sums are)
+      if (__any(fmaxf(sum[0], sum[1]) > (second ? -1.f : kLimit)))
+        move_reference(sc[S], pf[S], sum, No{}, std::bool_constant<BOTH>{}, second ? 8.f : 0.f);
       l_run[0] += sum[0];
       l_run[1] += sum[1];
     }
@@ -979,6 +980,7 @@ hipError_t launch_variant(AttnDev p, const AttnArgs& a, hipStream_t s) {
   p.n_heads = a.n_heads;
   p.n_pairs = a.batch * a.n_heads;
   p.n_qt = (attn_most_rows(a.seq, a.idx != nullptr, a.many_rows, a.active) + 32 * QW - 1) / (32 * QW);
+  p.second = attn_second_reference(p.n_pairs, attn_most_rows(a.seq, a.idx != nullptr, a.many_rows, a.active)) ? 1 : 0;
   p.turn = attn_turn(p.n_pairs, a.idx != nullptr, a.many_rows);
   p.at_once = a.idx && !a.many_rows ? attn_at_once(p.n_pairs, a.seq, DH) : 0;
   const long grid = (long)((p.n_pairs + 7) / 8) * p.n_qt * 8;

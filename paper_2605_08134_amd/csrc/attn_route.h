@@ -59,6 +59,13 @@ constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, b
   return blocks(256) >= 256 ? AttnRoute::kTall : AttnRoute::kWide;
 }
 
+// kTall with heads of 128 channels: whether the reference exponent of the softmax moves to the second key tile's maximum.  Fewer
+// than 256 blocks of 256 rows would be kWide's if that were as fast; its second key-wave starts at a maximum of its own, and one
+// wave that keeps the first tile's is further from the exact result (130 x 129 tokens 2.12e-3 for 1.99e-3, 1 x 1152 of 32 heads
+// 2.30e-3 for 2.28e-3).  From 256 such blocks on kWide is no choice, and the move would take 0.5 us of a block (3 x 777 tokens of
+// 32 heads 47.7 -> 48.3 us, 4 x 512 24.2 -> 24.5; 3 x 512, which has it, 22.6 -> 23.3, kWide 28.6).
+constexpr bool attn_second_reference(long pairs, int rows) { return pairs * ((rows + 255) / 256) < 256; }
+
 // Order of the workgroups of an XCD where there is one per possible block (kNarrow, kWide, kTall): the first blocks
 // of `turn` (sequence, head)s, then their second ones, and so on; then the next `turn`.
 // Listed rows, how many only the device knows: eight take turns.  One by one, a workgroup with rows lies next to

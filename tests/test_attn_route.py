@@ -64,6 +64,32 @@ def test_all_rows_behind_a_frozen_prefix_count_without_it(route, batch, heads, s
     assert route(batch, heads, seq, True, True, True, active=active) == want
 
 
+SECOND = r"""
+#include <initializer_list>
+#include "attn_route.h"
+using namespace dare;
+int main() {
+  for (int batch = 1; batch <= 300; batch += batch < 20 ? 1 : 7)
+    for (int heads : {1, 4, 8, 16, 24, 32, 64})
+      for (int rows = 1; rows <= 4200; rows += 1 + rows / 37) {
+        const long b128 = (long)batch * heads * ((rows + 127) / 128), b256 = (long)batch * heads * ((rows + 255) / 256);
+        const bool tall = attn_route(batch, heads, 4200, true, true, true, 128, rows) == AttnRoute::kTall;
+        if (tall != (b128 > 256) || attn_second_reference((long)batch * heads, rows) != (b256 < 256)) return 1;
+        // heads of 64 have no second reference: two key-waves wherever the rule asks for one
+        if (attn_second_reference((long)batch * heads, rows) && attn_route(batch, heads, 4200, true, true, true, 64, rows) == AttnRoute::kTall) return 2;
+      }
+  return 0;
+}
+"""
+
+
+def test_a_second_reference_where_two_key_waves_were_the_other_choice(tmp_path):
+    (tmp_path / "second.cpp").write_text(SECOND)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"), str(tmp_path / "second.cpp"),
+                    "-o", str(tmp_path / "second")], check=True)
+    assert subprocess.run([str(tmp_path / "second")]).returncode == 0
+
+
 PLACES = r"""
 #include <cstdio>
 #include <vector>

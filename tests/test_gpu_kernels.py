@@ -519,13 +519,17 @@ def test_attention_blocks_of_128_rows_at_tile_edges(B, batch, heads, seq):
         assert np.all(np.abs(got[b].transpose(1, 0, 2) - want) <= bound)
 
 
-@pytest.mark.parametrize("batch,heads", [(1, 8), (9, 32)])       # two key-waves per block, none
-@pytest.mark.parametrize("seq", [32, 50, 64, 65, 100, 128])
-def test_attention_largest_probability_of_a_tile_is_not_rounded(B, batch, heads, seq):
-    """Each of the first two tiles of 64 keys has its own maximum as reference exponent: the output is that of
+@pytest.mark.parametrize("batch,heads,refs", [
+    (1, 8, (0, 1, 0)),      # two key-waves per block, each with the maximum of its first tile
+    (130, 1, (0, 1, 1)),    # the same up to 128 keys; then none, and the reference moves to the second tile's maximum
+    (9, 32, (0, 0, 0)),     # none; it does not
+])
+@pytest.mark.parametrize("seq", [32, 50, 64, 65, 100, 128, 129, 150, 192])
+def test_attention_largest_probability_of_a_tile_is_not_rounded(B, batch, heads, refs, seq):
+    """refs: the tile of 64 keys whose maximum is the reference exponent of each tile.  The output is that of
     probabilities rounded to bf16 relative to it, normalised by their sum and rounded once.  fp32 sums and exponentials, off by
     some 2^-22, give another bf16 value where the result is that close to the middle of two, 2^-8 apart: about one in
-    10^4 for the output and for a probability, of which up to 128 are in each."""
+    10^4 for the output and for a probability, of which up to 192 are in each."""
     r = _rng(seq + heads)
     q, k, v = (store(a * r.standard_normal((batch * seq, heads * 128)), "bf16") for a in (1.13, 1.13, 1.0))
     out = torch.zeros((batch * seq, heads * 128), dtype=torch.bfloat16, device="cuda")
@@ -535,7 +539,8 @@ def test_attention_largest_probability_of_a_tile_is_not_rounded(B, batch, heads,
     z = Q @ K.transpose(0, 1, 3, 2) / np.sqrt(128)
     num, den = 0.0, 0.0
     for t in range(0, seq, 64):
-        top = z[..., t:t + 64].max(-1, keepdims=True)
+        of = refs[t // 64] * 64
+        top = z[..., of:of + 64].max(-1, keepdims=True)
         pr = synth.round_to_bf16(np.exp(z[..., t:t + 64] - top).astype(np.float32)).astype(np.float64) * np.exp(top)
         num, den = num + pr @ V[..., t:t + 64, :], den + pr.sum(-1, keepdims=True)
     want = synth.round_to_bf16((num / den).astype(np.float32))
