@@ -584,40 +584,38 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
     for (int n = 0; n < 8; ++n)
       if (kv0 + (n >> 2) * 16 + kq * 4 + (n & 3) >= T) x[0][n >> 2][n & 3] = x[1][n >> 2][n & 3] = -INFINITY;
   };
-  // The reference exponents of the rows move to the maxima of this subtile (BOTH: and of the other set's, of the same
-  // tile), which is scored again.  Any reference gives the same result up to rounding (O and the row sum share it), so
-  // they only move when probabilities grow large, which a lane's sum of them tells without the maximum of every
-  // subtile.  FIRST: there is none yet.
-  // The largest probability of a tile that the reference is taken from is 1, without a rounding, and short rows are the nearer
-  // to their exact value the more of their tiles have that.  So the first reference is the maximum of the wave's first tile, and
-  // where attn_second_reference says so it moves to that of the second tile too, also down (lower: how far in base 2, which
-  // bounds the probabilities in the sums).  Error against float64 with the first subtile's maximum, the first tile's, the first
-  // two tiles' and with two key-waves, in 10^-3: 64 keys 2.08, 1.99, 1.99, 1.99; 129 keys 2.18, 2.12, 1.99, 1.99; 300 keys 2.25, 2.23,
-  // 2.16, 2.16; 1152 keys 2.32, 2.30, 2.29, 2.28.
-  auto move_reference = [&](const f32x4 (&x)[2][2], bf16x8 (&pr)[2], float (&sum)[2], auto first_c, auto both_c, float lower) __attribute__((always_inline)) {
-    constexpr bool FIRST = decltype(first_c)::value, BOTH = decltype(both_c)::value;
+  // The reference exponents of a block of 16 rows move to the maxima of this subtile, which is scored again, and of the other
+  // set's, the next subtile (keys past the end are copies of the last one there).  Any reference gives the
+  // same result up to rounding (O and the row sum share it), so they only move when probabilities grow large, which a lane's sum of
+  // them tells without the maximum of every subtile.  FIRST: there is none yet.
+  //   * Steep logits: nearly every subtile has a row that grows, and a move takes a wave 350 cycles per block.  Hence one block
+  //     alone, and the next subtile as well, which then seldom moves them again (us by standard deviation of the logits in nats, 1.6, 9,
+  //     25; attn_block, both blocks and this subtile, now: 1 x 1024 tokens of 32 heads 23.8 24.8 24.8, 22.4 29.2 30.3, 22.5 25.8 26.4; 8
+  //     x 2048 581 611 604, 543 605 617, 541 590 601; 3 x 777 58.0 60.8 60.9, 47.2 54.3 54.9, 47.3 52.9 54.8).
+  //   * The largest probability of a tile that the reference is taken from is 1, without a rounding, and short rows are the
+  //     nearer to their exact value the more of their tiles have that.  So the first reference is the maximum of the wave's first tile, and
+  //     where attn_second_reference says so it moves to that of the second tile too, also down (by 8 at most).  Error against
+  //     float64 with the first subtile's maximum, the first tile's, the first two tiles' and with two key-waves, in 10^-3: 64 keys 2.08,
+  //     1.99, 1.99, 1.99; 129 keys 2.18, 2.12, 1.99, 1.99; 300 keys 2.25, 2.23, 2.16, 2.16; 1152 keys 2.32, 2.30, 2.29, 2.28.
+  auto move_reference = [&](auto r_c, const f32x4 (&x)[2][2], const f32x4 (&next)[2][2], bf16x8 (&pr)[2], float (&sum)[2], auto first_c, bool second) __attribute__((always_inline)) {
+    constexpr int r = decltype(r_c)::value;
+    float top = x[r][0][0];
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      float top = x[r][0][0];
+    for (int n = 1; n < 8; ++n) top = fmaxf(top, x[r][n >> 2][n & 3]);
 #pragma unroll
-      for (int n = 1; n < 8; ++n) top = fmaxf(top, x[r][n >> 2][n & 3]);
-      if constexpr (BOTH) {  // (keys past the end are copies of the last one here)
+    for (int n = 0; n < 8; ++n) top = fmaxf(top, next[r][n >> 2][n & 3]);
+    top = quarters_max(top) * p.scale_log2;  // scale > 0
+    const float m_new = fmaxf(fmaxf(m_run[r] - (second ? 8.f : 0.f), top), -__FLT_MAX__);  // (finite: logits of -infinity have probability 0)
+    if constexpr (!decltype(first_c)::value) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run[r] - m_new);
+      l_run[r] *= alpha;
 #pragma unroll
-        for (int n = 0; n < 8; ++n) top = fmaxf(top, sc[1][r][n >> 2][n & 3]);
-      }
-      top = quarters_max(top) * p.scale_log2;  // scale > 0
-      const float m_new = fmaxf(fmaxf(m_run[r] - lower, top), -__FLT_MAX__);  // (finite: logits of -infinity have probability 0)
-      if constexpr (!FIRST) {
-        const float alpha = __builtin_amdgcn_exp2f(m_run[r] - m_new);
-        l_run[r] *= alpha;
-#pragma unroll
-        for (int c = 0; c < CB; ++c) acc[c][r] *= alpha;
-      }
-      m_run[r] = m_new;
-      sum[r] = 0.f;
+      for (int c = 0; c < CB; ++c) acc[c][r] *= alpha;
     }
+    m_run[r] = m_new;
+    sum[r] = 0.f;
 #pragma unroll
-    for (int n = 0; n < 16; n += 2) {
+    for (int n = 8 * r; n < 8 * r + 8; n += 2) {
       exp_one(x, n);
       exp_one(x, n + 1);
       round_pair(pr, n, sum);
@@ -685,10 +683,12 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (SM) {
       round_pair(pf[S], 14, sum);
-      constexpr bool BOTH = KW == 1 && EDGE;
-      const bool second = BOTH && step == p.second;  // (whatever the sums are)
-      if (__any(fmaxf(sum[0], sum[1]) > (second ? -1.f : kLimit)))
-        move_reference(sc[S], pf[S], sum, No{}, std::bool_constant<BOTH>{}, second ? 8.f : 0.f);
+      const bool second = KW == 1 && EDGE && step == p.second;
+      const float above = second ? -1.f : kLimit;  // (-1: whatever the sums are)
+      if (__any(fmaxf(sum[0], sum[1]) > above)) {
+        if (__any(sum[0] > above)) move_reference(S0{}, sc[S], sc[S ^ 1], pf[S], sum, No{}, second);
+        if (__any(sum[1] > above)) move_reference(S1{}, sc[S], sc[S ^ 1], pf[S], sum, No{}, second);
+      }
       l_run[0] += sum[0];
       l_run[1] += sum[1];
     }
@@ -715,7 +715,8 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
       mask_keys(sc[0], key_of(0));
       mask_keys(sc[1], key_of(0) + 32);
     }
-    move_reference(sc[0], pf[0], l_run, Yes{}, Yes{}, 0.f);
+    move_reference(S0{}, sc[0], sc[1], pf[0], l_run, Yes{}, false);
+    move_reference(S1{}, sc[0], sc[1], pf[0], l_run, Yes{}, false);
     for (int step = 1; step < mine; ++step) {
       period(S1{}, Yes{}, Yes{}, Yes{}, Yes{}, step);
       if (key_of(step) + 32 > T) mask_keys(sc[0], key_of(step));
