@@ -47,7 +47,10 @@ struct AttnDev {
   int n_heads, n_pairs, n_qt;  // heads, batch*heads, query blocks launched per (sequence, head)
   int batch;
   int turn, at_once;           // order of the workgroups, readers ahead (attn_turn, attn_at_once)
-  int second;                  // attn_wide without key-waves: tile whose maximum the reference moves to (attn_second_reference)
+  // attn_wide without key-waves (attn_second_reference): tile to whose maximum the reference exponent moves (0: none), sum of a
+  // lane's probabilities from which on maxima are looked for, and how far above it in base 2 one has to be
+  int second;
+  float limit, grow;
   // keys of a query block cut over workgroups (attn_rows_bf16_kernel): partial results, and
   // counters that are 0 before and after the launch; nullptr = never cut
   float* part_out;
@@ -458,9 +461,9 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
   constexpr int CB = DH / 16;                      // 16-channel blocks of the output
   constexpr int NP = CB;                           // fragments of K, and of V, that a subtile takes
   constexpr int AHEAD = 3, RING = AHEAD + 1;       // fragments read ahead of their MFMAs
-  // sum of a lane's probabilities from which on the reference moves (a probability is at most that, as in attn_block, and times
-  // a value of up to 1e36 finite)
-  constexpr float kLimit = 256.f;
+  // The reference exponent of a row moves to a maximum that is 2^grow above it, looked for where a lane's sum of probabilities
+  // exceeds limit.  8 as in attn_block: a probability is at most 256, and times a value of up to 1e36 finite.
+  const float grow = KW == 1 ? p.grow : 8.f, limit = KW == 1 ? p.limit : 256.f;
   static_assert(KSTAGE / 1024 % NW == 0 && NP % RING == 0, "loads and fragments must divide");
   using Yes = std::true_type;
   using No = std::false_type;
@@ -585,18 +588,21 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
       if (kv0 + (n >> 2) * 16 + kq * 4 + (n & 3) >= T) x[0][n >> 2][n & 3] = x[1][n >> 2][n & 3] = -INFINITY;
   };
   // The reference exponents of a block of 16 rows move to the maxima of this subtile, which is scored again, and of the other
-  // set's, the next subtile (keys past the end are copies of the last one there).  Any reference gives the
-  // same result up to rounding (O and the row sum share it), so they only move when probabilities grow large, which a lane's sum of
-  // them tells without the maximum of every subtile.  FIRST: there is none yet.
+  // set's, the next subtile (keys past the end are copies of the last one there), where those are far enough above.  Any reference
+  // gives the same result up to rounding (O and the row sum share it), so they only move when probabilities grow large, which a
+  // lane's sum of them tells without the maximum of every subtile.  FIRST: there is none yet.
   //   * Steep logits: nearly every subtile has a row that grows, and a move takes a wave 350 cycles per block.  Hence one block
   //     alone, and the next subtile as well, which then seldom moves them again (us by standard deviation of the logits in nats, 1.6, 9,
-  //     25; attn_block, both blocks and this subtile, now: 1 x 1024 tokens of 32 heads 23.8 24.8 24.8, 22.4 29.2 30.3, 22.5 25.8 26.4; 8
-  //     x 2048 581 611 604, 543 605 617, 541 590 601; 3 x 777 58.0 60.8 60.9, 47.2 54.3 54.9, 47.3 52.9 54.8).
-  //   * The largest probability of a tile that the reference is taken from is 1, without a rounding, and short rows are the
-  //     nearer to their exact value the more of their tiles have that.  So the first reference is the maximum of the wave's first tile, and
-  //     where attn_second_reference says so it moves to that of the second tile too, also down (by 8 at most).  Error against
-  //     float64 with the first subtile's maximum, the first tile's, the first two tiles' and with two key-waves, in 10^-3: 64 keys 2.08,
-  //     1.99, 1.99, 1.99; 129 keys 2.18, 2.12, 1.99, 1.99; 300 keys 2.25, 2.23, 2.16, 2.16; 1152 keys 2.32, 2.30, 2.29, 2.28.
+  //     25; attn_block, both blocks and this subtile, now: 1 x 1024 tokens of 32 heads 23.6 24.8 24.9, 22.3 29.2 30.3, 22.4 26.7 26.6; 8
+  //     x 2048 581 612 608, 540 604 620, 539 599 606; 3 x 777 58.2 61.0 61.2, 47.2 54.5 55.0, 47.1 55.2 56.1).  A row with less growth than
+  //     grow stays where it is: moving it along is 2 to 5 % faster, but leaves long rows with fewer exact largest probabilities
+  //     (1 x 4096 tokens, logits of 4 nats, error 1.883e-3 for 1.864e-3).
+  //   * The largest probability of a tile that the reference is taken from is 1, without a rounding, and rows are the nearer to their
+  //     exact value the more of their tiles have that.  So the first reference is the maximum of the wave's first tile, and one wave
+  //     in the place of two (attn_second_reference) moves to that of its second tile too, also down (by 8 at most), and moves with less
+  //     growth, to any maximum above.  Error against float64 in 10^-3 with the first subtile's maximum, the first tile's, this,
+  //     and with two key-waves: 129 keys 2.18, 2.12, 1.99, 1.99; 300 keys 2.25, 2.23, 2.16, 2.16; with logits of 4 nats, first tile and
+  //     second, this, two key-waves: 512 keys 1.80, 1.77, 1.83; 2560 keys 1.87, 1.83, 1.85; 3840 keys 1.88, 1.84, 1.85.
   auto move_reference = [&](auto r_c, const f32x4 (&x)[2][2], const f32x4 (&next)[2][2], bf16x8 (&pr)[2], float (&sum)[2], auto first_c, bool second) __attribute__((always_inline)) {
     constexpr int r = decltype(r_c)::value;
     float top = x[r][0][0];
@@ -605,7 +611,8 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
 #pragma unroll
     for (int n = 0; n < 8; ++n) top = fmaxf(top, next[r][n >> 2][n & 3]);
     top = quarters_max(top) * p.scale_log2;  // scale > 0
-    const float m_new = fmaxf(fmaxf(m_run[r] - (second ? 8.f : 0.f), top), -__FLT_MAX__);  // (finite: logits of -infinity have probability 0)
+    const float moved = second ? fmaxf(top, m_run[r] - 8.f) : top > m_run[r] + grow ? top : m_run[r];
+    const float m_new = fmaxf(moved, -__FLT_MAX__);  // (finite: logits of -infinity have probability 0)
     if constexpr (!decltype(first_c)::value) {
       const float alpha = __builtin_amdgcn_exp2f(m_run[r] - m_new);
       l_run[r] *= alpha;
@@ -684,7 +691,7 @@ __device__ __forceinline__ void attn_wide(const AttnDev& p, int b, int h, int qt
     if constexpr (SM) {
       round_pair(pf[S], 14, sum);
       const bool second = KW == 1 && EDGE && step == p.second;
-      const float above = second ? -1.f : kLimit;  // (-1: whatever the sums are)
+      const float above = second ? -1.f : limit;  // (-1: whatever the sums are)
       if (__any(fmaxf(sum[0], sum[1]) > above)) {
         if (__any(sum[0] > above)) move_reference(S0{}, sc[S], sc[S ^ 1], pf[S], sum, No{}, second);
         if (__any(sum[1] > above)) move_reference(S1{}, sc[S], sc[S ^ 1], pf[S], sum, No{}, second);
@@ -982,6 +989,8 @@ hipError_t launch_variant(AttnDev p, const AttnArgs& a, hipStream_t s) {
   p.n_pairs = a.batch * a.n_heads;
   p.n_qt = (attn_most_rows(a.seq, a.idx != nullptr, a.many_rows, a.active) + 32 * QW - 1) / (32 * QW);
   p.second = attn_second_reference(p.n_pairs, attn_most_rows(a.seq, a.idx != nullptr, a.many_rows, a.active)) ? 1 : 0;
+  p.limit = p.second ? 32.f : 256.f;
+  p.grow = p.second ? 0.f : 8.f;
   p.turn = attn_turn(p.n_pairs, a.idx != nullptr, a.many_rows);
   p.at_once = a.idx && !a.many_rows ? attn_at_once(p.n_pairs, a.seq, DH) : 0;
   const long grid = (long)((p.n_pairs + 7) / 8) * p.n_qt * 8;

@@ -59,7 +59,8 @@ constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, b
   return blocks(256) >= 256 ? AttnRoute::kTall : AttnRoute::kWide;
 }
 
-// kTall with heads of 128 channels: whether the reference exponent of the softmax moves to the second key tile's maximum.  Fewer
+// kTall with heads of 128 channels: whether the reference exponent of the softmax moves to the second key tile's maximum, and
+// later ones with less growth.  Fewer
 // than 256 blocks of 256 rows would be kWide's if that were as fast; its second key-wave starts at a maximum of its own, and one
 // wave that keeps the first tile's is further from the exact result (130 x 129 tokens 2.12e-3 for 1.99e-3, 1 x 1152 of 32 heads
 // 2.30e-3 for 2.28e-3).  From 256 such blocks on kWide is no choice, and the move would take 0.5 us of a block (3 x 777 tokens of

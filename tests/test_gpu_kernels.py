@@ -519,22 +519,9 @@ def test_attention_blocks_of_128_rows_at_tile_edges(B, batch, heads, seq):
         assert np.all(np.abs(got[b].transpose(1, 0, 2) - want) <= bound)
 
 
-@pytest.mark.parametrize("batch,heads,refs", [
-    (1, 8, (0, 1, 0)),      # two key-waves per block, each with the maximum of its first tile
-    (130, 1, (0, 1, 1)),    # the same up to 128 keys; then none, and the reference moves to the second tile's maximum
-    (9, 32, (0, 0, 0)),     # none; it does not
-])
-@pytest.mark.parametrize("seq", [32, 50, 64, 65, 100, 128, 129, 150, 192])
-def test_attention_largest_probability_of_a_tile_is_not_rounded(B, batch, heads, refs, seq):
-    """refs: the tile of 64 keys whose maximum is the reference exponent of each tile.  The output is that of
-    probabilities rounded to bf16 relative to it, normalised by their sum and rounded once.  fp32 sums and exponentials, off by
-    some 2^-22, give another bf16 value where the result is that close to the middle of two, 2^-8 apart: about one in
-    10^4 for the output and for a probability, of which up to 192 are in each."""
-    r = _rng(seq + heads)
-    q, k, v = (store(a * r.standard_normal((batch * seq, heads * 128)), "bf16") for a in (1.13, 1.13, 1.0))
-    out = torch.zeros((batch * seq, heads * 128), dtype=torch.bfloat16, device="cuda")
-    B.dare_k_attention(dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), out, batch, seq, heads, 128)
-    torch.cuda.synchronize()
+def _attention_of_rounded_probabilities(q, k, v, batch, seq, heads, refs):
+    """float64, but probabilities rounded to bf16 relative to the maximum of a tile of 64 keys and the output rounded
+    once: [sequence, head, row, channel].  refs: the tile whose maximum it is, per tile."""
     Q, K, V = (a.reshape(batch, seq, heads, 128).astype(np.float64).transpose(0, 2, 1, 3) for a in (q, k, v))
     z = Q @ K.transpose(0, 1, 3, 2) / np.sqrt(128)
     num, den = 0.0, 0.0
@@ -543,9 +530,44 @@ def test_attention_largest_probability_of_a_tile_is_not_rounded(B, batch, heads,
         top = z[..., of:of + 64].max(-1, keepdims=True)
         pr = synth.round_to_bf16(np.exp(z[..., t:t + 64] - top).astype(np.float32)).astype(np.float64) * np.exp(top)
         num, den = num + pr @ V[..., t:t + 64, :], den + pr.sum(-1, keepdims=True)
-    want = synth.round_to_bf16((num / den).astype(np.float32))
+    return synth.round_to_bf16((num / den).astype(np.float32))
+
+
+@pytest.mark.parametrize("batch,heads,refs", [
+    (1, 8, (0, 1, 0)),      # two key-waves per block, each with the maximum of its first tile
+    (130, 1, (0, 1, 1)),    # the same up to 128 keys; then none, and the reference moves to the second tile's maximum
+    (9, 32, (0, 0, 0)),     # none; it does not
+])
+@pytest.mark.parametrize("seq", [32, 50, 64, 65, 100, 128, 129, 150, 192])
+def test_attention_largest_probability_of_a_tile_is_not_rounded(B, batch, heads, refs, seq):
+    """refs: the tile whose maximum is the reference exponent of each tile.  fp32 sums and exponentials, off by some 2^-22, give
+    another bf16 value than float64 where the result is that close to the middle of two, 2^-8 apart: about one in 10^4
+    for the output and for a probability, of which up to 192 are in each."""
+    r = _rng(seq + heads)
+    q, k, v = (store(a * r.standard_normal((batch * seq, heads * 128)), "bf16") for a in (1.13, 1.13, 1.0))
+    out = torch.zeros((batch * seq, heads * 128), dtype=torch.bfloat16, device="cuda")
+    B.dare_k_attention(dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), out, batch, seq, heads, 128)
+    torch.cuda.synchronize()
     got = host(out).reshape(batch, seq, heads, 128).transpose(0, 2, 1, 3)
-    assert np.mean(got != want) <= 0.02
+    assert np.mean(got != _attention_of_rounded_probabilities(q, k, v, batch, seq, heads, refs)) <= 0.02
+
+
+def test_attention_reference_moves_by_its_own_rows_growth(B):
+    """Logits that grow by 5 (even rows) and by 12 (odd rows) in base 2 from the first tile to the second: only the odd
+    rows' reference exponents move, whatever their neighbours in the block do.  Bound as above."""
+    batch, heads, seq = 9, 32, 128
+    r = _rng(3)
+    q, k, v = (0.6 * r.standard_normal((batch, seq, heads, 128)) for _ in range(3))
+    q[..., 0] = np.where(np.arange(seq) % 2, 12.0, 5.0)[None, :, None]
+    k[..., 0] = np.where(np.arange(seq) < 64, 0.0, np.sqrt(128) / np.log2(np.e))[None, :, None]
+    q, k, v = (store(a.reshape(batch * seq, heads * 128), "bf16") for a in (q, k, v))
+    out = torch.zeros((batch * seq, heads * 128), dtype=torch.bfloat16, device="cuda")
+    B.dare_k_attention(dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), out, batch, seq, heads, 128)
+    torch.cuda.synchronize()
+    got = host(out).reshape(batch, seq, heads, 128).transpose(0, 2, 1, 3)
+    for first, refs in ((0, (0, 0)), (1, (0, 1))):
+        want = _attention_of_rounded_probabilities(q, k, v, batch, seq, heads, refs)
+        assert np.mean(got[:, :, first::2] != want[:, :, first::2]) <= 0.02
 
 
 def _one_dominant_key(B, batch, heads, seq, at, log2_logit):
