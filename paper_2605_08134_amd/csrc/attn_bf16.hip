@@ -440,10 +440,11 @@ constexpr int wide_smem_bytes() {  // two stages of K and of V, a tile of 64 key
 //     (of 2.4), and takes up to 10 % longer (and 30 registers more).
 //   * QW = 4, KW = 1: two workgroups of four waves per CU, out of step with each other, one multiplies while the other
 //     waits at its barrier or starts and ends.  One workgroup of eight waves (256 rows) pulls half as much from the L2 and is
-//     slower all the same wherever sequences are short (3 x 777 tokens 56.9 us, two workgroups 46.5; 16 x 256 34.4 and 31.6;
-//     8 x 2048 510 and 511; 1 x 4096 233 and 240).
-// us, before (32 x 32 x 16, logits, softmax and values one after the other, 256 rows) and now, 32 heads: 8 x 2048 551 and 511 (1.08
-// PFLOP/s), 1 x 4096 254 and 240, 3 x 777 58.6 and 46.5, 16 x 256 35.2 and 31.6; KW = 2, 1 x 1024 22.8 and 21.8.  Heads of 64 channels
+//     slower all the same wherever sequences are short (when it was chosen: 3 x 777 tokens 56.9 us, two workgroups 46.5; 16 x
+//     256 34.4 and 31.6; 8 x 2048 510 and 511; 1 x 4096 233 and 240).
+// us, before (32 x 32 x 16, logits, softmax and values one after the other, 256 rows) and now, 32 heads, random inputs, one card: 8 x
+// 2048 561 and 534 (1.03 PFLOP/s; in a step, behind the projection, 539 to 564), 1 x 4096 260 and 247, 3 x 777 58.4 and 47.5, 16 x 256 36.0 and
+// 32.1; KW = 2, 1 x 1024 23.3 and 22.2.  Heads of 64 channels
 // keep attn_block, whose 120 registers let four waves share a SIMD: they have half of the MFMAs per exponential (8 x 2048 of
 // 32 such heads 283 us, with this loop 282 to 325; 1 x 4096 142 and 150).
 // Not faster: loads between the MFMAs instead of in a row behind the barrier (2 to 6 % slower), four stages (5 % slower),
@@ -868,7 +869,8 @@ __global__ void __launch_bounds__(QW* KW * 64, 2) attn_bf16_kernel(AttnDev p) {
 // grid is as many workgroups as run at once (kRowsGrid) and the query blocks are laid out from the
 // counts: 64 rows per block while that gives at most one block per workgroup, else 128 (a K/V tile then
 // feeds twice the rows: 3 x 777 tokens, 194 rows each: 24 against 35 us; 1 x 1024, 205 rows: 18 us against
-// 21 us the other way round).  Few blocks over long sequences leave most CUs without one and the others
+// 21 us the other way round), whose last round runs as blocks of 64 rows where it would leave half of the workgroups
+// idle (attn_whole_blocks; heads of 128 channels).  Few blocks over long sequences leave most CUs without one and the others
 // with a long chain of key steps: their keys are cut over workgroups, in parts of at least kPartSteps
 // steps (the hand-over costs about as much as four).
 // Blocks are numbered by sequence, head, part, query block; consecutive ones, which share keys,

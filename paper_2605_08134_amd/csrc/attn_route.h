@@ -49,8 +49,8 @@ constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, b
   }
   // Most rows of every sequence.  Heads of 128 channels: a workgroup of four waves per block and two of them on a CU,
   // unless one per CU is enough for all blocks, which then have a second wave per SIMD on the other half of the keys (us,
-  // two key-waves and none, 32 heads: 1 x 1024 tokens, 256 blocks, 21.8 and 33; 1 x 1152 44.8 and 38.5, 1 x 1280 48.5 and 40.6, 1 x
-  // 1536 56.7 and 48.4, 3 x 512 28.6 and 22.9, 2 x 640 31.2 and 24.8, 1 x 1920 63.5 and 63.6).  Frozen rows have no
+  // two key-waves and none, 32 heads: 1 x 1024 tokens, 256 blocks, 22.2 and 24.6; 1 x 1152 45.5 and 38.4, 1 x 1280 49.1 and 42.3, 1 x
+  // 1536 57.0 and 49.2, 1 x 1920 69.2 and 62.5, 3 x 512 28.5 and 23.4, 2 x 640 31.6 and 25.6, 8 x 2048 622 and 534).  Frozen rows have no
   // block (dense steps, blocks of the whole sequence counted and of the others: 1 x 1536 tokens with 512 of them frozen 177 and 162 us,
   // 1 x 2560 of 16 heads with 768 frozen 145 and 118; heads of 64, 1 x 4096 of 16 with 2048 frozen 114 and 86).
   if (head_dim == 128) return blocks(128) > 256 ? AttnRoute::kTall : AttnRoute::kWide;
@@ -59,12 +59,11 @@ constexpr AttnRoute attn_route(long batch, long n_heads, int seq, bool listed, b
   return blocks(256) >= 256 ? AttnRoute::kTall : AttnRoute::kWide;
 }
 
-// kTall with heads of 128 channels: whether the reference exponent of the softmax moves to the second key tile's maximum, and
-// later ones with less growth.  Fewer
-// than 256 blocks of 256 rows would be kWide's if that were as fast; its second key-wave starts at a maximum of its own, and one
-// wave that keeps the first tile's is further from the exact result (130 x 129 tokens 2.12e-3 for 1.99e-3, 1 x 1152 of 32 heads
-// 2.30e-3 for 2.28e-3).  From 256 such blocks on kWide is no choice, and the move would take 0.5 us of a block (3 x 777 tokens of
-// 32 heads 47.7 -> 48.3 us, 4 x 512 24.2 -> 24.5; 3 x 512, which has it, 22.6 -> 23.3, kWide 28.6).
+// kTall with heads of 128 channels: whether the reference exponent of the softmax moves to the second key tile's maximum, and to
+// later ones with less growth.  Fewer than 256 blocks of 256 rows would be kWide's if that were as fast; its second key-wave starts
+// at a maximum of its own, and one wave that keeps the first tile's is further from the exact result (130 x 129 tokens 2.12e-3
+// for 1.99e-3, 1 x 1152 of 32 heads 2.30e-3 for 2.28e-3).  From 256 such blocks on kWide is no choice (4 x 512 tokens 29.5 us, kTall 24.3), and
+// the move would take 0.5 us of a block (3 x 777 47.7 -> 48.3 us, 4 x 512 24.2 -> 24.5; 3 x 512, which has it, 22.6 -> 23.3).
 constexpr bool attn_second_reference(long pairs, int rows) { return pairs * ((rows + 255) / 256) < 256; }
 
 // Order of the workgroups of an XCD where there is one per possible block (kNarrow, kWide, kTall): the first blocks
