@@ -443,7 +443,7 @@ constexpr int wide_smem_bytes() {  // two stages of K and of V, a tile of 64 key
 //     slower all the same wherever sequences are short (when it was chosen: 3 x 777 tokens 56.9 us, two workgroups 46.5; 16 x
 //     256 34.4 and 31.6; 8 x 2048 510 and 511; 1 x 4096 233 and 240).
 // us, before (32 x 32 x 16, logits, softmax and values one after the other, 256 rows) and now, 32 heads, random inputs, one card: 8 x
-// 2048 561 and 534 (1.03 PFLOP/s; in a step, behind the projection, 539 to 564), 1 x 4096 260 and 247, 3 x 777 58.4 and 47.5, 16 x 256 36.0 and
+// 2048 561 and 534 (1.03 PFLOP/s; in a step, by card, 540 to 570), 1 x 4096 260 and 247, 3 x 777 58.4 and 47.5, 16 x 256 36.0 and
 // 32.1; KW = 2, 1 x 1024 23.3 and 22.2.  Heads of 64 channels
 // keep attn_block, whose 120 registers let four waves share a SIMD: they have half of the MFMAs per exponential (8 x 2048 of
 // 32 such heads 283 us, with this loop 282 to 325; 1 x 4096 142 and 150).
