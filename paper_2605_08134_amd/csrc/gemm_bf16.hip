@@ -128,6 +128,14 @@ constexpr int smem_bytes() {
   return STAGES * (BM + BN) * ROW_BYTES;
 }
 
+// silu(g) * u.  The quotient by hand (reciprocal, product, one correction: within 0.51 of its last bit; special values by v_div_fixup):
+// the compiler's division, which also scales for the smallest and largest numbers, takes twice as long.  1 + exp(-g) above 2^126 (g below -87.3)
+// gives 0 for what is less than 1e-36.
+__device__ __forceinline__ float swiglu(float g, float u) {
+  const float d = 1.0f + __expf(-g), r = __builtin_amdgcn_rcpf(d), q = g * r;
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, q, g), r, q), d, g) * u;
+}
+
 // Epilogue of a wave tile: W (4 or 8) neighbouring output columns col[j] .. col[j] + W - 1 (col[j] a multiple
 // of W; a segment, whose width is a multiple of 32, holds all of them) of tokens tok[i], live[i] or not,
 // value(i, j, e) each.  Plain: the fp32 copy of the scored columns (before any rotation), then
@@ -152,7 +160,7 @@ __device__ __forceinline__ void store_tile(const GemmDev& p, float* c32, const i
 #pragma unroll
         for (int e = 0; e < W / 2; ++e) {
           const float g = value(i, j, 2 * e);
-          o[e] = (bf16_t)(g / (1.0f + __expf(-g)) * value(i, j, 2 * e + 1));
+          o[e] = (bf16_t)swiglu(g, value(i, j, 2 * e + 1));
         }
         if (live[i] && col[j] < p.n) *reinterpret_cast<half_t*>(row + (col[j] >> 1)) = o;
       }
@@ -601,7 +609,7 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
   return true;
 }
 
-// ---- large tiles: 256 x (64 TN), eight waves in two groups that take turns ---------------
+// ---- large tiles of listed rows, and with k cut: 256 x (64 TN), eight waves in two groups that take turns ----
 // Waves w and w + 4 sit on the same SIMD.  Waves 0-3 (group 0) own the left half of the tile's
 // columns, waves 4-7 (group 1) the right half, each wave 64 rows x 32 TN columns.  A k-step of 64 is
 // cut into TN phases, one per block of 32 columns, and a phase into a memory part (fragment
@@ -934,6 +942,383 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   return true;
 }
 
+// ---- large tiles of all rows: 256 x (64 TN), four waves, one per SIMD ---------------------
+// A wave owns 128 rows x 32 TN columns, its sums in the accumulator registers, which leaves the others to two sets of
+// fragments: a slice of 32 k is multiplied while the next one's fragments are read.  Against gemm_tile_pp, whose eight waves take 64
+// rows each: a third fewer bytes read from LDS per k-step (131 KB for 196), one barrier for eight, and what these kernels are bound
+// by, power, goes with both (a 256 x 256 tile with 192 k-steps, random operands: 278 us, without the loads into LDS 224, without the
+// fragment reads 250, with neither 201).
+//   * One instruction stream.  A read every three MFMAs, a load every eight (TN = 4), the address of a load one MFMA later, nothing
+//     between two MFMAs that takes longer than one.  The MFMAs are inline assembly: the compiler, which may put the sums into either kind of
+//     registers, moved 400 of them per k-step.  It does not know these as MFMAs, so their results wait by hand (s_nop).
+//   * LDS: half-stages A(0), B(0), A(1), B(1), .. of a k-step each through a ring of five slots, 160 KB.  The barrier of a
+//     k-step lies between its two slices: every wave has read A(kt) and B(kt), and A(kt + 1) and B(kt + 1) have landed.  In front of
+//     it A(kt + 2) is loaded (into the slot of B(kt - 1)), behind it B(kt + 2) (into that of A(kt)): a load has one to three
+//     slices of 1024 cycles to arrive; never waiting for any is no faster.
+//   * The pipeline runs on from tile to tile: a workgroup per CU walks its tiles, the last two k-steps load the next tile's
+//     first two and the last slice reads its first fragments, so a tile ends without an empty ring.  Behind the last tile they
+//     load their own k-steps again, into slots that nobody reads: the same code, where code of its own for the end and the start, fetched
+//     once per launch, cost a launch of one round 3 us (a dense step of 1 x 1024 tokens 2.2 % slower than with gemm_tile_pp, now level).
+//   * Stores of whole 128-byte lines: rows 0 .. 7 of a block of 16 in one store and 8 .. 15 in the next, two column blocks side
+//     by side (lanes L and L ^ 8 swap halves).  Stores count in vmcnt with the loads, in order, and the loads of the next tile
+//     wait for them: with 64-byte runs they took 9 us per round of the CUs.
+// The sum over k is formed as in gemm_tile_pp and gemm_tile16, so results are the same bits.
+// us, gemm_tile_pp (256 x 128, 192 and 256) and now, one card: 16384 x 12288 x 4096 1148 and 1076 (1.53 PFLOP/s), 16384 x 4096 x 4096 384 and 362,
+// 4096 x 24576 x 4096 608 and 541, 4096 x 4096 x 12288 272 and 262, 2331 x 12288 x 4096 184 and 177, 1024 x 24576 x 4096 151 and 145, 1024 x
+// 12288 x 4096 77.1 and 74.5, 2048 x 4096 x 4096 56.1 and 52.4.  In steps, where the operands come from other kernels: 4096 x 24576 with
+// the gate 570 and 547, 8192 x 24576 1123 and 1079, 4096 x 4096 x 12288 277 and 270, Q, K and V of 4096 rows, rotated, 314 and 297.
+// The gate of 128 x 128 sums takes a wave 2.8 us (with the compiler's division 5.5), the rotation 2.
+// gemm_tile_pp stays where k is cut over two workgroups (1024 x 4096 x 12288 92.6 us, in this form 103.6: half as many waves store and add
+// the sums) and for listed rows, whose kernel has the eight waves that the small shapes want.
+constexpr int kQuadSlot = kPpRows * ROW_BYTES, kQuadSmem = 5 * kQuadSlot;
+constexpr int kQuadMinSteps = 3;  // k-steps: loads two ahead, and the first one's zero sums
+
+// Value of a lane from the lane 8 further on in its row of 16, in the lanes of BANKS (four lanes each); `own` in the others
+template <int BANKS>
+__device__ __forceinline__ unsigned from_half_row(unsigned own, unsigned other) {
+  return __builtin_amdgcn_update_dpp(own, other, 0x128, 0xf, BANKS, false);
+}
+// STREAM: past the L2
+template <bool STREAM>
+__device__ __forceinline__ void store16(bf16_t* to, const u32x4 v) {
+  if constexpr (STREAM)
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(to));
+  else
+    *reinterpret_cast<u32x4*>(to) = v;
+}
+
+// The tiles blockIdx.x, blockIdx.x + gridDim.x, ..; called by all 256 threads.  k of kQuadMinSteps k-steps or more.
+template <int TN, bool STREAM>
+__device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, unsigned char* smem) {
+  static_assert(TN >= 2 && TN <= 4, "column blocks of 32 per wave");
+  constexpr int BM = kPpRows, BN = 64 * TN;
+  constexpr int SLOT = kQuadSlot;
+  constexpr int AL = BM / 8 / 4, BL = BN / 8 / 4;  // loads of a wave per half-stage
+  constexpr int NA = 8, NB = 2 * TN;               // fragments of a slice
+  constexpr int NM = NA * NB, NR = NA + NB;        // its MFMAs and reads
+
+  const int tiles_m = (m + BM - 1) / BM, tiles_n = (p.n + BN - 1) / BN;
+  const int total = tiles_m * tiles_n;
+  const int per_xcd = (total + 7) >> 3;
+  int vb = blockIdx.x, m0, n0;
+  auto place = [&]() __attribute__((always_inline)) {
+    const int slot = vb >> 3, unit = (vb & 7) * per_xcd + slot;
+    if (slot >= per_xcd || unit >= total) return false;
+    int tile_m, tile_n;
+    tile_of_unit(unit, tiles_m, tiles_n, tile_m, tile_n);
+    m0 = tile_m * BM;
+    n0 = tile_n * BN;
+    return true;
+  };
+  if (!place()) return;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave & 1, wn = wave >> 1;
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int KT = p.k / BK;
+
+  // the rows of this lane's loads
+  int tok_in[AL];
+  auto rows = [&]() __attribute__((always_inline)) {
+    int row_in[AL];
+#pragma unroll
+    for (int i = 0; i < AL; ++i) {
+      const int row = m0 + (wave * AL + i) * 8 + (lane >> 3);
+      row_in[i] = row < m ? row : m - 1;
+    }
+    row_tokens(p.idx, nullptr, row_in, tok_in);
+  };
+  const bf16_t* src_a[AL];
+  const bf16_t* src_b[BL];
+  auto addresses = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < AL; ++i) {
+      const int r = (wave * AL + i) * 8 + (lane >> 3);
+      src_a[i] = p.a + (long)tok_in[i] * p.lda + ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+    }
+#pragma unroll
+    for (int j = 0; j < BL; ++j) {
+      const int r = (wave * BL + j) * 8 + (lane >> 3);
+      const int col = n0 + r < p.n ? n0 + r : p.n - 1;
+      src_b[j] = p.wt + (long)col * p.k + ((lane & 7) ^ pp_bkey(r & 31)) * 8;
+    }
+  };
+  const unsigned lds0 = (unsigned)(size_t)(lptr_t)smem;
+  // (the address is an operand in M0, set by the compiler, which then knows what M0 holds; a wait state, or an MFMA,
+  // between the move to M0 and the load)
+  auto load = [&](const bf16_t*& src, unsigned lds) __attribute__((always_inline)) {
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(lds) : "memory");
+    src += BK;
+  };
+
+  f32x4 acc[NA][NB];
+  int a_off[2], b_off[2];
+  const int brow = (l16 >> 2) * 8 + (l16 & 3);
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    a_off[ks] = (wm * 128 + l16) * ROW_BYTES + ((ks * 4 + kq) ^ ((l16 >> 1) & 7)) * 16;
+    b_off[ks] = (wn * 32 * TN + brow) * ROW_BYTES + ((ks * 4 + kq) ^ pp_bkey(brow)) * 16;
+  }
+  bf16x8 fa[2][NA], fb[2][NB];
+  typedef const __attribute__((address_space(3))) bf16x8* lds_frag_t;
+  // read n of a slice: the first column's fragment, the rows', the other columns'
+  auto read = [&](auto ks_c, int n, unsigned at_a, unsigned at_b) __attribute__((always_inline)) {
+    constexpr int ks = decltype(ks_c)::value;
+    if (n >= 1 && n <= NA)
+      fa[ks][n - 1] = *(lds_frag_t)(at_a + (n - 1) * 16 * ROW_BYTES);
+    else {
+      const int j = n == 0 ? 0 : n - NA;
+      fb[ks][j] = *(lds_frag_t)(at_b + (j >> 1) * 32 * ROW_BYTES + (j & 1) * 4 * ROW_BYTES);
+    }
+  };
+  // the MFMAs of a slice with the next slice's reads and the loads of a half-stage between them
+  auto slice = [&](auto ks_c, auto zero_c, auto n_loads, const bf16_t** src, unsigned to, int at_a, int at_b) __attribute__((always_inline)) {
+    constexpr int ks = decltype(ks_c)::value, NL = decltype(n_loads)::value;
+    const unsigned ra = lds0 + at_a + a_off[ks ^ 1], rb = lds0 + at_b + b_off[ks ^ 1];
+    constexpr int RS = NM / NR < 3 ? NM / NR : 3, LS = NM / NL;  // MFMAs per read, per load
+    static_assert(RS * NR <= NM && LS > 3, "every fragment must have its read, every load its place");
+#pragma unroll
+    for (int t = 0; t < NM; ++t) {
+      const int j = t / NA, i = t % NA;
+      const int l = t / LS;
+      const bool loads = t % LS == 2 && l < NL;
+      if constexpr (decltype(zero_c)::value) {
+        if (loads)
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0\n\tglobal_load_lds_dwordx4 %3, off" : "=a"(acc[i][j]) : "v"(fb[ks][j]), "v"(fa[ks][i]), "v"(src[l]), "{m0}"(to + l * 1024) : "memory");
+        else
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc[i][j]) : "v"(fb[ks][j]), "v"(fa[ks][i]));
+      } else {
+        if (loads)
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tglobal_load_lds_dwordx4 %3, off" : "+a"(acc[i][j]) : "v"(fb[ks][j]), "v"(fa[ks][i]), "v"(src[l]), "{m0}"(to + l * 1024) : "memory");
+        else
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fb[ks][j]), "v"(fa[ks][i]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (t % RS == 0 && t / RS < NR) {
+        read(std::integral_constant<int, ks ^ 1>{}, t / RS, ra, rb);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (t % LS == 3 && l < NL) {  // (next to an MFMA of its own)
+        src[l] += BK;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+#define DARE_N(n) std::integral_constant<int, n>{}
+  using Yes = std::true_type;
+  using No = std::false_type;
+  auto wrap = [](int at) __attribute__((always_inline)) { return at >= 5 * SLOT ? at - 5 * SLOT : at; };
+  int at = 0;  // slot of A(kt)
+  auto kstep = [&](auto zero_c) __attribute__((always_inline)) {
+    const int b0 = wrap(at + SLOT), a1 = wrap(at + 2 * SLOT), b1 = wrap(at + 3 * SLOT), a2 = wrap(at + 4 * SLOT);
+    slice(DARE_N(0), zero_c, DARE_N(AL), src_a, lds0 + a2 + wave * AL * 1024, at, b0);
+    wait_vmcnt_and_barrier<AL>();
+    __builtin_amdgcn_sched_barrier(0);
+    slice(DARE_N(1), No{}, DARE_N(BL), src_b, lds0 + at + wave * BL * 1024, a1, b1);
+    at = a1;
+  };
+
+  rows();
+  addresses();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+#pragma unroll
+    for (int i = 0; i < AL; ++i) load(src_a[i], lds0 + 2 * k * SLOT + (wave * AL + i) * 1024);
+#pragma unroll
+    for (int j = 0; j < BL; ++j) load(src_b[j], lds0 + (2 * k + 1) * SLOT + (wave * BL + j) * 1024);
+  }
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      asm volatile("" : "+a"(acc[i][j]));
+    }
+  wait_vmcnt_and_barrier<AL + BL>();
+#pragma unroll
+  for (int n = 0; n < NR; ++n) read(DARE_N(0), n, lds0 + a_off[0], lds0 + SLOT + b_off[0]);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int kt = 0;;) {
+    int row_out[NA], tok[NA];
+    bool live[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int row = m0 + wm * 128 + i * 16 + l16;
+      live[i] = row < m;
+      row_out[i] = row < m ? row : m - 1;
+    }
+    row_tokens(p.idx, nullptr, row_out, tok);
+    const int col0 = n0 + wn * (32 * TN);
+    vb += gridDim.x;
+    const bool more = place();
+    if (more) rows();
+    for (; kt < KT; ++kt) {
+      if (kt == KT - 2) {
+        if (more) {
+          addresses();
+        } else {  // the last two k-steps again, into slots that nobody reads
+#pragma unroll
+          for (int i = 0; i < AL; ++i) src_a[i] -= 2 * BK;
+#pragma unroll
+          for (int j = 0; j < BL; ++j) src_b[j] -= 2 * BK;
+        }
+      }
+      kstep(No{});
+    }
+    // (what the compiler would know of MFMAs of its own: their results are there 18 cycles later)
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    auto value = [&](int i, int j, int e) __attribute__((always_inline)) {
+      float v;
+      asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(acc[i][j * 2 + (e >> 2)][e & 3]));
+      return v;
+    };
+    // acc[i][2 j + h][e] = C[row, col], row = m0 + 128 wm + 16 i + l16, col = col0 + 32 j + 8 kq + 4 h + e
+    const bool low = l16 < 8;
+    if (p.swiglu_pairs) {
+      const long ldc = p.ldc;
+#pragma unroll
+      for (int i = 0; i < NA; ++i) {
+        u32x2 o[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          bf16x4 r;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float g = value(i, j, 2 * e);
+            r[e] = (bf16_t)swiglu(g, value(i, j, 2 * e + 1));
+          }
+          o[j] = __builtin_bit_cast(u32x2, r);
+        }
+        // lanes kq and kq ^ 1 share two column blocks: 16 bytes of one of them each
+        u32x4 w[TN / 2];
+#pragma unroll
+        for (int j = 0; j + 1 < TN; j += 2)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const auto sw = __builtin_amdgcn_permlane16_swap(o[j][q], o[j + 1][q], false, false);
+            w[j / 2][q] = sw[0];
+            w[j / 2][q + 2] = sw[1];
+          }
+        bf16_t* own = p.c0 + tok[i] * ldc + (col0 >> 1);
+        const int at_col = (kq & 1) * 16 + (kq >> 1) * 8;
+        if constexpr (TN == 4) {
+          const int other = from_half_row<0xf>(0, tok[i]);
+          const bool live_other = from_half_row<0xf>(0, live[i]) != 0;
+          u32x4 x, y;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            x[q] = from_half_row<0xc>(w[0][q], w[1][q]);
+            y[q] = from_half_row<0x3>(w[1][q], w[0][q]);
+          }
+          bf16_t* far = p.c0 + other * ldc + (col0 >> 1);
+          const int c = at_col + (low ? 0 : 32);
+          const bool in = col0 + (low ? 0 : 64) < p.n;
+          if (in && (low ? live[i] : live_other)) store16<STREAM>((low ? own : far) + c, x);
+          if (in && (low ? live_other : live[i])) store16<STREAM>((low ? far : own) + c, y);
+        } else {
+          if (live[i] && col0 + (kq & 1) * 32 < p.n) store16<STREAM>(own + at_col, w[0]);
+          if (TN == 3 && live[i] && col0 + 64 < p.n) *reinterpret_cast<u32x2*>(own + 32 + kq * 4) = o[TN - 1];
+        }
+      }
+    } else {
+      if (p.c32 && col0 < p.c32_cols) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            const int c = col0 + (j >> 1) * 32 + kq * 8 + (j & 1) * 4;
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = value(i, j >> 1, (j & 1) * 4 + e);
+            if (live[i] && c < p.c32_cols) *reinterpret_cast<f32x4*>(p.c32 + (long)tok[i] * p.c32_cols + c) = v;
+          }
+      }
+      if (p.rope && col0 < p.rope_cols) {
+        // (the table's rows a row of the tile ahead of their use; columns that are not rotated read one that is)
+        f32x4 cs[2][NB];
+        auto table = [&](int i) __attribute__((always_inline)) {
+          const float* row = p.rope + (long)((unsigned)tok[i] % (unsigned)p.rope_seq) * p.rope_dh;
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            const int c = col0 + (j >> 1) * 32 + kq * 8 + (j & 1) * 4;
+            cs[i & 1][j] = *reinterpret_cast<const f32x4*>(row + ((unsigned)(c < p.rope_cols ? c : col0) % (unsigned)p.rope_dh >> 1) * 2);
+          }
+        };
+        table(0);
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+          if (i + 1 < NA) table(i + 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            const bool turns = col0 + (j >> 1) * 32 + kq * 8 + (j & 1) * 4 < p.rope_cols;
+            float v[4], w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = w[e] = value(i, j >> 1, (j & 1) * 4 + e);
+            rope_rotate4(cs[i & 1][j], w[0], w[1], w[2], w[3]);
+            acc[i][j] = f32x4{turns ? w[0] : v[0], turns ? w[1] : v[1], turns ? w[2] : v[2], turns ? w[3] : v[3]};
+            asm volatile("" : "+a"(acc[i][j]));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      // the column blocks' places: a pair's first block in the lanes of rows 0 .. 7, its second one in the others
+      bf16_t* base[(TN + 1) / 2];
+#pragma unroll
+      for (int j = 0; j < TN; j += 2) {
+        const int c = col0 + j * 32 + (j + 1 < TN && !low ? 32 : 0);
+        const int seg = (c >= p.seg_n) + (c >= 2 * p.seg_n);
+        bf16_t* to = c >= p.n ? nullptr : seg == 0 ? p.c0 : seg == 1 ? p.c1 : p.c2;
+        base[j / 2] = to ? to + (c - seg * p.seg_n) + kq * 8 : nullptr;
+      }
+      const long ldc = p.ldc;
+#pragma unroll
+      for (int i = 0; i < NA; ++i) {
+        const int other = from_half_row<0xf>(0, tok[i]);
+        const bool live_other = from_half_row<0xf>(0, live[i]) != 0;
+        const long own = tok[i] * ldc, far = other * ldc;
+#pragma unroll
+        for (int j = 0; j < TN; j += 2) {
+          u32x4 o[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            if (j + h < TN) {
+              bf16x8 r;
+#pragma unroll
+              for (int e = 0; e < 8; ++e) r[e] = (bf16_t)value(i, j + h, e);
+              o[h] = __builtin_bit_cast(u32x4, r);
+            }
+          bf16_t* to = base[j / 2];
+          if (j + 1 < TN) {
+            u32x4 x, y;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              x[q] = from_half_row<0xc>(o[0][q], o[1][q]);
+              y[q] = from_half_row<0x3>(o[1][q], o[0][q]);
+            }
+            if (to && (low ? live[i] : live_other)) store16<STREAM>(to + (low ? own : far), x);
+            if (to && (low ? live_other : live[i])) store16<STREAM>(to + (low ? far : own), y);
+          } else if (to && live[i]) {
+            store16<STREAM>(to + own, o[0]);
+          }
+        }
+      }
+    }
+    if (!more) break;
+    kstep(Yes{});
+    kt = 1;
+  }
+#undef DARE_N
+  wait_vmcnt<0>();
+}
+
+template <int TN, bool STREAM>
+__global__ void __launch_bounds__(256, 1) gemm_bf16_quad_kernel(GemmDev p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kQuadSmem];
+  gemm_tiles_quad<TN, STREAM>(p, p.m_max, smem);
+}
+
 // ---- very few rows (at most 16 TMS): a stream over the weight matrix ------------------
 // With a handful of refreshed rows (one or two tokens unmasked per denoising step) the
 // projection is a matrix-vector product in disguise: what matters is that every CU pulls on
@@ -1029,11 +1414,9 @@ __global__ void __launch_bounds__(512) gemm_bf16_tile16_kernel(GemmDev p) {
   gemm_tile16<BM, BN, WAVES_M, WAVES_N, STAGES>(p, p.m_max, smem, threadIdx.x, blockIdx.x);
 }
 
-template <int TN, bool SPLIT>
-__global__ void __launch_bounds__(512) gemm_bf16_pp_kernel(GemmDev p) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[pp_smem_bytes<TN>()];
-  const int m = p.m_max;
-  gemm_tile_pp<TN, SPLIT>(p, m, smem, blockIdx.x);
+__global__ void __launch_bounds__(512) gemm_bf16_pp_split_kernel(GemmDev p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[pp_smem_bytes<2>()];
+  gemm_tile_pp<2, true>(p, p.m_max, smem, blockIdx.x);
 }
 
 // ---- row count read on the device: the tile shape follows it -------------------------
@@ -1491,6 +1874,22 @@ GemmDev to_dev(const GemmArgs& g) {
 
 int grid_for(int tiles) { return ((tiles + 7) / 8) * 8; }
 
+// Outputs larger than half of the last-level cache (256 MB) are stored past the L2: what the stages behind them read first is
+// no longer there anyway, and the operands stay in its place (us, stored through the L2 and past it, in a step of 8 x 2048 tokens of hidden 4096:
+// Q, K and V, 403 MB, 1136 and 1130, the score, the normalisation and the residual sum around them 10.4 and 9.0, 46.2 and 45.7, 70.0
+// and 64.9).  Smaller ones are not: 25 MB, 1 x 1024 x 12288, leave the attention behind them 32.2 us, and 33.4 stored past it.
+constexpr long kStreamBytes = 128l << 20;
+template <int TN>
+hipError_t launch_quad(const GemmArgs& g, hipStream_t s) {
+  const int tiles = grid_for(tiles_of(g.m_max, g.n, kPpRows, 64 * TN));
+  const dim3 grid(tiles < kWideGrid ? tiles : kWideGrid);
+  if (TN == 4 && (long)g.m_max * g.n * (g.swiglu_pairs ? 1 : 2) > kStreamBytes)
+    hipLaunchKernelGGL((gemm_bf16_quad_kernel<TN, TN == 4>), grid, dim3(256), 0, s, to_dev(g));
+  else
+    hipLaunchKernelGGL((gemm_bf16_quad_kernel<TN, false>), grid, dim3(256), 0, s, to_dev(g));
+  return hipGetLastError();
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
 hipError_t launch_ranges(const GemmArgs& g, hipStream_t s) {
   GemmDev p = to_dev(g);
@@ -1508,12 +1907,10 @@ hipError_t launch_tile16(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int TN, bool SPLIT = false>
-hipError_t launch_pp(const GemmArgs& g, hipStream_t s) {
-  const int tiles = tiles_of(g.m_max, g.n, kPpRows, 64 * TN);
-  if (SPLIT && (tiles > kSplitTiles || !g.split_tiles || !g.split_count)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((gemm_bf16_pp_kernel<TN, SPLIT>), dim3(grid_for(SPLIT ? 2 * tiles : tiles)), dim3(512), 0, s,
-                     to_dev(g));
+hipError_t launch_pp_split(const GemmArgs& g, hipStream_t s) {
+  const int tiles = tiles_of(g.m_max, g.n, kPpRows, 128);
+  if (tiles > kSplitTiles || !g.split_tiles || !g.split_count) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(gemm_bf16_pp_split_kernel, dim3(grid_for(2 * tiles)), dim3(512), 0, s, to_dev(g));
   return hipGetLastError();
 }
 
@@ -1538,11 +1935,15 @@ hipError_t launch_rows_wide(const GemmArgs& g, hipStream_t s) {
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   if (g.m_dev || g.sel_mask) return launch_rows_wide(g, s);
   if (g.m_max == 0) return hipSuccess;
-  switch (gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles && !g.c32)) {
-    case GemmRoute::kPp128Split: return launch_pp<2, true>(g, s);
-    case GemmRoute::kPp256: return launch_pp<4>(g, s);
-    case GemmRoute::kPp192: return launch_pp<3>(g, s);
-    case GemmRoute::kPp128: return launch_pp<2>(g, s);
+  GemmRoute route = gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles && !g.c32);
+  // (one and two k-steps: the pipeline of gemm_tiles_quad, which runs on into the next tile, is longer)
+  if (g.k < kQuadMinSteps * BK && (route == GemmRoute::kPp256 || route == GemmRoute::kPp192 || route == GemmRoute::kPp128))
+    route = GemmRoute::k128x128;
+  switch (route) {
+    case GemmRoute::kPp128Split: return launch_pp_split(g, s);
+    case GemmRoute::kPp256: return launch_quad<4>(g, s);
+    case GemmRoute::kPp192: return launch_quad<3>(g, s);
+    case GemmRoute::kPp128: return launch_quad<2>(g, s);
     case GemmRoute::k128x192: return launch_tile16<128, 192, 2, 4, 3>(g, s);
     case GemmRoute::k128x128: return launch_tile16<128, 128, 2, 4, 4>(g, s);
     case GemmRoute::k128x96: return launch_tile16<128, 96, 4, 2, 4>(g, s);

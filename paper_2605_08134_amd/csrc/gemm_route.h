@@ -16,7 +16,7 @@ enum class GemmRoute {
   k128x96,
   k128x128,
   k128x192,
-  kPp128,       // ping-pong tiles of 256 rows x 128, 192, 256 columns
+  kPp128,       // 256 rows x 128, 192, 256 columns: four waves (gemm_tiles_quad) for all rows, ping-pong tiles for listed ones
   kPp192,
   kPp256,
   kPp256Cut,    // the last round of 256 x 256 cut into 128 x 128 (listed rows)

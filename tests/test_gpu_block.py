@@ -136,6 +136,37 @@ def test_residual_add(B, dtype, n):
         assert np.array_equal(got.astype(np.float64), orc.round_storage(want, "bf16"))
 
 
+# 256-row tiles of all rows, more of them than CUs (a workgroup walks several): 192, 256 and 128 columns, three k-steps and
+# more, a last row tile of 156, 34 and 48 rows, column tiles that hold the end of a segment or of the rotated columns
+@pytest.mark.parametrize("m,seg,k,listed", [
+    (2716, 2112, 192, False), (4130, 2112, 192, False), (3120, 1664, 192, False),
+    (2716, 2112, 256, True), (4130, 2112, 320, True), (3120, 1664, 256, True),
+])
+def test_gemm_rope_large_tiles_in_passes(B, m, seg, k, listed):
+    """What a projection of all rows, or of the rows behind a frozen prefix, writes: rotated, plain and fp32 columns."""
+    r = _rng(m + k)
+    dh, gaps = 64, 50 if listed else 0
+    n_tok, n = m + gaps, 3 * seg
+    a = store(r.standard_normal((n_tok, k), dtype=np.float32), "bf16")
+    w = store(r.standard_normal((k, n), dtype=np.float32) * np.float32(0.08), "bf16")
+    wt = B.dare_k_pack_weight(dev(w, "bf16"))
+    table = B.dare_k_rope_table(n_tok, dh, ROPE_BASE)
+    outs = [torch.full((n_tok, seg), 3.0, dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    c32 = torch.zeros((n_tok, 2 * dh), dtype=torch.float32, device="cuda")
+    rows = np.sort(r.permutation(n_tok)[:m]).astype(np.int32)
+    kw = dict(idx=dev(rows), m_max=m) if listed else {}
+    B.dare_k_gemm_rope(dev(a, "bf16"), wt, outs, seg, table, 2 * seg, dh, n_tok, c32=c32, **kw)
+    torch.cuda.synchronize()
+    y = a.astype(np.float64) @ w.astype(np.float64)
+    pos = np.arange(n_tok).astype(np.float64)
+    want = np.concatenate([orc.rope(y[:, :seg], pos, seg // dh, ROPE_BASE),
+                           orc.rope(y[:, seg:2 * seg], pos, seg // dh, ROPE_BASE), y[:, 2 * seg:]], axis=1)
+    got = np.concatenate([host(o) for o in outs], axis=1)
+    assert np.all(got[np.setdiff1d(np.arange(n_tok), rows)] == 3.0)
+    assert_close(got[rows], want[rows], "bf16")
+    assert rel_err(host(c32)[rows], y[rows, :2 * dh]) <= 2e-6
+
+
 # ------------------------------------------------------------------ the block step
 class GpuBlock(pu.GpuLayer):
     def __init__(self, case, norm, rope_base, residual, use_bias=True, **kw):
