@@ -286,7 +286,11 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
            ksteps / (k_ranges * 2) >= 4 && (size_t)n_tok * sw * (k_ranges * 2) <= ctx->q_new_elems)
       k_ranges *= 2;
   }
-  if (mode == DARE_MODE_KVO && cf.dtype == DARE_BF16 && sw == cf.head_dim && score_in_projection(n_act, d)) {
+  // Output reuse where most queries would be read by nobody: they are projected with K and V once the refreshed rows are known
+  // (k_ranges is 1: the scored columns are summed as a projection of all rows sums them)
+  const bool q_later = mode == DARE_MODE_O && cf.dtype == DARE_BF16 && sw == cf.head_dim && queries_of_listed_rows(n_act, d);
+  if (q_later ||
+      (mode == DARE_MODE_KVO && cf.dtype == DARE_BF16 && sw == cf.head_dim && score_in_projection(n_act, d))) {
     // only the scored columns of Q for every row, scored in the same launch
     ScoreProjArgs g{};
     g.a = hidden;
@@ -404,6 +408,31 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
       r.rope_cols = 2 * d;
     }
     if ((e = gemm(ctx, r, s)) != hipSuccess) return fail_hip(ctx, e, "refreshed-row projection");
+  }
+
+  if (q_later) {  // Alg. 2 line 7 for every row, line 2 for those that line 8 reads
+    GemmArgs r{};
+    r.a = hidden;
+    r.lda = d;
+    r.k = d;
+    r.wt = wq_t;
+    r.n = 3 * d;
+    r.m_max = n_act;
+    r.idx = act_idx;
+    r.part_n = d;
+    r.part_idx = ctx->sel_idx;
+    r.part_m_dev = n_sel;
+    r.c[0] = ctx->q_buf;
+    r.c[1] = k_cache;
+    r.c[2] = v_cache;
+    r.ldc = d;
+    r.seg_n = d;
+    r.k_parts = 1;
+    r.rope = bx.rope;
+    r.rope_cols = 2 * d;
+    r.rope_dh = cf.head_dim;
+    r.rope_seq = seq;
+    if ((e = launch_gemm_bf16(r, s)) != hipSuccess) return fail_hip(ctx, e, "K, V and refreshed-row projection");
   }
 
   // 5. Attention (Alg. 1 line 10 / Alg. 2 line 8).

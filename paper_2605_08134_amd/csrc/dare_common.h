@@ -74,6 +74,11 @@ struct GemmArgs {
   // are 0 before the first launch and that every launch leaves even; one launch at a time
   float* split_tiles;
   int* split_count;
+  // > 0 (bf16, a multiple of 64, k of 192 or more): columns [0, part_n) only for the rows part_idx [*part_m_dev] (token ids,
+  // as in idx), the others for all rows (idx, m_max); no c32
+  int part_n;
+  const int32_t* part_idx;
+  const int32_t* part_m_dev;
 };
 constexpr int kSelMaxTokens = 2048, kSelMaxTokensF32 = 1024;
 constexpr size_t gemm_split_tiles_bytes() { return (size_t)kSplitTiles * 2 * kPpRows * 128 * sizeof(float); }

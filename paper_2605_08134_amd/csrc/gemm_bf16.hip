@@ -74,6 +74,10 @@ struct GemmDev {
   // [tiles] counters; nullptr = one workgroup per tile
   float* split_tiles;
   int* split_count;
+  // columns [0, part_n) for the rows of a second list only (gemm_bf16_part_kernel)
+  int part_n;
+  const int32_t* part_idx;
+  const int32_t* part_m_dev;
 };
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
@@ -971,7 +975,7 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
 // gemm_tile_pp stays where k is cut over two workgroups (1024 x 4096 x 12288 92.6 us, in this form 103.6: half as many waves store and add
 // the sums) and for listed rows, whose kernel has the eight waves that the small shapes want.
 constexpr int kQuadSlot = kPpRows * ROW_BYTES, kQuadSmem = 5 * kQuadSlot;
-constexpr int kQuadMinSteps = 3;  // k-steps: loads two ahead, and the first one's zero sums
+constexpr int kQuadMinSteps = kPartMinSteps;  // k-steps: loads two ahead, and the first one's zero sums
 
 // Value of a lane from the lane 8 further on in its row of 16, in the lanes of BANKS (four lanes each); `own` in the others
 template <int BANKS>
@@ -988,8 +992,9 @@ __device__ __forceinline__ void store16(bf16_t* to, const u32x4 v) {
 }
 
 // The tiles blockIdx.x, blockIdx.x + gridDim.x, ..; called by all 256 threads.  k of kQuadMinSteps k-steps or more.
-template <int TN, bool STREAM>
-__device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, unsigned char* smem) {
+// PART: the columns from part_n on for all rows, those in front of it for the part_m rows of the second list.
+template <int TN, bool STREAM, bool PART = false>
+__device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, unsigned char* smem, const int part_m = 0) {
   static_assert(TN >= 2 && TN <= 4, "column blocks of 32 per wave");
   constexpr int BM = kPpRows, BN = 64 * TN;
   constexpr int SLOT = kQuadSlot;
@@ -997,17 +1002,29 @@ __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, u
   constexpr int NA = 8, NB = 2 * TN;               // fragments of a slice
   constexpr int NM = NA * NB, NR = NA + NB;        // its MFMAs and reads
 
-  const int tiles_m = (m + BM - 1) / BM, tiles_n = (p.n + BN - 1) / BN;
-  const int total = tiles_m * tiles_n;
+  const int first_n = PART ? p.part_n : 0;
+  const int tiles_m = (m + BM - 1) / BM, tiles_n = (p.n - first_n + BN - 1) / BN, all = tiles_m * tiles_n;
+  const int part_tiles_m = (part_m + BM - 1) / BM, part_tiles_n = (first_n + BN - 1) / BN;
+  const int total = all + part_tiles_m * part_tiles_n;
   const int per_xcd = (total + 7) >> 3;
   int vb = blockIdx.x, m0, n0;
+  int rows_end = m, cols_end = p.n;     // of the tile's list and columns
+  const int32_t* list = p.idx;
   auto place = [&]() __attribute__((always_inline)) {
     const int slot = vb >> 3, unit = (vb & 7) * per_xcd + slot;
     if (slot >= per_xcd || unit >= total) return false;
     int tile_m, tile_n;
-    tile_of_unit(unit, tiles_m, tiles_n, tile_m, tile_n);
+    if (!PART || unit < all) {
+      tile_of_unit(unit, tiles_m, tiles_n, tile_m, tile_n);
+      n0 = first_n + tile_n * BN;
+    } else {
+      tile_of_unit(unit - all, part_tiles_m, part_tiles_n, tile_m, tile_n);
+      n0 = tile_n * BN;
+      rows_end = part_m;
+      cols_end = first_n;
+      list = p.part_idx;
+    }
     m0 = tile_m * BM;
-    n0 = tile_n * BN;
     return true;
   };
   if (!place()) return;
@@ -1025,9 +1042,9 @@ __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, u
 #pragma unroll
     for (int i = 0; i < AL; ++i) {
       const int row = m0 + (wave * AL + i) * 8 + (lane >> 3);
-      row_in[i] = row < m ? row : m - 1;
+      row_in[i] = row < rows_end ? row : rows_end - 1;
     }
-    row_tokens(p.idx, nullptr, row_in, tok_in);
+    row_tokens(list, nullptr, row_in, tok_in);
   };
   const bf16_t* src_a[AL];
   const bf16_t* src_b[BL];
@@ -1040,7 +1057,7 @@ __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, u
 #pragma unroll
     for (int j = 0; j < BL; ++j) {
       const int r = (wave * BL + j) * 8 + (lane >> 3);
-      const int col = n0 + r < p.n ? n0 + r : p.n - 1;
+      const int col = n0 + r < cols_end ? n0 + r : cols_end - 1;
       src_b[j] = p.wt + (long)col * p.k + ((lane & 7) ^ pp_bkey(r & 31)) * 8;
     }
   };
@@ -1145,11 +1162,11 @@ __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, u
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       const int row = m0 + wm * 128 + i * 16 + l16;
-      live[i] = row < m;
-      row_out[i] = row < m ? row : m - 1;
+      live[i] = row < rows_end;
+      row_out[i] = row < rows_end ? row : rows_end - 1;
     }
-    row_tokens(p.idx, nullptr, row_out, tok);
-    const int col0 = n0 + wn * (32 * TN);
+    row_tokens(list, nullptr, row_out, tok);
+    const int col0 = n0 + wn * (32 * TN), n_end = cols_end;
     vb += gridDim.x;
     const bool more = place();
     if (more) rows();
@@ -1213,12 +1230,12 @@ __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, u
           }
           bf16_t* far = p.c0 + other * ldc + (col0 >> 1);
           const int c = at_col + (low ? 0 : 32);
-          const bool in = col0 + (low ? 0 : 64) < p.n;
+          const bool in = col0 + (low ? 0 : 64) < n_end;
           if (in && (low ? live[i] : live_other)) store16<STREAM>((low ? own : far) + c, x);
           if (in && (low ? live_other : live[i])) store16<STREAM>((low ? far : own) + c, y);
         } else {
-          if (live[i] && col0 + (kq & 1) * 32 < p.n) store16<STREAM>(own + at_col, w[0]);
-          if (TN == 3 && live[i] && col0 + 64 < p.n) *reinterpret_cast<u32x2*>(own + 32 + kq * 4) = o[TN - 1];
+          if (live[i] && col0 + (kq & 1) * 32 < n_end) store16<STREAM>(own + at_col, w[0]);
+          if (TN == 3 && live[i] && col0 + 64 < n_end) *reinterpret_cast<u32x2*>(own + 32 + kq * 4) = o[TN - 1];
         }
       }
     } else {
@@ -1269,7 +1286,7 @@ __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, u
       for (int j = 0; j < TN; j += 2) {
         const int c = col0 + j * 32 + (j + 1 < TN && !low ? 32 : 0);
         const int seg = (c >= p.seg_n) + (c >= 2 * p.seg_n);
-        bf16_t* to = c >= p.n ? nullptr : seg == 0 ? p.c0 : seg == 1 ? p.c1 : p.c2;
+        bf16_t* to = c >= n_end ? nullptr : seg == 0 ? p.c0 : seg == 1 ? p.c1 : p.c2;
         base[j / 2] = to ? to + (c - seg * p.seg_n) + kq * 8 : nullptr;
       }
       const long ldc = p.ldc;
@@ -1311,6 +1328,18 @@ __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, u
   }
 #undef DARE_N
   wait_vmcnt<0>();
+}
+
+// Columns [0, part_n) for the listed rows, whose count the device knows, and the others for all rows: one launch for
+// both, in the shape of the least cost.
+__global__ void __launch_bounds__(256, 1) gemm_bf16_part_kernel(GemmDev p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kQuadSmem];
+  const int part_m = *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p.part_m_dev;
+  switch (part_columns(p.m_max, p.n, part_m, p.part_n)) {
+    case 2: return gemm_tiles_quad<2, false, true>(p, p.m_max, smem, part_m);
+    case 3: return gemm_tiles_quad<3, false, true>(p, p.m_max, smem, part_m);
+    default: return gemm_tiles_quad<4, false, true>(p, p.m_max, smem, part_m);
+  }
 }
 
 template <int TN, bool STREAM>
@@ -1869,6 +1898,9 @@ GemmDev to_dev(const GemmArgs& g) {
   p.ahead = 0;
   p.split_tiles = g.split_tiles;
   p.split_count = g.split_count;
+  p.part_n = g.part_n;
+  p.part_idx = g.part_idx;
+  p.part_m_dev = g.part_m_dev;
   return p;
 }
 
@@ -1933,6 +1965,14 @@ hipError_t launch_rows_wide(const GemmArgs& g, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
+  if (g.part_n > 0) {
+    if (g.m_max == 0) return hipSuccess;
+    if (g.m_dev || g.sel_mask || g.c32 || g.swiglu_pairs || !g.part_idx || !g.part_m_dev || g.part_n >= g.n || g.part_n % 64 != 0 ||
+        g.k < kQuadMinSteps * BK)
+      return hipErrorInvalidValue;
+    hipLaunchKernelGGL(gemm_bf16_part_kernel, dim3(kWideGrid), dim3(256), 0, s, to_dev(g));
+    return hipGetLastError();
+  }
   if (g.m_dev || g.sel_mask) return launch_rows_wide(g, s);
   if (g.m_max == 0) return hipSuccess;
   GemmRoute route = gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles && !g.c32);

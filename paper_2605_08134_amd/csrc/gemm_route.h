@@ -119,6 +119,48 @@ constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace)
   return best;
 }
 
+// What `tiles` tiles of 256 rows x 64 tn columns take in the four-wave form, in tile_cost's units (64 k-steps, one full round:
+// 52, 74 and 90 us).
+constexpr long quad_cost(long tiles, int tn) {
+  const long rounds = (tiles + 255) / 256;
+  return (tn == 2 ? 750 : tn == 3 ? 1050 : 1290) * (rounds * 256 + tiles);
+}
+
+// Columns [0, part_n) for part_m listed rows and [part_n, n) for all m rows in one launch: its tiles, and the width
+// (in 64 columns) of the least cost
+constexpr long part_tiles(int m, int n, int part_m, int part_n, int tn) {
+  return (long)tiles_of(m, n - part_n, kPpRows, 64 * tn) + tiles_of(part_m, part_n, kPpRows, 64 * tn);
+}
+__attribute__((always_inline)) constexpr int part_columns(int m, int n, int part_m, int part_n) {
+  int best = 4;
+  long least = quad_cost(part_tiles(m, n, part_m, part_n, 4), 4);
+  for (int tn = 3; tn >= 2; --tn) {
+    const long cost = quad_cost(part_tiles(m, n, part_m, part_n, tn), tn);
+    if (cost < least) {
+      least = cost;
+      best = tn;
+    }
+  }
+  return best;
+}
+
+// Output reuse (mode O): queries for the refreshed rows only, with K and V of all rows in one launch, instead of Q, K and V of all
+// rows.  The score then has its own pass over the hidden states, 6 us and 1.8 ns per row and 4096 of k more than what it takes as a
+// by-product, so the launch has to save rounds, or most of a round, with half of the tokens refreshed too; below 1024 rows
+// there is only one.  Block steps, 10, 30 and 50 % refreshed, Q of all rows and now (us): 1 x 1500 of 4096 195 161, 208 177, 235 208;
+// 1 x 2048 221 217, 252 253, 263 268; 3 x 777 252 225, 274 253, 301 307; 4 x 800 345 275, 365 304, 397 371; 4 x 1024 376 333, 424 421, 440
+// 442; 5 x 1024 473 394, 520 454, 561 562; 8 x 2048 25 % 1510 1315; 4 x 700 of 2048 127 106, 133 113, 139 124; 4 x 1400 of 1024 106 93, 109 98,
+// 133 121; but 1 x 600 of 4096 111 112, 111 112, 117 122.
+constexpr int kPartMinSteps = 3, kPartMinRows = 1024;
+constexpr bool queries_of_listed_rows(int m, int d) {
+  const int n = 3 * d, ksteps = d / kRouteBK;
+  if (ksteps < kPartMinSteps || m < kPartMinRows || tiles_of(m, n, kPpRows, 128) > (1 << 20)) return false;
+  const GemmRoute now = best_tile(m, n, false);
+  if (now != GemmRoute::kPp128 && now != GemmRoute::kPp192 && now != GemmRoute::kPp256) return false;
+  const int tn = part_columns(m, n, m / 2, d), all_tn = part_columns(m, n, 0, 0);
+  return quad_cost(part_tiles(m, n, m / 2, d, tn), tn) + 13l * m + 44000l * 64 / ksteps < quad_cost(part_tiles(m, n, 0, 0, all_tn), all_tn);
+}
+
 // Row list made in the kernel: loads per wave that bring the first 256 k of an XCD's share of n weight rows into its L2, two
 // rows by each of eight waves of a workgroup.  At most 8: 2 MB of the L2's 4 with a workgroup on every CU.
 constexpr int ahead_loads(int n, int workgroups) {

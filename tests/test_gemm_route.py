@@ -203,6 +203,40 @@ def test_gpu_tests_reach_the_shapes_that_they_name(tmp_path):
     assert {want[s] for s in want if s[0]} == {"64 x 64", "128 x 48", "128 x 64", "256 x 256 cut"} | large
 
 
+PART = r"""
+#include <cstdio>
+#include "gemm_route.h"
+using namespace dare;
+int main() {
+  long bad = 0, later = 0;
+  const struct { int m, d; bool want; } at[] = {
+      {2700, 2048, true}, {5600, 1024, true}, {2331, 4096, true}, {16384, 4096, true}, {1 << 29, 64, false}, {1 << 29, 4096, false},
+      {600, 4096, false}, {1024, 4096, false}, {1023, 8192, false}, {4096, 512, false}, {4096, 128, false}};
+  for (const auto& c : at)
+    if (queries_of_listed_rows(c.m, c.d) != c.want) std::printf("%d x %d\n", c.m, c.d), ++bad;
+  for (int d = 64; d <= 8192; d += 64)
+    for (int m = 1; m <= 40000; m = m < 600 ? m + 13 : m + 397) {
+      if (queries_of_listed_rows(m, d)) {
+        ++later;
+        if (m < kPartMinRows || d / kRouteBK < kPartMinSteps) ++bad;
+      }
+      for (int part = 0; part <= m; part += m / 3 + 1) {
+        const int tn = part_columns(m, 3 * d, part, d);
+        for (int o = 2; o <= 4; ++o)
+          if (tn < 2 || tn > 4 || quad_cost(part_tiles(m, 3 * d, part, d, o), o) < quad_cost(part_tiles(m, 3 * d, part, d, tn), tn)) ++bad;
+      }
+    }
+  std::printf("later %ld bad %ld\n", later, bad);
+  return bad != 0;
+}
+"""
+
+
+def test_queries_behind_the_score_where_they_save_rounds(tmp_path):
+    r = _run(tmp_path, PART)
+    assert r.returncode == 0, r.stdout
+
+
 LISTED = r"""
 #include <cstdio>
 #include "gemm_route.h"

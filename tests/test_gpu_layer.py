@@ -72,6 +72,28 @@ def test_unchanged_tokens_score_zero_in_the_scored_columns_alone(batch, seq, hid
     _unchanged_tokens_score_zero(batch, seq, hidden, first, orc.MODE_KVO, 0)
 
 
+# sizes of queries_of_listed_rows (tests/test_gemm_route.py): the device picks 256 x 192 and 256 x 256 tiles for them
+QUERIES_LATER = [(3, 900, 2048, 128), (4, 1400, 1024, 64)]
+
+
+@pytest.mark.parametrize("batch,seq,hidden,dh", QUERIES_LATER)
+def test_queries_of_the_refreshed_rows_only(batch, seq, hidden, dh):
+    """Mode O with the queries projected behind the score, in the launch of K and V: every row, some, one and none refreshed."""
+    case = synth.make_case("llada8b", seed=seq, batch=batch, seq=seq, hidden=hidden, n_heads=hidden // dh, head_dim=dh,
+                           fraction=(0.05, 0.4))
+    state, gl = pu.oracle_fill(case), pu.GpuLayer(case)
+    s = np.sort(pu.oracle_step(case, state, orc.MODE_O, 0.0)["scores"].reshape(-1))
+    for tau in (-1.0, synth.TAU_SEPARATING, float(np.float32(0.5 * (s[-1] + s[-2]))), 2.5):
+        _run(case, gl, state, orc.MODE_O, tau)
+    gl.layer.destroy()
+
+
+@pytest.mark.parametrize("first,second", [(orc.MODE_DENSE, orc.MODE_O), (orc.MODE_O, orc.MODE_KV), (orc.MODE_O, orc.MODE_O)])
+@pytest.mark.parametrize("batch,seq,hidden", [(3, 900, 2048), (3, 777, 4096)])
+def test_unchanged_tokens_score_zero_where_queries_come_later(batch, seq, hidden, first, second):
+    _unchanged_tokens_score_zero(batch, seq, hidden, first, second, 0)
+
+
 def _unchanged_tokens_score_zero(batch, seq, hidden, first, second, score_head):
     """The query of a token whose hidden state did not move is the same bit for bit in the next step,
     also when that step projects the scored columns in a launch of another width: drift exactly

@@ -68,6 +68,19 @@ def test_prefix_small_bf16(shape, P, mode):
     gl.layer.destroy()
 
 
+def test_prefix_with_queries_of_the_refreshed_rows_only():
+    """Mode O, 2700 rows left at hidden 2048: K and V of the listed rows and Q of the refreshed ones in one launch."""
+    P = 50
+    case = synth.make_case("llada8b", seed=950, batch=3, seq=950, hidden=2048, n_heads=16, head_dim=128, fraction=0.3)
+    state, gl = pu.oracle_fill(case), pu.GpuLayer(case)
+    gl.layer.set_prefix(P)
+    want = _oracle(case, state, orc.MODE_O, synth.TAU_SEPARATING, P)
+    got = gl.step(orc.MODE_O, synth.TAU_SEPARATING, case["x_cur"], state)
+    pu.check_step(got, want, state, orc.MODE_O, synth.TAU_SEPARATING, "bf16")
+    _frozen_rows_untouched(got, state, P)
+    gl.layer.destroy()
+
+
 @pytest.mark.parametrize("P", [400, 424])
 @pytest.mark.parametrize("mode", [orc.MODE_DENSE, orc.MODE_O])
 def test_prefix_leaves_rows_between_the_projection_routes(mode, P):
