@@ -1449,7 +1449,7 @@ __global__ void __launch_bounds__(512) gemm_bf16_pp_split_kernel(GemmDev p) {
 }
 
 // ---- row count read on the device: the tile shape follows it -------------------------
-// One kernel for every projection of refreshed rows, 8 waves and 144 KiB of LDS, one workgroup per CU
+// One kernel for every projection of refreshed rows that has a choice of shapes, 8 waves and 144 KiB of LDS, one workgroup per CU
 // whatever the count turns out to be (a grid sized for the worst case, whose surplus workgroups
 // return at once, costs 1 us more at 205 rows); the shape is the one that best_tile (gemm_route.h) names, and
 // its tiles are walked in passes.
@@ -1541,29 +1541,18 @@ __device__ __forceinline__ int derive_rows(const GemmDev& p, int32_t* list, int*
   return total;
 }
 
-// FUSED: the row list is derived from the mask bytes inside the kernel (two instantiations,
-// so that the plain one carries none of the list handling).
+// The count of listed rows and, FUSED, the list derived from the mask bytes inside the kernel (two instantiations,
+// so that the plain one carries none of the list handling), behind STAGES bytes of stage memory: 64 bytes of sums, the
+// list, 1 KiB that nobody reads; else that KiB alone.
 template <bool FUSED>
-__global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
-  // A row list derived from the mask lies behind the stage memory for the whole launch.  (In the stage memory
-  // it had to be read before the first load into LDS, a barrier between them, and derived again, seven copies of
-  // that code and 152 spilled scalars, in front of every further pass.  Steps, with the shape in line: 2 x 201 tokens
-  // of hidden 512 28.5 -> 27.6 us, 1 x 1024 of 4096 with 4 refreshed rows 60.9 -> 60.4, with 205 rows 89.8 -> 89.4.
-  // One array for both: see score_proj_kernel.)
-  constexpr int kListBytes = FUSED ? 64 + kSelMaxTokens * 4 + 1024 : 1024;
-  static_assert(kWideSmem + kListBytes <= 160 * 1024, "stage memory and row list must fit the LDS of a CU");
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kWideSmem + kListBytes];
-  static_assert(smem_bytes<64, 64, 8>() <= kWideSmem && smem_bytes<128, 48, 5>() <= kWideSmem &&
-                    smem_bytes<128, 64, 4>() <= kWideSmem && smem_bytes<128, 96, 4>() <= kWideSmem &&
-                    smem_bytes<128, 192, 3>() <= kWideSmem && smem_bytes<128, 128, 4>() <= kWideSmem &&
-                    pp_smem_bytes<3>() <= kWideSmem && pp_smem_bytes<4>() <= kWideSmem,
-                "shared buffer too small");
-  int m;
-  lds_idx_t lidx = nullptr;
+constexpr int kListBytes = FUSED ? 64 + kSelMaxTokens * 4 + 1024 : 1024;
+template <bool FUSED, int STAGES>
+__device__ __forceinline__ int listed_rows(const GemmDev& p, unsigned char* smem, lds_idx_t& lidx) {
   if constexpr (FUSED) {
-    int32_t* list = reinterpret_cast<int32_t*>(smem + kWideSmem + 64);
-    m = derive_rows(p, list, reinterpret_cast<int*>(smem + kWideSmem), smem + kWideSmem + 64 + kSelMaxTokens * 4);
+    int32_t* list = reinterpret_cast<int32_t*>(smem + STAGES + 64);
+    const int m = derive_rows(p, list, reinterpret_cast<int*>(smem + STAGES), smem + STAGES + 64 + kSelMaxTokens * 4);
     lidx = (lds_idx_t)list;
+    return m;
   } else {
     // (the weights ahead as in derive_rows, 16 rows per workgroup: the count and the list are a shorter wait, and the
     // list, which comes behind these loads, must not wait for more.  Steps over 1 x 1024 tokens with 205 refreshed rows, hidden
@@ -1573,20 +1562,53 @@ __global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
     const int last = first + per_xcd < p.n ? first + per_xcd - 1 : p.n - 1;
     const int r = first + ((blockIdx.x >> 3) * 8 + wave) * 2 + (lane >> 5);
     const bf16_t* ahead = p.wt + (long)(r < last ? r : last) * p.k + ((lane & 31) * 8 < p.k ? (lane & 31) * 8 : 0);
-    __builtin_amdgcn_global_load_lds((gptr_t)ahead, (lptr_t)(smem + kWideSmem), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((gptr_t)ahead, (lptr_t)(smem + STAGES), 16, 0, 0);
     // (a scalar load, which does not wait for the weights)
-    m = p.m_dev ? *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p.m_dev : p.m_max;
+    return p.m_dev ? *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p.m_dev : p.m_max;
   }
+}
+// Up to 32 rows and a narrow output (the output projection): the register-fed stream
+// (measured at n = 4096: 11-15 us against 17 us for 64 x 64 tiles, which give that width
+// only 64 workgroups).  Wide outputs keep the 64 x 64 tiles for few rows: with 192
+// column tiles they already stream the weights at 5 TB/s.
+__device__ __forceinline__ bool few_rows(const GemmDev& p, const int m, unsigned char* smem, lds_idx_t lidx) {
+  if (m > kSkinnyRows || p.n >= kSkinnyMaxN) return false;
+  if (m <= 16) skinny_tile<8, 1>(p, m, smem, threadIdx.x, lidx); else skinny_tile<8, 2>(p, m, smem, threadIdx.x, lidx);
+  return true;
+}
+
+// Sizes that 64 x 64 tiles serve in one round whatever the count turns out to be: without the other shapes and the rule (what
+// bounds such a launch is its own start: code fetched once, the list, the first reads).  Launches of 80 rows, 402 x 1536 x 512 and 402 x
+// 512 x 512, with the kernel of all shapes and with this one 5.48 and 5.14, 5.44 and 5.12 us; a step of 2 x 201 tokens of hidden 512 27.32 and 26.80.
+template <bool FUSED>
+__global__ void __launch_bounds__(512) gemm_bf16_rows_small_kernel(GemmDev p) {
+  constexpr int STAGES = smem_bytes<64, 64, 8>();
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES + kListBytes<FUSED>];
+  lds_idx_t lidx = nullptr;
+  const int m = listed_rows<FUSED, STAGES>(p, smem, lidx);
   // (every way out waits for the loads into LDS that are under way)
-  if (m <= 0) return wait_vmcnt<0>();
-  // Up to 32 rows and a narrow output (the output projection): the register-fed stream
-  // (measured at n = 4096: 11-15 us against 17 us for 64 x 64 tiles, which give that width
-  // only 64 workgroups).  Wide outputs keep the 64 x 64 tiles for few rows: with 192
-  // column tiles they already stream the weights at 5 TB/s.
-  if (m <= kSkinnyRows && p.n < kSkinnyMaxN) {
-    if (m <= 16) skinny_tile<8, 1>(p, m, smem, threadIdx.x, lidx); else skinny_tile<8, 2>(p, m, smem, threadIdx.x, lidx);
-    return wait_vmcnt<0>();
-  }
+  if (m > 0 && !few_rows(p, m, smem, lidx)) gemm_tile16<64, 64, 2, 4, 8>(p, m, smem, threadIdx.x, blockIdx.x, lidx);
+  wait_vmcnt<0>();
+}
+
+template <bool FUSED>
+__global__ void __launch_bounds__(512) gemm_bf16_rows_wide_kernel(GemmDev p) {
+  // A row list derived from the mask lies behind the stage memory for the whole launch.  (In the stage memory
+  // it had to be read before the first load into LDS, a barrier between them, and derived again, seven copies of
+  // that code and 152 spilled scalars, in front of every further pass.  Steps, with the shape in line: 2 x 201 tokens
+  // of hidden 512 28.5 -> 27.6 us, 1 x 1024 of 4096 with 4 refreshed rows 60.9 -> 60.4, with 205 rows 89.8 -> 89.4.
+  // One array for both: see score_proj_kernel.)
+  static_assert(kWideSmem + kListBytes<FUSED> <= 160 * 1024, "stage memory and row list must fit the LDS of a CU");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kWideSmem + kListBytes<FUSED>];
+  static_assert(smem_bytes<64, 64, 8>() <= kWideSmem && smem_bytes<128, 48, 5>() <= kWideSmem &&
+                    smem_bytes<128, 64, 4>() <= kWideSmem && smem_bytes<128, 96, 4>() <= kWideSmem &&
+                    smem_bytes<128, 192, 3>() <= kWideSmem && smem_bytes<128, 128, 4>() <= kWideSmem &&
+                    pp_smem_bytes<3>() <= kWideSmem && pp_smem_bytes<4>() <= kWideSmem,
+                "shared buffer too small");
+  lds_idx_t lidx = nullptr;
+  const int m = listed_rows<FUSED, kWideSmem>(p, smem, lidx);
+  // (every way out waits for the loads into LDS that are under way)
+  if (m <= 0 || few_rows(p, m, smem, lidx)) return wait_vmcnt<0>();
   // Tiles in passes, virtual block id = block id + pass * grid size.  Every thread of the workgroup
   // sees the same m and so takes the same branch and the same number of passes.
   auto passes = [&](int tiles, auto tile) __attribute__((always_inline)) {
@@ -1955,7 +1977,11 @@ hipError_t launch_rows_wide(const GemmArgs& g, hipStream_t s) {
   blocks = grid_for(blocks);
   GemmDev p = to_dev(g);
   p.ahead = ahead_loads(g.n, blocks);
-  if (g.sel_mask)
+  if (small <= kWideGrid && g.sel_mask)
+    hipLaunchKernelGGL(gemm_bf16_rows_small_kernel<true>, dim3(blocks), dim3(512), 0, s, p);
+  else if (small <= kWideGrid)
+    hipLaunchKernelGGL(gemm_bf16_rows_small_kernel<false>, dim3(blocks), dim3(512), 0, s, p);
+  else if (g.sel_mask)
     hipLaunchKernelGGL(gemm_bf16_rows_wide_kernel<true>, dim3(blocks), dim3(512), 0, s, p);
   else
     hipLaunchKernelGGL(gemm_bf16_rows_wide_kernel<false>, dim3(blocks), dim3(512), 0, s, p);

@@ -244,6 +244,26 @@ def test_gemm_selected_rows_long_k(B, n, count, shape):
     assert_close(got[rows], want, "bf16")
 
 
+@pytest.mark.parametrize("n_tok", [1024, 1025])   # 256 tiles of 64 x 64 for all rows: a kernel of that shape alone; 272: the one of all shapes
+@pytest.mark.parametrize("count", [0, 1, 16, 17, 32, 33, 1000, 1024])
+def test_gemm_listed_rows_around_one_round_of_the_smallest_tiles(B, n_tok, count):
+    n = k = 1024
+    r = _rng(n_tok + count)
+    a = store(r.standard_normal((n_tok, k), dtype=np.float32), "bf16")
+    w = store(r.standard_normal((k, n), dtype=np.float32) * np.float32(0.05), "bf16")
+    rows = np.sort(r.permutation(n_tok)[:count]).astype(np.int32)
+    idx = np.full(n_tok, 10 ** 6, dtype=np.int32)
+    idx[:count] = rows
+    out = torch.full((n_tok, n), 3.0, dtype=torch.bfloat16, device="cuda")
+    B.dare_k_gemm(dev(a, "bf16"), B.dare_k_pack_weight(dev(w, "bf16")), [out], n, idx=dev(idx),
+                  m_dev=torch.tensor([count], dtype=torch.int32, device="cuda"), m_max=n_tok)
+    torch.cuda.synchronize()
+    got = host(out)
+    assert np.all(got[np.setdiff1d(np.arange(n_tok), rows)] == 3.0)
+    if count:
+        assert_close(got[rows], a[rows].astype(np.float64) @ w.astype(np.float64), "bf16")
+
+
 # every shape of best_tile: ragged last row tile, n that is no multiple of the tile's columns, odd k-steps
 EVERY_TILE = {
     (False, 402, 512): "64 x 64", (False, 1000, 1536): "64 x 96", (False, 1001, 2048): "64 x 128",

@@ -72,6 +72,16 @@ def test_unchanged_tokens_score_zero_in_the_scored_columns_alone(batch, seq, hid
     _unchanged_tokens_score_zero(batch, seq, hidden, first, orc.MODE_KVO, 0)
 
 
+@pytest.mark.parametrize("seq", [640, 641])   # Q, K and V of all rows: 240 and 264 tiles of 64 x 64
+def test_row_list_in_the_projection_of_one_round(seq):
+    case = synth.make_case("llada8b", seed=seq, batch=1, seq=seq, hidden=512, n_heads=4, head_dim=128, fraction=0.3)
+    state, gl = pu.oracle_fill(case), pu.GpuLayer(case)
+    s = np.sort(pu.oracle_step(case, state, orc.MODE_KVO, 0.0)["scores"].reshape(-1))
+    for tau in (-1.0, synth.TAU_SEPARATING, float(np.float32(0.5 * (s[-1] + s[-2]))), 2.5):
+        _run(case, gl, state, orc.MODE_KVO, tau)
+    gl.layer.destroy()
+
+
 # sizes of queries_of_listed_rows (tests/test_gemm_route.py): the device picks 256 x 192 and 256 x 256 tiles for them
 QUERIES_LATER = [(3, 900, 2048, 128), (4, 1400, 1024, 64)]
 
