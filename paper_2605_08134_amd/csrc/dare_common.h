@@ -175,8 +175,12 @@ hipError_t launch_norm(int dtype, int kind, const void* x, const void* gain, con
                        int n_rows, int d, void* out, int seq, int prefix, hipStream_t s);
 hipError_t launch_residual_add(int dtype, const void* x, const void* o, void* out, long n_elems,
                                hipStream_t s);
+// What launch_residual_norm does with the rows of a frozen prefix.  kLeftOut: rows as in launch_norm; else n_rows is all rows, and a
+// frozen one gets the sum alone, or the norm of its x alone.  keep_x: the sums are stored.
+enum class FrozenRows { kLeftOut, kSumOnly, kNormOnly };
 hipError_t launch_residual_norm(int dtype, void* x, const void* o, const void* gain, float eps, int n_rows, int d,
-                                void* h, int seq, int prefix, hipStream_t s);
+                                void* h, int seq, int prefix, hipStream_t s, FrozenRows frozen_rows = FrozenRows::kLeftOut,
+                                bool keep_x = true);
 hipError_t launch_residual_rows(int dtype, void* x, const void* f, int n_rows, int d, const int32_t* idx,
                                 hipStream_t s);
 hipError_t launch_gather_rows(const void* src, void* dst, const int32_t* ids, int n_rows, int n_src,

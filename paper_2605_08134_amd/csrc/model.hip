@@ -413,8 +413,8 @@ dare_status dare_model_step(dare_model* m, const int32_t* modes, const float* th
     return mfail_hip(m, e, "embedding");
   // Every residual sum is fused with the normalisation that follows it (one pass over the
   // stream instead of two): x <- x + O, n = rmsnorm(x) before the feed-forward; x <- x + F,
-  // h = rmsnorm(x) before the next layer's attention.  Only the first normalisation and the
-  // last sum stand alone.
+  // h = rmsnorm(x) before the next layer's attention, the final norm behind the last one.  Only the first
+  // normalisation stands alone, and the last sum of a step whose hidden state nobody asks for.
   e = launch_norm(c.dtype, DARE_NORM_RMS, m->x, m->mem[0].attn_gain, nullptr, c.norm_eps, n_act, d, m->h1,
                   pre ? seq : 0, P, s);
   if (e != hipSuccess) return mfail_hip(m, e, "first norm");
@@ -426,8 +426,9 @@ dare_status dare_model_step(dare_model* m, const int32_t* modes, const float* th
                                 lm.v_cache, lm.o_cache, m->mask, refreshed ? refreshed + (size_t)l * batch : nullptr,
                                 m->parts, hip_stream);
     if (st != DARE_OK) return mfail(m, st, "layer " + std::to_string(l) + ": " + dare_last_error(m->layers[l]));
-    // x <- x + O for every row (frozen rows add their cached O), n = rmsnorm(x)
-    e = launch_residual_norm(c.dtype, m->x, lm.o_cache, lm.ffn_gain, c.norm_eps, n_tok, d, m->h2, 0, 0, s);
+    // x <- x + O for every row (frozen rows add their cached O), n = rmsnorm(x) for those that are not frozen
+    e = launch_residual_norm(c.dtype, m->x, lm.o_cache, lm.ffn_gain, c.norm_eps, n_tok, d, m->h2, pre ? seq : 0, P, s,
+                             FrozenRows::kSumOnly);
     if (e != hipSuccess) return mfail_hip(m, e, "attention residual + feed-forward norm");
     if ((e = snapshot(2 * l + 1)) != hipSuccess) return mfail_hip(m, e, "trace");
     // feed-forward on the rows that are not frozen: F = (silu(n Wg) * (n Wu)) Wd
@@ -473,6 +474,10 @@ dare_status dare_model_step(dare_model* m, const int32_t* modes, const float* th
       // x <- x + F on the rows that are not frozen, h = rmsnorm(x) for the next layer
       e = launch_residual_norm(c.dtype, m->x, m->f, m->mem[l + 1].attn_gain, c.norm_eps, n_act, d, m->h1,
                                pre ? seq : 0, P, s);
+    } else if (hidden_out) {
+      // the last sum with the final norm, of every row (a frozen one has no F); x itself is the trace's alone
+      e = launch_residual_norm(c.dtype, m->x, m->f, m->final_gain, c.norm_eps, n_tok, d, hidden_out, pre ? seq : 0, P, s,
+                               FrozenRows::kNormOnly, tr != nullptr);
     } else if (pre) {
       e = launch_residual_rows(c.dtype, m->x, m->f, n_act, d, act, s);
     } else {
@@ -481,10 +486,6 @@ dare_status dare_model_step(dare_model* m, const int32_t* modes, const float* th
     if (e != hipSuccess) return mfail_hip(m, e, "feed-forward residual");
   }
   if ((e = snapshot(2 * c.n_layers)) != hipSuccess) return mfail_hip(m, e, "trace");
-  if (hidden_out) {
-    e = launch_norm(c.dtype, DARE_NORM_RMS, m->x, m->final_gain, nullptr, c.norm_eps, n_tok, d, hidden_out, 0, 0, s);
-    if (e != hipSuccess) return mfail_hip(m, e, "final norm");
-  }
   return DARE_OK;
 }
 

@@ -130,6 +130,30 @@ def test_down_projection_cut_along_k(Bm, T, d, prefix, ffn):
     m.destroy()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,T,d,prefix", [(1, 5, 64, 0), (1, 33, 2048, 32), (2, 40, 128, 7), (2, 19, 1088, 1)])
+def test_hidden_state_with_and_without_trace(Bm, dtype, L, T, d, prefix):
+    """The last sum and the final norm are one pass, which stores the sum only for a trace: the hidden state is that of
+    the traced stream, frozen rows (the norm alone) included; a step that asks for neither runs too."""
+    cfg = dict(L=L, d=d, H=d // 64, ffn=2 * d, V=64, B=3, T=T)
+    params = synth.make_model_params(T, L, d, cfg["ffn"], cfg["V"], dtype, with_head=False)
+    m = _build(Bm, params, cfg, dtype)
+    ids = synth.make_ids(T, 3, T, cfg["V"], T // 3, cfg["V"] - 1)
+    step = lambda: _gpu_step(m, cfg, dtype, [orc.MODE_DENSE] * L, [0.0] * L, ids)
+    hidden, refreshed, tr = step()
+    caches = _check_step(cfg, dtype, params, _zero_caches(cfg), [orc.MODE_DENSE] * L, [0.0] * L, ids, hidden, refreshed, tr)
+    if prefix:
+        m.set_prefix(prefix)
+        hidden, refreshed, tr = step()
+        _check_step(cfg, dtype, params, caches, [orc.MODE_DENSE] * L, [0.0] * L, ids, hidden, refreshed, tr, prefix=prefix)
+    plain = torch.full((3, T, d), float("nan"), dtype=pu.tdtype(dtype), device="cuda")
+    m.step([orc.MODE_DENSE] * L, [0.0] * L, dev(ids), plain)
+    m.step([orc.MODE_DENSE] * L, [0.0] * L, dev(ids))
+    again = step()[0]
+    assert np.array_equal(host(plain), hidden) and np.array_equal(again, hidden)
+    m.destroy()
+
+
 def test_layers_share_the_workspace_of_attention_with_cut_keys(Bm):
     """The workspace that steps of 1921 tokens and more use (8.7 MB) is the model's: a layer takes
     no more memory at 2048 than at 1920 tokens than its own rows do (1/16 of about 14 MB)."""
