@@ -238,7 +238,7 @@ def main():
     dg_ms = e0.elapsed_time(e1) / 50
     dg_tflops = 2.0 * Bn * T * d * 3 * d / (dg_ms * 1e-3) / 1e12
     roofline_other = [{
-        "kernel": "gemm_bf16_pp_kernel (all-row Q/K/V projection, %d x %d x %d)" % (Bn * T, 3 * d, d),
+        "kernel": "gemm_bf16_quad_kernel (all-row Q/K/V projection, %d x %d x %d)" % (Bn * T, 3 * d, d),
         "bound": "mfma", "achieved": dg_tflops, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
         "frac": dg_tflops / MFMA_BF16_PEAK_TFLOPS, "us_per_launch": dg_ms * 1e3}]
 
@@ -689,7 +689,7 @@ def other_kernels_at_c2(torch, B, np, dev, d, H, Dh):
                 "frac": tf / MFMA_BF16_PEAK_TFLOPS, "us_per_launch": us})
     us = _time_us(torch, lambda n: [B.dare_k_gemm(src, wt, outs, d) for _ in range(n)], 5)
     tf = 2.0 * n_tok * d * 3 * d / (us * 1e-6) / 1e12
-    out.append({"kernel": "gemm_bf16_pp_kernel (all-row Q/K/V projection, %d x %d x %d)" % (n_tok, 3 * d, d),
+    out.append({"kernel": "gemm_bf16_quad_kernel (all-row Q/K/V projection, %d x %d x %d)" % (n_tok, 3 * d, d),
                 "bound": "mfma", "achieved": tf, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": tf / MFMA_BF16_PEAK_TFLOPS, "us_per_launch": us})
     # attention, all rows and refreshed rows
