@@ -967,12 +967,12 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
 //     by side (lanes L and L ^ 8 swap halves).  Stores count in vmcnt with the loads, in order, and the loads of the next tile
 //     wait for them: with 64-byte runs they took 9 us per round of the CUs.
 // The sum over k is formed as in gemm_tile_pp and gemm_tile16, so results are the same bits.
-// us, gemm_tile_pp (256 x 128, 192 and 256) and now, one card: 16384 x 12288 x 4096 1148 and 1076 (1.53 PFLOP/s), 16384 x 4096 x 4096 384 and 362,
+// us, gemm_tile_pp (256 x 192 and 256) and now, one card: 16384 x 12288 x 4096 1148 and 1076 (1.53 PFLOP/s), 16384 x 4096 x 4096 384 and 362,
 // 4096 x 24576 x 4096 608 and 541, 4096 x 4096 x 12288 272 and 262, 2331 x 12288 x 4096 184 and 177, 1024 x 24576 x 4096 151 and 145, 1024 x
-// 12288 x 4096 77.1 and 74.5, 2048 x 4096 x 4096 56.1 and 52.4.  In steps, where the operands come from other kernels: 4096 x 24576 with
+// 12288 x 4096 77.1 and 74.5.  In steps, where the operands come from other kernels: 4096 x 24576 with
 // the gate 570 and 547, 8192 x 24576 1123 and 1079, 4096 x 4096 x 12288 277 and 270, Q, K and V of 4096 rows, rotated, 314 and 297.
 // The gate of 128 x 128 sums takes a wave 2.8 us (with the compiler's division 5.5), the rotation 2.
-// gemm_tile_pp stays where k is cut over two workgroups (1024 x 4096 x 12288 92.6 us, in this form 103.6: half as many waves store and add
+// gemm_tile_pp stays for 256 x 128 (gemm_bf16_pp_kernel), where k is cut over two workgroups (1024 x 4096 x 12288 92.6 us, in this form 103.6: half as many waves store and add
 // the sums) and for listed rows, whose kernel has the eight waves that the small shapes want.
 constexpr int kQuadSlot = kPpRows * ROW_BYTES, kQuadSmem = 5 * kQuadSlot;
 constexpr int kQuadMinSteps = kPartMinSteps;  // k-steps: loads two ahead, and the first one's zero sums
@@ -1443,9 +1443,12 @@ __global__ void __launch_bounds__(512) gemm_bf16_tile16_kernel(GemmDev p) {
   gemm_tile16<BM, BN, WAVES_M, WAVES_N, STAGES>(p, p.m_max, smem, threadIdx.x, blockIdx.x);
 }
 
-__global__ void __launch_bounds__(512) gemm_bf16_pp_split_kernel(GemmDev p) {
+// 256 x 128, all rows.  With the weights in memory eight waves and three stages in flight are faster than four waves, whose ring holds two
+// and a half: 1320 x 3072 x 9216 102 us and 119, x 3072 x 3072 39-44 and 45-52 (in the caches 91.6 and 83.4, 34.9 and 33.2).
+template <bool SPLIT>
+__global__ void __launch_bounds__(512) gemm_bf16_pp_kernel(GemmDev p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[pp_smem_bytes<2>()];
-  gemm_tile_pp<2, true>(p, p.m_max, smem, blockIdx.x);
+  gemm_tile_pp<2, SPLIT>(p, p.m_max, smem, blockIdx.x);
 }
 
 // ---- row count read on the device: the tile shape follows it -------------------------
@@ -1961,10 +1964,11 @@ hipError_t launch_tile16(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_pp_split(const GemmArgs& g, hipStream_t s) {
+template <bool SPLIT>
+hipError_t launch_pp(const GemmArgs& g, hipStream_t s) {
   const int tiles = tiles_of(g.m_max, g.n, kPpRows, 128);
-  if (tiles > kSplitTiles || !g.split_tiles || !g.split_count) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gemm_bf16_pp_split_kernel, dim3(grid_for(2 * tiles)), dim3(512), 0, s, to_dev(g));
+  if (SPLIT && (tiles > kSplitTiles || !g.split_tiles || !g.split_count)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(gemm_bf16_pp_kernel<SPLIT>, dim3(grid_for(SPLIT ? 2 * tiles : tiles)), dim3(512), 0, s, to_dev(g));
   return hipGetLastError();
 }
 
@@ -2003,13 +2007,13 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   if (g.m_max == 0) return hipSuccess;
   GemmRoute route = gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles && !g.c32);
   // (one and two k-steps: the pipeline of gemm_tiles_quad, which runs on into the next tile, is longer)
-  if (g.k < kQuadMinSteps * BK && (route == GemmRoute::kPp256 || route == GemmRoute::kPp192 || route == GemmRoute::kPp128))
+  if (g.k < kQuadMinSteps * BK && (route == GemmRoute::kPp256 || route == GemmRoute::kPp192))
     route = GemmRoute::k128x128;
   switch (route) {
-    case GemmRoute::kPp128Split: return launch_pp_split(g, s);
+    case GemmRoute::kPp128Split: return launch_pp<true>(g, s);
     case GemmRoute::kPp256: return launch_quad<4>(g, s);
     case GemmRoute::kPp192: return launch_quad<3>(g, s);
-    case GemmRoute::kPp128: return launch_quad<2>(g, s);
+    case GemmRoute::kPp128: return launch_pp<false>(g, s);
     case GemmRoute::k128x192: return launch_tile16<128, 192, 2, 4, 3>(g, s);
     case GemmRoute::k128x128: return launch_tile16<128, 128, 2, 4, 4>(g, s);
     case GemmRoute::k128x96: return launch_tile16<128, 96, 4, 2, 4>(g, s);

@@ -16,8 +16,8 @@ enum class GemmRoute {
   k128x96,
   k128x128,
   k128x192,
-  kPp128,       // 256 rows x 128, 192, 256 columns: four waves (gemm_tiles_quad) for all rows, ping-pong tiles for listed ones
-  kPp192,
+  kPp128,       // 256 rows x 128 columns: ping-pong tiles
+  kPp192,       // x 192, 256: four waves (gemm_tiles_quad) for all rows, ping-pong tiles for listed ones
   kPp256,
   kPp256Cut,    // the last round of 256 x 256 cut into 128 x 128 (listed rows)
   kPp128Split,  // 256 x 128, two workgroups on the halves of a tile's k; needs the workspace
