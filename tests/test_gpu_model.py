@@ -15,11 +15,15 @@ from oracle import dare_oracle as orc
 from oracle import dllm_oracle as dl
 from paper_2605_08134_amd import synth
 import parity_util as pu
-from parity_util import dev, host
+from parity_util import dev, host, store
 
 pytestmark = pytest.mark.gpu
 
 EPS, ROPE = 1e-5, 10000.0
+
+
+def _rng_normal(n):
+    return np.random.default_rng(n).standard_normal(n)
 
 
 def _build(Bm, params, cfg, dtype):
@@ -152,6 +156,37 @@ def test_hidden_state_with_and_without_trace(Bm, dtype, L, T, d, prefix):
     again = step()[0]
     assert np.array_equal(host(plain), hidden) and np.array_equal(again, hidden)
     m.destroy()
+
+
+# 40 rows: small tiles; 8192 x 4096: two rounds of 256 x 256
+@pytest.mark.parametrize("B,T,ffn", [(1, 40, 256), (4, 2048, 2048)])
+def test_gate_over_its_whole_range(Bm, B, T, ffn):
+    """silu(g) * u for single gates g = v, -v and u = 1, -1 (one weight and one input each, so both are exact), from gates whose
+    divisor 1 + exp(-g) is near the largest float to infinite ones."""
+    d, n_gates = 256, 250
+    cfg = dict(L=1, d=d, H=2, ffn=ffn, V=64, B=B, T=T)
+    v = np.concatenate([np.arange(-88.5, -80.0, 0.5), [-64.5, -64.0, -63.5, 0.0, 1e-30, 1e-36, 1e30, 127.0],
+                        20 * _rng_normal(n_gates)])[:n_gates]
+    v = store(v.astype(np.float32), "bf16").astype(np.float64)
+    at = np.arange(n_gates) * (ffn // 256) + np.arange(n_gates) % (ffn // 256)     # a gate's column
+    z = np.zeros
+    lp = dict(attn_gain=np.ones(d), ffn_gain=np.ones(d), wq=z((d, d)), wk=z((d, d)), wv=z((d, d)), wo=z((d, d)),
+              w_gate=z((d, ffn)), w_up=z((d, ffn)), w_down=z((ffn, d)))
+    lp["w_gate"][0, at], lp["w_up"][0, at], lp["w_down"][at, 2 + np.arange(n_gates)] = v / 16, 1 / 16, 1.0
+    lp["w_gate"][1, at[5]], lp["w_up"][1, at[5]] = 3e38, 1 / 16
+    embed = z((64, d))
+    embed[:4, :2] = [[16, 0], [-16, 0], [0, 16], [0, -16]]      # normalised: the same, rounded to bf16
+    m = _build(Bm, dict(layers=[lp], embed=embed, final_gain=np.ones(d)), cfg, "bf16")
+    ids = np.arange(B * T, dtype=np.int32).reshape(B, T) % 4
+    x = _gpu_step(m, cfg, "bf16", [orc.MODE_DENSE], [0.0], ids)[2][2]
+    m.destroy()
+    for sign, got in ((1, x[ids == 0]), (-1, x[ids == 1])):
+        g = sign * v
+        want = np.where(g < -88.7, 0.0, g / (1 + np.exp(-np.maximum(g, -88.7)))) * sign       # (exp(-g) past the largest float: 0)
+        # a rounding to bf16 (2^-9) and exp of 32 bits (|g| 2^-24 and its own last bit)
+        assert np.all(np.abs(got[:, 2:2 + n_gates] - want) <= 2.0 ** -8 * np.abs(want) + 1e-38)
+    up, down = x[ids == 2], x[ids == 3]      # gates of +inf and -inf: inf and -inf / inf; 0 times them in the other columns
+    assert np.all(up[:, 7] == np.inf) and np.all(np.isnan(np.delete(up, 7, axis=1))) and np.all(np.isnan(down))
 
 
 def test_layers_share_the_workspace_of_attention_with_cut_keys(Bm):
