@@ -617,7 +617,8 @@ __device__ __forceinline__ bool gemm_tile16(const GemmDev& p, const int m, unsig
   return true;
 }
 
-// ---- large tiles of listed rows, and with k cut: 256 x (64 TN), eight waves in two groups that take turns ----
+// ---- large tiles: 256 x (64 TN), eight waves in two groups that take turns ----------------
+// (listed rows; all rows in 256 x 128, with k cut too, and in one round of the wider ones)
 // Waves w and w + 4 sit on the same SIMD.  Waves 0-3 (group 0) own the left half of the tile's
 // columns, waves 4-7 (group 1) the right half, each wave 64 rows x 32 TN columns.  A k-step of 64 is
 // cut into TN phases, one per block of 32 columns, and a phase into a memory part (fragment
@@ -950,7 +951,7 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
   return true;
 }
 
-// ---- large tiles of all rows: 256 x (64 TN), four waves, one per SIMD ---------------------
+// ---- several rounds of large tiles of all rows: 256 x (64 TN), four waves, one per SIMD ----
 // A wave owns 128 rows x 32 TN columns, its sums in the accumulator registers, which leaves the others to two sets of
 // fragments: a slice of 32 k is multiplied while the next one's fragments are read.  Against gemm_tile_pp, whose eight waves take 64
 // rows each: a third fewer bytes read from LDS per k-step (131 KB for 196), one barrier for eight, and what these kernels are bound
@@ -966,17 +967,18 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
 //   * The pipeline runs on from tile to tile: a workgroup per CU walks its tiles, the last two k-steps load the next tile's
 //     first two and the last slice reads its first fragments, so a tile ends without an empty ring.  Behind the last tile they
 //     load their own k-steps again, into slots that nobody reads: the same code, where code of its own for the end and the start, fetched
-//     once per launch, cost a launch of one round 3 us (a dense step of 1 x 1024 tokens 2.2 % slower than with gemm_tile_pp, now level).
+//     once per launch, cost a launch of one round 3 us.
 //   * Stores of whole 128-byte lines: rows 0 .. 7 of a block of 16 in one store and 8 .. 15 in the next, two column blocks side
 //     by side (lanes L and L ^ 8 swap halves).  Stores count in vmcnt with the loads, in order, and the loads of the next tile
 //     wait for them: with 64-byte runs they took 9 us per round of the CUs.
 // The sum over k is formed as in gemm_tile_pp and gemm_tile16, so results are the same bits.
 // us, gemm_tile_pp (256 x 192 and 256) and now, one card: 16384 x 12288 x 4096 1148 and 1076 (1.53 PFLOP/s), 16384 x 4096 x 4096 384 and 362,
-// 4096 x 24576 x 4096 608 and 541, 4096 x 4096 x 12288 272 and 262, 2331 x 12288 x 4096 184 and 177, 1024 x 24576 x 4096 151 and 145, 1024 x
-// 12288 x 4096 77.1 and 74.5.  In steps, where the operands come from other kernels: 4096 x 24576 with
-// the gate 570 and 547, 8192 x 24576 1123 and 1079, 4096 x 4096 x 12288 277 and 270, Q, K and V of 4096 rows, rotated, 314 and 297.
+// 4096 x 24576 x 4096 608 and 541, 4096 x 4096 x 12288 272 and 262, 2331 x 12288 x 4096 184 and 177, with operands in the caches.
+// In steps, where they come from other kernels and from memory: 4096 x 24576 with
+// the gate 570 and 547, 8192 x 24576 1123 and 1079, 4096 x 4096 x 12288 277 and 270, Q, K and V of 4096 rows, rotated, 314 and 297;
+// one round is better off with eight waves (four_waves, gemm_route.h).
 // The gate of 128 x 128 sums takes a wave 2.8 us (with the compiler's division 5.5), the rotation 2.
-// gemm_tile_pp stays for 256 x 128 (gemm_bf16_pp_kernel), where k is cut over two workgroups (1024 x 4096 x 12288 92.6 us, in this form 103.6: half as many waves store and add
+// gemm_tile_pp stays for 256 x 128 (gemm_bf16_pp_kernel), for one round, where k is cut over two workgroups (1024 x 4096 x 12288 92.6 us, in this form 103.6: half as many waves store and add
 // the sums) and for listed rows, whose kernel has the eight waves that the small shapes want.
 constexpr int kQuadSlot = kPpRows * ROW_BYTES, kQuadSmem = 5 * kQuadSlot;
 constexpr int kQuadMinSteps = kPartMinSteps;  // k-steps: loads two ahead, and the first one's zero sums
@@ -1462,12 +1464,13 @@ __global__ void __launch_bounds__(512) gemm_bf16_tile16_kernel(GemmDev p) {
   gemm_tile16<BM, BN, WAVES_M, WAVES_N, STAGES>(p, p.m_max, smem, threadIdx.x, blockIdx.x);
 }
 
-// 256 x 128, all rows.  With the weights in memory eight waves and three stages in flight are faster than four waves, whose ring holds two
-// and a half: 1320 x 3072 x 9216 102 us and 119, x 3072 x 3072 39-44 and 45-52 (in the caches 91.6 and 83.4, 34.9 and 33.2).
-template <bool SPLIT>
+// All rows: 256 x 128, and a round of 256 x 192 or 256 (four_waves, gemm_route.h).  256 x 128: with the weights in memory eight waves and
+// three stages in flight are faster than four waves, whose ring holds two and a half: 1320 x 3072 x 9216 102 us and 119, x 3072 x 3072
+// 39-44 and 45-52 (in the caches 91.6 and 83.4, 34.9 and 33.2).
+template <int TN, bool SPLIT>
 __global__ void __launch_bounds__(512) gemm_bf16_pp_kernel(GemmDev p) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[pp_smem_bytes<2>()];
-  gemm_tile_pp<2, SPLIT>(p, p.m_max, smem, blockIdx.x);
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[pp_smem_bytes<TN>()];
+  gemm_tile_pp<TN, SPLIT>(p, p.m_max, smem, blockIdx.x);
 }
 
 // ---- row count read on the device: the tile shape follows it -------------------------
@@ -1983,11 +1986,12 @@ hipError_t launch_tile16(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <bool SPLIT>
+template <int TN, bool SPLIT = false>
 hipError_t launch_pp(const GemmArgs& g, hipStream_t s) {
-  const int tiles = tiles_of(g.m_max, g.n, kPpRows, 128);
+  const int tiles = tiles_of(g.m_max, g.n, kPpRows, 64 * TN);
   if (SPLIT && (tiles > kSplitTiles || !g.split_tiles || !g.split_count)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gemm_bf16_pp_kernel<SPLIT>, dim3(grid_for(SPLIT ? 2 * tiles : tiles)), dim3(512), 0, s, to_dev(g));
+  hipLaunchKernelGGL((gemm_bf16_pp_kernel<TN, SPLIT>), dim3(grid_for(SPLIT ? 2 * tiles : tiles)), dim3(512), 0, s,
+                     to_dev(g));
   return hipGetLastError();
 }
 
@@ -2026,13 +2030,15 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   if (g.m_max == 0) return hipSuccess;
   GemmRoute route = gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles && !g.c32);
   // (one and two k-steps: the pipeline of gemm_tiles_quad, which runs on into the next tile, is longer)
-  if (g.k < kQuadMinSteps * BK && (route == GemmRoute::kPp256 || route == GemmRoute::kPp192))
+  if (g.k < kQuadMinSteps * BK && (route == GemmRoute::kQuad256 || route == GemmRoute::kQuad192))
     route = GemmRoute::k128x128;
   switch (route) {
-    case GemmRoute::kPp128Split: return launch_pp<true>(g, s);
-    case GemmRoute::kPp256: return launch_quad<4>(g, s);
-    case GemmRoute::kPp192: return launch_quad<3>(g, s);
-    case GemmRoute::kPp128: return launch_pp<false>(g, s);
+    case GemmRoute::kPp128Split: return launch_pp<2, true>(g, s);
+    case GemmRoute::kQuad256: return launch_quad<4>(g, s);
+    case GemmRoute::kQuad192: return launch_quad<3>(g, s);
+    case GemmRoute::kPp256: return launch_pp<4>(g, s);
+    case GemmRoute::kPp192: return launch_pp<3>(g, s);
+    case GemmRoute::kPp128: return launch_pp<2>(g, s);
     case GemmRoute::k128x192: return launch_tile16<128, 192, 2, 4, 3>(g, s);
     case GemmRoute::k128x128: return launch_tile16<128, 128, 2, 4, 4>(g, s);
     case GemmRoute::k128x96: return launch_tile16<128, 96, 4, 2, 4>(g, s);

@@ -16,11 +16,13 @@ enum class GemmRoute {
   k128x96,
   k128x128,
   k128x192,
-  kPp128,       // 256 rows x 128 columns: ping-pong tiles
-  kPp192,       // x 192, 256: four waves (gemm_tiles_quad) for all rows, ping-pong tiles for listed ones
+  kPp128,       // 256 rows x 128, 192, 256 columns: ping-pong tiles (eight waves)
+  kPp192,
   kPp256,
   kPp256Cut,    // the last round of 256 x 256 cut into 128 x 128 (listed rows)
   kPp128Split,  // 256 x 128, two workgroups on the halves of a tile's k; needs the workspace
+  kQuad192,     // 256 rows x 192, 256 columns: four waves, one pipeline over a workgroup's tiles (all rows)
+  kQuad256,
 };
 
 constexpr int kRouteBK = 64;        // k per k-step
@@ -96,6 +98,18 @@ __attribute__((always_inline)) constexpr GemmRoute best_tile(int m, int n, bool 
   return best;
 }
 
+// All rows in tiles of 256 x 192 or 256: four waves (gemm_tiles_quad) instead of eight.  They gain where a workgroup walks several
+// tiles; a launch of one round has only their longer start (us of a layer or block step, eight waves and four, weights from memory:
+// 1024 x 12288 x 4096 144.0 145.4, 640 x 12288 x 4096 121 126, 1320 x 6144 x 2048 84.6 88.0, 3600 x 3072 x 1024 65.2 67.0; two rounds,
+// 4096 x 6144 x 2048 156.2 154.0, 1024 x 24576 x 4096 412 408, 1536 x 12288 x 4096 224 224; three, 3000 x 12288 x 4096 368 361).  In a
+// round of 256 x 256 the k loop makes up for it with 64 k-steps and more, or with 32 where the weights, which come from memory, are
+// the smaller operand (3600 x 4096 x 4096 425 420, 5120 x 3072 x 3072 351 346, 8192 x 2048 x 2048 277 275, 7000 x 2048 x 2048 256 255, but 1536 x
+// 9216 x 3072 142.5 144.3, 2560 x 6144 x 2048 126.9 128.2, 5120 x 3072 x 1024 90.8 92.4).
+constexpr bool four_waves(int m, int n, int k, int columns) {
+  if (tiles_of(m, n, kPpRows, columns) > 256) return true;
+  return columns == 256 && (k >= 4096 || (k >= 2048 && n <= 2 * m));
+}
+
 // Row count known on the host.  With the workspace, two workgroups per tile of 256 x 128 instead of 128 x 128 tiles where
 // there are kSplitTiles / 2 to kSplitTiles of them and a long k: half of the tile's cost and the hand-over (1024 x 4096 x
 // 12288: 97 against 112 us).  Instead of 128 x 96 from 144 k-steps on, where the 16-wide loop
@@ -116,6 +130,8 @@ constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace)
   if (workspace && t2 >= kSplitTiles / 2 && t2 <= kSplitTiles && ksteps % 2 == 0 && ksteps >= kSplitMinSteps &&
       (best == GemmRoute::k128x128 || (best == GemmRoute::k128x96 && ksteps >= 144)))
     return GemmRoute::kPp128Split;
+  if (best == GemmRoute::kPp192 && four_waves(m, n, k, 192)) return GemmRoute::kQuad192;
+  if (best == GemmRoute::kPp256 && four_waves(m, n, k, 256)) return GemmRoute::kQuad256;
   return best;
 }
 

@@ -203,6 +203,42 @@ def test_gpu_tests_reach_the_shapes_that_they_name(tmp_path):
     assert {want[s] for s in want if s[0]} == {"64 x 64", "128 x 48", "128 x 64", "256 x 256 cut"} | large
 
 
+FORMS = r"""
+#include <cstdio>
+#include "gemm_route.h"
+using namespace dare;
+int main() {
+  long bad = 0, four = 0, eight = 0;
+  const struct { int m, n, k; GemmRoute want; } at[] = {
+      {1024, 12288, 4096, GemmRoute::kPp192}, {640, 12288, 4096, GemmRoute::kPp192}, {3600, 3072, 1024, GemmRoute::kPp192},   // one round
+      {1024, 24576, 4096, GemmRoute::kQuad192}, {1536, 12288, 4096, GemmRoute::kQuad192},                                     // two
+      {1536, 9216, 3072, GemmRoute::kPp256}, {2560, 6144, 2048, GemmRoute::kPp256}, {5120, 3072, 1024, GemmRoute::kPp256},
+      {7000, 2048, 2048, GemmRoute::kQuad256}, {4096, 4096, 4096, GemmRoute::kQuad256}, {4096, 24576, 4096, GemmRoute::kQuad256}};
+  for (const auto& c : at)
+    if (gemm_route(c.m, c.n, c.k, 1, false) != c.want) std::printf("%d x %d x %d\n", c.m, c.n, c.k), ++bad;
+  for (int n = 64; n <= 32768; n += 192)
+    for (int m = 1; m <= 40000; m = m < 600 ? m + 13 : m + 397)
+      for (int k = 256; k <= 12288; k *= 2) {
+        const GemmRoute r = gemm_route(m, n, k, 1, false), shape = best_tile(m, n, false);
+        const bool q192 = r == GemmRoute::kQuad192, q256 = r == GemmRoute::kQuad256;
+        if ((q192 ? GemmRoute::kPp192 : q256 ? GemmRoute::kPp256 : r) != shape) ++bad;                          // the form alone
+        const bool one = tiles_of(m, n, kPpRows, shape == GemmRoute::kPp192 ? 192 : 256) <= 256;
+        if (q192 && one) ++bad;
+        if ((shape == GemmRoute::kPp192 || shape == GemmRoute::kPp256) && !one && !q192 && !q256) ++bad;
+        four += q192 || q256;
+        eight += r == GemmRoute::kPp192 || r == GemmRoute::kPp256;
+      }
+  std::printf("four %ld eight %ld bad %ld\n", four, eight, bad);
+  return bad != 0 || four < 1000 || eight < 1000;
+}
+"""
+
+
+def test_one_round_of_large_tiles_keeps_eight_waves(tmp_path):
+    r = _run(tmp_path, FORMS)
+    assert r.returncode == 0, r.stdout
+
+
 PART = r"""
 #include <cstdio>
 #include "gemm_route.h"
