@@ -981,7 +981,6 @@ __device__ __forceinline__ bool gemm_tile_pp(const GemmDev& p, const int m, unsi
 // gemm_tile_pp stays for 256 x 128 (gemm_bf16_pp_kernel), for one round, where k is cut over two workgroups (1024 x 4096 x 12288 92.6 us, in this form 103.6: half as many waves store and add
 // the sums) and for listed rows, whose kernel has the eight waves that the small shapes want.
 constexpr int kQuadSlot = kPpRows * ROW_BYTES, kQuadSmem = 5 * kQuadSlot;
-constexpr int kQuadMinSteps = kPartMinSteps;  // k-steps: loads two ahead, and the first one's zero sums
 
 // Value of a lane from the lane 8 further on in its row of 16, in the lanes of BANKS (four lanes each); `own` in the others
 template <int BANKS>
@@ -997,7 +996,8 @@ __device__ __forceinline__ void store16(bf16_t* to, const u32x4 v) {
     *reinterpret_cast<u32x4*>(to) = v;
 }
 
-// The tiles blockIdx.x, blockIdx.x + gridDim.x, ..; called by all 256 threads.  k of kQuadMinSteps k-steps or more.
+// The tiles blockIdx.x, blockIdx.x + gridDim.x, ..; called by all 256 threads.  k of kQuadMinSteps k-steps or more (loads two ahead, and
+// the first one's zero sums).
 // PART: the columns from part_n on for all rows, those in front of it for the part_m rows of the second list.
 template <int TN, bool STREAM, bool PART = false>
 __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, unsigned char* smem, const int part_m = 0) {
@@ -2028,11 +2028,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   }
   if (g.m_dev || g.sel_mask) return launch_rows_wide(g, s);
   if (g.m_max == 0) return hipSuccess;
-  GemmRoute route = gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles && !g.c32);
-  // (one and two k-steps: the pipeline of gemm_tiles_quad, which runs on into the next tile, is longer)
-  if (g.k < kQuadMinSteps * BK && (route == GemmRoute::kQuad256 || route == GemmRoute::kQuad192))
-    route = GemmRoute::k128x128;
-  switch (route) {
+  switch (gemm_route(g.m_max, g.n, g.k, g.k_parts, g.split_tiles && !g.c32)) {
     case GemmRoute::kPp128Split: return launch_pp<2, true>(g, s);
     case GemmRoute::kQuad256: return launch_quad<4>(g, s);
     case GemmRoute::kQuad192: return launch_quad<3>(g, s);

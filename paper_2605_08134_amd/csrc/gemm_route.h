@@ -105,7 +105,10 @@ __attribute__((always_inline)) constexpr GemmRoute best_tile(int m, int n, bool 
 // round of 256 x 256 the k loop makes up for it with 64 k-steps and more, or with 32 where the weights, which come from memory, are
 // the smaller operand (3600 x 4096 x 4096 425 420, 5120 x 3072 x 3072 351 346, 8192 x 2048 x 2048 277 275, 7000 x 2048 x 2048 256 255, but 1536 x
 // 9216 x 3072 142.5 144.3, 2560 x 6144 x 2048 126.9 128.2, 5120 x 3072 x 1024 90.8 92.4).
+// Not for one and two k-steps, less than the pipeline is long.
+constexpr int kQuadMinSteps = 3;
 constexpr bool four_waves(int m, int n, int k, int columns) {
+  if (k / kRouteBK < kQuadMinSteps) return false;
   if (tiles_of(m, n, kPpRows, columns) > 256) return true;
   return columns == 256 && (k >= 4096 || (k >= 2048 && n <= 2 * m));
 }
@@ -167,10 +170,10 @@ __attribute__((always_inline)) constexpr int part_columns(int m, int n, int part
 // 1 x 2048 221 217, 252 253, 263 268; 3 x 777 252 225, 274 253, 301 307; 4 x 800 345 275, 365 304, 397 371; 4 x 1024 376 333, 424 421, 440
 // 442; 5 x 1024 473 394, 520 454, 561 562; 8 x 2048 25 % 1510 1315; 4 x 700 of 2048 127 106, 133 113, 139 124; 4 x 1400 of 1024 106 93, 109 98,
 // 133 121; but 1 x 600 of 4096 111 112, 111 112, 117 122.
-constexpr int kPartMinSteps = 3, kPartMinRows = 1024;
+constexpr int kPartMinRows = 1024;
 constexpr bool queries_of_listed_rows(int m, int d) {
   const int n = 3 * d, ksteps = d / kRouteBK;
-  if (ksteps < kPartMinSteps || m < kPartMinRows || tiles_of(m, n, kPpRows, 128) > (1 << 20)) return false;
+  if (ksteps < kQuadMinSteps || m < kPartMinRows || tiles_of(m, n, kPpRows, 128) > (1 << 20)) return false;
   const GemmRoute now = best_tile(m, n, false);
   if (now != GemmRoute::kPp128 && now != GemmRoute::kPp192 && now != GemmRoute::kPp256) return false;
   const int tn = part_columns(m, n, m / 2, d), all_tn = part_columns(m, n, 0, 0);

@@ -6,6 +6,7 @@ taken without a workspace, nor depend on how large a context was made."""
 import os
 import subprocess
 
+import test_gpu_block as block
 import test_gpu_kernels as kernels
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -172,34 +173,39 @@ SHAPES = r"""
 using namespace dare;
 int main() {
   const char* name[] = {"ranges 64 x 64", "ranges 128 x 128", "64 x 64", "64 x 96", "64 x 128", "128 x 48", "128 x 64", "128 x 96",
-                        "128 x 128", "128 x 192", "256 x 128", "256 x 192", "256 x 256", "256 x 256 cut", "split"};
-  static_assert((int)GemmRoute::kPp128Split == 14, "a shape without a name");
-  int listed, m, n;
-  while (std::scanf("%d %d %d", &listed, &m, &n) == 3) std::printf("%s\n", name[(int)best_tile(m, n, listed)]);
+                        "128 x 128", "128 x 192", "256 x 128", "256 x 192", "256 x 256", "256 x 256 cut", "split",
+                        "256 x 192 four waves", "256 x 256 four waves"};
+  static_assert((int)GemmRoute::kQuad256 == 16, "a shape without a name");
+  int listed, m, n, k;
+  while (std::scanf("%d %d %d %d", &listed, &m, &n, &k) == 4)
+    std::printf("%s\n", name[(int)(listed ? best_tile(m, n, true) : gemm_route(m, n, k, 1, false))]);
 }
 """
 
 
 def test_gpu_tests_reach_the_shapes_that_they_name(tmp_path):
-    """The sizes of tests/test_gpu_kernels.py, asked of the rule on the CPU: each gets the tile shape that its
-    text names, and between them they take every shape that all rows and that listed rows can get."""
+    """The sizes of tests/test_gpu_kernels.py and test_gpu_block.py, asked of the rule on the CPU: each gets the tile shape
+    that its text names, and between them they take every shape that all rows and that listed rows can get."""
     src, exe = tmp_path / "shapes.cpp", tmp_path / "shapes"
     src.write_text(SHAPES)
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"), str(src), "-o", str(exe)],
                    check=True)
-    want = dict(kernels.EVERY_TILE)
-    for m, n, _, _, text in kernels.LARGE_TILES:
-        want[False, m, n] = text.split(",")[0]
+    want = {size: kernels.EVERY_TILE[size[:3]] for size in kernels.EVERY_TILE_SIZES}
+    for m, n, k, _, text in kernels.LARGE_TILES:
+        want[False, m, n, k] = text.split(",")[0]
+    for m, seg, k, _, text in block.ROPE_TILES:      # (their lists have a length that the host knows)
+        want[False, m, 3 * seg, k] = text
     for n, count, text in kernels.LONG_K_TILES:
         if text.startswith("stream"):
             assert count <= 32 and n < 8192
         else:
-            want[True, count, n] = text.split(",")[0]
-    ask = "".join("%d %d %d\n" % size for size in want)
+            want[True, count, n, 4096] = text.split(",")[0]
+    ask = "".join("%d %d %d %d\n" % size for size in want)
     got = subprocess.run([str(exe)], input=ask, capture_output=True, text=True, check=True).stdout.splitlines()
     assert dict(zip(want, got)) == want
     large = {"128 x 96", "128 x 128", "128 x 192", "256 x 128", "256 x 192", "256 x 256"}
-    assert {want[s] for s in want if not s[0]} == {"64 x 64", "64 x 96", "64 x 128"} | large
+    assert {want[s] for s in want if not s[0]} == {"64 x 64", "64 x 96", "64 x 128", "256 x 192 four waves",
+                                                   "256 x 256 four waves"} | large
     assert {want[s] for s in want if s[0]} == {"64 x 64", "128 x 48", "128 x 64", "256 x 256 cut"} | large
 
 
@@ -218,13 +224,14 @@ int main() {
     if (gemm_route(c.m, c.n, c.k, 1, false) != c.want) std::printf("%d x %d x %d\n", c.m, c.n, c.k), ++bad;
   for (int n = 64; n <= 32768; n += 192)
     for (int m = 1; m <= 40000; m = m < 600 ? m + 13 : m + 397)
-      for (int k = 256; k <= 12288; k *= 2) {
+      for (int k = 64; k <= 12288; k *= 2) {
         const GemmRoute r = gemm_route(m, n, k, 1, false), shape = best_tile(m, n, false);
         const bool q192 = r == GemmRoute::kQuad192, q256 = r == GemmRoute::kQuad256;
         if ((q192 ? GemmRoute::kPp192 : q256 ? GemmRoute::kPp256 : r) != shape) ++bad;                          // the form alone
         const bool one = tiles_of(m, n, kPpRows, shape == GemmRoute::kPp192 ? 192 : 256) <= 256;
         if (q192 && one) ++bad;
-        if ((shape == GemmRoute::kPp192 || shape == GemmRoute::kPp256) && !one && !q192 && !q256) ++bad;
+        if ((q192 || q256) && k < 192) ++bad;
+        if ((shape == GemmRoute::kPp192 || shape == GemmRoute::kPp256) && !one && k >= 192 && !q192 && !q256) ++bad;
         four += q192 || q256;
         eight += r == GemmRoute::kPp192 || r == GemmRoute::kPp256;
       }
@@ -254,7 +261,7 @@ int main() {
     for (int m = 1; m <= 40000; m = m < 600 ? m + 13 : m + 397) {
       if (queries_of_listed_rows(m, d)) {
         ++later;
-        if (m < kPartMinRows || d / kRouteBK < kPartMinSteps) ++bad;
+        if (m < kPartMinRows || d / kRouteBK < kQuadMinSteps) ++bad;
       }
       for (int part = 0; part <= m; part += m / 3 + 1) {
         const int tn = part_columns(m, 3 * d, part, d);

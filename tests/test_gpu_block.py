@@ -136,12 +136,17 @@ def test_residual_add(B, dtype, n):
         assert np.array_equal(got.astype(np.float64), orc.round_storage(want, "bf16"))
 
 
-# 256-row tiles of all rows, more of them than CUs (a workgroup walks several): 192, 256 and 128 columns, three k-steps and
-# more, a last row tile of 156, 34 and 48 rows, column tiles that hold the end of a segment or of the rotated columns
-@pytest.mark.parametrize("m,seg,k,listed", [
-    (2716, 2112, 192, False), (4130, 2112, 192, False), (3120, 1664, 192, False),
-    (2716, 2112, 256, True), (4130, 2112, 320, True), (3120, 1664, 256, True),
-])
+# 256-row tiles of all rows, more of them than CUs (with four waves a workgroup walks several): three k-steps and more, a
+# last row tile of 156, 34 and 48 rows, column tiles that hold the end of a segment or of the rotated columns
+ROPE_TILES = [
+    (2716, 2112, 192, False, "256 x 192 four waves"), (4130, 2112, 192, False, "256 x 256 four waves"),
+    (3120, 1664, 192, False, "256 x 128"),
+    (2716, 2112, 256, True, "256 x 192 four waves"), (4130, 2112, 320, True, "256 x 256 four waves"),
+    (3120, 1664, 256, True, "256 x 128"),
+]
+
+
+@pytest.mark.parametrize("m,seg,k,listed", [size[:4] for size in ROPE_TILES])
 def test_gemm_rope_large_tiles_in_passes(B, m, seg, k, listed):
     """What a projection of all rows, or of the rows behind a frozen prefix, writes: rotated, plain and fp32 columns."""
     r = _rng(m + k)

@@ -62,6 +62,11 @@ LARGE_TILES = [
     (961, 12096, 192, 12096, "256 x 192, an odd number of k-steps, one row in the last tile's last 64"),
     (1024, 12480, 128, 4160, "256 x 256, ragged columns"),
     (1793, 8192, 320, 4096, "256 x 256, five k-steps, one row in the last tile"),
+    (1500, 12160, 192, 12160, "256 x 192 four waves, three k-steps, ragged both ways"),
+    (1500, 12160, 320, 12160, "256 x 192 four waves, five k-steps, ragged both ways"),
+    (1793, 12480, 256, 4160, "256 x 256 four waves, four k-steps, ragged columns, one row in the last tile"),
+    (1793, 12480, 448, 4160, "256 x 256 four waves, seven k-steps, ragged columns, one row in the last tile"),
+    (1793, 12480, 128, 4160, "256 x 256, two rounds of two k-steps"),
     (2100, 2112, 64, 2112, "256 x 128, one k-step, ragged both ways"),
     (2305, 2048, 320, 2048, "256 x 128, five k-steps, one row in the last tile"),
     (33, 24640, 64, 24640, "64 x 128, one k-step, ragged both ways"),
@@ -277,7 +282,7 @@ EVERY_TILE = {
 }
 
 
-@pytest.mark.parametrize("listed,m,n,k", [
+EVERY_TILE_SIZES = [
     (False, 402, 512, 192), (False, 1000, 1536, 128), (False, 1001, 2048, 64), (False, 2331, 1024, 192),
     (False, 1001, 4096, 64), (False, 1025, 6080, 128), (False, 1300, 6144, 64), (False, 1000, 9216, 128),
     (False, 2331, 6144, 64),
@@ -291,7 +296,10 @@ EVERY_TILE = {
       for k in (256, 320, 384, 448)),
     # 128 x 192, whose ring is the shortest: one to seven k-steps
     *((listed, 300, 12288, k) for listed in (False, True) for k in (64, 128, 192, 256, 320, 448)),
-])
+]
+
+
+@pytest.mark.parametrize("listed,m,n,k", EVERY_TILE_SIZES)
 def test_gemm_every_tile_shape(B, listed, m, n, k):
     assert (listed, m, n) in EVERY_TILE
     r = _rng(m + n + k)
