@@ -1001,7 +1001,7 @@ __device__ __forceinline__ void store16(bf16_t* to, const u32x4 v) {
 // PART: the columns from part_n on for all rows, those in front of it for the part_m rows of the second list.
 template <int TN, bool STREAM, bool PART = false>
 __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, unsigned char* smem, const int part_m = 0) {
-  static_assert(TN >= 2 && TN <= 4, "column blocks of 32 per wave");
+  static_assert(TN == 3 || TN == 4, "column blocks of 32 per wave");
   constexpr int BM = kPpRows, BN = 64 * TN;
   constexpr int SLOT = kQuadSlot;
   constexpr int AL = BM / 8 / 4, BL = BN / 8 / 4;  // loads of a wave per half-stage
@@ -1198,7 +1198,7 @@ __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, u
     };
     // acc[i][2 j + h][e] = C[row, col], row = m0 + 128 wm + 16 i + l16, col = col0 + 32 j + 8 kq + 4 h + e
     const bool low = l16 < 8;
-    if (p.swiglu_pairs) {
+    if (!PART && p.swiglu_pairs) {
       const long ldc = p.ldc;
 #pragma unroll
       for (int i = 0; i < NA; ++i) {
@@ -1256,11 +1256,11 @@ __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, u
           if (in && (low ? live_other : live[i])) store16<STREAM>((low ? far : own) + c, y);
         } else {
           if (live[i] && col0 + (kq & 1) * 32 < n_end) store16<STREAM>(own + at_col, w[0]);
-          if (TN == 3 && live[i] && col0 + 64 < n_end) *reinterpret_cast<u32x2*>(own + 32 + kq * 4) = o[TN - 1];
+          if (live[i] && col0 + 64 < n_end) *reinterpret_cast<u32x2*>(own + 32 + kq * 4) = o[TN - 1];
         }
       }
     } else {
-      if (p.c32 && col0 < p.c32_cols) {
+      if (!PART && p.c32 && col0 < p.c32_cols) {
 #pragma unroll
         for (int i = 0; i < NA; ++i)
 #pragma unroll
@@ -1352,15 +1352,14 @@ __device__ __forceinline__ void gemm_tiles_quad(const GemmDev& p, const int m, u
 }
 
 // Columns [0, part_n) for the listed rows, whose count the device knows, and the others for all rows: one launch for
-// both, in the shape of the least cost.
+// both, in the shape of the least cost.  Two shapes, no gate and no fp32 copy: 8310 instructions and no spilled scalar, where 256 x 128, which
+// is slower with the weights in memory, and those epilogues made it 22345 and 38 (block steps, with them and without, us: 5 x 1024 tokens
+// of hidden 4096, a twentieth refreshed, 403.8 400.7, 4 x 800 half refreshed 385.4 383.3, 16 x 1000 of hidden 2048 392.0 385.9).
 __global__ void __launch_bounds__(256, 1) gemm_bf16_part_kernel(GemmDev p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kQuadSmem];
   const int part_m = *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p.part_m_dev;
-  switch (part_columns(p.m_max, p.n, part_m, p.part_n)) {
-    case 2: return gemm_tiles_quad<2, false, true>(p, p.m_max, smem, part_m);
-    case 3: return gemm_tiles_quad<3, false, true>(p, p.m_max, smem, part_m);
-    default: return gemm_tiles_quad<4, false, true>(p, p.m_max, smem, part_m);
-  }
+  if (part_columns(p.m_max, p.n, part_m, p.part_n) == 3) return gemm_tiles_quad<3, false, true>(p, p.m_max, smem, part_m);
+  gemm_tiles_quad<4, false, true>(p, p.m_max, smem, part_m);
 }
 
 template <int TN, bool STREAM>

@@ -138,11 +138,11 @@ constexpr GemmRoute gemm_route(int m, int n, int k, int k_parts, bool workspace)
   return best;
 }
 
-// What `tiles` tiles of 256 rows x 64 tn columns take in the four-wave form, in tile_cost's units (64 k-steps, one full round:
-// 52, 74 and 90 us).
+// What `tiles` tiles of 256 rows x 64 tn columns, tn 3 or 4, take in the four-wave form, in tile_cost's units (64 k-steps, one
+// full round: 74 and 90 us).
 constexpr long quad_cost(long tiles, int tn) {
   const long rounds = (tiles + 255) / 256;
-  return (tn == 2 ? 750 : tn == 3 ? 1050 : 1290) * (rounds * 256 + tiles);
+  return (tn == 3 ? 1050 : 1290) * (rounds * 256 + tiles);
 }
 
 // Columns [0, part_n) for part_m listed rows and [part_n, n) for all m rows in one launch: its tiles, and the width
@@ -151,16 +151,7 @@ constexpr long part_tiles(int m, int n, int part_m, int part_n, int tn) {
   return (long)tiles_of(m, n - part_n, kPpRows, 64 * tn) + tiles_of(part_m, part_n, kPpRows, 64 * tn);
 }
 __attribute__((always_inline)) constexpr int part_columns(int m, int n, int part_m, int part_n) {
-  int best = 4;
-  long least = quad_cost(part_tiles(m, n, part_m, part_n, 4), 4);
-  for (int tn = 3; tn >= 2; --tn) {
-    const long cost = quad_cost(part_tiles(m, n, part_m, part_n, tn), tn);
-    if (cost < least) {
-      least = cost;
-      best = tn;
-    }
-  }
-  return best;
+  return quad_cost(part_tiles(m, n, part_m, part_n, 3), 3) < quad_cost(part_tiles(m, n, part_m, part_n, 4), 4) ? 3 : 4;
 }
 
 // Output reuse (mode O): queries for the refreshed rows only, with K and V of all rows in one launch, instead of Q, K and V of all

@@ -8,6 +8,7 @@ import subprocess
 
 import test_gpu_block as block
 import test_gpu_kernels as kernels
+import test_gpu_layer as layer
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -265,8 +266,8 @@ int main() {
       }
       for (int part = 0; part <= m; part += m / 3 + 1) {
         const int tn = part_columns(m, 3 * d, part, d);
-        for (int o = 2; o <= 4; ++o)
-          if (tn < 2 || tn > 4 || quad_cost(part_tiles(m, 3 * d, part, d, o), o) < quad_cost(part_tiles(m, 3 * d, part, d, tn), tn)) ++bad;
+        for (int o = 3; o <= 4; ++o)
+          if (tn < 3 || tn > 4 || quad_cost(part_tiles(m, 3 * d, part, d, o), o) < quad_cost(part_tiles(m, 3 * d, part, d, tn), tn)) ++bad;
       }
     }
   std::printf("later %ld bad %ld\n", later, bad);
@@ -278,6 +279,28 @@ int main() {
 def test_queries_behind_the_score_where_they_save_rounds(tmp_path):
     r = _run(tmp_path, PART)
     assert r.returncode == 0, r.stdout
+
+
+WIDTHS = r"""
+#include <cstdio>
+#include "gemm_route.h"
+int main() {
+  int m, d, part;
+  while (std::scanf("%d %d %d", &m, &d, &part) == 3) std::printf("%d\n", dare::part_columns(m, 3 * d, part, d));
+}
+"""
+
+
+def test_gpu_tests_reach_both_widths_of_the_joint_launch(tmp_path):
+    src, exe = tmp_path / "widths.cpp", tmp_path / "widths"
+    src.write_text(WIDTHS)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True)
+    for batch, seq, hidden, _ in layer.QUERIES_LATER:
+        counts = (batch * seq, batch * seq // 5, batch * seq // 3, 1, 0)
+        ask = "".join("%d %d %d\n" % (batch * seq, hidden, n) for n in counts)
+        got = subprocess.run([str(exe)], input=ask, capture_output=True, text=True, check=True).stdout.split()
+        assert set(got) == {"3", "4"}, (batch, seq, hidden, got)
 
 
 LISTED = r"""

@@ -82,7 +82,7 @@ def test_row_list_in_the_projection_of_one_round(seq):
     gl.layer.destroy()
 
 
-# sizes of queries_of_listed_rows (tests/test_gemm_route.py): the device picks 256 x 192 and 256 x 256 tiles for them
+# sizes of queries_of_listed_rows: by the count the device picks 256 x 192 or 256 x 256 tiles for them (tests/test_gemm_route.py)
 QUERIES_LATER = [(3, 900, 2048, 128), (4, 1400, 1024, 64)]
 
 
