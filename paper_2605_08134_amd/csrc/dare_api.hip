@@ -287,8 +287,11 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
       k_ranges *= 2;
   }
   // Output reuse where most queries would be read by nobody: they are projected with K and V once the refreshed rows are known
-  // (k_ranges is 1: the scored columns are summed as a projection of all rows sums them)
-  const bool q_later = mode == DARE_MODE_O && cf.dtype == DARE_BF16 && sw == cf.head_dim && queries_of_listed_rows(n_act, d);
+  // (k_ranges is 1: the scored columns are summed as a projection of all rows sums them).  How many those are is known here under a
+  // reuse rate, and below every score
+  const int reused = by_rate ? (int)ceilf(threshold * (float)(seq - P)) : 0;  // tokens of a sequence
+  const int expected = by_rate ? n_act - batch * reused : threshold < 0.f ? n_act : n_act / 2;
+  const bool q_later = mode == DARE_MODE_O && cf.dtype == DARE_BF16 && sw == cf.head_dim && queries_of_listed_rows(n_act, expected, d);
   if (q_later ||
       (mode == DARE_MODE_KVO && cf.dtype == DARE_BF16 && sw == cf.head_dim && score_in_projection(n_act, d))) {
     // only the scored columns of Q for every row, scored in the same launch
@@ -351,7 +354,7 @@ dare_status step_impl(dare_ctx* ctx, int mode, float threshold, int batch, int s
     if (e != hipSuccess) return fail_hip(ctx, e, "score");
   }
   if (by_rate || ctx->stats_on) {
-    const int rank = by_rate ? (int)ceilf(threshold * (float)(seq - P)) : -1;
+    const int rank = by_rate ? reused : -1;
     double* sum = ctx->stats_on ? ctx->stat_sum : nullptr;
     e = launch_quantile_mask(sc, batch, seq, P, seq - P, rank, mode == DARE_MODE_DENSE, ctx->tau_dev, reuse_mask,
                              sum, reinterpret_cast<unsigned long long*>(sum ? sum + cf.max_batch : nullptr), s);

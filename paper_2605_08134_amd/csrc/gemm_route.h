@@ -154,21 +154,34 @@ __attribute__((always_inline)) constexpr int part_columns(int m, int n, int part
   return quad_cost(part_tiles(m, n, part_m, part_n, 3), 3) < quad_cost(part_tiles(m, n, part_m, part_n, 4), 4) ? 3 : 4;
 }
 
+// What a launch of `tiles` tiles takes where it is compared with one of another number of tiles: rounds of the CUs above all, idle CUs
+// in a round save a quarter of their share.  `full` as in tile_cost.
+constexpr long rounds_cost(long tiles, int full) { return full * ((tiles + 255) / 256 * 768 + tiles) / 2; }
+
 // Output reuse (mode O): queries for the refreshed rows only, with K and V of all rows in one launch, instead of Q, K and V of all
-// rows.  The score then has its own pass over the hidden states, 6 us and 1.8 ns per row and 4096 of k more than what it takes as a
-// by-product, so the launch has to save rounds, or most of a round, with half of the tokens refreshed too; below 1024 rows
-// there is only one.  Block steps, 10, 30 and 50 % refreshed, Q of all rows and now (us): 1 x 1500 of 4096 195 161, 208 177, 235 208;
-// 1 x 2048 221 217, 252 253, 263 268; 3 x 777 252 225, 274 253, 301 307; 4 x 800 345 275, 365 304, 397 371; 4 x 1024 376 333, 424 421, 440
-// 442; 5 x 1024 473 394, 520 454, 561 562; 8 x 2048 25 % 1510 1315; 4 x 700 of 2048 127 106, 133 113, 139 124; 4 x 1400 of 1024 106 93, 109 98,
-// 133 121; but 1 x 600 of 4096 111 112, 111 112, 117 122.
+// rows.  The score then has its own pass over the hidden states, 5 us and 4 ns per row and 4096 of k more than what it takes as a
+// by-product (27 us against 5 at 3200 x 4096), so the launch has to save a round, or most of one; below 1024 rows there is only one.
+// refreshed: their number, known under a reuse rate; half of the rows where the score decides, so that no share up to a half loses.
+// Block steps, 5, 25, 50 and 80 % refreshed, Q of all rows and behind the score (us): 1 x 1500 of 4096 219 185, 233 201, 260 233, 290 311;
+// 4 x 800 353 284, 368 314, 409 383, 435 465; 8 x 2048 1372 1115, 1563 1351, 1833 1727, 2150 2224; 4 x 700 of 2048 140 115, 145 127, 153
+// 138, 174 161; 4 x 1400 of 1024 103 88, 114 104, 125 116, 143 136.  Only where the rate says so: 3 x 777 of 4096 268 247, 282 266, 313 322,
+// 326 342; 5 x 1024 477 401, 523 472, 557 582, 625 656.  Never: 1 x 2048 231 245, 251 267, 271 286, 316 335; 1 x 1024 145 163, 145 162, 154
+// 172, 173 202.  47 sizes with six or eight shares, 330 steps: at the number that is refreshed the rule takes the slower way in
+// 11, by 6 % once and else by 3 % or less; at half of the rows no step with up to a half loses, and with 80 % and all refreshed, where the
+// score's pass saves nothing, the sizes that it takes lose 1 to 7 %, two of them 11 % (1 x 3000 of 4096, all, 497 556).
 constexpr int kPartMinRows = 1024;
-constexpr bool queries_of_listed_rows(int m, int d) {
+constexpr bool queries_of_listed_rows(int m, int refreshed, int d) {
   const int n = 3 * d, ksteps = d / kRouteBK;
   if (ksteps < kQuadMinSteps || m < kPartMinRows || tiles_of(m, n, kPpRows, 128) > (1 << 20)) return false;
-  const GemmRoute now = best_tile(m, n, false);
-  if (now != GemmRoute::kPp128 && now != GemmRoute::kPp192 && now != GemmRoute::kPp256) return false;
-  const int tn = part_columns(m, n, m / 2, d), all_tn = part_columns(m, n, 0, 0);
-  return quad_cost(part_tiles(m, n, m / 2, d, tn), tn) + 13l * m + 44000l * 64 / ksteps < quad_cost(part_tiles(m, n, 0, 0, all_tn), all_tn);
+  // (the wider tiles of all rows by their four-wave form, also where one round of them has eight waves: those are not slower)
+  const GemmRoute shape = best_tile(m, n, false);
+  const int t2 = tiles_of(m, n, kPpRows, 128);
+  const long all = shape == GemmRoute::kPp256   ? rounds_cost(tiles_of(m, n, kPpRows, 256), 1290)
+                   : shape == GemmRoute::kPp192 ? rounds_cost(tiles_of(m, n, kPpRows, 192), 1050)
+                   : shape == GemmRoute::kPp128 ? rounds_cost(t2, t2 > 256 ? 848 : 800)
+                                                : 0;
+  const int tn = part_columns(m, n, refreshed, d);
+  return rounds_cost(part_tiles(m, n, refreshed, d, tn), tn == 3 ? 1050 : 1290) + 29l * m + 37000l * 64 / ksteps < all;
 }
 
 // Row list made in the kernel: loads per wave that bring the first 256 k of an XCD's share of n weight rows into its L2, two

@@ -253,16 +253,24 @@ PART = r"""
 using namespace dare;
 int main() {
   long bad = 0, later = 0;
-  const struct { int m, d; bool want; } at[] = {
-      {2700, 2048, true}, {5600, 1024, true}, {2331, 4096, true}, {16384, 4096, true}, {1 << 29, 64, false}, {1 << 29, 4096, false},
-      {600, 4096, false}, {1024, 4096, false}, {1023, 8192, false}, {4096, 512, false}, {4096, 128, false}};
+  // refreshed in per cent; both ways were measured at the first ones, and differ by 2 % or more
+  const struct { int m, percent, d; bool want; } at[] = {
+      {1500, 50, 4096, true}, {1500, 80, 4096, false}, {2048, 5, 4096, false}, {2048, 50, 4096, false}, {2331, 25, 4096, true},
+      {2331, 50, 4096, false}, {2560, 25, 4096, true}, {2560, 50, 4096, false}, {3200, 50, 4096, true}, {3200, 80, 4096, false},
+      {4096, 5, 4096, true}, {4096, 25, 4096, false}, {5120, 25, 4096, true}, {5120, 50, 4096, false}, {16384, 50, 4096, true},
+      {16384, 80, 4096, false}, {2800, 80, 2048, true}, {2800, 100, 2048, false}, {8192, 5, 2048, true}, {8192, 60, 2048, false},
+      {5600, 50, 1024, true}, {6000, 35, 3072, true}, {2048, 65, 3072, false}, {1700, 25, 4096, true}, {1700, 35, 4096, false},
+      {1 << 29, 50, 64, false}, {1 << 29, 50, 4096, false}, {600, 5, 4096, false}, {1024, 5, 4096, false}, {1023, 0, 8192, false},
+      {4096, 50, 512, false}, {4096, 50, 128, false}};
   for (const auto& c : at)
-    if (queries_of_listed_rows(c.m, c.d) != c.want) std::printf("%d x %d\n", c.m, c.d), ++bad;
+    if (queries_of_listed_rows(c.m, (long)c.m * c.percent / 100, c.d) != c.want) std::printf("%d x %d, %d\n", c.m, c.d, c.percent), ++bad;
   for (int d = 64; d <= 8192; d += 64)
     for (int m = 1; m <= 40000; m = m < 600 ? m + 13 : m + 397) {
-      if (queries_of_listed_rows(m, d)) {
+      if (queries_of_listed_rows(m, m, d)) ++bad;      // where every query is read there is nothing to save
+      if (queries_of_listed_rows(m, m / 2, d)) {
         ++later;
         if (m < kPartMinRows || d / kRouteBK < kQuadMinSteps) ++bad;
+        if (!queries_of_listed_rows(m, m / 4, d)) ++bad;      // fewer save no less
       }
       for (int part = 0; part <= m; part += m / 3 + 1) {
         const int tn = part_columns(m, 3 * d, part, d);
@@ -301,6 +309,29 @@ def test_gpu_tests_reach_both_widths_of_the_joint_launch(tmp_path):
         ask = "".join("%d %d %d\n" % (batch * seq, hidden, n) for n in counts)
         got = subprocess.run([str(exe)], input=ask, capture_output=True, text=True, check=True).stdout.split()
         assert set(got) == {"3", "4"}, (batch, seq, hidden, got)
+
+
+LATER = r"""
+#include <cstdio>
+#include "gemm_route.h"
+int main() {
+  int m, d, refreshed;
+  while (std::scanf("%d %d %d", &m, &d, &refreshed) == 3) std::printf("%d\n", dare::queries_of_listed_rows(m, refreshed, d));
+}
+"""
+
+
+def test_gpu_tests_reach_the_queries_behind_the_score(tmp_path):
+    src, exe = tmp_path / "later.cpp", tmp_path / "later"
+    src.write_text(LATER)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_08134_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True)
+    want = {(b * t, d, b * t // 2): "1" for b, t, d, _ in layer.QUERIES_LATER}
+    b, t, d = layer.BY_RATE
+    want.update({(b * t, d, b * t // 2): "0", (b * t, d, b * t // 4): "1", (1500, 4096, 750): "1"})
+    ask = "".join("%d %d %d\n" % size for size in want)
+    got = subprocess.run([str(exe)], input=ask, capture_output=True, text=True, check=True).stdout.split()
+    assert dict(zip(want, got)) == want
 
 
 LISTED = r"""

@@ -88,18 +88,48 @@ QUERIES_LATER = [(3, 900, 2048, 128), (4, 1400, 1024, 64)]
 
 @pytest.mark.parametrize("batch,seq,hidden,dh", QUERIES_LATER)
 def test_queries_of_the_refreshed_rows_only(batch, seq, hidden, dh):
-    """Mode O with the queries projected behind the score, in the launch of K and V: every row, some, one and none refreshed."""
+    """Mode O with the queries projected behind the score, in the launch of K and V: every row, some, one and none refreshed.
+    (Below every score, -1, they are projected with K and V of all rows.)"""
     case = synth.make_case("llada8b", seed=seq, batch=batch, seq=seq, hidden=hidden, n_heads=hidden // dh, head_dim=dh,
                            fraction=(0.05, 0.4))
     state, gl = pu.oracle_fill(case), pu.GpuLayer(case)
     s = np.sort(pu.oracle_step(case, state, orc.MODE_O, 0.0)["scores"].reshape(-1))
-    for tau in (-1.0, synth.TAU_SEPARATING, float(np.float32(0.5 * (s[-1] + s[-2]))), 2.5):
+    for tau in (-1.0, 0.0, synth.TAU_SEPARATING, float(np.float32(0.5 * (s[-1] + s[-2]))), 2.5):
         _run(case, gl, state, orc.MODE_O, tau)
     gl.layer.destroy()
 
 
+# by its score, which may refresh half of the tokens, and by a rate of a quarter the step projects its queries with all rows and
+# behind the score (tests/test_gemm_route.py)
+BY_RATE = (3, 777, 4096)
+
+
+def test_queries_behind_the_score_by_rate_are_the_same_bits():
+    batch, seq, hidden = BY_RATE
+    case = synth.make_case("llada8b", seed=seq, batch=batch, seq=seq, hidden=hidden, n_heads=hidden // 128, head_dim=128, fraction=0.25)
+    from paper_2605_08134_amd import binding as B
+    put = lambda key: pu.dev(case[key], "bf16")
+    layer = B.DareLayer(*(put(key) for key in ("wq", "wk", "wv", "wo")), n_heads=hidden // 128, max_batch=batch, max_seq=seq)
+    reused = int((~case["perturbed"][0]).sum())
+    got = []
+    for rule, at in ((B.RULE_SCORE, synth.TAU_SEPARATING), (B.RULE_QUANTILE, (reused - 0.5) / seq)):
+        st = layer.new_state(batch, seq)
+        mask = torch.full((batch, seq), 7, dtype=torch.uint8, device="cuda")
+        layer.set_threshold_rule(B.RULE_SCORE)
+        args = (st["q_prev"], st["k_cache"], st["v_cache"], st["o_cache"], st["o_cache"], mask)
+        layer.layer_step(B.MODE_DENSE, 0.0, put("x_prev"), *args)
+        layer.set_threshold_rule(rule)
+        layer.layer_step(B.MODE_O, at, put("x_cur"), *args)
+        got.append((mask, st))
+    layer.destroy()
+    assert np.array_equal(pu.host(got[0][0]).astype(bool), ~case["perturbed"])
+    assert torch.equal(got[0][0], got[1][0])
+    for key in got[0][1]:
+        assert torch.equal(got[0][1][key], got[1][1][key]), key
+
+
 @pytest.mark.parametrize("first,second", [(orc.MODE_DENSE, orc.MODE_O), (orc.MODE_O, orc.MODE_KV), (orc.MODE_O, orc.MODE_O)])
-@pytest.mark.parametrize("batch,seq,hidden", [(3, 900, 2048), (3, 777, 4096)])
+@pytest.mark.parametrize("batch,seq,hidden", [(3, 900, 2048), (3, 777, 4096), (1, 1500, 4096)])
 def test_unchanged_tokens_score_zero_where_queries_come_later(batch, seq, hidden, first, second):
     _unchanged_tokens_score_zero(batch, seq, hidden, first, second, 0)
 
