@@ -9,6 +9,7 @@ import subprocess
 import test_gpu_block as block
 import test_gpu_kernels as kernels
 import test_gpu_layer as layer
+import test_gpu_model as model
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -196,6 +197,10 @@ def test_gpu_tests_reach_the_shapes_that_they_name(tmp_path):
         want[False, m, n, k] = text.split(",")[0]
     for m, seg, k, _, text in block.ROPE_TILES:      # (their lists have a length that the host knows)
         want[False, m, 3 * seg, k] = text
+    m, seg, k, text = block.STREAM_TILE
+    want[False, m, 3 * seg, k] = text
+    (b, t, d, f), text = model.GATE_PAST_THE_L2
+    want[False, b * t, 2 * f, d] = text
     for n, count, text in kernels.LONG_K_TILES:
         if text.startswith("stream"):
             assert count <= 32 and n < 8192

@@ -172,6 +172,36 @@ def test_gemm_rope_large_tiles_in_passes(B, m, seg, k, listed):
     assert rel_err(host(c32)[rows], y[rows, :2 * dh]) <= 2e-6
 
 
+# an output of more than 128 MB, which is stored past the L2: three rows in the last row tile, 192 columns in the last column tile
+STREAM_TILE = (5891, 4160, 192, "256 x 256 four waves")
+
+
+@pytest.mark.parametrize("listed", [False, True])
+def test_gemm_rope_past_the_l2_has_the_bits_of_smaller_launches(B, listed):
+    m, seg, k, _ = STREAM_TILE
+    r = _rng(m)
+    dh, gaps = 64, 50 if listed else 0
+    n_tok, limit = m + gaps, 128 << 20
+    a = dev(r.standard_normal((n_tok, k), dtype=np.float32), "bf16")
+    wt = B.dare_k_pack_weight(dev(r.standard_normal((k, 3 * seg), dtype=np.float32) * np.float32(0.08), "bf16"))
+    table = B.dare_k_rope_table(n_tok, dh, ROPE_BASE)
+    rows = np.sort(r.permutation(n_tok)[:m]).astype(np.int32)
+    new = lambda: [torch.full((n_tok, seg), 3.0, dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    project = lambda outs, **kw: B.dare_k_gemm_rope(a, wt, outs, seg, table, 2 * seg, dh, n_tok, **kw)
+    got, want = new(), new()
+    assert m * 3 * seg * 2 > limit
+    project(got, **(dict(idx=dev(rows), m_max=m) if listed else {}))
+    for part in np.array_split(rows, 3):
+        assert part.size * 3 * seg * 2 < limit
+        project(want, idx=dev(part), m_max=part.size)
+    torch.cuda.synchronize()
+    for x, y in zip(got, want):
+        assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+    left = torch.ones(n_tok, dtype=torch.bool)
+    left[torch.from_numpy(rows).long()] = False
+    assert all(bool((o[left.cuda()] == 3.0).all()) for o in got)
+
+
 # ------------------------------------------------------------------ the block step
 class GpuBlock(pu.GpuLayer):
     def __init__(self, case, norm, rope_base, residual, use_bias=True, **kw):

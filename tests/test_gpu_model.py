@@ -189,6 +189,29 @@ def test_gate_over_its_whole_range(Bm, B, T, ffn):
     assert np.all(up[:, 7] == np.inf) and np.all(np.isnan(np.delete(up, 7, axis=1))) and np.all(np.isnan(down))
 
 
+# sequences, tokens, hidden, feed-forward: silu(gate) * up of more than 128 MB, stored past the L2, with 8 rows in the last row tile and half a
+# column tile
+GATE_PAST_THE_L2 = (4, 2050, 256, 8384), "256 x 256 four waves"
+
+
+def test_gate_past_the_l2_has_the_bits_of_a_smaller_launch(Bm):
+    """A sequence's rows of the last residual stream in a batch and alone; without attention, whose sums depend on the batch."""
+    (B, T, d, ffn), _ = GATE_PAST_THE_L2
+    assert B * T * ffn * 2 > 128 << 20 > T * ffn * 2
+    cfg = dict(L=1, d=d, H=2, ffn=ffn, V=192, B=B, T=T)
+    params = synth.make_model_params(17, 1, d, ffn, 192, "bf16", with_head=False)
+    params["layers"][0]["wo"] = np.zeros((d, d))
+    ids = np.random.default_rng(3).integers(0, 192, (B, T)).astype(np.int32)
+    m = _build(Bm, params, cfg, "bf16")
+    whole = _gpu_step(m, cfg, "bf16", [orc.MODE_DENSE], [0.0], ids)[2]
+    for b in range(B):
+        alone = _gpu_step(m, dict(cfg, B=1), "bf16", [orc.MODE_DENSE], [0.0], ids[b:b + 1])[2]
+        assert np.all(np.isfinite(alone)) and np.any(alone[2] != alone[1])
+        assert np.array_equal(whole[1][b], alone[1][0])
+        assert np.array_equal(whole[2][b], alone[2][0])
+    m.destroy()
+
+
 def test_layers_share_the_workspace_of_attention_with_cut_keys(Bm):
     """The workspace that steps of 1921 tokens and more use (8.7 MB) is the model's: a layer takes
     no more memory at 2048 than at 1920 tokens than its own rows do (1/16 of about 14 MB)."""
