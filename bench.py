@@ -238,7 +238,7 @@ def main():
     dg_ms = e0.elapsed_time(e1) / 50
     dg_tflops = 2.0 * Bn * T * d * 3 * d / (dg_ms * 1e-3) / 1e12
     roofline_other = [{
-        "kernel": "gemm_bf16_quad_kernel (all-row Q/K/V projection, %d x %d x %d)" % (Bn * T, 3 * d, d),
+        "kernel": "gemm_bf16_pp_kernel (all-row Q/K/V projection, %d x %d x %d)" % (Bn * T, 3 * d, d),
         "bound": "mfma", "achieved": dg_tflops, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
         "frac": dg_tflops / MFMA_BF16_PEAK_TFLOPS, "us_per_launch": dg_ms * 1e3}]
 

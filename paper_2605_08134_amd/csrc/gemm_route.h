@@ -47,8 +47,9 @@ constexpr bool gemm_may_split(long m, long n, long k) {
 // shared by those that work).  In several rounds it is `again` instead of `full`: nothing hides the ends of the
 // 16-wide loop's shapes, and small ones pull the weights again for every row of tiles (300 x 12288 x 4096: 64 x 64 73
 // us, 256 x 128 52).
-// Fitted to 120 products of 40 to 16384 rows by 512 to 24576 columns, k from 512 to 12288, in every shape: the
-// shape chosen is within 3 % of the fastest one but for 1300 x 4096 x 12288 (10 %: 192 x 128, which nothing else
+// Fitted to 120 products of 40 to 16384 rows by 512 to 24576 columns, k from 512 to 12288, in every shape with eight waves: the
+// shape chosen is within 3 % of the fastest one of those (several rounds of 256 x 192 and 256 of all rows have four and take 9 and 12 % less,
+// which the choice does not count) but for 1300 x 4096 x 12288 (10 %: 192 x 128, which nothing else
 // wants) and 256 x 24576 x 4096 (10 %).  A rule by
 // thresholds on tile counts, made for 1024 tokens of 4096, was off by up to 2 (us, before and now, the loop of gemm_tile16
 // included: 402 x 2048 x 2048 20.6 and 9.6, 256 x 4096 x 4096 34.1 and 16.6, 1000 x 9216 x 3072 75.9 and 50.2, 2331 x 4096 x
