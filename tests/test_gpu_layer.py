@@ -115,12 +115,13 @@ def test_queries_behind_the_score_by_rate_are_the_same_bits():
     for rule, at in ((B.RULE_SCORE, synth.TAU_SEPARATING), (B.RULE_QUANTILE, (reused - 0.5) / seq)):
         st = layer.new_state(batch, seq)
         mask = torch.full((batch, seq), 7, dtype=torch.uint8, device="cuda")
+        scores = torch.full((batch, seq), float("nan"), device="cuda")
         layer.set_threshold_rule(B.RULE_SCORE)
         args = (st["q_prev"], st["k_cache"], st["v_cache"], st["o_cache"], st["o_cache"], mask)
         layer.layer_step(B.MODE_DENSE, 0.0, put("x_prev"), *args)
         layer.set_threshold_rule(rule)
-        layer.layer_step(B.MODE_O, at, put("x_cur"), *args)
-        got.append((mask, st))
+        layer.layer_step(B.MODE_O, at, put("x_cur"), *args, scores=scores)
+        got.append((mask, dict(st, scores=scores)))
     layer.destroy()
     assert np.array_equal(pu.host(got[0][0]).astype(bool), ~case["perturbed"])
     assert torch.equal(got[0][0], got[1][0])
